@@ -471,6 +471,17 @@ def test_finalize_sweep_over_blocks():
         assert set(cols.tolist()) <= set(idx.cpu().tolist())
 
 
+@pytest.mark.parametrize("E,k", [(8, 3), (16, 16), (264, 1), (1024, 1000), (1032, 64), (8192, 80), (8200, 513),
+                                 (32768, 700)])
+def test_finalize_tile_edges(E, k):
+    """The ranking's groups of 16 and tiles of 8192 features and the selection's of 1024: sizes at
+    and just past their edges and the largest, most ranges tied (within a group and across)."""
+    rng = np.random.default_rng(E + k)
+    M_ref = rng.integers(0, 7, (9, E)).astype(np.float32)
+    m_ref = -rng.integers(0, 7, (9, E)).astype(np.float32)
+    _finalize_both(torch.from_numpy(m_ref).cuda(), torch.from_numpy(M_ref).cuda(), m_ref, M_ref, k)
+
+
 def test_hip_graph_replays_match_eager():
     """encode + decode_reduce of several blocks captured in one HIP graph: every replay, with
     eager work and synchronisation in between, gives the eager result."""
