@@ -743,7 +743,6 @@ static hipError_t launch_direct(const EncodeArgs &a_in, const RankPtrs &Y_in, co
         a.off_idx = o.idx;
         a.off_dirr = o.dirr;
         a.off_dsel = o.dsel;
-        a.off_dpos16 = o.dpos16;
         a.off_dslot8 = o.dslot8;
         a.off_dseg = o.dseg;
         a.off_drec = o.drec;

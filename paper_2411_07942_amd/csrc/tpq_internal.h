@@ -21,21 +21,12 @@ namespace tpq {
 //   src_of   uint16[chunks_padded * 8]  src_of[c] = feature index of compacted
 //                                       position c; positions >= r repeat the
 //                                       last real one (harmless for min / max)
-//   pass_col uint16[passes + 1]         column of the first feature of pass p
-//                                       (pass_col[passes] = E)
 //
 // Tables of the encoder, which reads each chunk's features with one 16-byte load
-// straight from the row ("window" of 8 columns starting at an even column):
-//   dpos     uint32[chunks_padded]      per chunk: bits 14..0 = first 32-bit word of its
-//                                       window within the row; kDirOdd: the chunk's 8
-//                                       features start at the upper half of that word and
-//                                       end with the lower half of the next lane's first
-//                                       word; kDirSlot: the chunk takes its features from
-//                                       its slot (bits 29..16 = slot number): an outlier
-//                                       splits it, it is ragged, it must lend its window to
-//                                       outliers next to it, or the next lane's window
-//                                       does not continue its own; kDirAbsent: beyond the row
-//   dflags   uint16[chunks_padded]      scratch of the build
+// straight from the row ("window" of 8 columns starting at an even column).  A chunk takes its
+// features from a slot if an outlier splits it, it is ragged, it must lend its window to
+// outliers next to it, or the next lane's window does not continue its own; slots are numbered
+// in chunk order.
 //   dirr     uint16[8 * dslots]         per slot: where the chunk's 8 features sit in the
 //                                       32 bytes the chunk loads (two windows: its own and
 //                                       the 8 columns after it, pulled back where that would
@@ -43,21 +34,20 @@ namespace tpq {
 //                                       of reach makes the slot "wide": kDirWide | column
 //   dsel     uint32[k rounded up to 4]  per selected feature: (slot << 5) | byte offset in
 //                                       the slot that holds it, or kDirFar: in no slot
-//   pass_dirr uint16[passes + 1]        slots below pass p
-//   dpos16   uint16[segs * 64 * 8]      dpos in the form the encoder loads: the row is cut
-//                                       into segs segments of dir_P passes (dir_passes_of());
-//                                       entry [(seg * 64 + lane) * 8 + p] belongs to lane
-//                                       `lane` of the segment's pass p: bits 13..0 = first
-//                                       word of the window, kDir16Odd, kDir16Slot (slots are
-//                                       numbered in chunk order, so a lane finds its own by
-//                                       counting the flagged lanes below it)
-//   dseg     uint32[2 * segs]           per segment: word 0 = first slot | slots << 16, word 1 =
+//   dseg     uint32[2 * segs]           the row is cut into segs segments of dir_P passes
+//                                       (dir_passes_of()); per segment: word 0 = first slot | slots << 16, word 1 =
 //                                       first selected feature it stores | how many << 16 (the
 //                                       selected columns below the next segment's first feature
 //                                       that no earlier segment owns)
 //   drec     uint32[segs * 64 * 8]      what lane l of a wave working on segment sg loads
 //                                       first, gathered in one 32-byte record [sg * 64 + l]:
-//                                       words 0..3 = its dpos16 entries, words 4, 5 = the
+//                                       words 0..3 = one 16-bit entry per pass of the segment:
+//                                       bits 13..0 = first 32-bit word of the chunk's window
+//                                       within the row; kDir16Odd: the chunk's 8 features start
+//                                       at the upper half of that word and end with the lower
+//                                       half of the next lane's first word; kDir16Slot: it has
+//                                       a slot (a lane finds its number by counting the flagged
+//                                       lanes below it); zero beyond the row.  Words 4, 5 = the
 //                                       dslot8 entry of the segment's l-th slot, word 6 = the
 //                                       dsel entry of the l-th selected feature the segment
 //                                       stores (where there is none: zero, and the
@@ -87,10 +77,6 @@ constexpr uint32_t kPlanMagic = 0x51505434u;  // "4TPQ"
 constexpr int kPlanOk = 1;
 constexpr int kPlanBadIndex = 2;
 constexpr int kPlanInternal = 3;  // a table of the build overflowed (never expected)
-// beyond the row: flag + no slot; the low bits then hold column E - 8
-constexpr uint32_t kDirOdd = 0x8000u;
-constexpr uint32_t kDirAbsent = 0x40000000u;
-constexpr uint32_t kDirSlot = 0x80000000u;
 constexpr uint32_t kDirWide = 0x8000u;      // in a dirr entry
 constexpr uint32_t kDirFar = 0x80000000u;   // in a dsel entry
 constexpr uint32_t kDir16Odd = 0x4000u;
@@ -107,23 +93,22 @@ struct PlanHeader {
     int32_t chunks_padded;  // chunks rounded up to a multiple of 64
     int32_t idx_offset;     // byte offsets from the start of the plan
     int32_t src_offset;
-    int32_t pass_col_offset;
-    int32_t dpos_offset;
+    int32_t reserved0[2];
     int32_t dirr_offset;
     int32_t dsel_offset;
-    int32_t pass_dirr_offset;
+    int32_t reserved1;
     int32_t n_dirr;       // slots in use
     int32_t dslots;       // slots the tables have room for
-    int32_t dpos16_offset;
+    int32_t reserved2;
     int32_t dslot8_offset;
-    int32_t dir_P;        // passes per segment the dpos16 table is laid out for
+    int32_t dir_P;        // passes per segment the records are laid out for
     int32_t dseg_offset;
     int32_t drec_offset;
     int32_t drec2_offset;
     int32_t spass_offset;
     int32_t sblk_offset;
     int32_t sblk_cap;     // entries sblk has room for
-    int32_t reserved[6];
+    int32_t reserved3[6];
 };
 static_assert(sizeof(PlanHeader) == 128, "plan header is 128 bytes");
 
@@ -163,11 +148,8 @@ __host__ __device__ inline int sblk_cap_of(int k, int r)
     return bound < 9 * cp ? bound : 9 * cp;
 }
 
-__host__ __device__ inline int pass_tab_bytes_of(int r) { return ((chunks_padded_of(r) / 64 + 1) * 2 + 15) / 16 * 16; }
-
 struct PlanOffsets {
-    int idx, src, pass_col;
-    int dpos, dflags, dirr, dsel, pass_dirr, dpos16, dslot8, dseg, drec, drec2, spass, sblk, total;
+    int idx, src, dirr, dsel, dslot8, dseg, drec, drec2, spass, sblk, total;
 };
 __host__ __device__ inline PlanOffsets plan_offsets(int k, int r, int G)
 {
@@ -175,14 +157,9 @@ __host__ __device__ inline PlanOffsets plan_offsets(int k, int r, int G)
     PlanOffsets o;
     o.idx = sizeof(PlanHeader);
     o.src = o.idx + idx_bytes_of(k);
-    o.pass_col = o.src + 16 * cp;
-    o.dpos = o.pass_col + pass_tab_bytes_of(r);
-    o.dflags = o.dpos + 4 * cp;
-    o.dirr = o.dflags + (2 * cp + 15) / 16 * 16;
+    o.dirr = o.src + 16 * cp;
     o.dsel = o.dirr + 16 * dir_slots_of(k, r);
-    o.pass_dirr = o.dsel + idx_bytes_of(k);
-    o.dpos16 = o.pass_dirr + pass_tab_bytes_of(r);
-    o.dslot8 = o.dpos16 + dir_segs_of(cp / 64) * 64 * 8 * 2;
+    o.dslot8 = o.dsel + idx_bytes_of(k);
     o.dseg = o.dslot8 + (8 * dir_slots_of(k, r) + 15) / 16 * 16;
     o.drec = o.dseg + (8 * dir_segs_of(cp / 64) + 15) / 16 * 16;
     o.drec2 = o.drec + dir_segs_of(cp / 64) * 64 * 32;
@@ -226,7 +203,7 @@ struct EncodeArgs {
     const float *inv_c;
     int32_t static_stride;
     // byte offsets of the plan's tables (what the header holds, known to the host too)
-    int32_t off_idx, off_dirr, off_dsel, off_dpos16, off_dslot8, off_dseg, off_drec, off_drec2;
+    int32_t off_idx, off_dirr, off_dsel, off_dslot8, off_dseg, off_drec, off_drec2;
 };
 
 struct DecodeArgs {

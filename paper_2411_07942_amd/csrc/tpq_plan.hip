@@ -1,100 +1,10 @@
 // Builds the compaction tables for a static outlier index set (paper Sec. 3: the
 // selected features are fixed across sequences and devices, so this runs once
-// per block, not per call).  Everything here is offline work on a few thousand
-// table entries; clarity wins over speed.
+// per block, not per call).
 #include "tpq_device.h"
 #include "tpq_internal.h"
 
 namespace tpq {
-
-__global__ void k_plan_init(uint8_t *plan, int E, int k, int G, int r, int chunks,
-                            int chunks_padded, PlanOffsets o)
-{
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        PlanHeader *h = reinterpret_cast<PlanHeader *>(plan);
-        h->magic = kPlanMagic;
-        h->status = kPlanOk;
-        h->E = E;
-        h->k = k;
-        h->G = G;
-        h->r = r;
-        h->chunks = chunks;
-        h->chunks_padded = chunks_padded;
-        h->idx_offset = o.idx;
-        h->src_offset = o.src;
-        h->pass_col_offset = o.pass_col;
-        h->dpos_offset = o.dpos;
-        h->dirr_offset = o.dirr;
-        h->dsel_offset = o.dsel;
-        h->pass_dirr_offset = o.pass_dirr;
-        h->n_dirr = 0;
-        h->dslots = dir_slots_of(k, r);
-        h->dpos16_offset = o.dpos16;
-        h->dslot8_offset = o.dslot8;
-        h->dir_P = dir_passes_of(chunks_padded / 64);
-        h->dseg_offset = o.dseg;
-        h->drec_offset = o.drec;
-        h->drec2_offset = o.drec2;
-        h->spass_offset = o.spass;
-        h->sblk_offset = o.sblk;
-        h->sblk_cap = sblk_cap_of(k, r);
-        for (int i = 0; i < 6; ++i) h->reserved[i] = 0;
-    }
-}
-
-// One thread per feature j: count the selected features below j (binary search
-// in idx) and, if j itself is not selected, record src_of[j - count] = j.
-// Threads p < k also validate idx[p] and copy it into the plan.
-__global__ void k_plan_build(uint8_t *plan, const int32_t *__restrict__ idx, int E, int k, int r,
-                             PlanOffsets o)
-{
-    PlanHeader *h = reinterpret_cast<PlanHeader *>(plan);
-    int32_t *pidx = reinterpret_cast<int32_t *>(plan + o.idx);
-    uint16_t *src = reinterpret_cast<uint16_t *>(plan + o.src);
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
-
-    if (j < k) {
-        const int v = idx[j];
-        bool ok = v >= 0 && v < E;
-        if (j > 0) ok = ok && v > idx[j - 1];
-        if (!ok) h->status = kPlanBadIndex;
-        pidx[j] = ok ? v : 0;
-    } else if (j < (k + 3) / 4 * 4) {
-        pidx[j] = 0;
-    }
-
-    if (j < E) {
-        // lower bound: number of idx entries < j
-        int lo = 0, hi = k;
-        while (lo < hi) {
-            const int mid = (lo + hi) >> 1;
-            if (idx[mid] < j) lo = mid + 1; else hi = mid;
-        }
-        const bool selected = lo < k && idx[lo] == j;
-        const int c = j - lo;
-        if (!selected && c >= 0 && c < r) src[c] = static_cast<uint16_t>(j);
-    }
-}
-
-// Positions r .. 8*chunks_padded-1 repeat the last real compacted feature.
-__global__ void k_plan_pad(uint8_t *plan, int r, int chunks_padded, PlanOffsets o)
-{
-    uint16_t *src = reinterpret_cast<uint16_t *>(plan + o.src);
-    const int c = r + blockIdx.x * blockDim.x + threadIdx.x;
-    if (r > 0 && c < 8 * chunks_padded) src[c] = src[r - 1];
-}
-
-// pass_col[p] = column of the first feature of pass p; pass_col[passes] = E
-__global__ void k_plan_pass_col(uint8_t *plan, int E, int chunks, int passes, PlanOffsets o)
-{
-    const uint16_t *src = reinterpret_cast<const uint16_t *>(plan + o.src);
-    uint16_t *pass_col = reinterpret_cast<uint16_t *>(plan + o.pass_col);
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p > passes) return;
-    pass_col[p] = (p < passes && 64 * p < chunks) ? src[512 * p] : static_cast<uint16_t>(E);
-}
-
-// ---- tables of the encoder that loads each chunk straight from the row -------------
 
 // First column of chunk c's own window: the even column at or below its first feature,
 // pulled back so that 8 columns from there stay inside the row.  Chunk 0 starts its
@@ -119,245 +29,313 @@ __device__ inline int dir_slot_offset(int col, int wa, int E)
     return -1;
 }
 
-// dflags[c] = 1 if chunk c needs a slot.
-__global__ void k_plan_dflags(uint8_t *plan, int E, int r, int chunks, int chunks_padded,
-                              PlanOffsets o)
+// does chunk c need a slot?
+__device__ inline bool dir_needs_slot(const uint16_t *src, int c, int E, int r)
 {
-    const PlanHeader *h = reinterpret_cast<const PlanHeader *>(plan);
-    const uint16_t *src = reinterpret_cast<const uint16_t *>(plan + o.src);
-    uint16_t *dflags = reinterpret_cast<uint16_t *>(plan + o.dflags);
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= chunks_padded) return;
-    uint16_t f = 0;
-    if (h->status == kPlanOk && c < chunks) {
-        const int nv = r - 8 * c < 8 ? r - 8 * c : 8;
-        const int c0 = src[8 * c], clast = src[8 * c + nv - 1];
-        const int next0 = 8 * c + 8 < r ? src[8 * c + 8] : -1;
-        const bool contiguous = nv == 8 && clast == c0 + 7;
-        // selected features inside the chunk, between it and the next one (or the row's
-        // end), or before the first chunk: this chunk's slot holds them
-        const bool hosts = clast - c0 != nv - 1 || (next0 >= 0 ? next0 : E) - clast - 1 > 0 ||
-                           (c == 0 && c0 > 0);
-        bool slot = !contiguous || hosts;
-        if (!slot && (c0 & 1)) {
-            // the 8th feature is the first half-word of the next lane's window
-            const bool next_ok = (c & 63) != 63 && next0 == c0 + 8 &&
-                                 dir_window_a(src, c + 1, E, r) == (c0 & ~1) + 8;
-            slot = !next_ok;
-        }
-        f = slot ? 1 : 0;
-    }
-    dflags[c] = f;
-}
-
-__global__ void k_plan_dslots(uint8_t *plan, int E, int r, int chunks, int chunks_padded,
-                              int dslots, PlanOffsets o)
-{
-    PlanHeader *h = reinterpret_cast<PlanHeader *>(plan);
-    const uint16_t *src = reinterpret_cast<const uint16_t *>(plan + o.src);
-    const uint16_t *dflags = reinterpret_cast<const uint16_t *>(plan + o.dflags);
-    uint32_t *dpos = reinterpret_cast<uint32_t *>(plan + o.dpos);
-    uint16_t *dirr = reinterpret_cast<uint16_t *>(plan + o.dirr);
-    uint16_t *pass_dirr = reinterpret_cast<uint16_t *>(plan + o.pass_dirr);
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c > chunks_padded) return;
-    int q = 0;
-    for (int b = 0; b < c; ++b) q += dflags[b];
-    if (c == chunks_padded) {
-        h->n_dirr = q;
-        pass_dirr[chunks_padded / 64] = static_cast<uint16_t>(q);
-        return;
-    }
-    if ((c & 63) == 0) pass_dirr[c / 64] = static_cast<uint16_t>(q);
-    // where this chunk's entry sits in the table laid out by segment
-    uint16_t *dpos16 = reinterpret_cast<uint16_t *>(plan + o.dpos16);
-    uint32_t *dslot8 = reinterpret_cast<uint32_t *>(plan + o.dslot8);
-    const int dirP = dir_passes_of(chunks_padded / 64);
-    const int pass = c / 64, seg = pass / dirP;
-    uint16_t *e16 = dpos16 + (seg * 64 + (c & 63)) * 8 + (pass - seg * dirP);
-    if (pass - seg * dirP == 0) {  // entries of passes the segment does not have
-        const int left = chunks_padded / 64 - seg * dirP;
-        for (int p = left < dirP ? left : dirP; p < 8; ++p) e16[p] = 0;
-    }
-    if (h->status != kPlanOk || c >= chunks) {
-        dpos[c] = kDirAbsent;
-        *e16 = 0;
-        return;
-    }
-    const int c0 = src[8 * c];
-    if (!dflags[c]) {
-        dpos[c] = static_cast<uint32_t>(c0 >> 1) | ((c0 & 1) ? kDirOdd : 0u);
-        *e16 = static_cast<uint16_t>((c0 >> 1) | ((c0 & 1) ? kDir16Odd : 0u));
-        return;
-    }
-    if (q >= dslots) {  // the bound of dir_slots_of() does not hold: refuse the plan
-        h->status = kPlanInternal;
-        dpos[c] = kDirAbsent;
-        *e16 = 0;
-        return;
-    }
     const int nv = r - 8 * c < 8 ? r - 8 * c : 8;
-    const int wa = dir_window_a(src, c, E, r);
-    dpos[c] = kDirSlot | (static_cast<uint32_t>(q) << 16) | static_cast<uint32_t>(wa >> 1);
-    bool wide = false;
-    for (int e = 0; e < 8; ++e) {
-        const int col = src[8 * c + (e < nv ? e : nv - 1)];  // absent features repeat the last one
-        if (dir_slot_offset(col, wa, E) < 0) wide = true;
+    const int c0 = src[8 * c], clast = src[8 * c + nv - 1];
+    const int next0 = 8 * c + 8 < r ? src[8 * c + 8] : -1;
+    const bool contiguous = nv == 8 && clast == c0 + 7;
+    // selected features inside the chunk, between it and the next one (or the row's
+    // end), or before the first chunk: this chunk's slot holds them
+    const bool hosts = clast - c0 != nv - 1 || (next0 >= 0 ? next0 : E) - clast - 1 > 0 ||
+                       (c == 0 && c0 > 0);
+    bool slot = !contiguous || hosts;
+    if (!slot && (c0 & 1)) {
+        // the 8th feature is the first half-word of the next lane's window
+        const bool next_ok = (c & 63) != 63 && next0 == c0 + 8 &&
+                             dir_window_a(src, c + 1, E, r) == (c0 & ~1) + 8;
+        slot = !next_ok;
     }
-    uint32_t nib = 0;
-    for (int e = 0; e < 8; ++e) {
-        const int col = src[8 * c + (e < nv ? e : nv - 1)];
-        dirr[8 * q + e] = wide ? static_cast<uint16_t>(kDirWide | col)
-                               : static_cast<uint16_t>(dir_slot_offset(col, wa, E));
-        if (!wide) nib |= static_cast<uint32_t>(dir_slot_offset(col, wa, E) >> 1) << (4 * e);
-    }
-    *e16 = static_cast<uint16_t>((wa >> 1) | kDir16Slot);
-    int wb = wa + 8;
-    if (wb > E - 8) wb = E - 8;
-    // does the next lane of the pass load exactly the second window?
-    bool next_has_b = false;
-    if ((c & 63) != 63 && c + 1 < chunks) {
-        const int next_w = dflags[c + 1] ? dir_window_a(src, c + 1, E, r) : (src[8 * (c + 1)] & ~1);
-        next_has_b = next_w == wb;
-    }
-    dslot8[2 * q] = nib;
-    dslot8[2 * q + 1] = static_cast<uint32_t>(2 * wb) | (wide ? kDirWide8 : 0u) | (next_has_b ? 0u : kDirLoadB8);
+    return slot;
 }
 
-// One thread per selected feature: the slot that holds its column.
-__global__ void k_plan_dsel(uint8_t *plan, int E, int k, int r, PlanOffsets o)
+// One wave: exclusive prefix sum over the lanes.
+__device__ inline int wave_exclusive_sum(int v, int lane)
 {
-    const PlanHeader *h = reinterpret_cast<const PlanHeader *>(plan);
-    const int32_t *pidx = reinterpret_cast<const int32_t *>(plan + o.idx);
-    const uint16_t *src = reinterpret_cast<const uint16_t *>(plan + o.src);
-    const uint32_t *dpos = reinterpret_cast<const uint32_t *>(plan + o.dpos);
-    uint32_t *dsel = reinterpret_cast<uint32_t *>(plan + o.dsel);
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= (k + 3) / 4 * 4) return;
-    uint32_t v = kDirFar;
-    if (p < k && r > 0 && h->status == kPlanOk) {
-        const int j = pidx[p];
-        const int f = j - p;                       // compacted features before column j
-        const int c = f >= 1 ? (f - 1) / 8 : 0;    // the chunk that holds the one before it
-        const uint32_t d = dpos[c];
-        if (d & kDirSlot) {
-            const int off = dir_slot_offset(j, dir_window_a(src, c, E, r), E);
-            if (off >= 0) v = (((d >> 16) & 0x3FFFu) << 5) | static_cast<uint32_t>(off);
-        }
+    int s = v;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const int o = __shfl_up(s, d, 64);
+        if (lane >= d) s += o;
     }
-    dsel[p] = v;
+    return s - v;
 }
 
-// One thread per segment of the direct encoder: its slots and selected features.
-__global__ void k_plan_dseg(uint8_t *plan, int k, int chunks_padded, PlanOffsets o)
-{
-    const uint16_t *pass_dirr = reinterpret_cast<const uint16_t *>(plan + o.pass_dirr);
-    const uint16_t *pass_col = reinterpret_cast<const uint16_t *>(plan + o.pass_col);
-    uint32_t *dseg = reinterpret_cast<uint32_t *>(plan + o.dseg);
-    const int passes = chunks_padded / 64, P = dir_passes_of(passes);
-    const int sg = blockIdx.x * blockDim.x + threadIdx.x;
-    if (sg >= dir_segs_of(passes)) return;
-    const int p0 = sg * P, p1 = p0 + P < passes ? p0 + P : passes;
-    const uint32_t q_lo = pass_dirr[p0], q_hi = pass_dirr[p1];
-    const uint32_t s_lo = sg == 0 ? 0u : pass_col[p0] - 512u * p0;
-    const uint32_t s_hi = p1 == passes ? static_cast<uint32_t>(k) : pass_col[p1] - 512u * p1;
-    dseg[2 * sg] = q_lo | ((q_hi - q_lo) << 16);
-    dseg[2 * sg + 1] = s_lo | ((s_hi - s_lo) << 16);
-}
-
-// One thread per (segment, lane): the record a lane of the direct encoder starts from.
-__global__ void k_plan_drec(uint8_t *plan, int chunks_padded, PlanOffsets o)
-{
-    const uint32_t *dpos16 = reinterpret_cast<const uint32_t *>(plan + o.dpos16);
-    const uint32_t *dslot8 = reinterpret_cast<const uint32_t *>(plan + o.dslot8);
-    const uint32_t *dsel = reinterpret_cast<const uint32_t *>(plan + o.dsel);
-    const uint32_t *dseg = reinterpret_cast<const uint32_t *>(plan + o.dseg);
-    uint32_t *drec = reinterpret_cast<uint32_t *>(plan + o.drec);
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= dir_segs_of(chunks_padded / 64) * 64) return;
-    const int sg = i / 64;
-    const uint32_t l = i % 64;
-    const uint32_t q_lo = dseg[2 * sg] & 0xFFFFu, n_q = dseg[2 * sg] >> 16;
-    const uint32_t s_lo = dseg[2 * sg + 1] & 0xFFFFu, n_sel = dseg[2 * sg + 1] >> 16;
-    uint32_t *rec = drec + 8 * i;
-    for (int w = 0; w < 4; ++w) rec[w] = dpos16[4 * i + w];
-    rec[4] = l < n_q ? dslot8[2 * (q_lo + l)] : 0u;
-    rec[5] = l < n_q ? dslot8[2 * (q_lo + l) + 1] : 0u;
-    rec[6] = l < n_sel ? dsel[s_lo + l] : (q_lo << 5);  // idle lanes read the segment's first slot
-    rec[7] = 0u;
-    uint32_t *rec2 = reinterpret_cast<uint32_t *>(plan + o.drec2) + 4 * i;
-    const uint32_t l2 = l + 64u;
-    rec2[0] = l2 < n_q ? dslot8[2 * (q_lo + l2)] : 0u;
-    rec2[1] = l2 < n_q ? dslot8[2 * (q_lo + l2) + 1] : 0u;
-    rec2[2] = l2 < n_sel ? dsel[s_lo + l2] : (q_lo << 5);
-    rec2[3] = 0u;
-}
-
-// Store blocks of the decoder, one workgroup of 512 threads per pass, thread = feature.
-// FILL = false: count the pass's blocks and narrow entries into spass; FILL = true
-// (after k_plan_sblk_offsets): write the entries.
+// The store entries of one pass, by one wave (tables of the decoder's stores): `starts` = the pass's
+// 512-bit mask of features that start a run, n = features of the pass.  Counts the blocks and the
+// narrow entries; FILL writes them (blocks from `out` on, narrow entries from out + n_blocks on).
 template <bool FILL>
-__global__ __launch_bounds__(512) void k_plan_sblk(uint8_t *plan, int r, PlanOffsets o, int cap)
+__device__ inline void pass_entries(const uint64_t *starts, int n, int lane, const uint16_t *src, uint32_t *out,
+                                    int n_blocks, int &blocks, int &narrow)
 {
-    __shared__ uint8_t start[512], kind[512];
-    PlanHeader *h = reinterpret_cast<PlanHeader *>(plan);
-    const uint16_t *src = reinterpret_cast<const uint16_t *>(plan + o.src);
-    uint32_t *spass = reinterpret_cast<uint32_t *>(plan + o.spass);
-    uint32_t *sblk = reinterpret_cast<uint32_t *>(plan + o.sblk);
-    const int p = blockIdx.x, a0 = threadIdx.x;
-    const int c = 512 * p + a0;
-    const int n = min(512, r - 512 * p);  // features of this pass
-    const bool real = a0 < n;
-    start[a0] = real && (a0 == 0 || src[c] != src[c - 1] + 1);
-    __syncthreads();
-    int rs = a0, re = a0 + 1;  // the run [rs, re) that holds this feature
-    if (real) {
-        while (!start[rs]) --rs;
-        while (re < n && !start[re]) ++re;
-    }
-    const int len = re - rs;
-    // 1: leads a block; 2: narrow
-    kind[a0] = !real ? 0 : (len < 8 ? 2 : ((a0 - rs) % 8 == 0 ? 1 : 0));
-    __syncthreads();
-    int before1 = 0, before2 = 0, n1 = 0, n2 = 0;
-    for (int i = 0; i < 512; ++i) {
-        const int kd = kind[i];
-        n1 += kd == 1;
-        n2 += kd == 2;
-        if (i < a0) {
-            before1 += kd == 1;
-            before2 += kd == 2;
+    int b = 0, w2 = 0, last = 0;
+    for (int w = 0; 64 * w < n; ++w) {
+        const uint64_t m = starts[w];
+        const int a0 = 64 * w + lane;
+        const uint64_t upto = m & (lane == 63 ? ~0ull : (2ull << lane) - 1ull), after = m & ~(lane == 63 ? ~0ull : (2ull << lane) - 1ull);
+        const int rs = upto ? 64 * w + 63 - __builtin_clzll(upto) : last;  // the run [rs, re) that holds a0
+        int re = n;
+        if (after) {
+            re = 64 * w + __builtin_ctzll(after);
+        } else {
+            for (int w1 = w + 1; 64 * w1 < n; ++w1)
+                if (starts[w1]) {
+                    re = 64 * w1 + __builtin_ctzll(starts[w1]);
+                    break;
+                }
         }
-    }
-    if (!FILL) {
-        if (a0 == 0) {
-            spass[4 * p + 1] = n1;
-            spass[4 * p + 2] = n2;
-            spass[4 * p + 3] = 0;
+        const bool real = a0 < n;
+        const bool lead = real && re - rs >= 8 && ((a0 - rs) & 7) == 0;
+        const bool single = real && re - rs < 8;
+        const uint64_t bl = __builtin_amdgcn_ballot_w64(lead), bn = __builtin_amdgcn_ballot_w64(single);
+        if (FILL) {
+            const uint64_t below = (1ull << lane) - 1ull;
+            if (lead) {
+                const int a = a0 + 8 <= re ? a0 : re - 8;
+                out[b + __builtin_popcountll(bl & below)] = src[a] | (static_cast<uint32_t>(a) << 16);
+            } else if (single) {
+                out[n_blocks + w2 + __builtin_popcountll(bn & below)] = src[a0] | (static_cast<uint32_t>(a0) << 16);
+            }
         }
-        return;
+        b += __builtin_popcountll(bl);
+        w2 += __builtin_popcountll(bn);
+        if (m) last = 64 * w + 63 - __builtin_clzll(m);
     }
-    const int first = spass[4 * p];
-    if (first + n1 + n2 > cap) {
-        if (a0 == 0) h->status = kPlanInternal;
-        return;
-    }
-    if (kind[a0] == 1) {
-        const int a = a0 + 8 <= re ? a0 : re - 8;
-        sblk[first + before1] = src[512 * p + a] | (static_cast<uint32_t>(a) << 16);
-    } else if (kind[a0] == 2) {
-        sblk[first + n1 + before2] = src[c] | (static_cast<uint32_t>(a0) << 16);
-    }
+    blocks = b;
+    narrow = w2;
 }
 
-__global__ void k_plan_sblk_offsets(uint8_t *plan, int passes, PlanOffsets o)
+// All tables in one launch.  A workgroup builds the tables of one of the encoder's segments (up to
+// 5 passes); what it needs of the rest of the row -- which feature sits where, how many slots and
+// store entries come before its own -- it works out itself in LDS (a few thousand integers), so
+// that no workgroup waits for another and no table makes a round trip through memory.  The work is
+// latency, not bytes: as twelve dependent launches, three of them serial walks over the row, it took
+// 165 us at E = 5120, k = 80; this takes 13.
+constexpr int kPlanThreads = 1024;
+constexpr int kPlanMaxPasses = TPQ_MAX_E / 512;
+static size_t plan_lds_bytes(int chunks_padded)
 {
-    uint32_t *spass = reinterpret_cast<uint32_t *>(plan + o.spass);
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        uint32_t at = 0;
-        for (int p = 0; p < passes; ++p) {
-            spass[4 * p] = at;
-            at += spass[4 * p + 1] + spass[4 * p + 2];
+    // features of the compacted positions, the bit per position that starts a run
+    return static_cast<size_t>(chunks_padded) * 16 + static_cast<size_t>(chunks_padded) + 16;
+}
+
+__global__ __launch_bounds__(kPlanThreads) void k_plan(uint8_t *plan, const int32_t *__restrict__ idx, int E, int k,
+                                                       int G, int r, int chunks, int chunks_padded, int dslots,
+                                                       int sblk_cap, PlanOffsets o)
+{
+    extern __shared__ u32x4 smem_plan[];
+    uint16_t *src = reinterpret_cast<uint16_t *>(smem_plan);                       // [8 * chunks_padded]
+    uint64_t *starts = reinterpret_cast<uint64_t *>(src + 8 * chunks_padded);      // [chunks_padded / 8]
+    __shared__ uint32_t sel[TPQ_MAX_E / 32];            // bit j: feature j is selected
+    __shared__ uint16_t sel_before[TPQ_MAX_E / 32];     // selected features below 32 w
+    __shared__ int wave_part[kPlanThreads / 64];
+    __shared__ uint64_t flags[kPlanMaxPasses];          // bit of chunk: has a slot
+    __shared__ int slots_before[kPlanMaxPasses + 1];
+    __shared__ int n_blocks[kPlanMaxPasses], n_narrow[kPlanMaxPasses], entry0[kPlanMaxPasses + 1];
+    __shared__ uint16_t pos16[64][8];                   // the segment's window entries
+    __shared__ uint32_t seg_slot[128][2], seg_sel[128]; // its first 128 slots and selected features
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int passes = chunks_padded / 64, P = dir_passes_of(passes);
+    const int sg = blockIdx.x, p0 = sg * P, p1 = min(p0 + P, passes);  // this workgroup's segment
+
+    // ---- the index set: valid? as a bit mask -------------------------------------------
+    const int words = (E + 31) / 32;
+    for (int w = tid; w < words; w += kPlanThreads) sel[w] = 0u;
+    if (tid < 512) pos16[tid >> 3][tid & 7] = 0;
+    __syncthreads();
+    bool bad = false;
+    int32_t *pidx = reinterpret_cast<int32_t *>(plan + o.idx);
+    for (int p = tid; p < (k + 3) / 4 * 4; p += kPlanThreads) {
+        int v = 0;
+        if (p < k) {
+            v = idx[p];
+            const bool ok = v >= 0 && v < E && (p == 0 || v > idx[p - 1]);
+            if (ok)
+                atomicOr(&sel[v >> 5], 1u << (v & 31));
+            else
+                v = 0;
+            bad |= !ok;
+        }
+        if (sg == 0) pidx[p] = v;
+    }
+    bad = __syncthreads_or(bad);
+
+    if (!bad) {
+        // ---- compacted positions -> features -----------------------------------------------
+        const int mine = tid < words ? __builtin_popcount(sel[tid]) : 0;  // (TPQ_MAX_E / 32 = one word a thread)
+        int before = wave_exclusive_sum(mine, lane);
+        if (lane == 63) wave_part[wave] = before + mine;
+        __syncthreads();
+        for (int w = 0; w < wave; ++w) before += wave_part[w];
+        if (tid < words) sel_before[tid] = static_cast<uint16_t>(before);
+        __syncthreads();
+        for (int j = tid; j < E; j += kPlanThreads) {
+            const uint32_t m = sel[j >> 5], bit = 1u << (j & 31);
+            if (!(m & bit)) src[j - sel_before[j >> 5] - __builtin_popcount(m & (bit - 1u))] = static_cast<uint16_t>(j);
+        }
+        __syncthreads();
+        // positions past r repeat the last real one
+        for (int c = r + tid; c < 8 * chunks_padded; c += kPlanThreads) src[c] = src[r - 1];
+        // runs of consecutive columns (cut at every pass), and the chunks that need a slot
+        for (int c = tid; c < 8 * chunks_padded; c += kPlanThreads) {
+            const bool s = c < r && ((c & 511) == 0 || src[c] != src[c - 1] + 1);
+            const uint64_t m = __builtin_amdgcn_ballot_w64(s);
+            if (lane == 0) starts[c >> 6] = m;
+        }
+        for (int c = tid; c < chunks_padded; c += kPlanThreads) {
+            const uint64_t m = __builtin_amdgcn_ballot_w64(c < chunks && dir_needs_slot(src, c, E, r));
+            if (lane == 0) flags[c >> 6] = m;
+        }
+        __syncthreads();
+
+        // ---- slots and store entries of every pass, and how many come before ---------------
+        for (int p = wave; p < passes; p += kPlanThreads / 64) {
+            int nb, nn;
+            pass_entries<false>(starts + 8 * p, min(512, r - 512 * p), lane, nullptr, nullptr, 0, nb, nn);
+            if (lane == 0) {
+                n_blocks[p] = nb;
+                n_narrow[p] = nn;
+            }
+        }
+        __syncthreads();
+        if (wave == 0) {
+            const int nq = lane < passes ? __builtin_popcountll(flags[lane]) : 0;
+            const int ne = lane < passes ? n_blocks[lane] + n_narrow[lane] : 0;
+            const int q = wave_exclusive_sum(nq, lane), e = wave_exclusive_sum(ne, lane);
+            slots_before[lane] = q;
+            entry0[lane] = e;
+            if (lane == 63) {
+                slots_before[64] = q + nq;
+                entry0[64] = e + ne;
+            }
+        }
+        __syncthreads();
+    }
+
+    // ---- header ------------------------------------------------------------------------
+    if (sg == 0 && tid == 0) {
+        PlanHeader h = {};
+        h.magic = kPlanMagic;
+        h.status = bad ? kPlanBadIndex : kPlanOk;
+        h.E = E;
+        h.k = k;
+        h.G = G;
+        h.r = r;
+        h.chunks = chunks;
+        h.chunks_padded = chunks_padded;
+        h.idx_offset = o.idx;
+        h.src_offset = o.src;
+        h.dirr_offset = o.dirr;
+        h.dsel_offset = o.dsel;
+        h.dslots = dslots;
+        h.dslot8_offset = o.dslot8;
+        h.dir_P = P;
+        h.dseg_offset = o.dseg;
+        h.drec_offset = o.drec;
+        h.drec2_offset = o.drec2;
+        h.spass_offset = o.spass;
+        h.sblk_offset = o.sblk;
+        h.sblk_cap = sblk_cap;
+        if (!bad) {
+            h.n_dirr = slots_before[64];
+            // the bounds of dir_slots_of() and sblk_cap_of() hold for every index set; a plan
+            // for which they did not would be refused
+            if (slots_before[64] > dslots || entry0[64] > sblk_cap) h.status = kPlanInternal;
+        }
+        *reinterpret_cast<PlanHeader *>(plan) = h;
+    }
+    if (bad || passes == 0 || slots_before[64] > dslots || entry0[64] > sblk_cap) return;
+
+    // ---- this segment's tables -----------------------------------------------------------
+    {
+        uint32_t *dst = reinterpret_cast<uint32_t *>(plan + o.src);
+        const uint32_t *s32 = reinterpret_cast<const uint32_t *>(src);
+        for (int i = 256 * p0 + tid; i < 256 * p1; i += kPlanThreads) dst[i] = s32[i];
+    }
+    const int q_lo = slots_before[p0], n_q = slots_before[p1] - q_lo;
+    const int s_lo = sg == 0 ? 0 : src[512 * p0] - 512 * p0;                      // selected columns below the
+    const int s_hi = p1 == passes ? k : src[512 * p1] - 512 * p1;                 // segment's first feature
+    // slot number and window of a chunk that has one
+    auto slot_of = [&](int c) {
+        return slots_before[c >> 6] + __builtin_popcountll(flags[c >> 6] & ((1ull << (c & 63)) - 1ull));
+    };
+    for (int c = 64 * p0 + tid; c < min(64 * p1, chunks); c += kPlanThreads) {
+        const int p = (c >> 6) - p0, c0 = src[8 * c];
+        if (!((flags[c >> 6] >> (c & 63)) & 1u)) {
+            pos16[c & 63][p] = static_cast<uint16_t>((c0 >> 1) | ((c0 & 1) ? kDir16Odd : 0u));
+            continue;
+        }
+        const int q = slot_of(c);
+        const int nv = min(r - 8 * c, 8), wa = dir_window_a(src, c, E, r), wb = min(wa + 8, E - 8);
+        pos16[c & 63][p] = static_cast<uint16_t>((wa >> 1) | kDir16Slot);
+        int at[8];
+        bool wide = false;
+        for (int e = 0; e < 8; ++e) {  // (absent features repeat the last one)
+            at[e] = dir_slot_offset(src[8 * c + min(e, nv - 1)], wa, E);
+            wide |= at[e] < 0;
+        }
+        uint16_t *dirr = reinterpret_cast<uint16_t *>(plan + o.dirr) + 8 * q;
+        uint32_t nib = 0;
+        for (int e = 0; e < 8; ++e) {
+            dirr[e] = static_cast<uint16_t>(wide ? kDirWide | src[8 * c + min(e, nv - 1)] : static_cast<uint32_t>(at[e]));
+            if (!wide) nib |= static_cast<uint32_t>(at[e] >> 1) << (4 * e);
+        }
+        // does the next lane of the pass load exactly the second window?
+        bool next_has_b = false;
+        if ((c & 63) != 63 && c + 1 < chunks) {
+            const bool next_slot = (flags[c >> 6] >> ((c & 63) + 1)) & 1u;
+            next_has_b = (next_slot ? dir_window_a(src, c + 1, E, r) : (src[8 * (c + 1)] & ~1)) == wb;
+        }
+        const uint32_t second = static_cast<uint32_t>(2 * wb) | (wide ? kDirWide8 : 0u) | (next_has_b ? 0u : kDirLoadB8);
+        *reinterpret_cast<uint2 *>(plan + o.dslot8 + 8 * q) = make_uint2(nib, second);
+        if (q - q_lo < 128) {
+            seg_slot[q - q_lo][0] = nib;
+            seg_slot[q - q_lo][1] = second;
+        }
+    }
+    // the slot that holds each selected column of the segment: that of the chunk with the feature
+    // before it
+    for (int p = s_lo + tid; p < s_hi; p += kPlanThreads) {
+        const int j = idx[p], f = j - p;  // compacted features before column j
+        const int c = f >= 1 ? (f - 1) / 8 : 0;
+        uint32_t v = kDirFar;
+        if ((flags[c >> 6] >> (c & 63)) & 1u) {
+            const int off = dir_slot_offset(j, dir_window_a(src, c, E, r), E);
+            if (off >= 0) v = (static_cast<uint32_t>(slot_of(c)) << 5) | static_cast<uint32_t>(off);
+        }
+        reinterpret_cast<uint32_t *>(plan + o.dsel)[p] = v;
+        if (p - s_lo < 128) seg_sel[p - s_lo] = v;
+    }
+    // store entries, from the last waves down (the first ones have the chunks)
+    for (int p = p0 + kPlanThreads / 64 - 1 - wave; p < p1; p += kPlanThreads / 64) {
+        if (lane == 0)
+            reinterpret_cast<uint4 *>(plan + o.spass)[p] =
+                make_uint4(static_cast<uint32_t>(entry0[p]), static_cast<uint32_t>(n_blocks[p]),
+                           static_cast<uint32_t>(n_narrow[p]), 0u);
+        int nb, nn;
+        pass_entries<true>(starts + 8 * p, min(512, r - 512 * p), lane, src + 512 * p,
+                           reinterpret_cast<uint32_t *>(plan + o.sblk) + entry0[p], n_blocks[p], nb, nn);
+    }
+    __syncthreads();
+    // the records the encoder's lanes start from
+    if (tid == 0)
+        *reinterpret_cast<uint2 *>(plan + o.dseg + 8 * sg) =
+            make_uint2(static_cast<uint32_t>(q_lo) | (static_cast<uint32_t>(n_q) << 16),
+                       static_cast<uint32_t>(s_lo) | (static_cast<uint32_t>(s_hi - s_lo) << 16));
+    if (tid < 128) {
+        const int n_sel = s_hi - s_lo;
+        const uint32_t a0 = tid < n_q ? seg_slot[tid][0] : 0u, a1 = tid < n_q ? seg_slot[tid][1] : 0u;
+        const uint32_t sv = tid < n_sel ? seg_sel[tid] : static_cast<uint32_t>(q_lo) << 5;  // idle: the first slot
+        if (tid < 64) {
+            u32x4 *rec = reinterpret_cast<u32x4 *>(plan + o.drec) + 2 * (64 * sg + tid);
+            const uint32_t *pw = reinterpret_cast<const uint32_t *>(pos16[tid]);
+            rec[0] = u32x4{pw[0], pw[1], pw[2], pw[3]};
+            rec[1] = u32x4{a0, a1, sv, 0u};
+        } else {
+            reinterpret_cast<u32x4 *>(plan + o.drec2)[64 * sg + lane] = u32x4{a0, a1, sv, 0u};
         }
     }
 }
@@ -402,25 +380,17 @@ int launch_static_params(const tpq_layout *L, const void *plan, const float *m, 
 
 int launch_plan_build(const tpq_layout *L, const int32_t *idx, void *plan, hipStream_t s)
 {
-    const int E = L->E, k = L->k, r = L->r;
-    const int chunks = chunks_of(r), cp = chunks_padded_of(r);
-    const PlanOffsets o = plan_offsets(k, r, L->G);
-    uint8_t *p = static_cast<uint8_t *>(plan);
-    k_plan_init<<<1, 64, 0, s>>>(p, E, k, L->G, r, chunks, cp, o);
-    k_plan_build<<<(E + 255) / 256, 256, 0, s>>>(p, idx, E, k, r, o);
-    const int tail = 8 * cp - r;
-    if (r > 0 && tail > 0) k_plan_pad<<<(tail + 255) / 256, 256, 0, s>>>(p, r, cp, o);
-    k_plan_pass_col<<<1, 128, 0, s>>>(p, E, chunks, cp / 64, o);
-    if (cp > 0) k_plan_dflags<<<(cp + 255) / 256, 256, 0, s>>>(p, E, r, chunks, cp, o);
-    k_plan_dslots<<<(cp + 1 + 255) / 256, 256, 0, s>>>(p, E, r, chunks, cp, dir_slots_of(k, r), o);
-    if (cp > 0) k_plan_dseg<<<1, 64, 0, s>>>(p, k, cp, o);
-    if (k > 0) k_plan_dsel<<<((k + 3) / 4 * 4 + 255) / 256, 256, 0, s>>>(p, E, k, r, o);
-    if (cp > 0) k_plan_drec<<<(dir_segs_of(cp / 64) * 64 + 255) / 256, 256, 0, s>>>(p, cp, o);
-    if (cp > 0) {
-        k_plan_sblk<false><<<cp / 64, 512, 0, s>>>(p, r, o, sblk_cap_of(k, r));
-        k_plan_sblk_offsets<<<1, 64, 0, s>>>(p, cp / 64, o);
-        k_plan_sblk<true><<<cp / 64, 512, 0, s>>>(p, r, o, sblk_cap_of(k, r));
+    const int cp = chunks_padded_of(L->r);
+    const size_t lds = plan_lds_bytes(cp);
+    if (lds > 49152) {  // (with the static tables past the default limit of 64 KiB)
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_plan),
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
+        if (e != hipSuccess) return hip_result(e);
     }
+    const int segs = dir_segs_of(cp / 64);
+    k_plan<<<segs > 0 ? segs : 1, kPlanThreads, lds, s>>>(
+        static_cast<uint8_t *>(plan), idx, L->E, L->k, L->G, L->r, chunks_of(L->r), cp, dir_slots_of(L->k, L->r),
+        sblk_cap_of(L->k, L->r), plan_offsets(L->k, L->r, L->G));
     return hip_result(hipGetLastError());
 }
 

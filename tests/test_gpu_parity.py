@@ -272,6 +272,19 @@ def test_plan_store_blocks(E, cols):
     assert at <= cap
 
 
+@pytest.mark.parametrize("E,cols", [
+    (8192, list(range(31, 8192, 32))),                        # one per word of the plan's bit mask
+    (5120, list(range(0, 200)) + list(range(4920, 5120))),    # whole words; the row's two ends
+    (5128, list(range(2, 5128, 17))),                         # more than 128 slots in a segment
+    (2568, [511, 512, 513, 1023, 1025, 2559, 2560, 2567]),    # around the passes' ends
+    (16384, list(range(1, 16384))),                           # one feature is left
+])
+def test_plan_table_edges(E, cols):
+    """Index sets at the edges of the plan build's words, passes and segments, through the codec."""
+    w = dataclasses.replace(wl.LLAMA_PREFILL, N=2, T=3, E=E, k=len(cols), G=128)
+    _codec_case(w, wl.partial_sums(w, device="cuda"), np.array(cols, np.int32))
+
+
 def test_determinism():
     w = dataclasses.replace(wl.LLAMA_PREFILL, T=64)
     Ys = wl.partial_sums(w, device="cuda")
