@@ -158,7 +158,7 @@ __global__ __launch_bounds__(256) void k_ema(const float *__restrict__ partial, 
 
 // The number of compute units of the current device (looked up once per device: the query is
 // slow compared with a launch).
-static hipError_t compute_units_of_current_device(int *out)
+hipError_t compute_units_of_current_device(int *out)
 {
     constexpr int kMaxDevices = 64;
     static std::atomic<int> known[kMaxDevices];

@@ -15,6 +15,26 @@
 // row operand and the tokens its column operand, so that a lane's 16 accumulators of a 32x32
 // block are 16 features of ONE token: the per-token statistics stay inside a lane (and its
 // partner 32 lanes on), and the nibbles of a chunk sit in at most two lanes.
+//
+// How it is fed.  A wave owns 128 features x 32 NTB tokens, so a k-step of 16 costs it 4 + NTB
+// fragment reads from LDS for 4 NTB products (with 64 x 64 per wave, LDS reads alone take as long
+// as the products).  Operands go straight from memory to LDS (buffer loads with the LDS bit) in
+// stages of 32 k, through a ring of 5 or more stages, so that a stage has 2 to 5 stages' time to
+// arrive; the two stages that share the rows' cache lines are loaded together, the second one
+// from L1.  Between two products stands at most one fetch or load wherever there are as many
+// products, in that order (the scheduler is pinned), and a stage costs one barrier.  One
+// workgroup holds a compute unit, one wave a SIMD.
+//
+// What bounds it, at T = 2048, E = 5120, K = 1728 (one MI355X, launched back to back): 37.5 us =
+// 966 TFLOP/s where operands that went through registers, 64 x 64 per wave and two barriers a
+// stage took 61 us; the loop runs at 85 % of the matrix cores' rate in cycles, at a clock that
+// the full chip's power limit holds near 1.6 GHz; about 10 us are the ends (first loads, epilogue,
+// launch), which a single round of tiles cannot hide.  With few tokens it is bound by what one
+// compute unit can have outstanding to memory beyond its L2, about 52 bytes/ns whatever the
+// access pattern, on E / 128 of them (a group's features stay on one): 18 -> 16 us against 30 us
+// before at T = 13, K = 1728, 9.4 against 14.1 at K = 640.
+#include <atomic>
+
 #include "tpq_device.h"
 #include "tpq_internal.h"
 
@@ -22,14 +42,6 @@ namespace tpq {
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
-
-// k per stage: a row of a stage is 128 bytes, one whole cache line per request to L2
-constexpr int kGemmBK = 64;
-constexpr int kGemmPPR = kGemmBK / 8;        // 16-byte pieces per operand row of a stage
-constexpr int kGemmRow = kGemmBK * 2;        // LDS bytes per operand row of a stage
-// piece p of row m sits at slot p ^ (m % 8): the lanes that fetch the same piece of consecutive
-// rows (an MFMA operand) spread over all banks, and so do the lanes that write a row's pieces
-__device__ __forceinline__ uint32_t gemm_swz(uint32_t row) { return row & 7u; }
 
 // Rows of Wt ([E][ldW], one row per output feature) -> Wp [E][K] in message order.
 __global__ __launch_bounds__(256) void k_gemm_weights(const uint8_t *plan, int E, int k, int G, int r,
@@ -56,289 +68,474 @@ struct GemmArgs {
     int64_t ldYm;
 };
 
-// One (token block of 32) of a wave's accumulators -> message.  y[fb][v]: feature
-// F0 + 32 fb + 8 (v / 4) + 4 h + v % 4 of token t, h = lane / 32 (a wave has 64 features:
-// fb = 0, 1).  RAGGED: the wave's 64 features are not all quantised ones (the row's last
-// groups, the outlier section, the padding past E); otherwise nothing needs a mask.
-// A group wider than the wave's 64 features lies in G / 64 waves of the workgroup that
-// work on the same tokens: their minima and maxima meet in LDS (xch).
-template <int G, int WF, bool RAGGED>
-__device__ __forceinline__ void gemm_epilogue(const GemmArgs &a, float (&y)[2][16], uint32_t F0, int64_t t,
-                                              bool t_ok, uint32_t h, float *xch, uint32_t wm, uint32_t tslot,
-                                              uint32_t n_tslots)
+// Tile of a workgroup: FW x TW waves, each with 128 features x 32 NTB tokens.  A group (up to 128 features) lies in
+// one wave, groups of 256 in the two waves of FW = 2.
+constexpr int kTileBK = 32;  // k per stage
+template <int FW, int TW, int NTB>
+struct TileShape {
+    static constexpr int waves = FW * TW, threads = 64 * waves;
+    static constexpr int ft = 128 * FW, tt = 32 * NTB * TW;          // features and tokens of the tile
+    static constexpr int stage = (ft + tt) * kTileBK * 2;            // LDS bytes of a stage
+    static constexpr int nla = ft / (16 * waves), nl = nla + tt / (16 * waves);  // loads of a wave per stage: weights, all
+    static constexpr int n1 = (2 * nl + 2) / 3, n2 = (2 * nl + 1 - n1) / 2 + n1;  // loads of a pair: three phases' shares
+    // pairs of stages on their way in: as many as LDS holds beside the half pair that is being freed, and the wait
+    // counter (63) can tell apart
+    static constexpr int pairs_lds = (163840 / stage - 1) / 2, pairs_cnt = (63 - n2) / (2 * nl) + 2;
+    static constexpr int pairs = pairs_lds < pairs_cnt ? pairs_lds : pairs_cnt;
+    static constexpr int nbuf = 2 * pairs + 1;
+    static constexpr int lds = nbuf * stage;
+    static_assert(pairs >= 2 && (pairs - 2) * 2 * nl + n2 <= 63 && tt * (ft * 2 + 16) <= lds, "tile fits");
+};
+
+#define TPQ_PIN __builtin_amdgcn_sched_barrier(0)
+
+// the value of lane ^ 32 beside the lane's own, in a fixed order: x = lower half's, y = upper half's
+__device__ __forceinline__ void both_halves(uint32_t v, uint32_t &x, uint32_t &y)
 {
-    constexpr float kBig = 3.3895314e38f;  // the largest finite bf16
-    const int r = a.r;
-    // the rounded product, if asked for
-    if (a.Ymsg && t_ok) {
-        uint16_t *yrow = a.Ymsg + t * a.ldYm;
+    const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    x = r[0];
+    y = r[1];
+}
+
+// A workgroup's tile in LDS, one row of FT features per token: the features that stay bf16, [r, E) of its columns, to the
+// outlier section; and the whole of it to the optional product.  Eight rows' reads at once: with one wave per SIMD
+// nothing else hides the LDS latency.
+template <int FT, int THREADS>
+__device__ __forceinline__ void rows_selected(const GemmArgs &a, const uint8_t *tile, uint32_t tileF, int64_t tileT,
+                                              int n_tok, uint32_t tid)
+{
+    constexpr uint32_t pitch = FT * 2 + 16;
+    const int o0 = max(static_cast<int>(tileF) - a.r, 0), o1 = min(static_cast<int>(tileF) + FT, a.E) - a.r;
+    if (o1 <= o0) return;
+    const int n_live = a.T - tileT < n_tok ? static_cast<int>(a.T - tileT) : n_tok;
+    const uint8_t *col0 = tile + 2 * (a.r - static_cast<int>(tileF));  // position 0 of the section (o0 on lies in the tile)
+    uint8_t *out0 = a.outl + tileT * a.pitch_outl;
+    const uint32_t po = static_cast<uint32_t>(a.pitch_outl);
+    // positions that share their 32-bit word with another tile's
+    for (uint32_t tt = tid; tt < static_cast<uint32_t>(n_live); tt += THREADS) {
+        if (o0 & 1)
+            *reinterpret_cast<uint16_t *>(out0 + tt * po + 2u * o0) = *reinterpret_cast<const uint16_t *>(col0 + tt * pitch + 2 * o0);
+        if (o1 & 1)
+            *reinterpret_cast<uint16_t *>(out0 + tt * po + 2u * (o1 - 1)) =
+                *reinterpret_cast<const uint16_t *>(col0 + tt * pitch + 2 * (o1 - 1));
+    }
+    const int d0 = (o0 + 1) >> 1, nd = (o1 >> 1) - d0;  // whole words
+    int lg = 3;                                         // lanes per token: 8 .. 64
+    while (lg < 6 && (1 << lg) < nd) ++lg;
+    const uint32_t step = static_cast<uint32_t>(THREADS) >> lg;
+    for (int d = static_cast<int>(tid & ((1u << lg) - 1u)); d < nd; d += 1 << lg) {
+        const uint8_t *src = col0 + 4 * (d0 + d);
+        uint8_t *dst = out0 + 4u * static_cast<uint32_t>(d0 + d);
+        for (uint32_t tt0 = tid >> lg; tt0 < static_cast<uint32_t>(n_live); tt0 += 8 * step) {
+            uint32_t x[8];
 #pragma unroll
-        for (int fb = 0; fb < 2; ++fb) {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const uint32_t f = F0 + 32u * fb + 8u * j + 4u * h;
-                if (f < static_cast<uint32_t>(a.E)) {
-                    const uint2 w = make_uint2(
-                        (__float_as_uint(y[fb][4 * j]) >> 16) | (__float_as_uint(y[fb][4 * j + 1]) & 0xFFFF0000u),
-                        (__float_as_uint(y[fb][4 * j + 2]) >> 16) | (__float_as_uint(y[fb][4 * j + 3]) & 0xFFFF0000u));
-                    *reinterpret_cast<uint2 *>(yrow + f) = w;
-                }
+            for (int u = 0; u < 8; ++u) {
+                const uint8_t *q = src + min(tt0 + u * step, static_cast<uint32_t>(n_live) - 1u) * pitch;
+                x[u] = *reinterpret_cast<const uint16_t *>(q) | (static_cast<uint32_t>(*reinterpret_cast<const uint16_t *>(q + 2)) << 16);
             }
-        }
-    }
-    // min / max per block of 32 features, over the quantised ones
-    float mn[2], mx[2];
 #pragma unroll
-    for (int fb = 0; fb < 2; ++fb) {
-        float lo = kBig, hi = -kBig;
-        const int lim = r - static_cast<int>(F0 + 32u * fb + 4u * h);  // element offsets below this are quantised
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const bool ok = !RAGGED || (8 * (v >> 2) + (v & 3)) < lim;
-            lo = fminf(lo, ok ? y[fb][v] : kBig);
-            hi = fmaxf(hi, ok ? y[fb][v] : -kBig);
-        }
-        mn[fb] = fminf(lo, __shfl_xor(lo, 32, 64));
-        mx[fb] = fmaxf(hi, __shfl_xor(hi, 32, 64));
-    }
-    if (G >= 64) {
-        mn[0] = mn[1] = fminf(mn[0], mn[1]);
-        mx[0] = mx[1] = fmaxf(mx[0], mx[1]);
-    }
-    constexpr int WPG = G > 64 ? G / 64 : 1;  // waves per group
-    static_assert(WPG <= WF, "a group must lie inside the workgroup's features");
-    if (WPG > 1) {
-        float *mine = xch + (wm * n_tslots + tslot) * 2u;
-        if (h == 0) {
-            mine[0] = mn[0];
-            mine[1] = mx[0];
-        }
-        __syncthreads();
-        const uint32_t w0 = wm & ~static_cast<uint32_t>(WPG - 1);
-        float lo = kBig, hi = -kBig;
-#pragma unroll
-        for (int q = 0; q < WPG; ++q) {
-            const float *o = xch + ((w0 + q) * n_tslots + tslot) * 2u;
-            lo = fminf(lo, o[0]);
-            hi = fmaxf(hi, o[1]);
-        }
-        __syncthreads();
-        mn[0] = mn[1] = lo;
-        mx[0] = mx[1] = hi;
-    }
-    // zero, bf16 scale, reciprocal (the arithmetic of the stand-alone encoder); lane h = 0
-    // stores the scales, its partner the zeros
-    float inv[2];
-    constexpr int NG = G == 32 ? 2 : 1;  // groups in the wave's 64 features
-#pragma unroll
-    for (int gi = 0; gi < NG; ++gi) {
-        mn[gi] = mn[gi] + 0.0f;  // a zero minimum is stored as +0
-        const float s32 = div_by_15(mx[gi] - mn[gi]);
-        const uint32_t sb = pack_bf16x2(s32, s32) & 0xFFFFu;
-        const float s = bf16_bits_to_f32(sb);
-        const bool constant = s < 1e-30f;
-        inv[gi] = constant ? 0.0f : reciprocal_of_scale(s);
-        const uint32_t g = G == 32 ? F0 / 32u + gi : F0 / static_cast<uint32_t>(G);
-        const bool owner = WPG == 1 || (wm & (WPG - 1)) == 0;
-        if (t_ok && owner && g < static_cast<uint32_t>(a.ng)) {
-            uint16_t *dst = reinterpret_cast<uint16_t *>((h ? a.zero : a.scale) + t * a.pitch_meta) + g;
-            *dst = static_cast<uint16_t>(h ? __float_as_uint(mn[gi]) >> 16 : (constant ? 0u : sb));
-        }
-    }
-    if (NG == 1) {
-        mn[1] = mn[0];
-        inv[1] = inv[0];
-    }
-    // codes: a lane has 4 consecutive features of every chunk (its low or its high half)
-    uint8_t *crow = a.codes + t * a.pitch_codes;
-#pragma unroll
-    for (int fb = 0; fb < 2; ++fb) {
-        uint32_t half[4];
-        const int lim = r - static_cast<int>(F0 + 32u * fb + 4u * h);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            uint32_t b = 0;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const bool ok = !RAGGED || (8 * j + e) < lim;
-                const float p = (y[fb][4 * j + e] - mn[fb]) * inv[fb];
-                b = __builtin_amdgcn_cvt_pk_u8_f32(ok ? p : 0.0f, e, b);
-            }
-            const uint32_t tt = b | (b >> 4);             // bytes 0 and 2: two nibbles each
-            half[j] = (tt & 0xFFu) | ((tt >> 8) & 0xFF00u);
-        }
-        const uint32_t p0 = half[0] | (half[1] << 16), p1 = half[2] | (half[3] << 16);
-        // lane h = 0 assembles chunks 0 and 1 of the block, its partner chunks 2 and 3
-        const uint32_t recv = __shfl_xor(h ? p0 : p1, 32, 64);
-        const uint32_t lo = h ? recv : p0, hi = h ? p1 : recv;
-        const uint32_t wa = (lo & 0xFFFFu) | (hi << 16), wb = (lo >> 16) | (hi & 0xFFFF0000u);
-        const uint32_t ca = (F0 + 32u * fb) / 8u + 2u * h;
-        if (t_ok) {
-            if (!RAGGED || ca + 1u < static_cast<uint32_t>(a.chunks))
-                *reinterpret_cast<uint2 *>(crow + 4u * ca) = make_uint2(wa, wb);
-            else if (ca < static_cast<uint32_t>(a.chunks))
-                *reinterpret_cast<uint32_t *>(crow + 4u * ca) = wa;
-        }
-    }
-    // the features that stay bf16
-    if (RAGGED && t_ok) {
-        uint16_t *orow = reinterpret_cast<uint16_t *>(a.outl + t * a.pitch_outl);
-#pragma unroll
-        for (int fb = 0; fb < 2; ++fb) {
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int f = static_cast<int>(F0 + 32u * fb + 4u * h) + 8 * (v >> 2) + (v & 3);
-                if (f >= r && f < a.E) orow[f - r] = static_cast<uint16_t>(__float_as_uint(y[fb][v]) >> 16);
+            for (int u = 0; u < 8; ++u) {  // (rows past the last write its values again)
+                const uint32_t tt = min(tt0 + u * step, static_cast<uint32_t>(n_live) - 1u);
+                *reinterpret_cast<uint32_t *>(dst + tt * po) = x[u];
             }
         }
     }
 }
 
-// Workgroup = WF x WT waves, each with a tile of 64 features x 64 tokens (four 32x32 blocks);
-// the workgroup's tile is 64 WF features x 64 WT tokens.  One LDS stage of 64 k; the next
-// stage's operands are loaded into registers while the current one is multiplied.
-template <int G, int WF, int WT>
-__global__ __launch_bounds__(64 * WF * WT, 768 / (64 * WF * WT)) void k_gemm_encode(GemmArgs a)
+template <int FT, int THREADS>
+__device__ __forceinline__ void rows_product(const GemmArgs &a, const uint8_t *tile, uint32_t tileF, int64_t tileT,
+                                             int n_tok, uint32_t tid)
 {
-    constexpr int NT = 64 * WF * WT;            // threads
-    constexpr int ROWS_A = 64 * WF, ROWS_B = 64 * WT;
-    constexpr int NP = (ROWS_A + ROWS_B) * kGemmPPR / NT;  // 16-byte pieces per thread and stage
-    static_assert((ROWS_A + ROWS_B) * kGemmPPR % NT == 0 && (ROWS_A * kGemmPPR) % NT == 0, "pieces divide evenly");
-    constexpr int NPA = ROWS_A * kGemmPPR / NT;     // ... of which the weights'
-    constexpr int RPP = NT / kGemmPPR;              // rows the threads cover in one pass
+    constexpr uint32_t pitch = FT * 2 + 16, LPT = FT / 8, STEP = THREADS / LPT;  // lanes per token, tokens at once
+    const uint32_t c = tid % LPT, n0 = tileF + 8u * c;
+    if (n0 >= static_cast<uint32_t>(a.E)) return;
+    for (uint32_t tt = tid / LPT; tt < static_cast<uint32_t>(n_tok); tt += STEP)
+        if (tileT + tt < a.T)
+            *reinterpret_cast<u32x4 *>(a.Ymsg + (tileT + tt) * a.ldYm + n0) =
+                *reinterpret_cast<const u32x4 *>(tile + tt * pitch + 16u * c);
+}
+
+// One block of 32 tokens of a wave's accumulators (128 features from F0 on) -> message.
+template <int G>
+__device__ __forceinline__ void tile_epilogue(const GemmArgs &a, float (&y)[4][16], bool ragged, uint32_t F0, int64_t t,
+                                              bool t_ok, uint32_t h, float *xch, uint32_t wf, uint32_t tslot)
+{
+    constexpr float kBig = 3.3895314e38f;
+    constexpr int NG = G >= 128 ? 1 : 128 / G, BPG = 4 / NG;  // groups of the wave, blocks of 32 features per group
+    if (ragged) {
+        // positions past the quantised features repeat their group's first one, so that the range stays its own
+        // (a group without any is not stored; groups of 256: one that starts past the row's end takes the other wave's
+        // range, which the exchange below leaves alone)
+        int lim = a.r - static_cast<int>(F0 + 4u * h);
+        asm volatile("" : "+v"(lim));  // (64 comparisons anew per block of tokens, not 64 kept masks)
+#pragma unroll
+        for (int g = 0; g < NG; ++g) {
+            uint32_t first, other;
+            both_halves(__float_as_uint(y[g * BPG][0]), first, other);
+#pragma unroll
+            for (int b = 0; b < BPG; ++b)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const int fb = g * BPG + b;
+                    y[fb][v] = 32 * fb + 8 * (v >> 2) + (v & 3) < lim ? y[fb][v] : __uint_as_float(first);
+                }
+        }
+    }
+    float mn[NG], mx[NG];
+#pragma unroll
+    for (int g = 0; g < NG; ++g) {
+        float lo = kBig, hi = -kBig;
+#pragma unroll
+        for (int b = 0; b < BPG; ++b)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int fb = g * BPG + b;
+                lo = fminf(lo, y[fb][v]);
+                hi = fmaxf(hi, y[fb][v]);
+            }
+        uint32_t p, q;
+        both_halves(__float_as_uint(lo), p, q);
+        mn[g] = fminf(__uint_as_float(p), __uint_as_float(q));
+        both_halves(__float_as_uint(hi), p, q);
+        mx[g] = fmaxf(__uint_as_float(p), __uint_as_float(q));
+    }
+    if (G == 256) {  // the two waves that share a group meet in LDS
+        float2 *x = reinterpret_cast<float2 *>(xch);
+        const bool none = ragged && F0 >= static_cast<uint32_t>(a.r);
+        if (h == 0) x[2u * tslot + wf] = none ? make_float2(kBig, -kBig) : make_float2(mn[0], mx[0]);
+        __syncthreads();
+        const float2 o = x[2u * tslot + (wf ^ 1u)];
+        mn[0] = none ? o.x : fminf(mn[0], o.x);
+        mx[0] = none ? o.y : fmaxf(mx[0], o.y);
+    }
+    float inv[NG];
+#pragma unroll
+    for (int g = 0; g < NG; ++g) {
+        mn[g] = mn[g] + 0.0f;
+        const float s32 = div_by_15(mx[g] - mn[g]);
+        const uint32_t sb = pack_bf16x2(s32, s32) & 0xFFFFu;
+        const float s = bf16_bits_to_f32(sb);
+        const bool constant = s < 1e-30f;
+        inv[g] = constant ? 0.0f : reciprocal_of_scale(s);
+        const uint32_t gi = F0 / static_cast<uint32_t>(G) + g;
+        if (t_ok && (G < 256 || wf == 0) && (!ragged || gi < static_cast<uint32_t>(a.ng)))
+            reinterpret_cast<uint16_t *>((h ? a.zero : a.scale) + t * a.pitch_meta)[gi] =
+                static_cast<uint16_t>(h ? __float_as_uint(mn[g]) >> 16 : (constant ? 0u : sb));
+    }
+    uint8_t *crow = a.codes + t * a.pitch_codes;
+#pragma unroll
+    for (int fp = 0; fp < 4; fp += 2) {
+        uint32_t A[2][2];
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+            const int fb = fp + b, g = fb / BPG;
+            uint32_t q[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                float p[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float df = y[fb][4 * j + e] - mn[g];
+                    p[e] = df * inv[g];
+                }
+                uint32_t w = __builtin_amdgcn_cvt_pk_u8_f32(p[1], 0u, 0u);
+                w = __builtin_amdgcn_cvt_pk_u8_f32(p[0], 1u, w);
+                w = __builtin_amdgcn_cvt_pk_u8_f32(p[3], 2u, w);
+                w = __builtin_amdgcn_cvt_pk_u8_f32(p[2], 3u, w);
+                q[j] = (w << 12) | w;
+            }
+            A[b][0] = __builtin_amdgcn_perm(q[1], q[0], 0x07050301u);
+            A[b][1] = __builtin_amdgcn_perm(q[3], q[2], 0x07050301u);
+        }
+        // lower lanes take block fp, upper lanes block fp + 1
+        u32x4 o;
+        {
+            const auto r0 = __builtin_amdgcn_permlane32_swap(A[0][0], A[1][0], false, false);
+            const auto r1 = __builtin_amdgcn_permlane32_swap(A[0][1], A[1][1], false, false);
+            const uint32_t x0 = r0[0], y0 = r0[1], x1 = r1[0], y1 = r1[1];
+            o.x = __builtin_amdgcn_perm(y0, x0, 0x05040100u);
+            o.y = __builtin_amdgcn_perm(y0, x0, 0x07060302u);
+            o.z = __builtin_amdgcn_perm(y1, x1, 0x05040100u);
+            o.w = __builtin_amdgcn_perm(y1, x1, 0x07060302u);
+        }
+        const uint32_t ch = F0 / 8u + 4u * (fp + h);
+        if (!ragged) {
+            if (t_ok) *reinterpret_cast<u32x4 *>(crow + 4u * ch) = o;
+        } else if (t_ok) {
+            const uint32_t w4[4] = {o.x, o.y, o.z, o.w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int n_valid = a.r - 8 * static_cast<int>(ch + e);
+                if (n_valid > 0)
+                    *reinterpret_cast<uint32_t *>(crow + 4u * (ch + e)) = n_valid < 8 ? w4[e] & ((1u << (4 * n_valid)) - 1u) : w4[e];
+            }
+        }
+    }
+}
+
+template <int G, int FW, int TW, int NTB>
+__global__ __launch_bounds__(64 * FW * TW, 1) void k_gemm_tile(GemmArgs a, uint32_t tiles_t)
+{
+    typedef TileShape<FW, TW, NTB> S;
+    static_assert(G <= 128 * FW, "a group lies inside the tile");
+    constexpr int NL = S::nl, NF = 4 + NTB;  // loads per stage; fragments per k-step: 4 of the weights, NTB of the tokens
     extern __shared__ u32x4 smem_gemm[];
     uint8_t *lds = reinterpret_cast<uint8_t *>(smem_gemm);
     const uint32_t tid = threadIdx.x, ln = tid & 63u;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const uint32_t wm = wave / WT, wn = wave % WT;
-    const uint32_t tileF = blockIdx.x * ROWS_A;
-    const int64_t tileT = static_cast<int64_t>(blockIdx.y) * ROWS_B;
+    const uint32_t wf = wave % FW, wt = wave / FW;
+    const uint32_t id = xcd_contiguous_index(blockIdx.x, gridDim.x);
+    const uint32_t tf = id / tiles_t, tt = id - tf * tiles_t;
+    const uint32_t tileF = tf * static_cast<uint32_t>(S::ft);
+    const int64_t tileT = static_cast<int64_t>(tt) * S::tt;
+    if (tileF >= static_cast<uint32_t>(a.E)) return;
     const int K = a.K;
 
-    // this thread's pieces of a stage (piece = 16 bytes = 8 k): row tid / 8 + RPP i of the
-    // weights' rows followed by the tokens' rows, piece tid % 8.  A piece's address is a
-    // uniform base (operand + the stage's first k) plus a 32-bit offset that never changes, so
-    // that no register is written on the way to a load but the load's own destination.
-    const uint32_t prow = tid / kGemmPPR, ppc = tid % kGemmPPR;
-    const int pk = static_cast<int>(ppc) * 8;
-    const int pkc = min(pk, K - 8);  // (K < 64: the pieces past K read a valid one, and count as zeros)
-    uint32_t voff[NP];
+    // a wave's load instruction fills 16 rows of 64 bytes
+    const uint32_t prow = tid / 4, slot = tid % 4;
+    const int pk = static_cast<int>(slot ^ ((prow >> 1) & 3u)) * 8;
+    const int pkc = min(pk, K - 8);
+    uint32_t voff[NL];
 #pragma unroll
-    for (int i = 0; i < NP; ++i) {
-        if (i < NPA) {
-            const uint32_t f = min(tileF + prow + RPP * i, static_cast<uint32_t>(a.E) - 1u);
-            voff[i] = (f * static_cast<uint32_t>(K) + static_cast<uint32_t>(pkc)) * 2u;
-        } else {
-            const int64_t t = min(tileT + prow + RPP * (i - NPA), a.T - 1);
-            voff[i] = static_cast<uint32_t>((t * a.ldX + pkc) * 2);
-        }
+    for (int i = 0; i < S::nla; ++i)
+        voff[i] = (min(tileF + prow + 16 * S::waves * i, static_cast<uint32_t>(a.E) - 1u) * static_cast<uint32_t>(K) + pkc) * 2u;
+#pragma unroll
+    for (int i = 0; i < NL - S::nla; ++i) {
+        const int64_t t = min(tileT + prow + 16 * S::waves * i, a.T - 1);
+        voff[S::nla + i] = static_cast<uint32_t>((t * a.ldX + pkc) * 2);
     }
-    const uint32_t lds_piece = prow * kGemmRow + (ppc ^ gemm_swz(prow)) * 16u;
-
-    // The next stage is on its way in registers while one is multiplied.  Every load is
-    // unconditional: stage kt reads the 64 k from kb = min(64 kt, K - 64) on (the last, partial
-    // stage reads the last 64 k of the row, the stage past the end reads them again), and what
-    // a piece holds counts only if its k is inside the stage: zeros otherwise, put in when the
-    // piece goes to LDS -- nothing may touch a loaded register before its stage is due, or the
-    // wave waits for the load there.
-    const int k_last = max(K - kGemmBK, 0);
-    u32x4 rg[NP];
-    // (buffer loads: descriptor and the stage's k offset in scalar registers, the piece's
-    // offset in a vector register that never changes -- no address arithmetic in vector
-    // registers, which the register allocator would place in the loads' destinations)
-    const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<uint16_t *>(a.Wp), 0, static_cast<int>(static_cast<int64_t>(a.E) * K * 2), 0x00020000);
-    const __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<uint16_t *>(a.X), 0, static_cast<int>(((a.T - 1) * a.ldX + K) * 2), 0x00020000);
-    auto load_stage = [&](int kt) {
-        const int kb = min(kt * kGemmBK, k_last);
-#pragma unroll
-        for (int i = 0; i < NP; ++i)
-            rg[i] = __builtin_amdgcn_raw_buffer_load_b128(i < NPA ? ra : rb, voff[i], 2 * kb, 0);
-    };
-    auto store_stage = [&](int kt) {
-        const int kpos = min(kt * kGemmBK, k_last) + pk;
-        const bool ok = kpos >= kt * kGemmBK && kpos < K;
-#pragma unroll
-        for (int i = 0; i < NP; ++i)
-            *reinterpret_cast<u32x4 *>(lds + lds_piece + RPP * i * kGemmRow) = ok ? rg[i] : u32x4{0u, 0u, 0u, 0u};
+    const uint64_t pa = reinterpret_cast<uint64_t>(a.Wp), pb = reinterpret_cast<uint64_t>(a.X);
+    const u32x4 ra = {static_cast<uint32_t>(pa), static_cast<uint32_t>(pa >> 32),
+                      static_cast<uint32_t>(static_cast<int64_t>(a.E) * K * 2), 0x00020000u};
+    const u32x4 rb = {static_cast<uint32_t>(pb), static_cast<uint32_t>(pb >> 32),
+                      static_cast<uint32_t>(((a.T - 1) * a.ldX + K) * 2), 0x00020000u};
+    const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) uint8_t *)lds)) + wave * 1024u;
+    const int nkt = (K + kTileBK - 1) / kTileBK, np = (nkt + 1) / 2;
+    const int k_last = max(K - kTileBK, 0);
+    auto k_bytes = [&](int kt) { return static_cast<uint32_t>(2 * min(kt * kTileBK, k_last)); };
+    auto dma = [&](int i, uint32_t kb2, uint32_t buf) {
+        const uint32_t m = lds0 + buf + 1024u * S::waves * i;
+        if (i < S::nla)
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(m), "v"(voff[i]), "s"(ra), "s"(kb2) : "memory");
+        else
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(m), "v"(voff[i]), "s"(rb), "s"(kb2) : "memory");
     };
 
-    f32x16 acc[2][2];
+    f32x16 acc[4][NTB];
 #pragma unroll
-    for (int fb = 0; fb < 2; ++fb)
+    for (int fb = 0; fb < 4; ++fb)
 #pragma unroll
-        for (int tb = 0; tb < 2; ++tb)
+        for (int tb = 0; tb < NTB; ++tb)
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[fb][tb][v] = 0.0f;
 
-    // operand fetch: lane = (row of the 32x32 block, half of the 16 k)
-    const uint32_t frag = (ln & 31u) * kGemmRow;
-    const uint32_t fa = (64u * wm) * kGemmRow + frag;
-    const uint32_t fbt = (ROWS_A + 64u * wn) * kGemmRow + frag;
-    uint32_t fk[kGemmBK / 16];  // byte offset in the row of this lane's piece of k-step ks
-#pragma unroll
-    for (int ks = 0; ks < kGemmBK / 16; ++ks) fk[ks] = ((2u * ks + (ln >> 5)) ^ gemm_swz(ln & 31u)) * 16u;
-
-    const int nkt = (K + kGemmBK - 1) / kGemmBK;
-    auto compute_stage = [&](const uint8_t *st) {
-#pragma unroll
-        for (int ks = 0; ks < kGemmBK / 16; ++ks) {
-            u32x4 av[2], bv[2];
-#pragma unroll
-            for (int fb = 0; fb < 2; ++fb)
-                av[fb] = *reinterpret_cast<const u32x4 *>(st + fa + 32u * fb * kGemmRow + fk[ks]);
-#pragma unroll
-            for (int tb = 0; tb < 2; ++tb)
-                bv[tb] = *reinterpret_cast<const u32x4 *>(st + fbt + 32u * tb * kGemmRow + fk[ks]);
-#pragma unroll
-            for (int fb = 0; fb < 2; ++fb)
-#pragma unroll
-                for (int tb = 0; tb < 2; ++tb)
-                    acc[fb][tb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                        __builtin_bit_cast(bf16x8_t, av[fb]), __builtin_bit_cast(bf16x8_t, bv[tb]),
-                        acc[fb][tb], 0, 0, 0);
-        }
+    // fragment i: 0..3 the weights' blocks, 4.. the tokens'
+    const uint32_t row = ln & 31u, h = ln >> 5;
+    const uint32_t fk0 = ((0u + h) ^ ((row >> 1) & 3u)) * 16u, fk1 = ((2u + h) ^ ((row >> 1) & 3u)) * 16u;
+    const uint32_t fa = (128u * wf + row) * 64u, fbt = (static_cast<uint32_t>(S::ft) + 32u * NTB * wt + row) * 64u;
+    u32x4 fr[2][NF];
+    auto fetch = [&](int i, int ks, uint32_t buf) {
+        const uint32_t at = buf + (i < 4 ? fa + 2048u * i : fbt + 2048u * (i - 4)) + (ks ? fk1 : fk0);
+        fr[ks][i] = *reinterpret_cast<const u32x4 *>(lds + at);
     };
-    // registers -> LDS, barrier, the next stage's loads leave, multiply, barrier
-    load_stage(0);
-    for (int kt = 0; kt < nkt; ++kt) {
-        store_stage(kt);
-        __syncthreads();
-        load_stage(kt + 1);
-        __builtin_amdgcn_sched_barrier(0);  // (the loads leave first: nothing is moved above them)
-        compute_stage(lds);
-        __syncthreads();
+    auto mfma = [&](int ks, int j) {
+        const int fb = j / NTB, tb = j % NTB;
+        acc[fb][tb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, fr[ks][fb]),
+                                                              __builtin_bit_cast(bf16x8_t, fr[ks][4 + tb]), acc[fb][tb], 0, 0, 0);
+    };
+    auto next_buf = [&](uint32_t b) { return b + S::stage == S::lds ? 0u : b + S::stage; };
+    auto prev_buf = [&](uint32_t b) { return b == 0u ? static_cast<uint32_t>(S::lds - S::stage) : b - S::stage; };
+    // load j of a pair of stages: piece j / 2 of stage j % 2 (the two halves of a row's cache line
+    // one after the other)
+    auto dma_pair = [&](int j, uint32_t k0, uint32_t k1, uint32_t b0, uint32_t b1) {
+        dma(j >> 1, (j & 1) ? k1 : k0, (j & 1) ? b1 : b0);
+    };
+    // One phase: the 4 NTB products of k-step KS, and between them the fetch of the other k-step's
+    // fragments and loads D0 .. D1 - 1 of the pair that is on its way in -- the fetches first, one memory
+    // instruction behind each product where there are as many.
+#define TPQ_PHASE(KS, FK, FBUF, D0, D1)                                                             \
+    _Pragma("unroll") for (int j = 0; j < SLOTS; ++j)                                               \
+    {                                                                                               \
+        if (j < 4 * NTB) mfma(KS, j);                                                               \
+        if (j < NF) fetch(j, FK, FBUF);                                                             \
+        const int q = D1 - 1 - (SLOTS - 1 - j);                                                     \
+        if (q >= D0 && q < D1) dma_pair(q, kb0, kb1, d0, d1);                                       \
+        TPQ_PIN;                                                                                    \
     }
-
-    // epilogue, one block of 32 tokens at a time
-    const uint32_t F0 = tileF + 64u * wm;
-    const uint32_t h = ln >> 5;
-    float *xch = reinterpret_cast<float *>(lds);  // (the stages are done with: the last barrier has passed)
-    const bool ragged = F0 + 64u > static_cast<uint32_t>(a.r);
+    constexpr int SLOTS = 4 * NTB > NF ? (4 * NTB > S::n1 ? 4 * NTB : S::n1) : (NF > S::n1 ? NF : S::n1);
+    constexpr int N1 = S::n1, N2 = S::n2;
+    // prologue
 #pragma unroll
-    for (int tb = 0; tb < 2; ++tb) {
-        const int64_t t = tileT + 64 * wn + 32 * tb + (ln & 31u);
-        const bool t_ok = t < a.T;
-        float y[2][16];
+    for (int p = 0; p < S::pairs; ++p)
 #pragma unroll
-        for (int fb = 0; fb < 2; ++fb)
+        for (int j = 0; j < 2 * NL; ++j)
+            dma_pair(j, k_bytes(2 * p), k_bytes(2 * p + 1), (2 * p) * S::stage, (2 * p + 1) * S::stage);
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"((S::pairs - 1) * 2 * NL) : "memory");
+    __builtin_amdgcn_s_barrier();
+    uint32_t b0 = 0;
 #pragma unroll
-            for (int v = 0; v < 16; ++v) y[fb][v] = round_via_bf16(acc[fb][tb][v]);
-        const uint32_t tslot = 64u * wn + 32u * tb + (ln & 31u);
-        const int64_t tc = t_ok ? t : 0;
-        if (G > 64) {
-            // (the waves of a group pass the barriers inside together: the workgroup takes one path)
-            if (tileF + ROWS_A > static_cast<uint32_t>(a.r))
-                gemm_epilogue<G, WF, true>(a, y, F0, tc, t_ok, h, xch, wm, tslot, ROWS_B);
-            else
-                gemm_epilogue<G, WF, false>(a, y, F0, tc, t_ok, h, xch, wm, tslot, ROWS_B);
-        } else if (ragged) {
-            gemm_epilogue<G, WF, true>(a, y, F0, tc, t_ok, h, xch, wm, tslot, ROWS_B);
-        } else {
-            gemm_epilogue<G, WF, false>(a, y, F0, tc, t_ok, h, xch, wm, tslot, ROWS_B);
+    for (int i = 0; i < NF; ++i) fetch(i, 0, b0);
+    for (int p = 0; p < np - 1; ++p) {
+        const uint32_t b1 = next_buf(b0), b2 = next_buf(b1);
+        const uint32_t d0 = prev_buf(b0), d1 = b0;
+        const uint32_t kb0 = k_bytes(2 * (p + S::pairs)), kb1 = k_bytes(2 * (p + S::pairs) + 1);
+        TPQ_PIN;
+        TPQ_PHASE(0, 1, b0, 0, 0)
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        TPQ_PIN;
+        TPQ_PHASE(1, 0, b1, 0, N1)
+        TPQ_PHASE(0, 1, b1, N1, N2)
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((S::pairs - 2) * 2 * NL + N2) : "memory");
+        __builtin_amdgcn_s_barrier();
+        TPQ_PIN;
+        TPQ_PHASE(1, 0, b2, N2, 2 * NL)
+        b0 = b2;
+    }
+    // the last pair: k past the row's end counts as zero
+    {
+        const uint32_t b1 = next_buf(b0);
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const int kt = 2 * np - 2 + q, kb = static_cast<int>(k_bytes(kt)) / 2;
+            const int p0 = kb + 8 * static_cast<int>(h), p1 = p0 + 16;
+            const bool ok0 = p0 >= kt * kTileBK && p0 < K, ok1 = p1 >= kt * kTileBK && p1 < K;
+            if (q == 1) {
+#pragma unroll
+                for (int i = 0; i < NF; ++i) fetch(i, 0, b1);
+            }
+#pragma unroll
+            for (int i = 0; i < NF; ++i) fetch(i, 1, q ? b1 : b0);
+#pragma unroll
+            for (int i = 4; i < NF; ++i) {
+                fr[0][i] = ok0 ? fr[0][i] : u32x4{0u, 0u, 0u, 0u};
+                fr[1][i] = ok1 ? fr[1][i] : u32x4{0u, 0u, 0u, 0u};
+            }
+#pragma unroll
+            for (int j = 0; j < 4 * NTB; ++j) mfma(0, j);
+#pragma unroll
+            for (int j = 0; j < 4 * NTB; ++j) mfma(1, j);
         }
     }
+#undef TPQ_PHASE
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+
+    const uint32_t F0 = tileF + 128u * wf;
+    const bool ragged = tileF + static_cast<uint32_t>(S::ft) > static_cast<uint32_t>(a.r);
+    if (a.Ymsg || ragged) {
+#pragma unroll
+        for (int tb = 0; tb < NTB; ++tb) {
+            uint8_t *orow = lds + (32u * (NTB * wt + tb) + row) * (S::ft * 2 + 16) + (128u * wf + 4u * h) * 2u;
+#pragma unroll
+            for (int fb = 0; fb < 4; ++fb)
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    *reinterpret_cast<uint2 *>(orow + (32 * fb + 8 * j) * 2) =
+                        make_uint2(pack_bf16x2(acc[fb][tb][4 * j], acc[fb][tb][4 * j + 1]),
+                                   pack_bf16x2(acc[fb][tb][4 * j + 2], acc[fb][tb][4 * j + 3]));
+        }
+        __syncthreads();
+        rows_selected<S::ft, S::threads>(a, lds, tileF, tileT, S::tt, tid);
+        if (a.Ymsg) rows_product<S::ft, S::threads>(a, lds, tileF, tileT, S::tt, tid);
+        __syncthreads();
+    }
+    // (one copy of the epilogue's code for all blocks of tokens: unrolled it is no faster, and NTB times as long)
+#pragma nounroll
+    for (int tb = 0; tb < NTB; ++tb) {
+        float y[4][16];
+#define TPQ_TAKE(TB)                                                                        \
+    if (TB < NTB && tb == TB) {                                                             \
+        _Pragma("unroll") for (int fb = 0; fb < 4; ++fb)                                    \
+            _Pragma("unroll") for (int v = 0; v < 16; ++v) y[fb][v] = acc[fb][TB < NTB ? TB : 0][v]; \
+    }
+        TPQ_TAKE(0)
+        else TPQ_TAKE(1)
+        else TPQ_TAKE(2)
+        else TPQ_TAKE(3)
+#undef TPQ_TAKE
+#pragma unroll
+        for (int fb = 0; fb < 4; ++fb)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) y[fb][v] = round_via_bf16(y[fb][v]);
+        const uint32_t tslot = 32u * (NTB * wt + tb) + row;
+        const int64_t t = tileT + tslot;
+        const bool t_ok = t < a.T;
+        tile_epilogue<G>(a, y, ragged, F0, t_ok ? t : 0, t_ok, h, reinterpret_cast<float *>(lds), wf, tslot);
+    }
+}
+
+template <int G, int FW, int TW, int NTB>
+static int launch_tile_g(const GemmArgs &a, hipStream_t s)
+{
+    typedef TileShape<FW, TW, NTB> S;
+    const auto kernel = &k_gemm_tile<G, FW, TW, NTB>;
+    const int64_t tiles_f = (a.E + S::ft - 1) / S::ft, tiles_t = (a.T + S::tt - 1) / S::tt;
+    const int64_t blocks = (tiles_f * tiles_t + 7) / 8 * 8;  // (a multiple of 8 for the XCD order)
+    if (blocks * S::threads >= (1ll << 32)) return TPQ_ERR_SHAPE;
+    // more than 64 KiB of LDS: allowed once per device
+    static std::atomic<uint64_t> allowed;
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return hip_result(e);
+    const uint64_t bit = dev < 64 ? 1ull << dev : 0ull;
+    if (!(allowed.load(std::memory_order_relaxed) & bit)) {
+        e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, S::lds);
+        if (e != hipSuccess) return hip_result(e);
+        allowed.fetch_or(bit, std::memory_order_relaxed);
+    }
+    launch_kernel(kernel, dim3(static_cast<unsigned>(blocks)), dim3(S::threads), static_cast<size_t>(S::lds), s, a,
+                  static_cast<uint32_t>(tiles_t));
+    return hip_result(hipGetLastError());
+}
+
+template <int FW, int TW, int NTB>
+static int launch_tile(const GemmArgs &a, hipStream_t s)
+{
+    switch (a.G) {
+    case 32: return launch_tile_g<32, FW, TW, NTB>(a, s);
+    case 64: return launch_tile_g<64, FW, TW, NTB>(a, s);
+    case 128: return launch_tile_g<128, FW, TW, NTB>(a, s);
+    case 256:
+        if constexpr (FW == 2) return launch_tile_g<256, FW, TW, NTB>(a, s);
+        return TPQ_ERR_UNSUPPORTED;
+    default: return TPQ_ERR_UNSUPPORTED;
+    }
+}
+
+// The tile: the one whose rounds over the chip cost least.  A compute unit holds one workgroup, so a launch
+// takes ceil(tiles / compute units) rounds; a round of a tile costs what the table says, measured at
+// K = 1728 (and in the same ratios at K = 640), E = 5120, in us of a launch of one round: 128 features x 64 tokens
+// 16.3, 128 x 128 17.5, 256 x 64 17.7 (the loads' time: more tokens are free), 256 x 128 24, 256 x 192 31, 256 x 256
+// 39 (the products' time, and 8 to 10 us of ends whatever the tile).  Where a smaller tile needs no further round it
+// wins: 512 tokens 18.7 us at 128 x 128 against 23.7 at 256 x 128; 1024 tokens 25.6 at 256 x 128 against 33.9
+// (two rounds) and 31.7 (256 x 192); 2048 tokens 37.5 at 256 x 192 against 49 and 54 (two and three rounds)
+// and 44 (256 x 256).
+static int launch_tiles(const GemmArgs &a, hipStream_t s)
+{
+    struct Tile {
+        int ft, tt, cost;
+        int (*launch)(const GemmArgs &, hipStream_t);
+    };
+    static const Tile tiles[] = {
+        {128, 64, 16, launch_tile<1, 2, 1>},  {128, 128, 17, launch_tile<1, 4, 1>}, {256, 64, 18, launch_tile<2, 2, 1>},
+        {256, 128, 24, launch_tile<2, 2, 2>}, {256, 192, 31, launch_tile<2, 2, 3>}, {256, 256, 39, launch_tile<2, 2, 4>},
+    };
+    int cus = 0;
+    const hipError_t e = compute_units_of_current_device(&cus);
+    if (e != hipSuccess) return hip_result(e);
+    const Tile *best = nullptr;
+    int64_t least = 0;
+    for (const Tile &t : tiles) {
+        if (a.G > t.ft) continue;  // a group lies inside a tile
+        const int64_t n = ((a.E + t.ft - 1) / t.ft) * ((a.T + t.tt - 1) / t.tt);
+        const int64_t cost = (n + cus - 1) / cus * t.cost;
+        if (!best || cost < least) {
+            best = &t;
+            least = cost;
+        }
+    }
+    return best->launch(a, s);
 }
 
 int launch_gemm_weights(const tpq_layout *L, const void *plan, const uint16_t *Wt, int64_t ldW, int K,
@@ -375,28 +572,7 @@ int launch_gemm_encode(const tpq_layout *L, const uint16_t *X, int64_t T, int64_
     a.pitch_outl = L->pitch_outl;
     a.Ymsg = Ymsg;
     a.ldYm = ldYm;
-    hipError_t e = hipSuccess;
-    // groups up to 128: workgroups of 2 x 2 waves (128 features x 128 tokens); groups of 256
-    // need 256 features in the workgroup: 4 x 1 waves (256 features x 64 tokens)
-#define TPQ_GEMM(GG, WF, WT)                                                                              \
-    case GG: {                                                                                            \
-        const int64_t tiles_t = (T + 64 * WT - 1) / (64 * WT);                                            \
-        if (tiles_t > 65535) return TPQ_ERR_SHAPE;                                                        \
-        const dim3 grid(static_cast<unsigned>((L->E + 64 * WF - 1) / (64 * WF)), static_cast<unsigned>(tiles_t)); \
-        const size_t lds = 64 * (WF + WT) * kGemmRow;                                                 \
-        launch_kernel(k_gemm_encode<GG, WF, WT>, grid, dim3(64 * WF * WT), lds, s, a);                    \
-        break;                                                                                            \
-    }
-    switch (L->G) {
-        TPQ_GEMM(32, 2, 2)
-        TPQ_GEMM(64, 2, 2)
-        TPQ_GEMM(128, 2, 2)
-        TPQ_GEMM(256, 4, 1)
-    default: return TPQ_ERR_UNSUPPORTED;
-    }
-#undef TPQ_GEMM
-    if (e != hipSuccess) return hip_result(e);
-    return hip_result(hipGetLastError());
+    return launch_tiles(a, s);
 }
 
 }  // namespace tpq

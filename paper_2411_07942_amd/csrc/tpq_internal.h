@@ -276,6 +276,7 @@ int launch_gemm_weights(const tpq_layout *L, const void *plan, const uint16_t *W
 int launch_gemm_encode(const tpq_layout *L, const uint16_t *X, int64_t T, int64_t ldX, int K,
                        const uint16_t *Wp, uint8_t *codes, uint16_t *scale, uint16_t *zero,
                        uint16_t *outl, uint16_t *Ymsg, int64_t ldYm, hipStream_t s);
+hipError_t compute_units_of_current_device(int *out);
 // calibration workspace: up to kCalMaxParts slices of partial minima / maxima
 constexpr int kCalMaxParts = 128;
 size_t calibrate_workspace_bytes(int E);

@@ -140,6 +140,22 @@ def test_random_shapes(seed):
     _run(T, K, E, int(idx.size), G, seed=seed, integer=bool(seed % 4 == 3), idx=idx)
 
 
+@pytest.mark.parametrize("T,K,E,k,G", [
+    (65, 72, 5120, 80, 128),      # tiles of 128 features x 64 tokens, one token in the second
+    (500, 104, 5128, 77, 64),     # 128 x 128, three stages of k and a quarter
+    (900, 40, 5128, 77, 32),      # 256 x 128, an odd selection that starts inside a chunk
+    (300, 328, 5120, 80, 256),    # 256 x 64 (a group of 256 in two waves)
+    (2040, 200, 5120, 80, 128),   # 256 x 192, the last tile ragged in tokens
+    (2040, 200, 5120, 300, 256),  # the same with groups of 256, one of them past the quantised features' end
+    (4090, 136, 8192, 341, 64),   # 256 x 256
+])
+def test_every_tile_at_its_edges(T, K, E, k, G):
+    """The product's tile follows from the sizes: one case per tile, first and last rows of every
+    tile of tokens, k not a multiple of the stages (in pairs of 32)."""
+    edges = np.concatenate([np.arange(0, T, 64), np.arange(0, T, 64) - 1, [T - 1]])
+    _run(T, K, E, k, G, seed=T + G, rows=np.unique(edges[(edges >= 0) & (edges < T)]))
+
+
 def test_padded_rows_and_no_product_output():
     L, idx, msg_a, _ = _run(77, 96, 512, 8, 128, seed=5, ld_pad=24)
     L, idx, msg_b, _ = _run(77, 96, 512, 8, 128, seed=5, ld_pad=24, want_y=False)
