@@ -3,8 +3,10 @@ partial sums (calibration, encode, decode-and-reduce).
 
 This module only marshals arguments: torch tensors provide device memory and the
 current stream, every step of the path runs in the library's HIP kernels.  The
-function names are those of ``include/tpq.h`` without the ``tpq_`` prefix.  There
-is no CPU fallback: if ``libtpq.so`` has not been built
+calls of the online path are taken apart by a native module (``_binding.so``,
+``csrc/tpq_binding.cpp``), the others through ctypes.  The function names are those
+of ``include/tpq.h`` without the ``tpq_`` prefix.  There is no CPU fallback: if
+``libtpq.so`` and ``_binding.so`` have not been built
 (``python -m paper_2411_07942_amd.build``), importing succeeds but the first call
 raises.
 """
@@ -111,13 +113,31 @@ def _check(rc: int, where: str) -> None:
         raise TpqError(rc, where)
 
 
+_native_module = None
+
+
+def _native():
+    """The native half of the binding (linked against libtpq.so)."""
+    global _native_module
+    if _native_module is None:
+        _load()
+        try:
+            from . import _binding
+        except ImportError as e:
+            raise RuntimeError("_binding.so is not built: run `python -m paper_2411_07942_amd.build` "
+                               "(there is no fallback path)") from e
+        _binding.setup(_check, torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream)
+        _native_module = _binding
+    return _native_module
+
+
 def _ptr(t: Optional[torch.Tensor]):
     return None if t is None else ctypes.c_void_p(t.data_ptr())
 
 
 def _stream(stream=None):
-    if stream is None:
-        stream = torch.cuda.current_stream()
+    if stream is None:  # the current stream's handle, without a Stream object around it
+        return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()))
     return ctypes.c_void_p(stream.cuda_stream)
 
 
@@ -157,8 +177,7 @@ def plan_build(L: Layout, idx_sorted: torch.Tensor, plan: Optional[torch.Tensor]
     """idx_sorted: int32 device tensor [k].  Returns the (uint8, device) plan buffer."""
     if plan is None:
         plan = torch.empty(plan_bytes(L), dtype=torch.uint8, device=idx_sorted.device)
-    _check(_load().tpq_plan_build(ctypes.byref(L), _ptr(idx_sorted), _ptr(plan), plan.numel(),
-                                  _stream(stream)), "tpq_plan_build")
+    _native().plan_build(L, idx_sorted, plan, stream)
     return plan
 
 
@@ -175,11 +194,7 @@ def calibrate_workspace_bytes(S: int, E: int) -> int:
 def calibrate(Y: torch.Tensor, rank: int, n_ranks: int, seq_index: int, gamma: float,
               m: torch.Tensor, M: torch.Tensor, workspace: torch.Tensor, stream=None) -> None:
     """One sequence Y (bf16 [S,E], row stride Y.stride(0)) of device `rank`; m, M fp32 [n_ranks,E]."""
-    S, E = Y.shape
-    _check(_load().tpq_calibrate(_ptr(Y), S, Y.stride(0) if S > 1 else max(E, Y.stride(0)), E,
-                                 rank, n_ranks, seq_index, gamma, _ptr(m), _ptr(M),
-                                 _ptr(workspace), workspace.numel() * workspace.element_size(),
-                                 _stream(stream)), "tpq_calibrate")
+    _native().calibrate(Y, rank, n_ranks, seq_index, gamma, m, M, workspace, stream)
 
 
 def calibrate_workspace(S: int, E: int, device) -> torch.Tensor:
@@ -190,10 +205,7 @@ def calibrate_workspace(S: int, E: int, device) -> torch.Tensor:
 def calibrate_fixed(Y: torch.Tensor, rank: int, n_ranks: int, seq_index: int, gamma: float,
                     m: torch.Tensor, M: torch.Tensor, stream=None) -> None:
     """calibrate() with the library's own scratch buffer instead of a workspace (tpq_calibrate_fixed)."""
-    S, E = Y.shape
-    _check(_load().tpq_calibrate_fixed(_ptr(Y), S, Y.stride(0) if S > 1 else max(E, Y.stride(0)), E,
-                                       rank, n_ranks, seq_index, gamma, _ptr(m), _ptr(M),
-                                       _stream(stream)), "tpq_calibrate_fixed")
+    _native().calibrate_fixed(Y, rank, n_ranks, seq_index, gamma, m, M, stream)
 
 
 def calibrate_finalize_workspace_bytes(E: int) -> int:
@@ -250,27 +262,13 @@ def encode_call(L: Layout, plan: torch.Tensor, Y: Sequence[torch.Tensor],
                 msgs: Sequence[Message]):
     """Marshal a tpq_encode call once; the returned function(stream=None) issues it.
     The tensors must stay alive (and in place) for as long as the function is used."""
-    lib = _load()
-    n = len(Y)
-    T = Y[0].shape[0]
-    ldY = Y[0].stride(0) if T > 1 else max(L.E, Y[0].stride(0))
-    for y in Y:
-        assert y.dtype == torch.bfloat16 and y.shape == Y[0].shape and y.stride(1) == 1
-        assert T <= 1 or y.stride(0) == ldY
-    args = (ctypes.byref(L), _ptr(plan), _ptr_array(Y, n), ldY, n, T,
-            _ptr_array([m.codes for m in msgs], n), _ptr_array([m.scale for m in msgs], n),
-            _ptr_array([m.zero for m in msgs], n), _ptr_array([m.outl for m in msgs], n))
-    keep = (L, plan, list(Y), list(msgs))
-
-    def call(stream=None, _keep=keep):
-        _check(lib.tpq_encode(*args, _stream(stream)), "tpq_encode")
-    return call
+    return _native().encode_call(L, plan, Y, msgs)
 
 
 def encode(L: Layout, plan: torch.Tensor, Y: Sequence[torch.Tensor], msgs: Sequence[Message],
            stream=None) -> None:
     """Encode the ranks' partial sums Y[i] (bf16 [T,E]) into msgs[i] in one launch."""
-    encode_call(L, plan, Y, msgs)(stream)
+    _native().encode(L, plan, Y, msgs, stream)
 
 
 def bench_time_next_launch(start: Optional[torch.cuda.Event], stop: Optional[torch.cuda.Event]) -> None:
@@ -289,30 +287,13 @@ def bench_time_next_launch(start: Optional[torch.cuda.Event], stop: Optional[tor
 def hop_call(L: Layout, plan: torch.Tensor, Y: Sequence[torch.Tensor], in_msgs: Sequence[Message],
              out_msgs: Sequence[Message], accum: int = ACC_BF16):
     """Marshal a tpq_hop call once; the returned function(stream=None) issues it."""
-    lib = _load()
-    n = len(Y)
-    T = Y[0].shape[0]
-    ldY = Y[0].stride(0) if T > 1 else max(L.E, Y[0].stride(0))
-    for y in Y:
-        assert y.dtype == torch.bfloat16 and y.shape == Y[0].shape and y.stride(1) == 1
-        assert T <= 1 or y.stride(0) == ldY
-    assert len(in_msgs) == n and len(out_msgs) == n
-    args = (ctypes.byref(L), _ptr(plan), _ptr_array(Y, n), ldY, n, T,
-            _ptr_array([m.codes for m in in_msgs], n), _ptr_array([m.scale for m in in_msgs], n),
-            _ptr_array([m.zero for m in in_msgs], n), _ptr_array([m.outl for m in in_msgs], n), accum,
-            _ptr_array([m.codes for m in out_msgs], n), _ptr_array([m.scale for m in out_msgs], n),
-            _ptr_array([m.zero for m in out_msgs], n), _ptr_array([m.outl for m in out_msgs], n))
-    keep = (L, plan, list(Y), list(in_msgs), list(out_msgs))
-
-    def call(stream=None, _keep=keep):
-        _check(lib.tpq_hop(*args, _stream(stream)), "tpq_hop")
-    return call
+    return _native().hop_call(L, plan, Y, in_msgs, out_msgs, accum)
 
 
 def hop(L: Layout, plan: torch.Tensor, Y: Sequence[torch.Tensor], in_msgs: Sequence[Message],
         out_msgs: Sequence[Message], accum: int = ACC_BF16, stream=None) -> None:
     """Ring step: out_msgs[i] = encode(bf16(dequantised in_msgs[i] (+) Y[i])), one launch."""
-    hop_call(L, plan, Y, in_msgs, out_msgs, accum)(stream)
+    _native().hop(L, plan, Y, in_msgs, out_msgs, accum, stream)
 
 
 def gemm_weights(L: Layout, plan: torch.Tensor, Wt: torch.Tensor, stream=None) -> torch.Tensor:
@@ -332,54 +313,25 @@ def gemm_encode_call(L: Layout, X: torch.Tensor, Wp: torch.Tensor, msg: Message,
     """Marshal a tpq_gemm_encode call once; the returned function(stream=None) issues it.
     X bf16 [T, K]; Wp from gemm_weights; Y_msg: optional bf16 [T, >= E] for the rounded product
     in message order."""
-    lib = _load()
-    assert X.dtype == torch.bfloat16 and X.dim() == 2 and X.stride(1) == 1
-    assert Wp.dtype == torch.bfloat16 and Wp.is_contiguous() and Wp.shape == (L.E, X.shape[1])
-    T, K = X.shape
-    ldX = X.stride(0) if T > 1 else max(K, X.stride(0))
-    ldYm = 0
-    if Y_msg is not None:
-        assert Y_msg.dtype == torch.bfloat16 and Y_msg.shape[0] == T and Y_msg.stride(1) == 1
-        ldYm = Y_msg.stride(0) if T > 1 else max(L.E, Y_msg.stride(0))
-    args = (ctypes.byref(L), _ptr(X), T, ldX, K, _ptr(Wp), _ptr(msg.codes), _ptr(msg.scale), _ptr(msg.zero),
-            _ptr(msg.outl), _ptr(Y_msg) if Y_msg is not None else None, ldYm)
-    keep = (L, X, Wp, msg, Y_msg)
-
-    def call(stream=None, _keep=keep):
-        _check(lib.tpq_gemm_encode(*args, _stream(stream)), "tpq_gemm_encode")
-    return call
+    return _native().gemm_encode_call(L, X, Wp, msg, Y_msg)
 
 
 def gemm_encode(L: Layout, X: torch.Tensor, Wp: torch.Tensor, msg: Message,
                 Y_msg: Optional[torch.Tensor] = None, stream=None) -> None:
     """msg = encode(bf16(X @ W)) for one device, the product never stored (unless Y_msg asks)."""
-    gemm_encode_call(L, X, Wp, msg, Y_msg)(stream)
+    _native().gemm_encode(L, X, Wp, msg, Y_msg, stream)
 
 
 def decode_reduce_call(L: Layout, plan: torch.Tensor, msgs: Sequence[Message], out: torch.Tensor,
                        accum: int = ACC_FP32):
     """Marshal a tpq_decode_reduce call once; the returned function(stream=None) issues it."""
-    lib = _load()
-    n = len(msgs)
-    T = out.shape[0]
-    out_dtype = OUT_FP32 if out.dtype == torch.float32 else OUT_BF16
-    assert out.dtype in (torch.float32, torch.bfloat16) and out.stride(1) == 1
-    ldOut = out.stride(0) if T > 1 else max(L.E, out.stride(0))
-    args = (ctypes.byref(L), _ptr(plan), n, T,
-            _ptr_array([m.codes for m in msgs], n), _ptr_array([m.scale for m in msgs], n),
-            _ptr_array([m.zero for m in msgs], n), _ptr_array([m.outl for m in msgs], n),
-            accum, out_dtype, _ptr(out), ldOut)
-    keep = (L, plan, list(msgs), out)
-
-    def call(stream=None, _keep=keep):
-        _check(lib.tpq_decode_reduce(*args, _stream(stream)), "tpq_decode_reduce")
-    return call
+    return _native().decode_reduce_call(L, plan, msgs, out, accum)
 
 
 def decode_reduce(L: Layout, plan: torch.Tensor, msgs: Sequence[Message], out: torch.Tensor,
                   accum: int = ACC_FP32, stream=None) -> None:
     """Dequantise and add msgs[0..n-1] into out ([T,E] bf16 or fp32)."""
-    decode_reduce_call(L, plan, msgs, out, accum)(stream)
+    _native().decode_reduce(L, plan, msgs, out, accum, stream)
 
 
 def decode_reduce_fused_call(L: Layout, plan: torch.Tensor, msgs: Sequence[Message], out: torch.Tensor,
@@ -387,32 +339,12 @@ def decode_reduce_fused_call(L: Layout, plan: torch.Tensor, msgs: Sequence[Messa
                              accum: int = ACC_FP32):
     """Marshal a tpq_decode_reduce_fused call once; the returned function(stream=None) issues it.
     addend: bf16 [T, E] (row stride free) or None; bias: bf16 [E] or None."""
-    lib = _load()
-    n = len(msgs)
-    T = out.shape[0]
-    out_dtype = OUT_FP32 if out.dtype == torch.float32 else OUT_BF16
-    assert out.dtype in (torch.float32, torch.bfloat16) and out.stride(1) == 1
-    ldOut = out.stride(0) if T > 1 else max(L.E, out.stride(0))
-    ldAdd = 0
-    if addend is not None:
-        assert addend.dtype == torch.bfloat16 and addend.shape == (T, L.E) and addend.stride(1) == 1
-        ldAdd = addend.stride(0) if T > 1 else max(L.E, addend.stride(0))
-    if bias is not None:
-        assert bias.dtype == torch.bfloat16 and bias.shape == (L.E,) and bias.is_contiguous()
-    args = (ctypes.byref(L), _ptr(plan), n, T,
-            _ptr_array([m.codes for m in msgs], n), _ptr_array([m.scale for m in msgs], n),
-            _ptr_array([m.zero for m in msgs], n), _ptr_array([m.outl for m in msgs], n),
-            _ptr(addend), ldAdd, _ptr(bias), accum, out_dtype, _ptr(out), ldOut)
-    keep = (L, plan, list(msgs), out, addend, bias)
-
-    def call(stream=None, _keep=keep):
-        _check(lib.tpq_decode_reduce_fused(*args, _stream(stream)), "tpq_decode_reduce_fused")
-    return call
+    return _native().decode_reduce_fused_call(L, plan, msgs, out, addend, bias, accum)
 
 
 def decode_reduce_fused(L, plan, msgs, out, addend=None, bias=None, accum: int = ACC_FP32, stream=None) -> None:
     """out = ((sum of the dequantised msgs) + addend) + bias, in one kernel."""
-    decode_reduce_fused_call(L, plan, msgs, out, addend, bias, accum)(stream)
+    _native().decode_reduce_fused(L, plan, msgs, out, addend, bias, accum, stream)
 
 
 # ---- static symmetric mode -------------------------------------------------------
@@ -440,47 +372,19 @@ def encode_static_call(L: Layout, plan: torch.Tensor, Y: Sequence[torch.Tensor],
                        inv: torch.Tensor, msgs: Sequence[Message]):
     """Marshal a tpq_encode_static call once (inv: the rows of the ranks in Y, in order);
     the returned function(stream=None) issues it."""
-    lib = _load()
-    n = len(Y)
-    T = Y[0].shape[0]
-    ldY = Y[0].stride(0) if T > 1 else max(L.E, Y[0].stride(0))
-    for y in Y:
-        assert y.dtype == torch.bfloat16 and y.shape == Y[0].shape and y.stride(1) == 1
-        assert T <= 1 or y.stride(0) == ldY
-    assert inv.dtype == torch.float32 and inv.is_contiguous() and inv.shape[0] >= n
-    args = (ctypes.byref(L), _ptr(plan), _ptr_array(Y, n), ldY, n, T, _ptr(inv),
-            _ptr_array([m.codes for m in msgs], n), _ptr_array([m.outl for m in msgs], n))
-    keep = (L, plan, list(Y), inv, list(msgs))
-
-    def call(stream=None, _keep=keep):
-        _check(lib.tpq_encode_static(*args, _stream(stream)), "tpq_encode_static")
-    return call
+    return _native().encode_static_call(L, plan, Y, inv, msgs)
 
 
 def encode_static(L, plan, Y, inv, msgs, stream=None) -> None:
-    encode_static_call(L, plan, Y, inv, msgs)(stream)
+    _native().encode_static(L, plan, Y, inv, msgs, stream)
 
 
 def decode_reduce_static_call(L: Layout, plan: torch.Tensor, msgs: Sequence[Message],
                               step: torch.Tensor, out: torch.Tensor, accum: int = ACC_FP32):
     """Marshal a tpq_decode_reduce_static call once; the returned function(stream=None)
     issues it."""
-    lib = _load()
-    n = len(msgs)
-    T = out.shape[0]
-    out_dtype = OUT_FP32 if out.dtype == torch.float32 else OUT_BF16
-    assert out.dtype in (torch.float32, torch.bfloat16) and out.stride(1) == 1
-    assert step.dtype == torch.float32 and step.is_contiguous() and step.shape[0] >= n
-    ldOut = out.stride(0) if T > 1 else max(L.E, out.stride(0))
-    args = (ctypes.byref(L), _ptr(plan), n, T,
-            _ptr_array([m.codes for m in msgs], n), _ptr_array([m.outl for m in msgs], n),
-            _ptr(step), accum, out_dtype, _ptr(out), ldOut)
-    keep = (L, plan, list(msgs), step, out)
-
-    def call(stream=None, _keep=keep):
-        _check(lib.tpq_decode_reduce_static(*args, _stream(stream)), "tpq_decode_reduce_static")
-    return call
+    return _native().decode_reduce_static_call(L, plan, msgs, step, out, accum)
 
 
 def decode_reduce_static(L, plan, msgs, step, out, accum: int = ACC_FP32, stream=None) -> None:
-    decode_reduce_static_call(L, plan, msgs, step, out, accum)(stream)
+    _native().decode_reduce_static(L, plan, msgs, step, out, accum, stream)

@@ -1,4 +1,4 @@
-"""Builds libtpq.so (HIP, gfx950) in-tree with hipcc.
+"""Builds libtpq.so (HIP, gfx950) with hipcc and the Python binding's native half with g++, in-tree.
 
     python -m paper_2411_07942_amd.build            # compile every source, link
 """
@@ -48,7 +48,35 @@ def build(extra_flags=(), jobs: int = 5) -> str:
     tmp = LIB + ".tmp%d" % os.getpid()
     subprocess.run(["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp, *objs], check=True)
     os.replace(tmp, LIB)
+    build_binding()
     return LIB
+
+
+BINDING = os.path.join(PKG, "_binding.so")
+
+
+def build_binding() -> str:
+    """The native half of the Python binding: plain C++ against torch's headers, linked to libtpq.so."""
+    import sysconfig
+
+    import torch
+    t = os.path.dirname(os.path.abspath(torch.__file__))
+    tmp = BINDING + ".tmp%d" % os.getpid()
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI),
+           "-I", os.path.join(ROOT, "include"), "-isystem", os.path.join(t, "include"),
+           "-isystem", os.path.join(t, "include", "torch", "csrc", "api", "include"),
+           "-isystem", sysconfig.get_paths()["include"],
+           os.path.join(CSRC, "tpq_binding.cpp"), "-o", tmp,
+           "-L", os.path.join(t, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-L", PKG, "-ltpq",
+           "-Wl,-rpath,$ORIGIN"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("g++ failed for tpq_binding.cpp:\n" + r.stderr)
+    if r.stderr.strip():
+        sys.stderr.write(r.stderr)
+    os.replace(tmp, BINDING)
+    return BINDING
 
 
 PROBE_SRC = os.path.join(ROOT, "tests", "probes", "hw_probe.hip")

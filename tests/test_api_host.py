@@ -9,6 +9,7 @@ import os
 import re
 
 import pytest
+import torch
 
 import paper_2411_07942_amd as tpq
 from refmath import payload_bits, wire_bytes_per_row
@@ -181,6 +182,55 @@ def test_calibrate_and_plan_argument_errors():
     assert lib.tpq_plan_build(ctypes.byref(L), f(), f(), tpq.plan_bytes(L) - 1, None) == tpq.ERR_WORKSPACE
     assert lib.tpq_plan_build(ctypes.byref(L), None, f(), tpq.plan_bytes(L), None) == tpq.ERR_NULL
     assert lib.tpq_plan_build(ctypes.byref(L), f(), f(0x10004), tpq.plan_bytes(L), None) == tpq.ERR_ALIGN
+
+
+class _NullStream:
+    cuda_stream = 0
+
+
+@pytest.mark.parametrize("seq", [list, tuple])
+def test_binding_checks_tensors_before_anything_is_enqueued(seq):
+    """The native half of the binding: what the Python entry points assert (types, shapes, strides),
+    the library's own errors as TpqError, immediate and marshalled calls alike."""
+    E, T = 512, 4
+    L = tpq.layout_init(E, 8, 128)
+    plan = torch.zeros(tpq.plan_bytes(L), dtype=torch.uint8)
+    Y = [torch.zeros((T, E), dtype=torch.bfloat16) for _ in range(3)]
+    msgs = [tpq.Message(L, T, "cpu") for _ in range(3)]
+    out = torch.zeros((T, E), dtype=torch.float32)
+    bad = {"dtype": torch.zeros((T, E)), "shape": Y[0][:3], "columns": torch.zeros((E, T), dtype=torch.bfloat16).t(),
+           "row stride": torch.zeros((T, E + 8), dtype=torch.bfloat16)[:, :E]}
+    for what, y in bad.items():
+        for f in (lambda: tpq.encode(L, plan, seq([Y[0], y]), seq(msgs[:2]), stream=_NullStream()),
+                  lambda: tpq.encode_call(L, plan, seq([Y[0], y]), seq(msgs[:2]))):
+            with pytest.raises(AssertionError):
+                f()
+    with pytest.raises(IndexError):
+        tpq.encode(L, plan, seq(Y), seq(msgs[:2]), stream=_NullStream())
+    with pytest.raises(AssertionError):
+        tpq.hop_call(L, plan, seq(Y), seq(msgs[:2]), seq(msgs))
+    with pytest.raises(AssertionError):
+        tpq.decode_reduce(L, plan, seq(msgs), out.double(), stream=_NullStream())
+    with pytest.raises(AssertionError):
+        tpq.decode_reduce_fused(L, plan, seq(msgs), out, addend=out, stream=_NullStream())
+    with pytest.raises(AssertionError):
+        tpq.decode_reduce_static(L, plan, seq(msgs), out[:2], out, stream=_NullStream())
+    with pytest.raises(AssertionError):
+        tpq.gemm_encode_call(L, Y[0], torch.zeros((E, 8), dtype=torch.bfloat16), msgs[0])
+    with pytest.raises(TypeError):
+        tpq.encode(L, plan, seq([1.0]), seq(msgs), stream=_NullStream())
+    # the library's answer: more ranks than it takes, an accumulate mode it does not know
+    many = seq([msgs[0]] * (tpq.MAX_RANKS + 1))
+    for f in (lambda: tpq.decode_reduce(L, plan, many, out, stream=_NullStream()),
+              lambda: tpq.decode_reduce_call(L, plan, many, out)(_NullStream())):
+        with pytest.raises(tpq.TpqError) as e:
+            f()
+        assert e.value.code == tpq.ERR_SHAPE
+    with pytest.raises(tpq.TpqError) as e:
+        tpq.decode_reduce_call(L, plan, seq(msgs), out, 7)(stream=_NullStream())
+    assert e.value.code == tpq.ERR_UNSUPPORTED
+    with pytest.raises(TypeError):
+        tpq.decode_reduce_call(L, plan, seq(msgs), out)(1, 2)
 
 
 def test_strerror_covers_every_code():
