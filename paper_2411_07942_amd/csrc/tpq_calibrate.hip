@@ -115,46 +115,129 @@ __global__ __launch_bounds__(kStripLanes *kWavesPerBlock) void k_colminmax(
     }
 }
 
-// Combine the parts and apply Eq. (1), (2) to one device's state.  A block owns 64
-// features; its 4 waves take interleaved parts and are combined through LDS.
-__global__ __launch_bounds__(256) void k_ema(const float *__restrict__ partial, int parts, int E,
-                                             int first, float gamma, float *__restrict__ m,
-                                             float *__restrict__ M)
+// One feature's extreme c of the sequence -> its moving average (Eq. (1), (2))
+__device__ __forceinline__ void ema_update(float *state, float c, int first, float gamma)
+{
+    c += 0.0f;  // a zero is taken as +0
+    if (first) {
+        *state = c;
+    } else {
+        const float keep = 1.0f - gamma;
+        const float x = keep * *state;
+        const float y = gamma * c;
+        *state = x + y;
+    }
+}
+
+// Combine the parts and apply Eq. (1), (2) to one device's state.  A block owns 64 features; its
+// 16 waves take interleaved parts, up to 8 of them (kCalMaxParts in all) with every load in flight at once, and
+// are combined through LDS.  Bound by latency: with 4 waves that walked over their parts one
+// after the other it took 4.7 us at 28 parts and 11.5 at 128, now 2.6 and 3.
+constexpr int kEmaWaves = 16;
+__global__ __launch_bounds__(64 * kEmaWaves) void k_ema(const float *__restrict__ partial, int parts, int E,
+                                                        int first, float gamma, float *__restrict__ m,
+                                                        float *__restrict__ M)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int j = blockIdx.x * 64 + lane;
     float cmin = 3.4028235e38f, cmax = -3.4028235e38f;
     if (j < E) {
-        for (int p = wave; p < parts; p += 4) {
-            cmin = fminf(cmin, partial[(2 * static_cast<int64_t>(p)) * E + j]);
-            cmax = fmaxf(cmax, partial[(2 * static_cast<int64_t>(p) + 1) * E + j]);
+        for (int p0 = wave; p0 < parts; p0 += 2 * kEmaWaves) {
+            // (a part past the last is the last one again)
+            const int64_t a = p0, b = min(p0 + kEmaWaves, parts - 1);
+            const float lo0 = partial[2 * a * E + j], hi0 = partial[(2 * a + 1) * E + j];
+            const float lo1 = partial[2 * b * E + j], hi1 = partial[(2 * b + 1) * E + j];
+            cmin = fminf(cmin, fminf(lo0, lo1));
+            cmax = fmaxf(cmax, fmaxf(hi0, hi1));
         }
     }
-    __shared__ float red[4][2][64];
-    red[wave][0][lane] = cmin;
-    red[wave][1][lane] = cmax;
+    __shared__ float red[2][kEmaWaves][64];
+    red[0][wave][lane] = cmin;
+    red[1][wave][lane] = cmax;
     __syncthreads();
-    if (wave != 0 || j >= E) return;
+    if (wave > 1 || j >= E) return;
+    float c = red[wave][0][lane];
 #pragma unroll
-    for (int w2 = 1; w2 < 4; ++w2) {
-        cmin = fminf(cmin, red[w2][0][lane]);
-        cmax = fmaxf(cmax, red[w2][1][lane]);
-    }
-    cmin += 0.0f;  // a zero is taken as +0
-    cmax += 0.0f;
-    if (first) {
-        m[j] = cmin;
-        M[j] = cmax;
-    } else {
-        const float keep = 1.0f - gamma;
-        float x = keep * m[j];
-        float y = gamma * cmin;
-        m[j] = x + y;
-        x = keep * M[j];
-        y = gamma * cmax;
-        M[j] = x + y;
-    }
+    for (int w2 = 1; w2 < kEmaWaves; ++w2) c = wave ? fmaxf(c, red[wave][w2][lane]) : fminf(c, red[wave][w2][lane]);
+    ema_update((wave ? M : m) + j, c, first, gamma);
 }
+
+// Short sequences: both steps in one launch.  A workgroup owns 32 features for all rows, so that
+// nothing has to meet in memory: 4 lanes span the features (64 bytes of a row), a wave's load covers 16
+// rows, 8 of them in flight per lane.  Minima are kept negated, so that all 64 results of a workgroup are
+// maxima: 16 lanes meet by DPP, the rows of lanes through LDS, 8 threads per result.
+// Bound by launch and latency, then by what E / 32 compute units can have outstanding: measured at E = 5120,
+// back to back, against the two launches above: 64 rows 3.5 / 6.0 us, 256 rows 4.3 / 6.2, 512 rows 5.0 / 6.6,
+// 1024 rows 6.9 / 7.6 (E = 512: 5.5 / 6.8), 2048 rows 11.2 / 10.5 (8.5 / 8.1), 4096 rows 19.5 / 13.9 -- hence the line at 1024.
+constexpr int64_t kColumnsMaxRows = 1024;
+constexpr int kColLanes = 4, kColFeatures = 8 * kColLanes, kColWaves = 8;
+__global__ __launch_bounds__(64 * kColWaves) void k_columns(const uint16_t *__restrict__ Y, int S, int64_t ldY,
+                                                            int E, int first, float gamma, float *__restrict__ m,
+                                                            float *__restrict__ M)
+{
+    constexpr int kRows = 64 / kColLanes, kStep = kRows * kColWaves;  // rows of a load; of a step of the workgroup
+    constexpr int kParts = 4 * kColWaves;                             // rows of 16 lanes
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int col8 = blockIdx.x * kColLanes + (lane & (kColLanes - 1));
+    float lo[8], hi[8];  // the minima negated
+#pragma unroll
+    for (int e = 0; e < 8; ++e) lo[e] = hi[e] = -3.4028235e38f;
+    if (col8 * 8 < E) {
+        const u32x4_cal *p = reinterpret_cast<const u32x4_cal *>(Y + col8 * 8);
+        const int64_t stride = ldY / 8;  // in 16-byte units
+        for (int t = wave * kRows + lane / kColLanes; t < S; t += kUnroll * kStep) {
+            u32x4_cal v[kUnroll];
+#pragma unroll
+            for (int u = 0; u < kUnroll; ++u)  // (a row past the last is the last one again)
+                v[u] = __builtin_nontemporal_load(p + min(t + u * kStep, S - 1) * stride);
+#pragma unroll
+            for (int u = 0; u < kUnroll; ++u) {
+                const uint32_t w[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float x0 = bf16_lo_to_f32(w[e]), x1 = __uint_as_float(w[e]);
+                    lo[2 * e] = fmaxf(lo[2 * e], -x0);
+                    hi[2 * e] = fmaxf(hi[2 * e], x0);
+                    lo[2 * e + 1] = fmaxf(lo[2 * e + 1], -x1);
+                    hi[2 * e + 1] = fmaxf(hi[2 * e + 1], x1);
+                }
+            }
+        }
+#pragma unroll
+        for (int e = 1; e < 8; e += 2) {
+            lo[e] = __uint_as_float(__float_as_uint(lo[e]) & 0xFFFF0000u);
+            hi[e] = __uint_as_float(__float_as_uint(hi[e]) & 0xFFFF0000u);
+        }
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {  // lanes 4 and 8 on in the row of 16
+        lo[e] = fmaxf(lo[e], dpp_f32<0x124>(lo[e]));
+        hi[e] = fmaxf(hi[e], dpp_f32<0x124>(hi[e]));
+        lo[e] = fmaxf(lo[e], dpp_f32<0x128>(lo[e]));
+        hi[e] = fmaxf(hi[e], dpp_f32<0x128>(hi[e]));
+    }
+    __shared__ float red[kParts][2 * kColFeatures + 1];
+    if ((lane & 15) < kColLanes) {
+        float *r = red[wave * 4 + lane / 16] + 8 * (lane & (kColLanes - 1));
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            r[e] = lo[e];
+            r[kColFeatures + e] = hi[e];
+        }
+    }
+    __syncthreads();
+    const int v = threadIdx.x / 8, s = threadIdx.x & 7;  // result; slice of the parts
+    float c = red[s][v];
+#pragma unroll
+    for (int i = 8; i < kParts; i += 8) c = fmaxf(c, red[s + i][v]);
+    c = fmaxf(c, dpp_f32<0xB1>(c));
+    c = fmaxf(c, dpp_f32<0x4E>(c));
+    c = fmaxf(c, dpp_f32<0x141>(c));
+    const bool low = v < kColFeatures;
+    const int j = blockIdx.x * kColFeatures + (low ? v : v - kColFeatures);
+    if (s == 0 && j < E) ema_update((low ? m : M) + j, low ? -c : c, first, gamma);
+}
+static_assert(64 * kColWaves == 8 * 2 * kColFeatures, "eight threads per result");
 
 // The number of compute units of the current device (looked up once per device: the query is
 // slow compared with a launch).
@@ -184,6 +267,11 @@ hipError_t compute_units_of_current_device(int *out)
 int launch_colminmax_ema(const uint16_t *Y, int64_t S, int64_t ldY, int E, int first,
                          float gamma, float *m, float *M, void *ws, int max_parts, hipStream_t s)
 {
+    if (S <= kColumnsMaxRows) {
+        k_columns<<<(E + kColFeatures - 1) / kColFeatures, 64 * kColWaves, 0, s>>>(Y, static_cast<int>(S), ldY, E, first,
+                                                                                    gamma, m, M);
+        return hip_result(hipGetLastError());
+    }
     int cus = 0;
     const hipError_t e0 = compute_units_of_current_device(&cus);
     if (e0 != hipSuccess) return hip_result(e0);
@@ -194,7 +282,7 @@ int launch_colminmax_ema(const uint16_t *Y, int64_t S, int64_t ldY, int E, int f
     const dim3 grid((E + kStripCols - 1) / kStripCols, live_parts);
     float *partial = static_cast<float *>(ws);
     k_colminmax<<<grid, kStripLanes * kWavesPerBlock, 0, s>>>(Y, S, ldY, E, rows_per_part, partial);
-    k_ema<<<(E + 63) / 64, 256, 0, s>>>(partial, live_parts, E, first, gamma, m, M);
+    k_ema<<<(E + 63) / 64, 64 * kEmaWaves, 0, s>>>(partial, live_parts, E, first, gamma, m, M);
     return hip_result(hipGetLastError());
 }
 

@@ -408,6 +408,17 @@ def test_calibrate_shapes(S, E, N, n_seq, ld_pad):
         _finalize_both(m, M, m_ref, M_ref, k)
 
 
+@pytest.mark.parametrize("S,E,ld_pad", [
+    (1, 8, 0), (15, 40, 8), (17, 512, 0), (128, 5000, 16), (129, 1032, 0), (1023, 264, 0), (1024, 4608, 0),  # one launch
+    (1025, 264, 8), (2048 + 63, 8, 0), (16384, 512, 0), (16384 - 5, 5000, 0),                              # row slices
+])
+def test_calibrate_either_side_of_the_row_limit(S, E, ld_pad):
+    """Short sequences take one launch, long ones row slices (up to 128 at E = 512) and a second
+    launch: rows and columns around what a load, a workgroup and a slice cover."""
+    w = dataclasses.replace(wl.TINY, E=E, k=max(1, E // 64))
+    _calibrate_both(w, 2, S, N=2, ld_pad=ld_pad)
+
+
 def test_calibrate_ties_and_gamma():
     E, N = 512, 2
     m = -torch.ones((N, E), device="cuda")
