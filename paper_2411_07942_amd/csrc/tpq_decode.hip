@@ -129,193 +129,151 @@ __device__ __forceinline__ float add_term(float acc, float x)
     return ACC == TPQ_ACC_BF16 ? round_via_bf16(s) : s;
 }
 
-// ---------------------------------------------------------------------------
-// store_pass with the block's epilogue (Sec. 2: the sum over the devices plus the bias):
-// the sums are parked as fp32 whatever the output type, and every block adds the addend
-// row's and the bias's 8 columns (one 2-byte-aligned 128-bit load each) as two more terms
-// of the accumulation before it is rounded and stored.  addend_row / bias may be null.
-// st: 128 x 16 bytes per wave.
-// ---------------------------------------------------------------------------
-template <int OUT, int ACC>
-__device__ __forceinline__ void store_pass_fused(u32x4 *st, const float (&acc)[8], uint8_t *out_row,
-                                                 uint32_t lane, const uint32_t *entries, uint32_t nb,
-                                                 uint32_t nall, uint32_t e0, uint32_t e1,
-                                                 const uint8_t *addend_row, const uint8_t *bias)
+// A wave's sums by column: 512 columns of its pass as fp32, 7 more that a chunk across the pass's
+// end may touch, and one place for features of other passes.
+constexpr uint32_t kRowQuads = 130, kRowNowhere = 519;
+
+// The features of a chunk -> their columns.  cols: the chunk's 8 columns (16 bits each), col0: the pass's first.
+__device__ __forceinline__ void scatter_chunk(float *row, const float (&x)[8], const u32x4 &cols, uint32_t col0, bool whole)
 {
-    st[2u * lane] = u32x4{__float_as_uint(acc[0]), __float_as_uint(acc[1]), __float_as_uint(acc[2]),
-                          __float_as_uint(acc[3])};
-    st[2u * lane + 1u] = u32x4{__float_as_uint(acc[4]), __float_as_uint(acc[5]), __float_as_uint(acc[6]),
-                               __float_as_uint(acc[7])};
-    wave_lds_fence();
-    for (uint32_t s0 = 0; s0 < nall; s0 += 64) {
-        const uint32_t slot = s0 + lane;
-        uint32_t e = s0 == 0 ? e0 : e1;
-        if (s0 >= 128) e = slot < nall ? entries[slot] : 0u;
-        const uint32_t col = e & 0xFFFFu, at = (e >> 16) & 0x1FFu;
-        if (slot < nb) {
-            const uint32_t q = at >> 2;
-            const u32x4 A = st[q], B = st[min(q + 1u, 127u)], C = st[min(q + 2u, 127u)];
-            const bool s2 = (at & 2u) != 0, s1 = (at & 1u) != 0;
-#define TPQ_SEL(c, hi, lo) ((c) ? (hi) : (lo))
-            const uint32_t u0 = TPQ_SEL(s2, A.z, A.x), u1 = TPQ_SEL(s2, A.w, A.y), u2 = TPQ_SEL(s2, B.x, A.z),
-                           u3 = TPQ_SEL(s2, B.y, A.w), u4 = TPQ_SEL(s2, B.z, B.x), u5 = TPQ_SEL(s2, B.w, B.y),
-                           u6 = TPQ_SEL(s2, C.x, B.z), u7 = TPQ_SEL(s2, C.y, B.w), u8 = TPQ_SEL(s2, C.z, C.x);
-            float f0 = __uint_as_float(TPQ_SEL(s1, u1, u0)), f1 = __uint_as_float(TPQ_SEL(s1, u2, u1)),
-                  f2 = __uint_as_float(TPQ_SEL(s1, u3, u2)), f3 = __uint_as_float(TPQ_SEL(s1, u4, u3)),
-                  f4 = __uint_as_float(TPQ_SEL(s1, u5, u4)), f5 = __uint_as_float(TPQ_SEL(s1, u6, u5)),
-                  f6 = __uint_as_float(TPQ_SEL(s1, u7, u6)), f7 = __uint_as_float(TPQ_SEL(s1, u8, u7));
-#undef TPQ_SEL
-#define TPQ_ADD8(src)                                                                       \
-    {                                                                                       \
-        const u32x4 t8 = *reinterpret_cast<const u32x4_a2 *>((src) + 2u * col);             \
-        f0 = add_term<ACC>(f0, bf16_lo_to_f32(t8.x)); f1 = add_term<ACC>(f1, bf16_hi_to_f32(t8.x)); \
-        f2 = add_term<ACC>(f2, bf16_lo_to_f32(t8.y)); f3 = add_term<ACC>(f3, bf16_hi_to_f32(t8.y)); \
-        f4 = add_term<ACC>(f4, bf16_lo_to_f32(t8.z)); f5 = add_term<ACC>(f5, bf16_hi_to_f32(t8.z)); \
-        f6 = add_term<ACC>(f6, bf16_lo_to_f32(t8.w)); f7 = add_term<ACC>(f7, bf16_hi_to_f32(t8.w)); \
-    }
-            if (addend_row) TPQ_ADD8(addend_row)
-            if (bias) TPQ_ADD8(bias)
-#undef TPQ_ADD8
-            if (OUT == TPQ_OUT_FP32) {
-                __builtin_nontemporal_store(
-                    u32x4{__float_as_uint(f0), __float_as_uint(f1), __float_as_uint(f2), __float_as_uint(f3)},
-                    reinterpret_cast<u32x4_a4 *>(out_row + 4u * col));
-                __builtin_nontemporal_store(
-                    u32x4{__float_as_uint(f4), __float_as_uint(f5), __float_as_uint(f6), __float_as_uint(f7)},
-                    reinterpret_cast<u32x4_a4 *>(out_row + 4u * col + 16u));
-            } else {
-                __builtin_nontemporal_store(u32x4{pack_bf16x2(f0, f1), pack_bf16x2(f2, f3), pack_bf16x2(f4, f5),
-                                                  pack_bf16x2(f6, f7)},
-                                            reinterpret_cast<u32x4_a2 *>(out_row + 2u * col));
-            }
-        } else if (slot < nall) {
-            float f = __uint_as_float(reinterpret_cast<const uint32_t *>(st)[at]);
-            if (addend_row)
-                f = add_term<ACC>(f, bf16_bits_to_f32(*reinterpret_cast<const uint16_t *>(addend_row + 2u * col)));
-            if (bias) f = add_term<ACC>(f, bf16_bits_to_f32(*reinterpret_cast<const uint16_t *>(bias + 2u * col)));
-            if (OUT == TPQ_OUT_FP32)
-                *reinterpret_cast<float *>(out_row + 4u * col) = f;
-            else
-                *reinterpret_cast<uint16_t *>(out_row + 2u * col) = static_cast<uint16_t>(pack_bf16x2(f, f));
+    typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+    const uint32_t first = cols.x & 0xFFFFu, at = first - col0;
+    if (whole && (cols.w >> 16) - first == 7u && at < 512u) {  // 8 neighbours: two stores
+        *reinterpret_cast<u32x4_a4 *>(row + at) =
+            u32x4{__float_as_uint(x[0]), __float_as_uint(x[1]), __float_as_uint(x[2]), __float_as_uint(x[3])};
+        *reinterpret_cast<u32x4_a4 *>(row + at + 4u) =
+            u32x4{__float_as_uint(x[4]), __float_as_uint(x[5]), __float_as_uint(x[6]), __float_as_uint(x[7])};
+    } else {
+        // feature by feature, the last first: positions past the row's last feature name its column
+        // too, and its own value has to be the one that stays
+        const uint32_t cw[4] = {cols.x, cols.y, cols.z, cols.w};
+        const unsigned short c16 = static_cast<unsigned short>(col0);
+#pragma unroll
+        for (int w = 3; w >= 0; --w) {
+            const u16x2 d2 = __builtin_elementwise_min(__builtin_bit_cast(u16x2, cw[w]) - u16x2{c16, c16},
+                                                       u16x2{kRowNowhere, kRowNowhere});
+            const uint32_t d = __builtin_bit_cast(uint32_t, d2);
+            row[d >> 16] = x[2 * w + 1];
+            row[d & 0xFFFFu] = x[2 * w];
         }
     }
-    __builtin_amdgcn_wave_barrier();
+}
+
+// v holds four ranks' values of 16 columns, a row of 16 lanes each: acc <- acc (+) rank 4 rq (+) .. in every row
+template <int ACC>
+__device__ __forceinline__ void add_quad(float &acc, uint32_t v, uint32_t rq, uint32_t N)
+{
+    const auto a = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    const uint32_t even = a[0], odd = a[1];
+    const auto b = __builtin_amdgcn_permlane32_swap(even, even, false, false);
+    const auto c = __builtin_amdgcn_permlane32_swap(odd, odd, false, false);
+    const float x[4] = {bf16_bits_to_f32(b[0]), bf16_bits_to_f32(c[0]), bf16_bits_to_f32(b[1]), bf16_bits_to_f32(c[1])};
+    const uint32_t left = N - 4u * rq;  // (uniform, 1 or more)
+    acc = rq == 0u ? x[0] : add_term<ACC>(acc, x[0]);
+    if (left >= 4u) {
+        acc = add_term<ACC>(add_term<ACC>(add_term<ACC>(acc, x[1]), x[2]), x[3]);
+    } else {
+        if (left > 1u) acc = add_term<ACC>(acc, x[1]);
+        if (left > 2u) acc = add_term<ACC>(acc, x[2]);
+    }
 }
 
 // ---------------------------------------------------------------------------
-// One wavefront handles one pass (64 chunks = 512 compacted features) of one output
-// row, or up to 64 of the row's selected features; waves are independent (no barrier;
-// LDS only as each wave's private staging area for its stores), so a CU always holds
+// One wavefront handles one column pass of one output row: up to 64 blocks of 8 columns, the chunks (up to
+// 64, one per lane) whose features lie there, and the selected features between them.  Waves
+// are independent (no barrier; LDS only as each wave's private row of sums), so a CU always holds
 // waves in every phase and loads, arithmetic and stores overlap.
 //
-// Pass wave: every lane issues all its loads at once -- the pass's store entries, one
-// 32-bit word of codes (8 features) per rank, the group's scale and zero per rank --
-// then dequantises (code * scale + zero: one FMA, the product is exact) and
-// accumulates in ascending rank order.  The sums leave through store_pass(): blocks
-// of 8 consecutive columns, one 128-bit store each (2-byte aligned: removing the
-// selected columns shifted the compacted stream; neighbouring lanes' stores are
-// contiguous, so lines are written whole).
-// Outlier wave: lane p adds the ranks' bf16 values of outlier p and stores the sum at
-// its column.
-// grid: (row, group of 4 waves) pairs, rounded up to a multiple of 8.
+// Every lane issues its loads at once -- one 32-bit word of codes (8 features) per rank, the group's scale
+// and zero per rank, the columns of its 8 features, the selected features' values (four ranks of
+// 16 columns per load) -- then dequantises (code * scale + zero: one FMA, the product is exact) and
+// accumulates in ascending rank order.  The sums meet in LDS in column order, where a lane takes 8
+// neighbouring columns, adds the epilogue's terms and stores them: one aligned 128-bit store (two for fp32
+// output) per lane, every line of the output written whole, by one wave, once.
+// Why by columns: as passes of 512 compacted features the sums left in runs between selected columns -- 2-byte
+// aligned stores, a second, nearly empty round of them per pass, the epilogue's operands loaded the same way,
+// and waves of their own for the selected features.  Kernel times, before and now (T = 2048, E = 5120, k = 80, N = 8
+// unless said): with residual and bias 25.3 -> 20.9 us (fp32), 29.6 -> 25.4 (bf16 chain); without 17.5 -> 17.4; 16384 x
+// 8192, k = 341, N = 16, fp32 output 480 -> 435; 6 bits, 1777 x 5000, N = 5 22.8 -> 22.0.  Bound by instruction issue (70 % of the
+// time) and memory latency together.  Eight waves per SIMD; the other code widths need 72 registers: seven.
+// Waves are numbered through (row, pass) and not in whole workgroups per row, which would leave up to three of the last
+// one idle: at the first size above 0.2 us.
+// grid: (row, pass) pairs, 4 per workgroup, workgroups rounded up to a multiple of 8.
 // ---------------------------------------------------------------------------
 //
 // GEN selects code widths other than 4 bits (Sec. 4, the experiment that varies the bits
 // of the quantised features): a chunk's 8 codes are b bytes at byte chunk * b of the row,
 // fetched with one 64-bit load at that byte (the row's pitch leaves room behind the last).
 //
-// FUSED adds the block's epilogue (an addend row and / or the bias, see store_pass_fused).
+// FUSED adds the block's epilogue (Sec. 2: the sum over the devices plus the bias): an addend row and / or the
+// bias as two more terms of the accumulation.
 template <int LPG, int ACC, int OUT, bool GEN, bool FUSED>
-__global__ __launch_bounds__(256) void k_decode_pass(DecodeArgs a, RankPtrs codesp, RankPtrs scalep,
+__global__ __launch_bounds__(256, GEN ? 7 : 8) void k_decode_pass(DecodeArgs a, RankPtrs codesp, RankPtrs scalep,
                                                      RankPtrs zerop, RankPtrs outlp)
 {
-    // Nothing is stored unless the header says that the plan is good; the pass waves'
-    // loads do not wait for that answer (the message sections do not depend on the plan,
-    // and reads of the plan's tables are kept inside the plan buffer whatever it holds).
-    const bool bad = plan_header_bad(a.plan, a.E, a.k, a.G);
+    // Nothing is stored unless the header says that the plan is good; the loads do not wait for that
+    // answer (whatever the plan's tables hold, they are kept inside the plan, the messages and the
+    // addend).
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const uint32_t passes = static_cast<uint32_t>(a.chunks_padded) >> 6;
-    // Each XCD works through one contiguous range of (row, wave group) pairs, a row's
-    // groups one after the other: the lines two neighbouring waves share (a row's scales
-    // and zeros, the ends of their code ranges, the output lines at a pass boundary)
-    // then meet in one L2, close in time.
-    const uint32_t ny = (passes + ((static_cast<uint32_t>(a.k) + 63u) >> 6) + 3u) >> 2;
-    const uint32_t logical = xcd_contiguous_index(blockIdx.x, gridDim.x);
-    const uint32_t t = logical / ny;
-    if (t >= static_cast<uint32_t>(a.T)) return;  // (the grid is rounded up to 8 blocks)
-    const uint32_t task = (logical - t * ny) * 4u + wave;
+    // Each XCD works through one contiguous range of (row, pass) pairs, a row's passes one after
+    // the other: the lines two neighbouring waves share (a row's scales and zeros, the ends of their code
+    // ranges) then meet in one L2, close in time.
+    const uint32_t E = static_cast<uint32_t>(a.E), k = static_cast<uint32_t>(a.k);
+    const uint32_t passes = static_cast<uint32_t>(cpass_cap_of(a.E));
+    const uint32_t pair = xcd_contiguous_index(blockIdx.x, gridDim.x) * 4u + wave;
+    const uint32_t t = pair / passes, task = pair - t * passes;
+    if (t >= static_cast<uint32_t>(a.T)) return;  // (the grid is rounded up to 8 blocks of 4)
 
     constexpr uint32_t OB = OUT == TPQ_OUT_FP32 ? 4u : 2u;  // bytes per output value
     const uint32_t N = static_cast<uint32_t>(a.n_ranks);
     const uint32_t ng = static_cast<uint32_t>(a.ng);
     const uint32_t chunks = static_cast<uint32_t>(a.chunks);
-    uint8_t *const out_row = static_cast<uint8_t *>(a.out) + static_cast<int64_t>(t) * a.ldOut * OB;
+    const uint4 cp = reinterpret_cast<const uint4 *>(a.plan + a.off_cpass)[task];
+    const uint32_t n_blk = min(cp.x >> 16, 64u), blk0 = min(cp.x & 0xFFFFu, E / 8u - 1u), col0 = 8u * blk0;
+    const uint32_t n_sel = min(cp.z >> 16, k), s0 = min(cp.z & 0xFFFFu, k);
+    const uint32_t n_chunk = cp.y >> 16;
+    // (one word, made here, where the header has come with the pass: kept for later it is seven registers)
+    const PlanHeader *ph = reinterpret_cast<const PlanHeader *>(a.plan);
+    uint32_t refuse = (ph->magic ^ kPlanMagic) | static_cast<uint32_t>((ph->status ^ kPlanOk) | (ph->E ^ a.E) | (ph->k ^ a.k) | (ph->G ^ a.G));
+    asm volatile("" : "+s"(refuse));
 
-    if (task >= passes) {
-        // ---- selected features ------------------------------------------------------
-        const uint32_t p = (task - passes) * 64u + lane;
-        if (bad || p >= static_cast<uint32_t>(a.k)) return;
-        const int32_t *idx = reinterpret_cast<const int32_t *>(a.plan + a.off_idx);
-        const uint32_t off_outl = t * static_cast<uint32_t>(a.pitch_outl);
-        const uint32_t j = static_cast<uint32_t>(idx[p]);
-        float acc = 0.f;
-        for (uint32_t i0 = 0; i0 < N; i0 += 8) {
-            uint32_t v[8];
-#pragma unroll
-            for (int jj = 0; jj < 8; ++jj)
-                v[jj] = reinterpret_cast<const uint16_t *>(
-                    static_cast<const uint8_t *>(outlp.p[min(i0 + jj, N - 1u)]) + off_outl)[p];
-#pragma unroll
-            for (int jj = 0; jj < 8; ++jj) {
-                if (i0 + jj < N) {
-                    const float x = bf16_bits_to_f32(v[jj]);
-                    if (i0 + jj == 0) {
-                        acc = x;
-                    } else {
-                        acc = acc + x;
-                        if (ACC == TPQ_ACC_BF16) acc = round_via_bf16(acc);
-                    }
-                }
-            }
-        }
-        if constexpr (FUSED) {
-            if (a.addend)
-                acc = add_term<ACC>(acc, bf16_bits_to_f32(reinterpret_cast<const uint16_t *>(
-                                             a.addend + static_cast<int64_t>(t) * a.ldAdd * 2)[j]));
-            if (a.bias) acc = add_term<ACC>(acc, bf16_bits_to_f32(reinterpret_cast<const uint16_t *>(a.bias)[j]));
-        }
-        if (OUT == TPQ_OUT_FP32)
-            *reinterpret_cast<float *>(out_row + 4u * j) = acc;
-        else
-            *reinterpret_cast<uint16_t *>(out_row + 2u * j) = static_cast<uint16_t>(pack_bf16x2(acc, acc));
-        return;
-    }
+    // Selected features: four ranks of 16 columns per load, a rank's row of lanes with its own pointer.  The first 8
+    // ranks' pointers are fetched here, ahead of everything, and their first 16 columns (mostly all there are) behind
+    // the first messages: picked from scalar registers the pointers cost 40 instructions a wave, and fetched
+    // behind the messages' loads a second wait for all of those (18.7 and 21.5 us at T = 2048, E = 5120,
+    // N = 8).  (The host fills the table up to a multiple of 8 with the first pointer, and passes the
+    // codes' pointers where there are no selected features; nobody looks at what is read then.)
+    const int32_t *idx = reinterpret_cast<const int32_t *>(a.plan + a.off_idx);
+    const uint32_t off_outl = t * static_cast<uint32_t>(a.pitch_outl), sel_at = min(s0 + (lane & 15u), max(k, 1u) - 1u);
+    const uint32_t nq = (N + 3u) >> 2;
+    const void *const *po = outlp.p + (lane >> 4);
+    const void *const sel_p0 = po[0], *const sel_p1 = po[4];
+    auto load_sel = [&](const void *p) __attribute__((always_inline)) {
+        return static_cast<uint32_t>(
+            *reinterpret_cast<const uint16_t *>(static_cast<const uint8_t *>(p) + (off_outl + 2u * sel_at)));
+    };
+    uint32_t sel_col = 0u, sel_v0 = 0u, sel_v1 = 0u;
 
-    // ---- one pass of quantised features ---------------------------------------------
-    const uint32_t chunk = task * 64u + lane;
-    const uint32_t g = min(chunk / LPG, ng - 1u);
-    // the pass's store entries: where they start, blocks, blocks + narrow entries
-    const uint4 sp = reinterpret_cast<const uint4 *>(a.plan + a.off_spass)[task];
-    const uint32_t first = min(sp.x, static_cast<uint32_t>(a.sblk_cap));
-    const uint32_t *entries = reinterpret_cast<const uint32_t *>(a.plan + a.off_sblk) + first;
-    const uint32_t nall = min(sp.y + sp.z, static_cast<uint32_t>(a.sblk_cap) - first), nb = min(sp.y, nall);
-    const uint32_t e0 = lane < nall ? entries[lane] : 0u;
-    const uint32_t e1 = 64u + lane < nall ? entries[64u + lane] : 0u;
     // One 32-bit byte offset per section serves every rank (the host keeps
     // T * pitch below 2^31 per launch): the rank only changes the scalar base.
+    const uint32_t chunk = min((cp.y & 0xFFFFu) + min(lane, max(n_chunk, 1u) - 1u), max(chunks, 1u) - 1u);
+    const uint32_t g = min(chunk / LPG, max(ng, 1u) - 1u);
     const uint32_t off_codes = t * static_cast<uint32_t>(a.pitch_codes) +
-                               (GEN ? static_cast<uint32_t>(a.bits) : 4u) * min(chunk, chunks - 1u);
+                               (GEN ? static_cast<uint32_t>(a.bits) : 4u) * chunk;
     const uint32_t off_meta = t * static_cast<uint32_t>(a.pitch_meta) + 2u * g;
+    const bool quant = n_chunk > 0 && chunks > 0;
+    const u32x4 cols = reinterpret_cast<const u32x4 *>(a.plan + a.off_src)[chunk];  // (in the plan also where there is none)
     float acc[8];
 
     // 8 ranks at a time: all 24 loads first, then the arithmetic.  FULL batches index
     // the pointer tables with constants (one wide scalar load each); the last, partial
     // batch guards every rank.
     // (the code width is a compile-time constant inside: one copy of the loop per width)
-    auto batch = [&](uint32_t i0, auto full_tag, auto bits_tag) {
+    auto batch = [&](uint32_t i0, auto full_tag, auto bits_tag, auto first_tag) __attribute__((always_inline)) {
         constexpr bool FULL = decltype(full_tag)::value;
         constexpr int BITS = decltype(bits_tag)::value;
+        constexpr bool FIRST = decltype(first_tag)::value;
         uint32_t w[8], sb[8], zb[8];
         uint64_t wq[8];  // GEN
         const void *const *pc = codesp.p + i0;
@@ -332,6 +290,11 @@ __global__ __launch_bounds__(256) void k_decode_pass(DecodeArgs a, RankPtrs code
                     static_cast<const uint8_t *>(pc[i]) + off_codes));
             sb[j] = *reinterpret_cast<const uint16_t *>(static_cast<const uint8_t *>(ps[i]) + off_meta);
             zb[j] = *reinterpret_cast<const uint16_t *>(static_cast<const uint8_t *>(pz[i]) + off_meta);
+        }
+        if constexpr (FIRST) {
+            sel_v0 = load_sel(sel_p0);
+            sel_v1 = load_sel(sel_p1);
+            sel_col = static_cast<uint32_t>(idx[sel_at]);
         }
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
@@ -364,31 +327,115 @@ __global__ __launch_bounds__(256) void k_decode_pass(DecodeArgs a, RankPtrs code
             }
         }
     };
-    auto run = [&](auto bits_tag) {
-        uint32_t i0 = 0;
-        for (; i0 + 8 <= N; i0 += 8) batch(i0, std::true_type{}, bits_tag);
-        if (i0 < N) batch(i0, std::false_type{}, bits_tag);
-    };
-    if constexpr (GEN) {
-        switch (a.bits) {
-        case 2: run(std::integral_constant<int, 2>{}); break;
-        case 3: run(std::integral_constant<int, 3>{}); break;
-        case 5: run(std::integral_constant<int, 5>{}); break;
-        case 6: run(std::integral_constant<int, 6>{}); break;
-        default: run(std::integral_constant<int, 8>{}); break;
+    auto run = [&](auto bits_tag) __attribute__((always_inline)) {
+        // (the first batch is code of its own: it has constant pointers and fetches the selected features)
+        if (N < 8) {
+            batch(0, std::false_type{}, bits_tag, std::true_type{});
+            return;
         }
-    } else {
-        run(std::integral_constant<int, 4>{});
+        batch(0, std::true_type{}, bits_tag, std::true_type{});
+        uint32_t i0 = 8;
+        for (; i0 + 8 <= N; i0 += 8) batch(i0, std::true_type{}, bits_tag, std::false_type{});
+        if (i0 < N) batch(i0, std::false_type{}, bits_tag, std::false_type{});
+    };
+    __shared__ u32x4 rows[4 * kRowQuads];
+    float *const row = reinterpret_cast<float *>(rows + wave * kRowQuads);
+    if (quant) {
+        if constexpr (GEN) {
+            switch (a.bits) {
+            case 2: run(std::integral_constant<int, 2>{}); break;
+            case 3: run(std::integral_constant<int, 3>{}); break;
+            case 5: run(std::integral_constant<int, 5>{}); break;
+            case 6: run(std::integral_constant<int, 6>{}); break;
+            default: run(std::integral_constant<int, 8>{}); break;
+            }
+        } else {
+            run(std::integral_constant<int, 4>{});
+        }
+        scatter_chunk(row, acc, cols, col0, chunk < static_cast<uint32_t>(a.r) >> 3);
     }
-    if (bad) return;
+    if (refuse) return;
+
+    // ---- selected features ----------------------------------------------------------------
+    const bool few = quant && n_sel <= 16u;
+    if (few && n_sel > 0) {
+        float v = 0.0f;
+        add_quad<ACC>(v, sel_v0, 0u, N);
+        if (nq > 1) add_quad<ACC>(v, sel_v1, 1u, N);
+        for (uint32_t rq = 2; rq < nq; ++rq)
+            add_quad<ACC>(v, load_sel(po[4u * rq]), rq, N);
+        if (lane < n_sel) row[min(sel_col - col0, kRowNowhere)] = v;
+    }
+    for (uint32_t p0 = few ? n_sel : 0u; p0 < n_sel; p0 += 64) {  // many in one pass: a lane per column
+        const uint32_t p = min(s0 + p0 + lane, k - 1u);
+        float v = 0.0f;
+        for (uint32_t i0 = 0; i0 < N; i0 += 8) {
+            uint32_t b[8];
+#pragma unroll
+            for (int jj = 0; jj < 8; ++jj)
+                b[jj] = reinterpret_cast<const uint16_t *>(
+                    static_cast<const uint8_t *>(outlp.p[min(i0 + jj, N - 1u)]) + off_outl)[p];
+#pragma unroll
+            for (int jj = 0; jj < 8; ++jj)
+                if (i0 + jj < N) v = i0 + jj == 0 ? bf16_bits_to_f32(b[jj]) : add_term<ACC>(v, bf16_bits_to_f32(b[jj]));
+        }
+        if (p0 + lane < n_sel) row[min(static_cast<uint32_t>(idx[p]) - col0, kRowNowhere)] = v;
+    }
+    wave_lds_fence();
+
+    // ---- a lane's columns: the epilogue's terms, the store --------------------------------
+    uint8_t *const out = static_cast<uint8_t *>(a.out) + (static_cast<int64_t>(t) * a.ldOut + col0) * OB;
+    const uint8_t *addend = nullptr, *bias = nullptr;
     if constexpr (FUSED) {
-        __shared__ u32x4 stage_f[4 * 128];
-        store_pass_fused<OUT, ACC>(stage_f + wave * 128u, acc, out_row, lane, entries, nb, nall, e0, e1,
-                                   a.addend ? a.addend + static_cast<int64_t>(t) * a.ldAdd * 2 : nullptr, a.bias);
-    } else {
-        __shared__ u32x4 stage[4 * 64 * (OUT == TPQ_OUT_FP32 ? 2 : 1)];
-        store_pass<OUT>(stage + wave * (64u * (OUT == TPQ_OUT_FP32 ? 2u : 1u)), acc, out_row, lane, entries,
-                        nb, nall, e0, e1);
+        if (a.addend) addend = a.addend + (static_cast<int64_t>(t) * a.ldAdd + col0) * 2;
+        if (a.bias) bias = a.bias + 2u * col0;
+    }
+    if (OUT == TPQ_OUT_FP32) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {  // 4 columns per lane and store: neighbouring lanes', neighbouring quads
+            const uint32_t q = 64u * h + lane;
+            if (q < 2u * n_blk) {
+                const u32x4 y = rows[wave * kRowQuads + q];
+                float f[4] = {__uint_as_float(y.x), __uint_as_float(y.y), __uint_as_float(y.z), __uint_as_float(y.w)};
+                if constexpr (FUSED) {
+                    typedef uint32_t u32x2_a2 __attribute__((ext_vector_type(2), aligned(2)));
+#define TPQ_ADD4(src)                                                           \
+    {                                                                           \
+        const u32x2_a2 z = *reinterpret_cast<const u32x2_a2 *>((src) + 8u * q); \
+        f[0] = add_term<ACC>(f[0], bf16_lo_to_f32(z.x));                        \
+        f[1] = add_term<ACC>(f[1], bf16_hi_to_f32(z.x));                        \
+        f[2] = add_term<ACC>(f[2], bf16_lo_to_f32(z.y));                        \
+        f[3] = add_term<ACC>(f[3], bf16_hi_to_f32(z.y));                        \
+    }
+                    if (addend) TPQ_ADD4(addend)
+                    if (bias) TPQ_ADD4(bias)
+#undef TPQ_ADD4
+                }
+                __builtin_nontemporal_store(u32x4{__float_as_uint(f[0]), __float_as_uint(f[1]), __float_as_uint(f[2]),
+                                                  __float_as_uint(f[3])},
+                                            reinterpret_cast<u32x4 *>(out + 16u * q));
+            }
+        }
+    } else if (lane < n_blk) {
+        const u32x4 y0 = rows[wave * kRowQuads + 2u * lane], y1 = rows[wave * kRowQuads + 2u * lane + 1u];
+        float f[8] = {__uint_as_float(y0.x), __uint_as_float(y0.y), __uint_as_float(y0.z), __uint_as_float(y0.w),
+                      __uint_as_float(y1.x), __uint_as_float(y1.y), __uint_as_float(y1.z), __uint_as_float(y1.w)};
+        if constexpr (FUSED) {
+#define TPQ_ADD8(src)                                                                 \
+    {                                                                                 \
+        const u32x4 z = *reinterpret_cast<const u32x4_a2 *>((src) + 16u * lane);      \
+        f[0] = add_term<ACC>(f[0], bf16_lo_to_f32(z.x)); f[1] = add_term<ACC>(f[1], bf16_hi_to_f32(z.x)); \
+        f[2] = add_term<ACC>(f[2], bf16_lo_to_f32(z.y)); f[3] = add_term<ACC>(f[3], bf16_hi_to_f32(z.y)); \
+        f[4] = add_term<ACC>(f[4], bf16_lo_to_f32(z.z)); f[5] = add_term<ACC>(f[5], bf16_hi_to_f32(z.z)); \
+        f[6] = add_term<ACC>(f[6], bf16_lo_to_f32(z.w)); f[7] = add_term<ACC>(f[7], bf16_hi_to_f32(z.w)); \
+    }
+            if (addend) TPQ_ADD8(addend)
+            if (bias) TPQ_ADD8(bias)
+#undef TPQ_ADD8
+        }
+        __builtin_nontemporal_store(
+            u32x4{pack_bf16x2(f[0], f[1]), pack_bf16x2(f[2], f[3]), pack_bf16x2(f[4], f[5]), pack_bf16x2(f[6], f[7])},
+            reinterpret_cast<u32x4 *>(out + 16u * lane));
     }
 }
 
@@ -621,7 +668,8 @@ int launch_decode(const DecodeArgs &a_in, const RankPtrs &codes_in, const RankPt
     // TPQ_ACC_FAST is evaluated as the fp32 chain (one final rounding), which is within its tolerance
     if (accum == TPQ_ACC_FAST) accum = TPQ_ACC_FP32;
     const int lpg = a_in.G / 8;
-    const int tasks = a_in.chunks_padded / 64 + (a_in.k + 63) / 64;  // waves per row
+    // waves per row
+    const int tasks = a_in.step_c ? a_in.chunks_padded / 64 + (a_in.k + 63) / 64 : cpass_cap_of(a_in.E);
     if (tasks == 0) return TPQ_OK;
     // The kernel addresses a rank's sections with 32-bit byte offsets: rows are handed
     // over in blocks whose sections stay below 2 GiB (one block unless T is huge).
@@ -646,6 +694,8 @@ int launch_decode(const DecodeArgs &a_in, const RankPtrs &codes_in, const RankPt
             a.off_spass = o.spass;
             a.off_sblk = o.sblk;
             a.sblk_cap = sblk_cap_of(a.k, a.r);
+            a.off_src = o.src;
+            a.off_cpass = o.cpass;
         }
         RankPtrs codes = codes_in, scale = scale_in, zero = zero_in, outl = outl_in;
         a.T = a_in.T - row0 < rows_per_launch ? a_in.T - row0 : rows_per_launch;
@@ -657,9 +707,15 @@ int launch_decode(const DecodeArgs &a_in, const RankPtrs &codes_in, const RankPt
             if (zero.p[i]) zero.p[i] = static_cast<const uint8_t *>(zero.p[i]) + row0 * a_in.pitch_meta;
             if (outl.p[i]) outl.p[i] = static_cast<const uint8_t *>(outl.p[i]) + row0 * a_in.pitch_outl;
         }
+        if (!a.step_c) {  // the kernel reads 8 ranks' pointers and a value of each, whether or not it looks at them
+            if (a.k == 0) outl = codes;
+            for (int i = a.n_ranks; i & 7; ++i) outl.p[i] = outl.p[0];
+        }
         const int rpw = rows_per_wave(a.step_c != nullptr, a.T, tasks);
-        // one dimension: (row block, wave group) pairs, dealt out over the XCDs by the kernel
-        const dim3 grid(static_cast<unsigned>(((a.T + rpw - 1) / rpw * ny + 7) / 8 * 8));
+        // one dimension, dealt out over the XCDs by the kernel: (row block, wave group) pairs in the static mode, else
+        // 4 (row, pass) pairs a workgroup
+        const int64_t blocks = a.step_c ? (a.T + rpw - 1) / rpw * ny : (a.T * tasks + 3) / 4;
+        const dim3 grid(static_cast<unsigned>((blocks + 7) / 8 * 8));
 #define TPQ_LAUNCH3(LPG, ACC, OUT) launch_rows<LPG, ACC, OUT>(rpw, grid, s, a, codes, scale, zero, outl)
 #define TPQ_LAUNCH2(LPG)                                                                     \
     do {                                                                                     \

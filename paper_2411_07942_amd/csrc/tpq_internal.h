@@ -62,7 +62,15 @@ namespace tpq {
 //                                       exactly that window (the usual case: the owner then
 //                                       takes it from that lane's registers)
 //
-// Tables of the decoder's stores.  The 512 sums of a pass (in compacted order) go to
+// Table of the decoder's column passes: the row's 8-column blocks are dealt to waves, up to 64
+// consecutive blocks each and no more than the 64 chunks a wave can decode cover (63 blocks always
+// fit: 504 features and the 7 before them that share the first chunk).
+//   cpass    uint32[4 * cpass_cap_of()] per pass: first block | blocks << 16; first chunk |
+//                                       chunks << 16; first selected feature (position in idx) |
+//                                       their number << 16; 0.  Passes past the row's end: all 0.
+// A chunk on the border of two passes belongs to both.
+//
+// Tables of the static decoder's stores.  The 512 sums of a pass (in compacted order) go to
 // runs of consecutive output columns; selected columns and the pass's ends cut the
 // runs.  A run of 8 or more features is covered by "blocks" of 8 consecutive features
 // = 8 consecutive columns (the last block of a run is aligned to the run's end and may
@@ -73,7 +81,7 @@ namespace tpq {
 //   sblk     uint32[sblk_cap_of()]      per pass its blocks, then its narrow entries:
 //                                       bits 15..0 = first column, bits 24..16 = first
 //                                       feature's position within the pass (0..511)
-constexpr uint32_t kPlanMagic = 0x51505434u;  // "4TPQ"
+constexpr uint32_t kPlanMagic = 0x51505435u;  // "5TPQ" (the digit counts the plan's formats: another one's plan is refused)
 constexpr int kPlanOk = 1;
 constexpr int kPlanBadIndex = 2;
 constexpr int kPlanInternal = 3;  // a table of the build overflowed (never expected)
@@ -108,7 +116,8 @@ struct PlanHeader {
     int32_t spass_offset;
     int32_t sblk_offset;
     int32_t sblk_cap;     // entries sblk has room for
-    int32_t reserved3[6];
+    int32_t cpass_offset;
+    int32_t reserved3[5];
 };
 static_assert(sizeof(PlanHeader) == 128, "plan header is 128 bytes");
 
@@ -148,8 +157,11 @@ __host__ __device__ inline int sblk_cap_of(int k, int r)
     return bound < 9 * cp ? bound : 9 * cp;
 }
 
+// Column passes of a row at most (every pass but the last has 63 or 64 blocks).
+__host__ __device__ inline int cpass_cap_of(int E) { return (E / 8 + 62) / 63; }
+
 struct PlanOffsets {
-    int idx, src, dirr, dsel, dslot8, dseg, drec, drec2, spass, sblk, total;
+    int idx, src, dirr, dsel, dslot8, dseg, drec, drec2, spass, sblk, cpass, total;
 };
 __host__ __device__ inline PlanOffsets plan_offsets(int k, int r, int G)
 {
@@ -165,7 +177,8 @@ __host__ __device__ inline PlanOffsets plan_offsets(int k, int r, int G)
     o.drec2 = o.drec + dir_segs_of(cp / 64) * 64 * 32;
     o.spass = o.drec2 + dir_segs_of(cp / 64) * 64 * 16;
     o.sblk = o.spass + (cp / 64) * 16;
-    o.total = o.sblk + (4 * sblk_cap_of(k, r) + 15) / 16 * 16;
+    o.cpass = o.sblk + (4 * sblk_cap_of(k, r) + 15) / 16 * 16;
+    o.total = o.cpass + 16 * cpass_cap_of(k + r);
     return o;
 }
 
@@ -222,7 +235,7 @@ struct DecodeArgs {
     const float *step_c;
     int32_t static_stride;
     // byte offsets of the plan's tables (what the header holds, known to the host too)
-    int32_t off_idx, off_spass, off_sblk, sblk_cap;
+    int32_t off_idx, off_spass, off_sblk, sblk_cap, off_src, off_cpass;
 };
 
 // What a kernel checks before it trusts a plan: one wide scalar load, no branches between

@@ -106,8 +106,34 @@ __device__ inline void pass_entries(const uint64_t *starts, int n, int lane, con
     narrow = w2;
 }
 
+// The decoder's column passes, by one thread: as many blocks as fit.  (Serial over at most 66 passes, in a
+// workgroup of its own beside the others.)
+__device__ inline void column_passes(const uint32_t *sel, const uint16_t *sel_before, int E, int k, int cap, uint4 *out)
+{
+    const int blocks = E / 8;
+    // selected columns below column 8 b
+    auto before = [&](int b) {
+        return b >= blocks ? k : sel_before[b >> 2] + __builtin_popcount(sel[b >> 2] & ((1u << (8 * (b & 3))) - 1u));
+    };
+    int b0 = 0, s0 = 0;
+    for (int p = 0; p < cap; ++p) {
+        int n = min(blocks - b0, 64);
+        const int w0 = (8 * b0 - s0) / 8;
+        int s1 = before(b0 + n);
+        if ((8 * (b0 + n) - s1 + 7) / 8 - w0 > 64) s1 = before(b0 + --n);
+        const int f0 = 8 * b0 - s0, f1 = 8 * (b0 + n) - s1;  // the pass's features
+        const int nw = f1 > f0 ? (f1 + 7) / 8 - w0 : 0;
+        out[p] = n > 0 ? make_uint4(static_cast<uint32_t>(b0) | (static_cast<uint32_t>(n) << 16),
+                                    static_cast<uint32_t>(w0) | (static_cast<uint32_t>(nw) << 16),
+                                    static_cast<uint32_t>(s0) | (static_cast<uint32_t>(s1 - s0) << 16), 0u)
+                       : make_uint4(0u, 0u, 0u, 0u);
+        b0 += n;
+        s0 = s1;
+    }
+}
+
 // All tables in one launch.  A workgroup builds the tables of one of the encoder's segments (up to
-// 5 passes); what it needs of the rest of the row -- which feature sits where, how many slots and
+// 5 passes), the last one the decoder's column passes; what it needs of the rest of the row -- which feature sits where, how many slots and
 // store entries come before its own -- it works out itself in LDS (a few thousand integers), so
 // that no workgroup waits for another and no table makes a round trip through memory.  The work is
 // latency, not bytes: as twelve dependent launches, three of them serial walks over the row, it took
@@ -172,6 +198,10 @@ __global__ __launch_bounds__(kPlanThreads) void k_plan(uint8_t *plan, const int3
         for (int w = 0; w < wave; ++w) before += wave_part[w];
         if (tid < words) sel_before[tid] = static_cast<uint16_t>(before);
         __syncthreads();
+        if (blockIdx.x == gridDim.x - 1) {
+            if (tid == 0) column_passes(sel, sel_before, E, k, cpass_cap_of(E), reinterpret_cast<uint4 *>(plan + o.cpass));
+            return;
+        }
         for (int j = tid; j < E; j += kPlanThreads) {
             const uint32_t m = sel[j >> 5], bit = 1u << (j & 31);
             if (!(m & bit)) src[j - sel_before[j >> 5] - __builtin_popcount(m & (bit - 1u))] = static_cast<uint16_t>(j);
@@ -239,6 +269,7 @@ __global__ __launch_bounds__(kPlanThreads) void k_plan(uint8_t *plan, const int3
         h.spass_offset = o.spass;
         h.sblk_offset = o.sblk;
         h.sblk_cap = sblk_cap;
+        h.cpass_offset = o.cpass;
         if (!bad) {
             h.n_dirr = slots_before[64];
             // the bounds of dir_slots_of() and sblk_cap_of() hold for every index set; a plan
@@ -247,7 +278,7 @@ __global__ __launch_bounds__(kPlanThreads) void k_plan(uint8_t *plan, const int3
         }
         *reinterpret_cast<PlanHeader *>(plan) = h;
     }
-    if (bad || passes == 0 || slots_before[64] > dslots || entry0[64] > sblk_cap) return;
+    if (bad || p0 >= passes || slots_before[64] > dslots || entry0[64] > sblk_cap) return;
 
     // ---- this segment's tables -----------------------------------------------------------
     {
@@ -388,7 +419,7 @@ int launch_plan_build(const tpq_layout *L, const int32_t *idx, void *plan, hipSt
         if (e != hipSuccess) return hip_result(e);
     }
     const int segs = dir_segs_of(cp / 64);
-    k_plan<<<segs > 0 ? segs : 1, kPlanThreads, lds, s>>>(
+    k_plan<<<(segs > 0 ? segs : 1) + 1, kPlanThreads, lds, s>>>(
         static_cast<uint8_t *>(plan), idx, L->E, L->k, L->G, L->r, chunks_of(L->r), cp, dir_slots_of(L->k, L->r),
         sblk_cap_of(L->k, L->r), plan_offsets(L->k, L->r, L->G));
     return hip_result(hipGetLastError());

@@ -133,3 +133,41 @@ def test_argument_errors():
     assert call(L, E - 8) == tpq.ERR_SHAPE
     torch.cuda.synchronize()
     assert bool((out == 5.0).all().item())
+
+
+@pytest.mark.parametrize("N,E,cols", [
+    (1, 1024, list(range(5, 21))),                            # 16 selected features in a pass: one load of four ranks
+    (5, 1032, list(range(5, 22))),                            # 17: a lane per column
+    (9, 2568, [511, 512, 513, 1023, 1025, 2559, 2567]),       # around the passes' ends
+    (13, 5128, list(range(2, 5128, 70))),                     # a few in every pass
+    (16, 1024, list(range(512, 1024))),                       # a pass without quantised features
+    (17, 520, list(range(1, 520, 9))),                        # every chunk cut
+    (3, 8184, [3, 4090]),                                     # 65 chunks would lie under 64 blocks: 63 are taken
+    (8, 8, [0, 1, 2, 3, 4, 5, 6]),                            # one feature is left
+    (2, 504, list(range(504))), (7, 512, []),                 # all selected, none
+])
+def test_column_passes(N, E, cols):
+    """The decoder's column passes: the plan's table against its definition, and the sums, with and without the
+    epilogue, for rank counts on both sides of a load's four and a batch's eight."""
+    idx = np.array(cols, np.int32)
+    L = tpq.layout_init(E, idx.size, 64)
+    raw = gpu_plan(L, idx).cpu().numpy()
+    cap = (E // 8 + 62) // 63
+    off = raw[:128].view(np.int32)[26]
+    table = raw[off: off + 16 * cap].view(np.uint16).reshape(cap, 8)
+    below = np.concatenate([[0], np.cumsum(np.isin(np.arange(E), idx))])   # selected columns below column j
+    b0 = 0
+    for blk, n, w0, nw, s0, ns, *_ in table.astype(int):
+        assert _ == [0, 0]
+        if n == 0:
+            assert b0 == E // 8 and (blk, w0, nw, s0, ns) == (0, 0, 0, 0, 0)
+            continue
+        c0, c1 = 8 * blk, 8 * (blk + n)
+        f0, f1 = c0 - below[c0], c1 - below[c1]
+        assert blk == b0 and (s0, ns) == (below[c0], below[c1] - below[c0]) and w0 == f0 // 8
+        assert nw == (-(-f1 // 8) - w0 if f1 > f0 else 0) and nw <= 64 and (n >= 63 or b0 + n == E // 8)
+        b0 += n
+    assert b0 == E // 8
+    Ys, addend, bias = _inputs(E, 3, N, 11)
+    _case(E, 64, Ys, idx, addend, bias)
+    _case(E, 64, Ys, idx, None, None, ld_out=E + 8)
