@@ -194,10 +194,8 @@ __device__ __forceinline__ void add_quad(float &acc, uint32_t v, uint32_t rq, ui
 // aligned stores, a second, nearly empty round of them per pass, the epilogue's operands loaded the same way,
 // and waves of their own for the selected features.  Kernel times, before and now (T = 2048, E = 5120, k = 80, N = 8
 // unless said): with residual and bias 25.3 -> 20.9 us (fp32), 29.6 -> 25.4 (bf16 chain); without 17.5 -> 17.4; 16384 x
-// 8192, k = 341, N = 16, fp32 output 480 -> 435; 6 bits, 1777 x 5000, N = 5 22.8 -> 22.0.  Bound by instruction issue (70 % of the
-// time) and memory latency together.  Eight waves per SIMD; the other code widths need 72 registers: seven.
-// Waves are numbered through (row, pass) and not in whole workgroups per row, which would leave up to three of the last
-// one idle: at the first size above 0.2 us.
+// 8192, k = 341, N = 16, fp32 output 480 -> 431; 6 bits, 1777 x 5000, N = 5 22.8 -> 22.0.  Bound by instruction issue and
+// memory latency together.  Eight waves per SIMD; the other code widths need 72 registers: seven.
 // grid: (row, pass) pairs, 4 per workgroup, workgroups rounded up to a multiple of 8.
 // ---------------------------------------------------------------------------
 //
@@ -222,8 +220,9 @@ __global__ __launch_bounds__(256, GEN ? 7 : 8) void k_decode_pass(DecodeArgs a, 
     const uint32_t E = static_cast<uint32_t>(a.E), k = static_cast<uint32_t>(a.k);
     const uint32_t passes = static_cast<uint32_t>(cpass_cap_of(a.E));
     const uint32_t pair = xcd_contiguous_index(blockIdx.x, gridDim.x) * 4u + wave;
-    const uint32_t t = pair / passes, task = pair - t * passes;
-    if (t >= static_cast<uint32_t>(a.T)) return;  // (the grid is rounded up to 8 blocks of 4)
+    const uint32_t stride = static_cast<uint32_t>(cpass_stride_of(a.E));
+    const uint32_t t = pair / stride, task = pair - t * stride;
+    if (t >= static_cast<uint32_t>(a.T) || task >= passes) return;  // (the grid is rounded up to 8 blocks of 4)
 
     constexpr uint32_t OB = OUT == TPQ_OUT_FP32 ? 4u : 2u;  // bytes per output value
     const uint32_t N = static_cast<uint32_t>(a.n_ranks);
@@ -714,7 +713,7 @@ int launch_decode(const DecodeArgs &a_in, const RankPtrs &codes_in, const RankPt
         const int rpw = rows_per_wave(a.step_c != nullptr, a.T, tasks);
         // one dimension, dealt out over the XCDs by the kernel: (row block, wave group) pairs in the static mode, else
         // 4 (row, pass) pairs a workgroup
-        const int64_t blocks = a.step_c ? (a.T + rpw - 1) / rpw * ny : (a.T * tasks + 3) / 4;
+        const int64_t blocks = a.step_c ? (a.T + rpw - 1) / rpw * ny : (a.T * cpass_stride_of(a.E) + 3) / 4;
         const dim3 grid(static_cast<unsigned>((blocks + 7) / 8 * 8));
 #define TPQ_LAUNCH3(LPG, ACC, OUT) launch_rows<LPG, ACC, OUT>(rpw, grid, s, a, codes, scale, zero, outl)
 #define TPQ_LAUNCH2(LPG)                                                                     \
