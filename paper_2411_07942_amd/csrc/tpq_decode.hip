@@ -242,7 +242,7 @@ __global__ __launch_bounds__(256, GEN ? 7 : 8) void k_decode_pass(DecodeArgs a, 
     // the first messages: picked from scalar registers the pointers cost 40 instructions a wave, and fetched
     // behind the messages' loads a second wait for all of those (18.7 and 21.5 us at T = 2048, E = 5120,
     // N = 8).  (The host fills the table up to a multiple of 8 with the first pointer, and passes the
-    // codes' pointers where there are no selected features; nobody looks at what is read then.)
+    // codes' pointers at a pitch of 0 where there are no selected features; nobody looks at what is read then.)
     const int32_t *idx = reinterpret_cast<const int32_t *>(a.plan + a.off_idx);
     const uint32_t off_outl = t * static_cast<uint32_t>(a.pitch_outl), sel_at = min(s0 + (lane & 15u), max(k, 1u) - 1u);
     const uint32_t nq = (N + 3u) >> 2;
@@ -707,7 +707,10 @@ int launch_decode(const DecodeArgs &a_in, const RankPtrs &codes_in, const RankPt
             if (outl.p[i]) outl.p[i] = static_cast<const uint8_t *>(outl.p[i]) + row0 * a_in.pitch_outl;
         }
         if (!a.step_c) {  // the kernel reads 8 ranks' pointers and a value of each, whether or not it looks at them
-            if (a.k == 0) outl = codes;
+            if (a.k == 0) {  // no section to read from: the codes' first bytes, whatever pitch_outl the caller chose
+                outl = codes;
+                a.pitch_outl = 0;
+            }
             for (int i = a.n_ranks; i & 7; ++i) outl.p[i] = outl.p[0];
         }
         const int rpw = rows_per_wave(a.step_c != nullptr, a.T, tasks);

@@ -171,3 +171,21 @@ def test_column_passes(N, E, cols):
     Ys, addend, bias = _inputs(E, 3, N, 11)
     _case(E, 64, Ys, idx, addend, bias)
     _case(E, 64, Ys, idx, None, None, ld_out=E + 8)
+
+
+@pytest.mark.parametrize("bits", [4, 6])
+def test_no_selected_features_at_a_raised_pitch(bits):
+    """k = 0: pitch_outl may be anything and no outl section is read (there is none here)."""
+    E, T, N = 512, 9, 8
+    Ys, _, _ = _inputs(E, T, N, 17)
+    L = tpq.layout_init(E, 0, 64, bits)
+    plan = gpu_plan(L, np.zeros(0, np.int32))
+    msgs = gpu_encode(L, plan, Ys)
+    want, got = (torch.zeros((T, E), dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    tpq.decode_reduce(L, plan, msgs, want, tpq.ACC_FP32)
+    L.pitch_outl = 1 << 20
+    for m in msgs:
+        m.outl = torch.zeros(16, dtype=torch.uint8, device="cuda")
+    tpq.decode_reduce(L, plan, msgs, got, tpq.ACC_FP32)
+    torch.cuda.synchronize()
+    assert torch.equal(want, got)
