@@ -11,6 +11,7 @@
 
 #include <string.h>
 
+#include <exception>
 #include <new>
 #include <vector>
 
@@ -24,6 +25,41 @@ PyObject *g_check;         // Python: raises TpqError for a code that is not TPQ
 PyObject *g_get_device;    // torch._C._cuda_getDevice
 PyObject *g_get_stream;    // torch._C._cuda_getCurrentRawStream
 PyObject *s_codes, *s_scale, *s_zero, *s_outl, *s_cuda_stream, *s_stream;
+
+// ---- at the boundary to C ------------------------------------------------------------------
+
+struct Ref {  // an owned reference
+    PyObject *p;
+    explicit Ref(PyObject *o = nullptr) : p(o) {}
+    Ref(const Ref &) = delete;
+    Ref &operator=(const Ref &) = delete;
+    ~Ref() { Py_XDECREF(p); }
+};
+
+struct WithoutGil {
+    PyThreadState *state = PyEval_SaveThread();
+    ~WithoutGil() { PyEval_RestoreThread(state); }
+};
+
+// torch throws where a tensor has no address or no strides (sparse, or wrapped by a transform that is
+// tracing or batching it): the exception becomes Python's here, or it would end the process
+// in the interpreter's C frames.
+template <typename F>
+PyObject *no_throw(F &&f)
+{
+    try {
+        return f();
+    } catch (const std::bad_alloc &) {
+        PyErr_NoMemory();
+    } catch (const c10::Error &e) {
+        PyErr_SetString(PyExc_RuntimeError, e.what_without_backtrace());
+    } catch (const std::exception &e) {
+        PyErr_SetString(PyExc_RuntimeError, e.what());
+    } catch (...) {
+        PyErr_SetString(PyExc_RuntimeError, "unknown C++ exception");
+    }
+    return nullptr;
+}
 
 // ---- pieces of an argument list ---------------------------------------------------------
 
@@ -90,11 +126,8 @@ bool sections(const Sequence &msgs, Py_ssize_t n, PyObject *name, Pointers &dst)
     }
     dst.resize(static_cast<size_t>(n));
     for (Py_ssize_t i = 0; i < n; ++i) {
-        PyObject *t = PyObject_GetAttr(msgs.item[i], name);
-        if (!t) return false;
-        const bool ok = pointer(t, dst.p[i]);
-        Py_DECREF(t);
-        if (!ok) return false;
+        const Ref t(PyObject_GetAttr(msgs.item[i], name));
+        if (!t.p || !pointer(t.p, dst.p[i])) return false;
     }
     return true;
 }
@@ -265,11 +298,8 @@ struct Call {
                 ld2 = row_stride(*y, T, E);
             }
             Sequence m;
-            PyObject *one = PyTuple_Pack(1, a[3]);
-            if (!one) return false;
-            const bool ok = m.take(one) && message(m, 1, true);
-            Py_DECREF(one);
-            return ok;
+            const Ref one(PyTuple_Pack(1, a[3]));
+            return one.p && m.take(one.p) && message(m, 1, true);
         }
         case kDecode:          // L, plan, msgs, out, accum
         case kFused:           // L, plan, msgs, out, addend, bias, accum
@@ -349,10 +379,10 @@ struct Call {
                                             "tpq_decode_reduce_fused", "tpq_encode_static", "tpq_decode_reduce_static"};
         void *s;
         if (!stream_of(stream, s)) return false;
-        int rc;
-        Py_BEGIN_ALLOW_THREADS
-        rc = issue(s);
-        Py_END_ALLOW_THREADS
+        const int rc = [&] {
+            const WithoutGil free;
+            return issue(s);
+        }();
         return check(rc, names[kind]);
     }
 };
@@ -377,8 +407,10 @@ PyObject *call_object_call(PyObject *self, PyObject *const *args, size_t nargsf,
         return nullptr;
     }
     if (nkw == 1) stream = args[0];
-    if (!reinterpret_cast<CallObject *>(self)->call->run(stream)) return nullptr;
-    Py_RETURN_NONE;
+    return no_throw([&]() -> PyObject * {
+        if (!reinterpret_cast<CallObject *>(self)->call->run(stream)) return nullptr;
+        Py_RETURN_NONE;
+    });
 }
 
 void call_object_free(PyObject *self)
@@ -417,9 +449,11 @@ template <Kind K>
 PyObject *do_now(PyObject *, PyObject *const *args, Py_ssize_t nargs)
 {
     if (!arg_count(nargs, kArgs[K] + 1)) return nullptr;
-    Call c;
-    if (!c.take(K, args) || !c.run(args[kArgs[K]])) return nullptr;
-    Py_RETURN_NONE;
+    return no_throw([&]() -> PyObject * {
+        Call c;
+        if (!c.take(K, args) || !c.run(args[kArgs[K]])) return nullptr;
+        Py_RETURN_NONE;
+    });
 }
 
 template <Kind K>
@@ -439,20 +473,18 @@ PyObject *do_make(PyObject *, PyObject *const *args, Py_ssize_t nargs)
         if (ok) PyTuple_SET_ITEM(o->keep, i, k);
     }
     if (!ok && !PyErr_Occurred()) PyErr_NoMemory();
-    if (!ok || !o->call->take(K, args)) {
-        Py_DECREF(reinterpret_cast<PyObject *>(o));
-        return nullptr;
-    }
-    return reinterpret_cast<PyObject *>(o);
+    PyObject *self = reinterpret_cast<PyObject *>(o);
+    if (ok && no_throw([&]() -> PyObject * { return o->call->take(K, args) ? self : nullptr; })) return self;
+    Py_DECREF(self);
+    return nullptr;
 }
 
 // ---- calibration and plan -----------------------------------------------------------------
 
 // (Y, rank, n_ranks, seq_index, gamma, m, M, workspace, stream); tpq_calibrate_fixed without the workspace
 template <bool fixed>
-PyObject *do_calibrate(PyObject *, PyObject *const *a, Py_ssize_t nargs)
+PyObject *calibrate(PyObject *const *a)
 {
-    if (!arg_count(nargs, fixed ? 8 : 9)) return nullptr;
     const at::Tensor *Y = tensor(a[0]);
     if (!Y) return nullptr;
     if (Y->dim() != 2) {
@@ -475,30 +507,43 @@ PyObject *do_calibrate(PyObject *, PyObject *const *a, Py_ssize_t nargs)
     }
     const uint16_t *y = static_cast<const uint16_t *>(Y->data_ptr());
     const int64_t ld = row_stride(*Y, S, E);
-    int rc;
-    Py_BEGIN_ALLOW_THREADS
-    rc = fixed ? tpq_calibrate_fixed(y, S, ld, static_cast<int>(E), static_cast<int>(rank), static_cast<int>(n_ranks), seq,
-                                     static_cast<float>(gamma), static_cast<float *>(m), static_cast<float *>(M), s)
-               : tpq_calibrate(y, S, ld, static_cast<int>(E), static_cast<int>(rank), static_cast<int>(n_ranks), seq,
-                               static_cast<float>(gamma), static_cast<float *>(m), static_cast<float *>(M), ws, ws_bytes, s);
-    Py_END_ALLOW_THREADS
+    const int rc = [&] {
+        const WithoutGil free;
+        return fixed ? tpq_calibrate_fixed(y, S, ld, static_cast<int>(E), static_cast<int>(rank), static_cast<int>(n_ranks), seq,
+                                           static_cast<float>(gamma), static_cast<float *>(m), static_cast<float *>(M), s)
+                     : tpq_calibrate(y, S, ld, static_cast<int>(E), static_cast<int>(rank), static_cast<int>(n_ranks), seq,
+                                     static_cast<float>(gamma), static_cast<float *>(m), static_cast<float *>(M), ws, ws_bytes, s);
+    }();
     if (!check(rc, fixed ? "tpq_calibrate_fixed" : "tpq_calibrate")) return nullptr;
     Py_RETURN_NONE;
 }
 
+template <bool fixed>
+PyObject *do_calibrate(PyObject *, PyObject *const *a, Py_ssize_t nargs)
+{
+    if (!arg_count(nargs, fixed ? 8 : 9)) return nullptr;
+    return no_throw([&] { return calibrate<fixed>(a); });
+}
+
 // (L, idx_sorted, plan, stream)
-PyObject *do_plan_build(PyObject *, PyObject *const *a, Py_ssize_t nargs)
+PyObject *plan_build(PyObject *const *a)
 {
     Layout L;
     void *idx, *plan, *s;
-    if (!arg_count(nargs, 4) || !L.take(a[0]) || !pointer(a[1], idx) || !pointer(a[2], plan) || !stream_of(a[3], s)) return nullptr;
+    if (!L.take(a[0]) || !pointer(a[1], idx) || !pointer(a[2], plan) || !stream_of(a[3], s)) return nullptr;
     const size_t bytes = static_cast<size_t>(THPVariable_Unpack(a[2]).numel());
-    int rc;
-    Py_BEGIN_ALLOW_THREADS
-    rc = tpq_plan_build(L.p, static_cast<const int32_t *>(idx), plan, bytes, s);
-    Py_END_ALLOW_THREADS
+    const int rc = [&] {
+        const WithoutGil free;
+        return tpq_plan_build(L.p, static_cast<const int32_t *>(idx), plan, bytes, s);
+    }();
     if (!check(rc, "tpq_plan_build")) return nullptr;
     Py_RETURN_NONE;
+}
+
+PyObject *do_plan_build(PyObject *, PyObject *const *a, Py_ssize_t nargs)
+{
+    if (!arg_count(nargs, 4)) return nullptr;
+    return no_throw([&] { return plan_build(a); });
 }
 
 // (check, get_device, get_stream): what this module calls back

@@ -7,6 +7,8 @@ pointers are never dereferenced and the tests run without a GPU.
 import ctypes
 import os
 import re
+import subprocess
+import sys
 
 import pytest
 import torch
@@ -231,6 +233,43 @@ def test_binding_checks_tensors_before_anything_is_enqueued(seq):
     assert e.value.code == tpq.ERR_UNSUPPORTED
     with pytest.raises(TypeError):
         tpq.decode_reduce_call(L, plan, seq(msgs), out)(1, 2)
+
+
+def _binding_case(T=4, E=512):
+    L = tpq.layout_init(E, 8, 128)
+    plan = torch.zeros(tpq.plan_bytes(L), dtype=torch.uint8)
+    return (L, plan, [torch.zeros((T, E), dtype=torch.bfloat16) for _ in range(2)],
+            [tpq.Message(L, T, "cpu") for _ in range(2)])
+
+
+def _without_address(what):
+    """Each ends the process if the C++ exception behind it is not caught (run in a process of its own)."""
+    L, plan, Y, msgs = _binding_case()
+    sparse = torch.zeros((4, 512), dtype=torch.bfloat16).to_sparse()
+    state = torch.zeros((2, 512))
+    if what == "section":
+        msgs[0].codes = sparse
+        tpq.encode_call(L, plan, Y, msgs)
+    elif what == "plan":
+        tpq.decode_reduce(L, sparse, msgs, torch.zeros((4, 512)), stream=_NullStream())
+    elif what == "plan to build":
+        tpq.plan_build(L, torch.zeros(8, dtype=torch.int32), sparse, stream=_NullStream())
+    elif what == "calibrate":
+        tpq.calibrate(sparse, 0, 2, 0, 0.01, state, state, tpq.calibrate_workspace(4, 512, "cpu"), stream=_NullStream())
+    elif what == "calibrate_fixed":
+        tpq.calibrate_fixed(sparse, 0, 2, 0, 0.01, state, state, stream=_NullStream())
+    elif what == "vmap":
+        torch.vmap(lambda y: tpq.encode(L, plan, [y], msgs, stream=_NullStream()))(torch.stack(Y))
+    elif what == "jvp":
+        torch.func.jvp(lambda y: tpq.encode_call(L, plan, [y], msgs), (Y[0],), (Y[1],))
+
+
+@pytest.mark.parametrize("what", ["section", "plan", "plan to build", "calibrate", "calibrate_fixed", "vmap", "jvp"])
+def test_binding_raises_where_a_tensor_has_no_address(what):
+    code = ("import sys; sys.path[:0] = %r\nimport test_api_host as t\ntry:\n    t._without_address(%r)\n"
+            "except RuntimeError as e:\n    print('raised', e)" % ([ROOT, os.path.join(ROOT, "tests")], what))
+    r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0 and r.stdout.startswith("raised"), (r.returncode, r.stdout, r.stderr[-400:])
 
 
 def test_strerror_covers_every_code():
