@@ -529,9 +529,11 @@ PyObject *do_calibrate(PyObject *, PyObject *const *a, Py_ssize_t nargs)
 PyObject *plan_build(PyObject *const *a)
 {
     Layout L;
-    void *idx, *plan, *s;
-    if (!L.take(a[0]) || !pointer(a[1], idx) || !pointer(a[2], plan) || !stream_of(a[3], s)) return nullptr;
-    const size_t bytes = static_cast<size_t>(THPVariable_Unpack(a[2]).numel());
+    void *idx, *s;
+    const at::Tensor *buffer = tensor(a[2]);
+    if (!buffer || !L.take(a[0]) || !pointer(a[1], idx) || !stream_of(a[3], s)) return nullptr;
+    void *const plan = buffer->data_ptr();
+    const size_t bytes = static_cast<size_t>(buffer->numel());
     const int rc = [&] {
         const WithoutGil free;
         return tpq_plan_build(L.p, static_cast<const int32_t *>(idx), plan, bytes, s);

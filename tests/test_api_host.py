@@ -243,7 +243,7 @@ def _binding_case(T=4, E=512):
 
 
 def _without_address(what):
-    """Each ends the process if the C++ exception behind it is not caught (run in a process of its own)."""
+    """Each ends the process if the binding trusts the tensor (run in a process of its own)."""
     L, plan, Y, msgs = _binding_case()
     sparse = torch.zeros((4, 512), dtype=torch.bfloat16).to_sparse()
     state = torch.zeros((2, 512))
@@ -254,6 +254,8 @@ def _without_address(what):
         tpq.decode_reduce(L, sparse, msgs, torch.zeros((4, 512)), stream=_NullStream())
     elif what == "plan to build":
         tpq.plan_build(L, torch.zeros(8, dtype=torch.int32), sparse, stream=_NullStream())
+    elif what == "no plan":
+        tpq._native().plan_build(L, torch.zeros(8, dtype=torch.int32), None, _NullStream())
     elif what == "calibrate":
         tpq.calibrate(sparse, 0, 2, 0, 0.01, state, state, tpq.calibrate_workspace(4, 512, "cpu"), stream=_NullStream())
     elif what == "calibrate_fixed":
@@ -264,10 +266,10 @@ def _without_address(what):
         torch.func.jvp(lambda y: tpq.encode_call(L, plan, [y], msgs), (Y[0],), (Y[1],))
 
 
-@pytest.mark.parametrize("what", ["section", "plan", "plan to build", "calibrate", "calibrate_fixed", "vmap", "jvp"])
+@pytest.mark.parametrize("what", ["section", "plan", "plan to build", "no plan", "calibrate", "calibrate_fixed", "vmap", "jvp"])
 def test_binding_raises_where_a_tensor_has_no_address(what):
     code = ("import sys; sys.path[:0] = %r\nimport test_api_host as t\ntry:\n    t._without_address(%r)\n"
-            "except RuntimeError as e:\n    print('raised', e)" % ([ROOT, os.path.join(ROOT, "tests")], what))
+            "except (RuntimeError, TypeError) as e:\n    print('raised', e)" % ([ROOT, os.path.join(ROOT, "tests")], what))
     r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0 and r.stdout.startswith("raised"), (r.returncode, r.stdout, r.stderr[-400:])
 
