@@ -103,19 +103,44 @@ struct Pointers {
     }
 };
 
-struct Sequence {  // a borrowed view of a Python sequence
-    PyObject *fast = nullptr;
-    Py_ssize_t n = 0;
-    PyObject **item = nullptr;
-    bool take(PyObject *o)
+// What a call was given, held by value: a sequence as a tuple of its elements at that time, so that neither
+// a list emptied later nor elements made on the way leave pointers to freed memory behind.
+struct Kept {
+    PyObject *p = nullptr;
+    Kept() = default;
+    Kept(const Kept &) = delete;
+    Kept &operator=(const Kept &) = delete;
+    ~Kept() { Py_XDECREF(p); }
+    void object(PyObject *o)
     {
-        fast = PySequence_Fast(o, "a sequence is expected");
-        if (!fast) return false;
-        n = PySequence_Fast_GET_SIZE(fast);
-        item = PySequence_Fast_ITEMS(fast);
+        Py_INCREF(o);
+        Py_XSETREF(p, o);
+    }
+    bool sequence(PyObject *o)
+    {
+        // (what len() and indexing take; a generator or a set is refused)
+        if (PyObject_Size(o) < 0) return false;
+        if (!PySequence_Check(o) && !PyMapping_Check(o)) {
+            PyErr_Format(PyExc_TypeError, "a sequence is expected, not %s", Py_TYPE(o)->tp_name);
+            return false;
+        }
+        PyObject *t = PySequence_Tuple(o);
+        if (!t) return false;
+        Py_XSETREF(p, t);
         return true;
     }
-    ~Sequence() { Py_XDECREF(fast); }
+};
+
+struct Sequence {  // the elements of a tuple that is kept elsewhere
+    Py_ssize_t n = 0;
+    PyObject **item = nullptr;
+    bool take(PyObject *o, Kept &kept)
+    {
+        if (!kept.sequence(o)) return false;
+        n = PyTuple_GET_SIZE(kept.p);
+        item = PySequence_Fast_ITEMS(kept.p);
+        return true;
+    }
 };
 
 bool sections(const Sequence &msgs, Py_ssize_t n, PyObject *name, Pointers &dst)
@@ -235,8 +260,11 @@ bool check(int rc, const char *where)
 
 enum Kind { kEncode, kHop, kGemm, kDecode, kFused, kEncodeStatic, kDecodeStatic };
 
+constexpr Py_ssize_t kArgs[] = {4, 6, 5, 5, 7, 5, 6}, kMaxArgs = 7;
+
 struct Call {
     Kind kind;
+    Kept arg[kMaxArgs];  // every argument, as it was taken
     Layout L;
     void *plan = nullptr, *out = nullptr, *x = nullptr, *w = nullptr, *addend = nullptr, *bias = nullptr;
     const float *tab = nullptr;
@@ -259,18 +287,21 @@ struct Call {
     bool take(Kind k, PyObject *const *a)
     {
         kind = k;
+        for (Py_ssize_t i = 0; i < kArgs[k]; ++i) arg[i].object(a[i]);
         if (!L.take(a[0])) return false;
         const int64_t E = L.p->E;
         switch (kind) {
         case kEncode: {  // L, plan, Y, msgs
             Sequence y, m;
-            if (!pointer(a[1], plan) || !y.take(a[2]) || !m.take(a[3])) return false;
+            if (!pointer(a[1], plan) || !y.take(a[2], arg[2]) || !m.take(a[3], arg[3])) return false;
             n = static_cast<int>(y.n);
             return partial_sums(y, E, Y, T, ld) && message(m, y.n, true);
         }
         case kHop: {  // L, plan, Y, in_msgs, out_msgs, accum
             Sequence y, i, m;
-            if (!pointer(a[1], plan) || !y.take(a[2]) || !i.take(a[3]) || !m.take(a[4]) || !accumulate(a[5])) return false;
+            if (!pointer(a[1], plan) || !y.take(a[2], arg[2]) || !i.take(a[3], arg[3]) || !m.take(a[4], arg[4]) ||
+                !accumulate(a[5]))
+                return false;
             n = static_cast<int>(y.n);
             if (!partial_sums(y, E, Y, T, ld)) return false;
             if (i.n != y.n || m.n != y.n) return failed_check("a message in and out for every partial sum");
@@ -298,14 +329,15 @@ struct Call {
                 ld2 = row_stride(*y, T, E);
             }
             Sequence m;
-            const Ref one(PyTuple_Pack(1, a[3]));
-            return one.p && m.take(one.p) && message(m, 1, true);
+            m.n = 1;
+            m.item = &arg[3].p;
+            return message(m, 1, true);
         }
         case kDecode:          // L, plan, msgs, out, accum
         case kFused:           // L, plan, msgs, out, addend, bias, accum
         case kDecodeStatic: {  // L, plan, msgs, step, out, accum
             Sequence m;
-            if (!pointer(a[1], plan) || !m.take(a[2])) return false;
+            if (!pointer(a[1], plan) || !m.take(a[2], arg[2])) return false;
             n = static_cast<int>(m.n);
             if (!out_tensor(a[kind == kDecodeStatic ? 4 : 3], E, T, out_dtype, out, ld)) return false;
             if (!accumulate(a[kind == kDecode ? 4 : kind == kFused ? 6 : 5])) return false;
@@ -329,7 +361,7 @@ struct Call {
         }
         case kEncodeStatic: {  // L, plan, Y, inv, msgs
             Sequence y, m;
-            if (!pointer(a[1], plan) || !y.take(a[2]) || !m.take(a[4])) return false;
+            if (!pointer(a[1], plan) || !y.take(a[2], arg[2]) || !m.take(a[4], arg[4])) return false;
             n = static_cast<int>(y.n);
             return partial_sums(y, E, Y, T, ld) && table(a[3], y.n, tab) && message(m, y.n, false);
         }
@@ -387,15 +419,12 @@ struct Call {
     }
 };
 
-constexpr Py_ssize_t kArgs[] = {4, 6, 5, 5, 7, 5, 6};
-
 // A marshalled call: callable as call(stream=None).  Holds references to everything it was made of
-// (the tensors must stay in place).
+// (the messages' sections must stay in place).
 struct CallObject {
     PyObject_HEAD
     vectorcallfunc vectorcall;
     Call *call;
-    PyObject *keep;
 };
 
 PyObject *call_object_call(PyObject *self, PyObject *const *args, size_t nargsf, PyObject *kwnames)
@@ -417,7 +446,6 @@ void call_object_free(PyObject *self)
 {
     CallObject *o = reinterpret_cast<CallObject *>(self);
     delete o->call;
-    Py_XDECREF(o->keep);
     PyTypeObject *type = Py_TYPE(self);
     type->tp_free(self);
     Py_DECREF(type);
@@ -463,18 +491,12 @@ PyObject *do_make(PyObject *, PyObject *const *args, Py_ssize_t nargs)
     CallObject *o = reinterpret_cast<CallObject *>(g_call_type->tp_alloc(g_call_type, 0));
     if (!o) return nullptr;
     o->vectorcall = call_object_call;
-    o->call = new (std::nothrow) Call;
-    // lists of tensors and messages by value: the caller's list may change
-    o->keep = PyTuple_New(nargs);
-    bool ok = o->call && o->keep;
-    for (Py_ssize_t i = 0; ok && i < nargs; ++i) {
-        PyObject *k = PyList_Check(args[i]) ? PyList_AsTuple(args[i]) : (Py_INCREF(args[i]), args[i]);
-        ok = k != nullptr;
-        if (ok) PyTuple_SET_ITEM(o->keep, i, k);
-    }
-    if (!ok && !PyErr_Occurred()) PyErr_NoMemory();
     PyObject *self = reinterpret_cast<PyObject *>(o);
-    if (ok && no_throw([&]() -> PyObject * { return o->call->take(K, args) ? self : nullptr; })) return self;
+    if (no_throw([&]() -> PyObject * {
+            o->call = new Call;
+            return o->call->take(K, args) ? self : nullptr;
+        }))
+        return self;
     Py_DECREF(self);
     return nullptr;
 }

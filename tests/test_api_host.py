@@ -4,11 +4,13 @@ No compute call is made here: every call below either fails its argument check
 (detected before anything is enqueued) or has nothing to do (T = 0), so the fake
 pointers are never dereferenced and the tests run without a GPU.
 """
+import collections
 import ctypes
 import os
 import re
 import subprocess
 import sys
+import weakref
 
 import pytest
 import torch
@@ -272,6 +274,61 @@ def test_binding_raises_where_a_tensor_has_no_address(what):
             "except (RuntimeError, TypeError) as e:\n    print('raised', e)" % ([ROOT, os.path.join(ROOT, "tests")], what))
     r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0 and r.stdout.startswith("raised"), (r.returncode, r.stdout, r.stderr[-400:])
+
+
+class _Made:
+    """A sequence whose elements exist only while someone holds them."""
+
+    def __init__(self, make):
+        self.make = make
+
+    def __len__(self):
+        return 2
+
+    def __getitem__(self, i):
+        if i >= 2:
+            raise IndexError(i)
+        return self.make()
+
+
+@pytest.mark.parametrize("seq", [list, tuple, collections.deque, _Made])
+def test_marshalled_calls_keep_what_they_point_to(seq):
+    """A call's tensors and messages live as long as it does, whatever sequence they came in."""
+    L, plan, _, _ = _binding_case()
+    alive = []
+
+    def tensor():
+        t = torch.zeros((4, 512), dtype=torch.bfloat16)
+        alive.append(weakref.ref(t))
+        return t
+
+    def message():
+        m = tpq.Message(L, 4, "cpu")
+        alive.append(weakref.ref(m))
+        return m
+    if seq is _Made:
+        Y, msgs = _Made(tensor), _Made(message)
+    else:
+        Y, msgs = (seq([f(), f()]) for f in (tensor, message))
+    call = tpq.encode_call(L, plan, Y, msgs)
+    for s in (Y, msgs):
+        if hasattr(s, "clear"):
+            s.clear()
+    del Y, msgs, s
+    assert len(alive) == 4 and all(r() is not None for r in alive)
+    del call
+    assert all(r() is None for r in alive)
+
+
+@pytest.mark.parametrize("no_sequence", [iter, set, lambda y: (t for t in y), lambda y: dict(enumerate(y))])
+def test_what_is_no_sequence_is_refused(no_sequence):
+    L, plan, Y, msgs = _binding_case()
+    for f in (lambda: tpq.encode_call(L, plan, no_sequence(Y), msgs),
+              lambda: tpq.encode(L, plan, no_sequence(Y), msgs, stream=_NullStream())):
+        with pytest.raises(TypeError):
+            f()
+    # a tensor is one: a row per rank
+    tpq.encode_call(L, plan, torch.stack(Y), msgs)
 
 
 def test_strerror_covers_every_code():
