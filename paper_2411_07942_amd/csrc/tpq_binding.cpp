@@ -436,16 +436,41 @@ PyObject *call_object_call(PyObject *self, PyObject *const *args, size_t nargsf,
         return nullptr;
     }
     if (nkw == 1) stream = args[0];
+    const Call *const call = reinterpret_cast<CallObject *>(self)->call;
+    if (!call) {
+        PyErr_SetString(PyExc_RuntimeError, "the call has been collected");
+        return nullptr;
+    }
     return no_throw([&]() -> PyObject * {
-        if (!reinterpret_cast<CallObject *>(self)->call->run(stream)) return nullptr;
+        if (!call->run(stream)) return nullptr;
         Py_RETURN_NONE;
     });
 }
 
-void call_object_free(PyObject *self)
+// (a cycle through a message or a module that holds its own calls is the collector's to free)
+int call_object_traverse(PyObject *self, visitproc visit, void *arg)
+{
+    Py_VISIT(Py_TYPE(self));
+    if (const Call *c = reinterpret_cast<CallObject *>(self)->call) {
+        if (c->L.p) Py_VISIT(c->L.view.obj);
+        for (const Kept &k : c->arg) Py_VISIT(k.p);
+    }
+    return 0;
+}
+
+int call_object_clear(PyObject *self)
 {
     CallObject *o = reinterpret_cast<CallObject *>(self);
-    delete o->call;
+    Call *c = o->call;
+    o->call = nullptr;
+    delete c;
+    return 0;
+}
+
+void call_object_free(PyObject *self)
+{
+    PyObject_GC_UnTrack(self);
+    call_object_clear(self);
     PyTypeObject *type = Py_TYPE(self);
     type->tp_free(self);
     Py_DECREF(type);
@@ -457,12 +482,14 @@ PyMemberDef call_members[] = {
 };
 PyType_Slot call_slots[] = {
     {Py_tp_dealloc, reinterpret_cast<void *>(call_object_free)},
+    {Py_tp_traverse, reinterpret_cast<void *>(call_object_traverse)},
+    {Py_tp_clear, reinterpret_cast<void *>(call_object_clear)},
     {Py_tp_call, reinterpret_cast<void *>(PyVectorcall_Call)},
     {Py_tp_members, call_members},
     {0, nullptr},
 };
 PyType_Spec call_spec = {"paper_2411_07942_amd._binding.Call", sizeof(CallObject), 0,
-                         Py_TPFLAGS_DEFAULT | Py_TPFLAGS_HAVE_VECTORCALL, call_slots};
+                         Py_TPFLAGS_DEFAULT | Py_TPFLAGS_HAVE_VECTORCALL | Py_TPFLAGS_HAVE_GC, call_slots};
 PyTypeObject *g_call_type;
 
 bool arg_count(Py_ssize_t got, Py_ssize_t want)

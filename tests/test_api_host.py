@@ -6,6 +6,7 @@ pointers are never dereferenced and the tests run without a GPU.
 """
 import collections
 import ctypes
+import gc
 import os
 import re
 import subprocess
@@ -318,6 +319,15 @@ def test_marshalled_calls_keep_what_they_point_to(seq):
     assert len(alive) == 4 and all(r() is not None for r in alive)
     del call
     assert all(r() is None for r in alive)
+
+
+def test_a_message_that_holds_its_own_call_is_collected():
+    L, plan, Y, msgs = _binding_case()
+    msgs[0].call = tpq.encode_call(L, plan, Y, msgs)
+    held = weakref.ref(msgs[0])
+    del msgs
+    gc.collect()
+    assert held() is None
 
 
 @pytest.mark.parametrize("no_sequence", [iter, set, lambda y: (t for t in y), lambda y: dict(enumerate(y))])
