@@ -24,7 +24,7 @@ namespace {
 PyObject *g_check;         // Python: raises TpqError for a code that is not TPQ_OK
 PyObject *g_get_device;    // torch._C._cuda_getDevice
 PyObject *g_get_stream;    // torch._C._cuda_getCurrentRawStream
-PyObject *s_codes, *s_scale, *s_zero, *s_outl, *s_cuda_stream, *s_stream;
+PyObject *s_codes, *s_scale, *s_zero, *s_outl, *s_cuda_stream, *s_stream, *s_data_ptr;
 
 // ---- at the boundary to C ------------------------------------------------------------------
 
@@ -78,14 +78,18 @@ const at::Tensor *tensor(PyObject *o)
     return &THPVariable_Unpack(o);
 }
 
-bool pointer(PyObject *o, void *&p)  // None: null
+bool pointer(PyObject *o, void *&p)  // None: null; any object with a data_ptr() (a storage, say) has an address
 {
     p = nullptr;
     if (o == Py_None) return true;
-    const at::Tensor *t = tensor(o);
-    if (!t) return false;
-    p = t->data_ptr();
-    return true;
+    if (THPVariable_CheckExact(o)) {
+        p = THPVariable_Unpack(o).data_ptr();
+        return true;
+    }
+    const Ref a(PyObject_CallMethodNoArgs(o, s_data_ptr));
+    if (!a.p) return false;
+    p = PyLong_AsVoidPtr(a.p);
+    return !PyErr_Occurred();
 }
 
 struct Pointers {
@@ -164,7 +168,8 @@ int64_t row_stride(const at::Tensor &t, int64_t T, int64_t E)
     return T > 1 ? s : (s > E ? s : E);
 }
 
-// the ranks' partial sums: bf16, one shape, unit column stride, one row stride
+// the ranks' partial sums: bf16, one shape, unit column stride, one row stride (dimensions past the second are
+// the caller's, here and for the outputs: a [T, E, 1] is rows and columns too)
 bool partial_sums(const Sequence &Y, int64_t E, Pointers &dst, int64_t &T, int64_t &ld)
 {
     dst.resize(static_cast<size_t>(Y.n));
@@ -177,15 +182,14 @@ bool partial_sums(const Sequence &Y, int64_t E, Pointers &dst, int64_t &T, int64
         const at::Tensor *y = tensor(Y.item[i]);
         if (!y) return false;
         if (i == 0) {
-            if (y->dim() != 2) return failed_check("partial sums are two-dimensional");
+            if (y->dim() < 2) return failed_check("partial sums have rows and columns");
             first = y;
             T = y->size(0);
             ld = row_stride(*y, T, E);
         }
-        if (y->scalar_type() != at::kBFloat16 || y->dim() != 2 || y->size(0) != T || y->size(1) != first->size(1) ||
-            y->stride(1) != 1 || (T > 1 && y->stride(0) != ld))
+        if (y->scalar_type() != at::kBFloat16 || y->sizes() != first->sizes() || y->stride(1) != 1 || (T > 1 && y->stride(0) != ld))
             return failed_check("partial sums are bf16 tensors of one shape and row stride, unit column stride");
-        dst.p[i] = y->data_ptr();
+        if (!pointer(Y.item[i], dst.p[i])) return false;
     }
     return true;
 }
@@ -194,13 +198,12 @@ bool out_tensor(PyObject *o, int64_t E, int64_t &T, int &dtype, void *&p, int64_
 {
     const at::Tensor *t = tensor(o);
     if (!t) return false;
-    if ((t->scalar_type() != at::kFloat && t->scalar_type() != at::kBFloat16) || t->dim() != 2 || t->stride(1) != 1)
+    if ((t->scalar_type() != at::kFloat && t->scalar_type() != at::kBFloat16) || t->dim() < 2 || t->stride(1) != 1)
         return failed_check("out is a bf16 or fp32 matrix with unit column stride");
     T = t->size(0);
     dtype = t->scalar_type() == at::kFloat ? TPQ_OUT_FP32 : TPQ_OUT_BF16;
-    p = t->data_ptr();
     ld = row_stride(*t, T, E);
-    return true;
+    return pointer(o, p);
 }
 
 bool table(PyObject *o, Py_ssize_t n, const float *&p)  // step or inv: fp32, contiguous, a row per rank
@@ -209,7 +212,9 @@ bool table(PyObject *o, Py_ssize_t n, const float *&p)  // step or inv: fp32, co
     if (!t) return false;
     if (t->scalar_type() != at::kFloat || !t->is_contiguous() || t->dim() < 1 || t->size(0) < n)
         return failed_check("the step table is a contiguous fp32 tensor with a row per rank");
-    p = static_cast<const float *>(t->data_ptr());
+    void *v;
+    if (!pointer(o, v)) return false;
+    p = static_cast<const float *>(v);
     return true;
 }
 
@@ -317,15 +322,14 @@ struct Call {
             K = static_cast<int>(X->size(1));
             if (W->scalar_type() != at::kBFloat16 || !W->is_contiguous() || W->dim() != 2 || W->size(0) != E || W->size(1) != K)
                 return failed_check("Wp is the contiguous bf16 [E, K] of gemm_weights");
-            x = X->data_ptr();
-            w = W->data_ptr();
+            if (!pointer(a[1], x) || !pointer(a[2], w)) return false;
             ld = row_stride(*X, T, K);
             if (a[4] != Py_None) {
                 const at::Tensor *y = tensor(a[4]);
                 if (!y) return false;
-                if (y->scalar_type() != at::kBFloat16 || y->dim() != 2 || y->size(0) != T || y->stride(1) != 1)
+                if (y->scalar_type() != at::kBFloat16 || y->dim() < 2 || y->size(0) != T || y->stride(1) != 1)
                     return failed_check("Y_msg is a bf16 matrix with a row per token and unit column stride");
-                out = y->data_ptr();
+                if (!pointer(a[4], out)) return false;
                 ld2 = row_stride(*y, T, E);
             }
             Sequence m;
@@ -347,7 +351,7 @@ struct Call {
                 if (!t) return false;
                 if (t->scalar_type() != at::kBFloat16 || t->dim() != 2 || t->size(0) != T || t->size(1) != E || t->stride(1) != 1)
                     return failed_check("addend is a bf16 [T, E] with unit column stride");
-                addend = t->data_ptr();
+                if (!pointer(a[4], addend)) return false;
                 ld2 = row_stride(*t, T, E);
             }
             if (kind == kFused && a[5] != Py_None) {
@@ -355,7 +359,7 @@ struct Call {
                 if (!t) return false;
                 if (t->scalar_type() != at::kBFloat16 || t->dim() != 1 || t->size(0) != E || !t->is_contiguous())
                     return failed_check("bias is a contiguous bf16 [E]");
-                bias = t->data_ptr();
+                if (!pointer(a[5], bias)) return false;
             }
             return message(m, m.n, kind != kDecodeStatic);
         }
@@ -551,16 +555,17 @@ PyObject *calibrate(PyObject *const *a)
     if (!fixed) {
         const at::Tensor *t = tensor(a[7]);
         if (!t) return nullptr;
-        ws = t->data_ptr();
+        if (!pointer(a[7], ws)) return nullptr;
         ws_bytes = static_cast<size_t>(t->numel()) * t->element_size();
     }
-    const uint16_t *y = static_cast<const uint16_t *>(Y->data_ptr());
+    void *y;
+    if (!pointer(a[0], y)) return nullptr;
     const int64_t ld = row_stride(*Y, S, E);
     const int rc = [&] {
         const WithoutGil free;
-        return fixed ? tpq_calibrate_fixed(y, S, ld, static_cast<int>(E), static_cast<int>(rank), static_cast<int>(n_ranks), seq,
+        return fixed ? tpq_calibrate_fixed(static_cast<const uint16_t *>(y), S, ld, static_cast<int>(E), static_cast<int>(rank), static_cast<int>(n_ranks), seq,
                                            static_cast<float>(gamma), static_cast<float *>(m), static_cast<float *>(M), s)
-                     : tpq_calibrate(y, S, ld, static_cast<int>(E), static_cast<int>(rank), static_cast<int>(n_ranks), seq,
+                     : tpq_calibrate(static_cast<const uint16_t *>(y), S, ld, static_cast<int>(E), static_cast<int>(rank), static_cast<int>(n_ranks), seq,
                                      static_cast<float>(gamma), static_cast<float *>(m), static_cast<float *>(M), ws, ws_bytes, s);
     }();
     if (!check(rc, fixed ? "tpq_calibrate_fixed" : "tpq_calibrate")) return nullptr;
@@ -578,10 +583,9 @@ PyObject *do_calibrate(PyObject *, PyObject *const *a, Py_ssize_t nargs)
 PyObject *plan_build(PyObject *const *a)
 {
     Layout L;
-    void *idx, *s;
+    void *idx, *plan, *s;
     const at::Tensor *buffer = tensor(a[2]);
-    if (!buffer || !L.take(a[0]) || !pointer(a[1], idx) || !stream_of(a[3], s)) return nullptr;
-    void *const plan = buffer->data_ptr();
+    if (!buffer || !L.take(a[0]) || !pointer(a[1], idx) || !pointer(a[2], plan) || !stream_of(a[3], s)) return nullptr;
     const size_t bytes = static_cast<size_t>(buffer->numel());
     const int rc = [&] {
         const WithoutGil free;
@@ -634,7 +638,8 @@ PyMODINIT_FUNC PyInit__binding(void)
     s_outl = PyUnicode_InternFromString("outl");
     s_cuda_stream = PyUnicode_InternFromString("cuda_stream");
     s_stream = PyUnicode_InternFromString("stream");
+    s_data_ptr = PyUnicode_InternFromString("data_ptr");
     g_call_type = reinterpret_cast<PyTypeObject *>(PyType_FromSpec(&call_spec));
-    if (!g_call_type || !s_codes || !s_scale || !s_zero || !s_outl || !s_cuda_stream || !s_stream) return nullptr;
+    if (!g_call_type || !s_codes || !s_scale || !s_zero || !s_outl || !s_cuda_stream || !s_stream || !s_data_ptr) return nullptr;
     return PyModule_Create(&module);
 }

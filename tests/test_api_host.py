@@ -321,6 +321,30 @@ def test_marshalled_calls_keep_what_they_point_to(seq):
     assert all(r() is None for r in alive)
 
 
+def test_what_has_an_address_and_rows_is_taken():
+    """Objects with a data_ptr() (a storage, a tensor subclass with its own) and dimensions past rows and columns."""
+    class Elsewhere(torch.Tensor):
+        def data_ptr(self):
+            return self.address
+
+    L, plan, Y, msgs = _binding_case()
+    out = torch.zeros((4, 512, 1))
+    tpq.encode_call(L, plan.untyped_storage(), [y.unsqueeze(-1) for y in Y], msgs)
+    tpq.decode_reduce_call(L, plan.untyped_storage(), msgs, out)
+    tpq.gemm_encode_call(L, Y[0][:, :8], torch.zeros((512, 8), dtype=torch.bfloat16), msgs[0], Y[0].unsqueeze(-1))
+    with pytest.raises(AssertionError):
+        tpq.encode_call(L, plan, [Y[0].unsqueeze(-1), Y[1]], msgs)
+    with pytest.raises(AttributeError):
+        tpq.encode_call(L, 1.0, Y, msgs)
+    for address, code in ((0x10008, tpq.ERR_ALIGN), (0, tpq.ERR_NULL)):
+        for m in msgs:
+            m.codes = m.codes.as_subclass(Elsewhere)
+            m.codes.address = address
+        with pytest.raises(tpq.TpqError) as e:
+            tpq.decode_reduce(L, plan, msgs, out, stream=_NullStream())
+        assert e.value.code == code
+
+
 def test_a_message_that_holds_its_own_call_is_collected():
     L, plan, Y, msgs = _binding_case()
     msgs[0].call = tpq.encode_call(L, plan, Y, msgs)
