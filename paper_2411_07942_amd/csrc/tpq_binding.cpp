@@ -71,7 +71,8 @@ bool failed_check(const char *what)
 
 const at::Tensor *tensor(PyObject *o)
 {
-    if (!THPVariable_Check(o)) {
+    // (by its real type: isinstance() also holds for a weak reference's proxy, which has no tensor inside)
+    if (!THPVariable_CheckExact(o) && !PyObject_TypeCheck(o, reinterpret_cast<PyTypeObject *>(THPVariableClass))) {
         PyErr_SetString(PyExc_TypeError, "a torch.Tensor is expected");
         return nullptr;
     }

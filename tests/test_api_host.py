@@ -263,13 +263,16 @@ def _without_address(what):
         tpq.calibrate(sparse, 0, 2, 0, 0.01, state, state, tpq.calibrate_workspace(4, 512, "cpu"), stream=_NullStream())
     elif what == "calibrate_fixed":
         tpq.calibrate_fixed(sparse, 0, 2, 0, 0.01, state, state, stream=_NullStream())
+    elif what == "proxy":
+        tpq.encode_call(L, plan, [weakref.proxy(y) for y in Y], msgs)
     elif what == "vmap":
         torch.vmap(lambda y: tpq.encode(L, plan, [y], msgs, stream=_NullStream()))(torch.stack(Y))
     elif what == "jvp":
         torch.func.jvp(lambda y: tpq.encode_call(L, plan, [y], msgs), (Y[0],), (Y[1],))
 
 
-@pytest.mark.parametrize("what", ["section", "plan", "plan to build", "no plan", "calibrate", "calibrate_fixed", "vmap", "jvp"])
+@pytest.mark.parametrize("what", ["section", "plan", "plan to build", "no plan", "calibrate", "calibrate_fixed", "proxy", "vmap",
+                                  "jvp"])
 def test_binding_raises_where_a_tensor_has_no_address(what):
     code = ("import sys; sys.path[:0] = %r\nimport test_api_host as t\ntry:\n    t._without_address(%r)\n"
             "except (RuntimeError, TypeError) as e:\n    print('raised', e)" % ([ROOT, os.path.join(ROOT, "tests")], what))
