@@ -431,7 +431,7 @@ __global__ __launch_bounds__(kSelectTile) void k_select(const int32_t *__restric
     int pos = __builtin_popcountll(sel & ((1ull << lane) - 1ull));
 #pragma unroll
     for (int w = 0; w < kSelectTile / 64; ++w) pos += wave_sum[0][w] + (w < wave ? wave_sum[1][w] : 0);
-    if (rank < k) idx_sorted[pos] = j;
+    if (rank < k && pos < k) idx_sorted[pos] = j;  // (ranges that are NaN share ranks: more than k features may have one below k)
 }
 
 int launch_finalize(const float *m, const float *M, int N, int E, int k, float *R, float *Rbar,

@@ -506,6 +506,22 @@ def test_finalize_tile_edges(E, k):
     _finalize_both(torch.from_numpy(m_ref).cuda(), torch.from_numpy(M_ref).cuda(), m_ref, M_ref, k)
 
 
+@pytest.mark.parametrize("E,k", [(512, 8), (5120, 80)])
+def test_finalize_stays_in_bounds_with_unordered_ranges(E, k):
+    """Ranges that are NaN (calibration over an infinity) have no rank of their own: which indices come out is
+    unspecified, but they are features, and nothing is written past the k-th."""
+    M = torch.rand((2, E), device="cuda")
+    M[:, ::3] = float("nan")
+    Rbar = torch.empty(E, device="cuda")
+    idx, ranked = (torch.full((k + 1024,), -7, dtype=torch.int32, device="cuda") for _ in range(2))
+    ws = torch.empty(tpq.calibrate_finalize_workspace_bytes(E), dtype=torch.uint8, device="cuda")
+    tpq.calibrate_finalize(-M, M, k, Rbar, idx, ranked, ws)
+    torch.cuda.synchronize()
+    for t in (idx, ranked):
+        assert bool((t[k:] == -7).all().item())
+        assert bool(((t[:k] == -7) | ((t[:k] >= 0) & (t[:k] < E))).all().item())
+
+
 def test_hip_graph_replays_match_eager():
     """encode + decode_reduce of several blocks captured in one HIP graph: every replay, with
     eager work and synchronisation in between, gives the eager result."""
