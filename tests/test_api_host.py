@@ -163,6 +163,16 @@ def test_decode_argument_errors():
     assert call(T=0) == tpq.OK
 
 
+@pytest.mark.parametrize("G,most", [(32, 65535 * 128), (128, 65535 * 128), (256, 65535 * 64)])
+def test_linear_layer_refuses_more_rows_than_it_states(G, most):
+    """With a misaligned message, so that nothing is enqueued for a row count that is taken either."""
+    lib = tpq._load()
+    L = tpq.layout_init(512, 8, G)
+    for T, want in ((most, tpq.ERR_ALIGN), (most + 1, tpq.ERR_SHAPE), (1 << 26, tpq.ERR_SHAPE)):
+        assert lib.tpq_gemm_encode(ctypes.byref(L), _fake(), T, 8, 8, _fake(), _fake(0x10008), _fake(), _fake(), _fake(),
+                                   None, 0, None) == want
+
+
 def test_calibrate_and_plan_argument_errors():
     lib = tpq._load()
     f = _fake
