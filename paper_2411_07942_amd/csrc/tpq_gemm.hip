@@ -84,7 +84,8 @@ struct TileShape {
     static constexpr int pairs = pairs_lds < pairs_cnt ? pairs_lds : pairs_cnt;
     static constexpr int nbuf = 2 * pairs + 1;
     static constexpr int lds = nbuf * stage;
-    static_assert(pairs >= 2 && (pairs - 2) * 2 * nl + n2 <= 63 && tt * (ft * 2 + 16) <= lds, "tile fits");
+    static_assert(pairs >= 2 && tt * (ft * 2 + 16) <= lds, "tile fits");
+    static_assert((pairs - 2) * 2 * nl + n2 <= 63 && (pairs - 1) * 2 * nl <= 63, "the loop's and the prologue's waits can be counted");
 };
 
 #define TPQ_PIN __builtin_amdgcn_sched_barrier(0)
@@ -313,6 +314,8 @@ __global__ __launch_bounds__(64 * FW * TW, 1) void k_gemm_tile(GemmArgs a, uint3
     const int nkt = (K + kTileBK - 1) / kTileBK, np = (nkt + 1) / 2;
     const int k_last = max(K - kTileBK, 0);
     auto k_bytes = [&](int kt) { return static_cast<uint32_t>(2 * min(kt * kTileBK, k_last)); };
+    // (m0 is reserved, so it cannot be named as changed: the compiler keeps nothing in it, and no other
+    // instruction of this kernel needs it)
     auto dma = [&](int i, uint32_t kb2, uint32_t buf) {
         const uint32_t m = lds0 + buf + 1024u * S::waves * i;
         if (i < S::nla)
