@@ -130,9 +130,10 @@ __device__ __forceinline__ void ema_update(float *state, float c, int first, flo
 }
 
 // Combine the parts and apply Eq. (1), (2) to one device's state.  A block owns 64 features; its
-// 16 waves take interleaved parts, up to 8 of them (kCalMaxParts in all) with every load in flight at once, and
-// are combined through LDS.  Bound by latency: with 4 waves that walked over their parts one
-// after the other a 16384 x 4608 chunk took 1.5 us longer (28 parts; four chunks and what follows 148 -> 142 us).
+// 16 waves take interleaved parts, two at a time with their loads in flight together (so that up to 32 parts
+// are one wait for memory, kCalMaxParts four), and are combined through LDS.  Bound by latency: with 4 waves that walked
+// over their parts one after the other a 16384 x 4608 chunk took 1.5 us longer (28 parts; four chunks and what follows
+// 148 -> 142 us).
 constexpr int kEmaWaves = 16;
 __global__ __launch_bounds__(64 * kEmaWaves) void k_ema(const float *__restrict__ partial, int parts, int E,
                                                         int first, float gamma, float *__restrict__ m,
@@ -166,10 +167,8 @@ __global__ __launch_bounds__(64 * kEmaWaves) void k_ema(const float *__restrict_
 // nothing has to meet in memory: 4 lanes span the features (64 bytes of a row), a wave's load covers 16
 // rows, 8 of them in flight per lane.  Minima are kept negated, so that all 64 results of a workgroup are
 // maxima: 16 lanes meet by DPP, the rows of lanes through LDS, 8 threads per result.
-// Bound by launch and latency, then by what E / 32 compute units can have outstanding: measured at E = 5120,
-// back to back, against the two launches above: 64 rows 3.5 / 6.0 us, 256 rows 4.3 / 6.2, 512 rows 5.0 / 6.6,
-// 1024 rows 6.9 / 7.6 (E = 512: 5.5 / 6.8), 2048 rows 11.2 / 10.5 (8.5 / 8.1), 4096 rows 19.5 / 13.9 -- hence the line at 1024.
-constexpr int64_t kColumnsMaxRows = 1024;
+// Bound by launch and latency, then by what E / 32 compute units can have outstanding; the lines below
+// say up to which size that is less than the two launches above.
 constexpr int kColLanes = 4, kColFeatures = 8 * kColLanes, kColWaves = 8;
 __global__ __launch_bounds__(64 * kColWaves) void k_columns(const uint16_t *__restrict__ Y, int S, int64_t ldY,
                                                             int E, int first, float gamma, float *__restrict__ m,
@@ -239,6 +238,18 @@ __global__ __launch_bounds__(64 * kColWaves) void k_columns(const uint16_t *__re
 }
 static_assert(64 * kColWaves == 8 * 2 * kColFeatures, "eight threads per result");
 
+// Up to how many rows a sequence is short: one launch takes as long as a compute unit needs for its share of the
+// columns, so what counts is how many workgroups of 32 features share one.  Measured against the two
+// launches, inputs from memory, in us, one / two: E = 5120 (a unit each) 256 rows 4.2 / 6.5, 768 rows 6.5 / 6.8, 896 7.1 / 7.1,
+// 1024 7.7 / 7.0; E = 512 896 rows 5.7 / 5.8, 1024 6.2 / 5.9; E = 10240 (two) 256 rows 5.6 / 6.6, 320 6.2 / 6.8, 448 7.4 / 6.9,
+// 1024 12.9 / 9.4; E = 24576 (three) 192 rows 6.8 / 6.8, 256 7.6 / 7.3; E = 32768 (four) 128 rows 7.0 / 7.0, 192 8.1 / 7.6, 1024 25.6 /
+// 14.8.
+int64_t calibrate_columns_rows(int E, int compute_units)
+{
+    const int share = ((E + kColFeatures - 1) / kColFeatures + compute_units - 1) / compute_units;
+    return share <= 1 ? 896 : 576 / share;
+}
+
 // The number of compute units of the current device (looked up once per device: the query is
 // slow compared with a launch).
 hipError_t compute_units_of_current_device(int *out)
@@ -267,14 +278,14 @@ hipError_t compute_units_of_current_device(int *out)
 int launch_colminmax_ema(const uint16_t *Y, int64_t S, int64_t ldY, int E, int first,
                          float gamma, float *m, float *M, void *ws, int max_parts, hipStream_t s)
 {
-    if (S <= kColumnsMaxRows) {
+    int cus = 0;
+    const hipError_t e0 = compute_units_of_current_device(&cus);
+    if (e0 != hipSuccess) return hip_result(e0);
+    if (S <= calibrate_columns_rows(E, cus)) {
         k_columns<<<(E + kColFeatures - 1) / kColFeatures, 64 * kColWaves, 0, s>>>(Y, static_cast<int>(S), ldY, E, first,
                                                                                     gamma, m, M);
         return hip_result(hipGetLastError());
     }
-    int cus = 0;
-    const hipError_t e0 = compute_units_of_current_device(&cus);
-    if (e0 != hipSuccess) return hip_result(e0);
     const int parts = calibrate_parts(S, E, cus, max_parts);
     const int rows_per_part = static_cast<int>((S + parts - 1) / parts);
     // the last parts may be empty when S is not a multiple; recompute the live count
