@@ -39,7 +39,8 @@ typedef unsigned int u32x4_cal __attribute__((ext_vector_type(4)));
 
 // Column min / max over one slice of rows.  Lane l of every wave owns columns
 // 8*(64*blockIdx.x + l) .. +7 and keeps 8 running minima and maxima in registers;
-// the block's waves take interleaved rows, kUnroll 128-bit loads in flight each,
+// the block's waves take interleaved rows, kUnroll 128-bit loads in flight each (one after the other, the
+// rows past the last whole step of a slice cost 1.5 to 2.5 us: 450 rows of 16384 features 10.1 -> 7.8 us),
 // and are combined through LDS.  The upper bf16 of a word is compared as the whole
 // word (it orders like the value itself; the low half is masked off at the end).
 // Partials go to `partial` as [part][0 = min, 1 = max][E].
@@ -85,7 +86,14 @@ __global__ __launch_bounds__(kStripLanes *kWavesPerBlock) void k_colminmax(
 #pragma unroll
             for (int u = 0; u < kUnroll; ++u) fold(v[u]);
         }
-        for (; t < row1; t += kWavesPerBlock) fold(__builtin_nontemporal_load(p + t * stride));
+        if (t < row1) {  // the rest in one step too (a row past the slice's last is the last one again)
+            u32x4_cal v[kUnroll];
+#pragma unroll
+            for (int u = 0; u < kUnroll; ++u)
+                v[u] = __builtin_nontemporal_load(p + min(t + u * kWavesPerBlock, row1 - 1) * stride);
+#pragma unroll
+            for (int u = 0; u < kUnroll; ++u) fold(v[u]);
+        }
 #pragma unroll
         for (int e = 1; e < 8; e += 2) {
             mn[e] = __uint_as_float(__float_as_uint(mn[e]) & 0xFFFF0000u);
@@ -130,11 +138,13 @@ __device__ __forceinline__ void ema_update(float *state, float c, int first, flo
 }
 
 // Combine the parts and apply Eq. (1), (2) to one device's state.  A block owns 64 features; its
-// 16 waves take interleaved parts, two at a time with their loads in flight together (so that up to 32 parts
-// are one wait for memory, kCalMaxParts four), and are combined through LDS.  Bound by latency: with 4 waves that walked
-// over their parts one after the other a 16384 x 4608 chunk took 1.5 us longer (28 parts; four chunks and what follows
-// 148 -> 142 us).
-constexpr int kEmaWaves = 16;
+// kEmaWaves waves take interleaved parts, two at a time with their loads in flight together (so that with 16 waves up to
+// 32 parts are one wait for memory, kCalMaxParts four), and are combined through LDS.  Bound by latency: with 4 waves
+// that walked over their parts one after the other a 16384 x 4608 chunk took 1.5 us longer (28 parts; four chunks and what
+// follows 148 -> 142 us).  Wide rows have few parts and many blocks, and 16 waves a block are then idle ones that are
+// launched all the same: up to 8 parts take 4 waves (both launches at E = 32768, 512 rows:
+// 10.75 -> 10.5 us).
+template <int kEmaWaves>
 __global__ __launch_bounds__(64 * kEmaWaves) void k_ema(const float *__restrict__ partial, int parts, int E,
                                                         int first, float gamma, float *__restrict__ m,
                                                         float *__restrict__ M)
@@ -239,15 +249,14 @@ __global__ __launch_bounds__(64 * kColWaves) void k_columns(const uint16_t *__re
 static_assert(64 * kColWaves == 8 * 2 * kColFeatures, "eight threads per result");
 
 // Up to how many rows a sequence is short: one launch takes as long as a compute unit needs for its share of the
-// columns, so what counts is how many workgroups of 32 features share one.  Measured against the two
-// launches, inputs from memory, in us, one / two: E = 5120 (a unit each) 256 rows 4.2 / 6.5, 768 rows 6.5 / 6.8, 896 7.1 / 7.1,
-// 1024 7.7 / 7.0; E = 512 896 rows 5.7 / 5.8, 1024 6.2 / 5.9; E = 10240 (two) 256 rows 5.6 / 6.6, 320 6.2 / 6.8, 448 7.4 / 6.9,
-// 1024 12.9 / 9.4; E = 24576 (three) 192 rows 6.8 / 6.8, 256 7.6 / 7.3; E = 32768 (four) 128 rows 7.0 / 7.0, 192 8.1 / 7.6, 1024 25.6 /
-// 14.8.
+// columns, so what counts is how many workgroups of 32 features share one.  Measured against the two launches, inputs from
+// memory, in us, one / two: E = 5120 (a unit each) 400 rows 4.8 / 6.5, 800 rows 6.7 / 7.1, 900 7.1 / 7.1, 1024 7.7 / 7.2; E = 512
+// 800 rows 5.2 / 6.0, 1024 6.0 / 5.8; E = 12288 (two) 300 rows 6.1 / 7.3, 400 7.0 / 7.0, 450 7.4 / 6.9; E = 24576 (three) 150 rows
+// 6.2 / 7.4, 192 6.7 / 6.7, 256 7.6 / 7.1; E = 32768 (four) 100 rows 6.3 / 7.2, 150 7.4 / 7.5, 192 8.1 / 7.3, 1024 25.6 / 14.8.
 int64_t calibrate_columns_rows(int E, int compute_units)
 {
     const int share = ((E + kColFeatures - 1) / kColFeatures + compute_units - 1) / compute_units;
-    return share <= 1 ? 896 : 576 / share;
+    return share <= 1 ? 896 : share == 2 ? 400 : 600 / share;
 }
 
 // The number of compute units of the current device (looked up once per device: the query is
@@ -293,7 +302,10 @@ int launch_colminmax_ema(const uint16_t *Y, int64_t S, int64_t ldY, int E, int f
     const dim3 grid((E + kStripCols - 1) / kStripCols, live_parts);
     float *partial = static_cast<float *>(ws);
     k_colminmax<<<grid, kStripLanes * kWavesPerBlock, 0, s>>>(Y, S, ldY, E, rows_per_part, partial);
-    k_ema<<<(E + 63) / 64, 64 * kEmaWaves, 0, s>>>(partial, live_parts, E, first, gamma, m, M);
+    if (live_parts <= 8)
+        k_ema<4><<<(E + 63) / 64, 64 * 4, 0, s>>>(partial, live_parts, E, first, gamma, m, M);
+    else
+        k_ema<16><<<(E + 63) / 64, 64 * 16, 0, s>>>(partial, live_parts, E, first, gamma, m, M);
     return hip_result(hipGetLastError());
 }
 
