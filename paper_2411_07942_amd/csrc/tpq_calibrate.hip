@@ -251,12 +251,12 @@ static_assert(64 * kColWaves == 8 * 2 * kColFeatures, "eight threads per result"
 // Up to how many rows a sequence is short: one launch takes as long as a compute unit needs for its share of the
 // columns, so what counts is how many workgroups of 32 features share one.  Measured against the two launches, inputs from
 // memory, in us, one / two: E = 5120 (a unit each) 400 rows 4.8 / 6.5, 800 rows 6.7 / 7.1, 900 7.1 / 7.1, 1024 7.7 / 7.2; E = 512
-// 800 rows 5.2 / 6.0, 1024 6.0 / 5.8; E = 12288 (two) 300 rows 6.1 / 7.3, 400 7.0 / 7.0, 450 7.4 / 6.9; E = 24576 (three) 150 rows
+// 900 rows 5.6 / 6.0 to 6.4, 1024 6.0 / 5.8 to 6.3; E = 12288 (two) 300 rows 6.1 / 7.3, 400 7.0 / 7.0, 450 7.4 / 6.9; E = 24576 (three) 150 rows
 // 6.2 / 7.4, 192 6.7 / 6.7, 256 7.6 / 7.1; E = 32768 (four) 100 rows 6.3 / 7.2, 150 7.4 / 7.5, 192 8.1 / 7.3, 1024 25.6 / 14.8.
 int64_t calibrate_columns_rows(int E, int compute_units)
 {
     const int share = ((E + kColFeatures - 1) / kColFeatures + compute_units - 1) / compute_units;
-    return share <= 1 ? 896 : share == 2 ? 400 : 600 / share;
+    return share <= 1 ? 1024 : share == 2 ? 400 : 600 / share;
 }
 
 // The number of compute units of the current device (looked up once per device: the query is

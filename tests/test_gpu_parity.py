@@ -419,7 +419,7 @@ def test_calibrate_either_side_of_the_row_limit(S, E, ld_pad):
     _calibrate_both(w, 2, S, N=2, ld_pad=ld_pad)
 
 
-@pytest.mark.parametrize("S,E", [(896, 8192), (897, 8192), (400, 8200), (401, 8200), (200, 16392), (201, 16392),
+@pytest.mark.parametrize("S,E", [(1024, 8192), (1025, 8192), (400, 8200), (401, 8200), (200, 16392), (201, 16392),
                                  (150, 32768), (151, 32768), (1024, 32768)])
 def test_calibrate_row_limit_by_width(S, E):
     """How many rows take one launch goes down with the workgroups a compute unit (of 256) would have to share: both
