@@ -161,13 +161,14 @@ __host__ __device__ inline int sblk_cap_of(int k, int r)
 __host__ __device__ inline int cpass_cap_of(int E) { return (E / 8 + 62) / 63; }
 
 // Waves the decoder numbers per row.  Passes mostly have 64 blocks, so that ceil(E / 512) of the numbers are used: where
-// those fill whole workgroups of 4 a row starts a new one (16384 x 8192, fp32 output: 431 us, numbered through 444),
-// elsewhere rows are numbered through, or the last workgroup of each would be partly idle (a prefill step
-// at E = 5120, 10 passes: 60.1 against 60.3 us).
+// those fill whole workgroups of 4 a row starts a new one, unless that makes an even number of workgroups a row: the idle
+// last one would then always fall to the same shader engines (an XCD's are dealt consecutive workgroups in turn).  N = 8,
+// whole workgroups / numbered through: 8192 x 2048 (2 a row) 35.9 / 23.7 us, 2048 x 6144 (4) 21.7 / 19.1; 512 x 4096 (3) 4.8 / 5.3,
+// 8192 x 4096 45.0 / 48.4, N = 16, fp32 output, 8192 x 8192 (5) 202 / 208.
 __host__ __device__ inline int cpass_stride_of(int E)
 {
-    const int cap = cpass_cap_of(E);
-    return (E + 511) / 512 % 4 == 0 ? (cap + 3) / 4 * 4 : cap;
+    const int cap = cpass_cap_of(E), groups = (cap + 3) / 4;
+    return (E + 511) / 512 % 4 == 0 && groups % 2 == 1 ? 4 * groups : cap;
 }
 
 struct PlanOffsets {
