@@ -205,8 +205,16 @@ __device__ __forceinline__ void add_quad(float &acc, uint32_t v, uint32_t rq, ui
 //
 // FUSED adds the block's epilogue (Sec. 2: the sum over the devices plus the bias): an addend row and / or the
 // bias as two more terms of the accumulation.
-template <int LPG, int ACC, int OUT, bool GEN, bool FUSED>
-__global__ __launch_bounds__(256, GEN ? 7 : 8) void k_decode_pass(DecodeArgs a, RankPtrs codesp, RankPtrs scalep,
+// LANES: how the selected features come.  Without it (8 ranks at most, few selected features): four ranks of 16 columns
+// per load, a rank's row of lanes with its own pointer.  The pointers are fetched ahead of everything, and the first 16
+// columns (mostly all there are) behind the first messages: picked from scalar registers the pointers cost 40 instructions a
+// wave, and fetched behind the messages' loads a second wait for all of those (18.7 and 21.5 us at T = 2048, E = 5120, N = 8).
+// With it: a lane per column, 64 of them loaded and added with every 8 ranks' messages; 8 loads and 3 registers more (seven waves per
+// SIMD), but nothing waits for pointers behind the messages, and 17 or more columns are no path of their own.  Kernel
+// times without / with / as rows (k_decode_rows), bf16 output: N = 4, k = 80 14.8 / 16.0 / 16.0 us; N = 8, k = 80 16.4 / 16.4 / 16.8; N = 8, k = 213
+// 18.8 / 16.5 / 21.7; N = 64, 64 rows 14.5 / 11.8 / 10.1.
+template <int LPG, int ACC, int OUT, bool GEN, bool FUSED, bool LANES>
+__global__ __launch_bounds__(256, (GEN ? 7 : 8) - LANES) void k_decode_pass(DecodeArgs a, RankPtrs codesp, RankPtrs scalep,
                                                      RankPtrs zerop, RankPtrs outlp)
 {
     // Nothing is stored unless the header says that the plan is good; the loads do not wait for that
@@ -237,22 +245,22 @@ __global__ __launch_bounds__(256, GEN ? 7 : 8) void k_decode_pass(DecodeArgs a, 
     uint32_t refuse = (ph->magic ^ kPlanMagic) | static_cast<uint32_t>((ph->status ^ kPlanOk) | (ph->E ^ a.E) | (ph->k ^ a.k) | (ph->G ^ a.G));
     asm volatile("" : "+s"(refuse));
 
-    // Selected features: four ranks of 16 columns per load, a rank's row of lanes with its own pointer.  The first 8
-    // ranks' pointers are fetched here, ahead of everything, and their first 16 columns (mostly all there are) behind
-    // the first messages: picked from scalar registers the pointers cost 40 instructions a wave, and fetched
-    // behind the messages' loads a second wait for all of those (18.7 and 21.5 us at T = 2048, E = 5120,
-    // N = 8).  (The host fills the table up to a multiple of 8 with the first pointer, and passes the
-    // codes' pointers at a pitch of 0 where there are no selected features; nobody looks at what is read then.)
+    // (The host fills the table up to a multiple of 8 with the first pointer, and passes the codes' pointers at a
+    // pitch of 0 where there are no selected features; nobody looks at what is read then.)
     const int32_t *idx = reinterpret_cast<const int32_t *>(a.plan + a.off_idx);
-    const uint32_t off_outl = t * static_cast<uint32_t>(a.pitch_outl), sel_at = min(s0 + (lane & 15u), max(k, 1u) - 1u);
-    const uint32_t nq = (N + 3u) >> 2;
-    const void *const *po = outlp.p + (lane >> 4);
-    const void *const sel_p0 = po[0], *const sel_p1 = po[4];
+    const uint32_t off_outl = t * static_cast<uint32_t>(a.pitch_outl);
+    const uint32_t sel_at = min(s0 + (LANES ? lane : lane & 15u), max(k, 1u) - 1u), off_sel = off_outl + 2u * sel_at;
+    const void *sel_p0 = nullptr, *sel_p1 = nullptr;
+    if constexpr (!LANES) {
+        const void *const *po = outlp.p + (lane >> 4);
+        sel_p0 = po[0];
+        sel_p1 = po[4];
+    }
     auto load_sel = [&](const void *p) __attribute__((always_inline)) {
-        return static_cast<uint32_t>(
-            *reinterpret_cast<const uint16_t *>(static_cast<const uint8_t *>(p) + (off_outl + 2u * sel_at)));
+        return static_cast<uint32_t>(*reinterpret_cast<const uint16_t *>(static_cast<const uint8_t *>(p) + off_sel));
     };
     uint32_t sel_col = 0u, sel_v0 = 0u, sel_v1 = 0u;
+    float sel = 0.0f;
 
     // One 32-bit byte offset per section serves every rank (the host keeps
     // T * pitch below 2^31 per launch): the rank only changes the scalar base.
@@ -278,6 +286,12 @@ __global__ __launch_bounds__(256, GEN ? 7 : 8) void k_decode_pass(DecodeArgs a, 
         const void *const *pc = codesp.p + i0;
         const void *const *ps = scalep.p + i0;
         const void *const *pz = zerop.p + i0;
+        uint32_t vb[8];  // LANES
+        if constexpr (LANES) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+                vb[j] = load_sel((outlp.p + i0)[FULL ? static_cast<uint32_t>(j) : min(static_cast<uint32_t>(j), N - 1u - i0)]);
+        }
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
             const uint32_t i = FULL ? static_cast<uint32_t>(j) : min(static_cast<uint32_t>(j), N - 1u - i0);
@@ -290,10 +304,17 @@ __global__ __launch_bounds__(256, GEN ? 7 : 8) void k_decode_pass(DecodeArgs a, 
             sb[j] = *reinterpret_cast<const uint16_t *>(static_cast<const uint8_t *>(ps[i]) + off_meta);
             zb[j] = *reinterpret_cast<const uint16_t *>(static_cast<const uint8_t *>(pz[i]) + off_meta);
         }
-        if constexpr (FIRST) {
+        if constexpr (FIRST && !LANES) {
             sel_v0 = load_sel(sel_p0);
             sel_v1 = load_sel(sel_p1);
             sel_col = static_cast<uint32_t>(idx[sel_at]);
+        }
+        if constexpr (LANES) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const float v = bf16_bits_to_f32(vb[j]);
+                if (FULL || i0 + j < N) sel = FIRST && j == 0 ? v : add_term<ACC>(sel, v);  // uniform
+            }
         }
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
@@ -356,16 +377,22 @@ __global__ __launch_bounds__(256, GEN ? 7 : 8) void k_decode_pass(DecodeArgs a, 
     if (refuse) return;
 
     // ---- selected features ----------------------------------------------------------------
-    const bool few = quant && n_sel <= 16u;
-    if (few && n_sel > 0) {
-        float v = 0.0f;
-        add_quad<ACC>(v, sel_v0, 0u, N);
-        if (nq > 1) add_quad<ACC>(v, sel_v1, 1u, N);
-        for (uint32_t rq = 2; rq < nq; ++rq)
-            add_quad<ACC>(v, load_sel(po[4u * rq]), rq, N);
-        if (lane < n_sel) row[min(sel_col - col0, kRowNowhere)] = v;
+    uint32_t done = 0u;
+    if constexpr (LANES) {
+        if (quant) {
+            if (lane < n_sel) row[min(static_cast<uint32_t>(idx[sel_at]) - col0, kRowNowhere)] = sel;
+            done = 64u;
+        }
+    } else if (quant && n_sel <= 16u) {
+        if (n_sel > 0) {
+            float v = 0.0f;
+            add_quad<ACC>(v, sel_v0, 0u, N);
+            if (N > 4u) add_quad<ACC>(v, sel_v1, 1u, N);
+            if (lane < n_sel) row[min(sel_col - col0, kRowNowhere)] = v;
+        }
+        done = n_sel;
     }
-    for (uint32_t p0 = few ? n_sel : 0u; p0 < n_sel; p0 += 64) {  // many in one pass: a lane per column
+    for (uint32_t p0 = done; p0 < n_sel; p0 += 64) {  // those that are left: a lane per column
         const uint32_t p = min(s0 + p0 + lane, k - 1u);
         float v = 0.0f;
         for (uint32_t i0 = 0; i0 < N; i0 += 8) {
@@ -436,6 +463,168 @@ __global__ __launch_bounds__(256, GEN ? 7 : 8) void k_decode_pass(DecodeArgs a, 
             u32x4{pack_bf16x2(f[0], f[1]), pack_bf16x2(f[2], f[3]), pack_bf16x2(f[4], f[5]), pack_bf16x2(f[6], f[7])},
             reinterpret_cast<u32x4 *>(out + 16u * lane));
     }
+}
+
+// ---------------------------------------------------------------------------
+// The same sums by passes of 512 compacted features, selected features in waves of their own: for more than 8 ranks, bf16
+// output and no epilogue (decode_form()).  With that many ranks the loads are what counts: a pass's codes are two whole lines
+// per rank (a column pass's lie across three), and the selected features' lines are asked for once a row instead of in every
+// pass, so that the L2 gets 10.3 million requests where column passes make 12.4 (N = 16, 8192 x 8192, k = 128).  Kernel
+// times, rows / column passes (LANES): that 166 / 193 us; N = 12, 8192 x 5120, k = 80 85.7 / 91.7; N = 16, 8192 x 5120 100 / 116;
+// N = 64, 64 x 5120 10.1 / 11.8.  But the sums leave at 2-byte alignment between selected columns, so that column passes win
+// with more of those (N = 16, 8192 x 5120, k = 213 133 / 118), with fp32 output and with an epilogue.
+// grid: (row, group of 4 waves) pairs, rounded up to a multiple of 8.
+// ---------------------------------------------------------------------------
+template <int LPG, int ACC, bool GEN>
+__global__ __launch_bounds__(256) void k_decode_rows(DecodeArgs a, RankPtrs codesp, RankPtrs scalep,
+                                                     RankPtrs zerop, RankPtrs outlp)
+{
+    // Nothing is stored unless the header says that the plan is good; the pass waves'
+    // loads do not wait for that answer (the message sections do not depend on the plan,
+    // and reads of the plan's tables are kept inside the plan buffer whatever it holds).
+    const bool bad = plan_header_bad(a.plan, a.E, a.k, a.G);
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t passes = static_cast<uint32_t>(a.chunks_padded) >> 6;
+    // Each XCD works through one contiguous range of (row, wave group) pairs, a row's
+    // groups one after the other: the lines two neighbouring waves share (a row's scales
+    // and zeros, the ends of their code ranges, the output lines at a pass boundary)
+    // then meet in one L2, close in time.
+    const uint32_t ny = (passes + ((static_cast<uint32_t>(a.k) + 63u) >> 6) + 3u) >> 2;
+    const uint32_t logical = xcd_contiguous_index(blockIdx.x, gridDim.x);
+    const uint32_t t = logical / ny;
+    if (t >= static_cast<uint32_t>(a.T)) return;  // (the grid is rounded up to 8 blocks)
+    const uint32_t task = (logical - t * ny) * 4u + wave;
+
+    constexpr int OUT = TPQ_OUT_BF16;
+    constexpr uint32_t OB = 2u;  // bytes per output value
+    const uint32_t N = static_cast<uint32_t>(a.n_ranks);
+    const uint32_t ng = static_cast<uint32_t>(a.ng);
+    const uint32_t chunks = static_cast<uint32_t>(a.chunks);
+    uint8_t *const out_row = static_cast<uint8_t *>(a.out) + static_cast<int64_t>(t) * a.ldOut * OB;
+
+    if (task >= passes) {
+        // ---- selected features ------------------------------------------------------
+        const uint32_t p = (task - passes) * 64u + lane;
+        if (bad || p >= static_cast<uint32_t>(a.k)) return;
+        const int32_t *idx = reinterpret_cast<const int32_t *>(a.plan + a.off_idx);
+        const uint32_t off_outl = t * static_cast<uint32_t>(a.pitch_outl);
+        const uint32_t j = static_cast<uint32_t>(idx[p]);
+        float acc = 0.f;
+        for (uint32_t i0 = 0; i0 < N; i0 += 8) {
+            uint32_t v[8];
+#pragma unroll
+            for (int jj = 0; jj < 8; ++jj)
+                v[jj] = reinterpret_cast<const uint16_t *>(
+                    static_cast<const uint8_t *>(outlp.p[min(i0 + jj, N - 1u)]) + off_outl)[p];
+#pragma unroll
+            for (int jj = 0; jj < 8; ++jj) {
+                if (i0 + jj < N) {
+                    const float x = bf16_bits_to_f32(v[jj]);
+                    if (i0 + jj == 0) {
+                        acc = x;
+                    } else {
+                        acc = acc + x;
+                        if (ACC == TPQ_ACC_BF16) acc = round_via_bf16(acc);
+                    }
+                }
+            }
+        }
+        *reinterpret_cast<uint16_t *>(out_row + 2u * j) = static_cast<uint16_t>(pack_bf16x2(acc, acc));
+        return;
+    }
+
+    // ---- one pass of quantised features ---------------------------------------------
+    const uint32_t chunk = task * 64u + lane;
+    const uint32_t g = min(chunk / LPG, ng - 1u);
+    // the pass's store entries: where they start, blocks, blocks + narrow entries
+    const uint4 sp = reinterpret_cast<const uint4 *>(a.plan + a.off_spass)[task];
+    const uint32_t first = min(sp.x, static_cast<uint32_t>(a.sblk_cap));
+    const uint32_t *entries = reinterpret_cast<const uint32_t *>(a.plan + a.off_sblk) + first;
+    const uint32_t nall = min(sp.y + sp.z, static_cast<uint32_t>(a.sblk_cap) - first), nb = min(sp.y, nall);
+    const uint32_t e0 = lane < nall ? entries[lane] : 0u;
+    const uint32_t e1 = 64u + lane < nall ? entries[64u + lane] : 0u;
+    // One 32-bit byte offset per section serves every rank (the host keeps
+    // T * pitch below 2^31 per launch): the rank only changes the scalar base.
+    const uint32_t off_codes = t * static_cast<uint32_t>(a.pitch_codes) +
+                               (GEN ? static_cast<uint32_t>(a.bits) : 4u) * min(chunk, chunks - 1u);
+    const uint32_t off_meta = t * static_cast<uint32_t>(a.pitch_meta) + 2u * g;
+    float acc[8];
+
+    // 8 ranks at a time: all 24 loads first, then the arithmetic.  FULL batches index
+    // the pointer tables with constants (one wide scalar load each); the last, partial
+    // batch guards every rank.
+    // (the code width is a compile-time constant inside: one copy of the loop per width)
+    auto batch = [&](uint32_t i0, auto full_tag, auto bits_tag) {
+        constexpr bool FULL = decltype(full_tag)::value;
+        constexpr int BITS = decltype(bits_tag)::value;
+        uint32_t w[8], sb[8], zb[8];
+        uint64_t wq[8];  // GEN
+        const void *const *pc = codesp.p + i0;
+        const void *const *ps = scalep.p + i0;
+        const void *const *pz = zerop.p + i0;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const uint32_t i = FULL ? static_cast<uint32_t>(j) : min(static_cast<uint32_t>(j), N - 1u - i0);
+            if constexpr (GEN)
+                wq[j] = __builtin_nontemporal_load(reinterpret_cast<const u64_a1 *>(
+                    static_cast<const uint8_t *>(pc[i]) + off_codes));
+            else
+                w[j] = __builtin_nontemporal_load(reinterpret_cast<const uint32_t *>(
+                    static_cast<const uint8_t *>(pc[i]) + off_codes));
+            sb[j] = *reinterpret_cast<const uint16_t *>(static_cast<const uint8_t *>(ps[i]) + off_meta);
+            zb[j] = *reinterpret_cast<const uint16_t *>(static_cast<const uint8_t *>(pz[i]) + off_meta);
+        }
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            if (FULL || i0 + j < N) {  // uniform
+                const float sc = bf16_bits_to_f32(sb[j]), ze = bf16_bits_to_f32(zb[j]);
+                // one code per byte, so that each converts with a single byte-to-float
+                // instruction (the masks are hidden from the optimiser, which would
+                // otherwise fold them into separate bit-field extracts)
+                float x[8];
+                if constexpr (GEN) {
+                    float c[8];
+                    unpack_codes<BITS>(wq[j], c);
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) x[e] = __builtin_fmaf(c[e], sc, ze);  // product exact
+                } else {
+                    // one code per byte; the bytes 0 .. 15 read as FP8 (E4M3) are the codes
+                    // times 2^-9 (subnormals and the first binade have the same spacing), so
+                    // the scaled pair conversion turns two codes into floats at once
+                    const uint32_t lo = w[j] & 0x0F0F0F0Fu, hi = (w[j] >> 4) & 0x0F0F0F0Fu;
+                    const f32x2 c02 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(lo, 512.0f, false);
+                    const f32x2 c46 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(lo, 512.0f, true);
+                    const f32x2 c13 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(hi, 512.0f, false);
+                    const f32x2 c57 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(hi, 512.0f, true);
+                    x[0] = __builtin_fmaf(c02.x, sc, ze); x[1] = __builtin_fmaf(c13.x, sc, ze);
+                    x[2] = __builtin_fmaf(c02.y, sc, ze); x[3] = __builtin_fmaf(c13.y, sc, ze);
+                    x[4] = __builtin_fmaf(c46.x, sc, ze); x[5] = __builtin_fmaf(c57.x, sc, ze);
+                    x[6] = __builtin_fmaf(c46.y, sc, ze); x[7] = __builtin_fmaf(c57.y, sc, ze);
+                }
+                accumulate8<ACC>(acc, x, i0 + j == 0);
+            }
+        }
+    };
+    auto run = [&](auto bits_tag) {
+        uint32_t i0 = 0;
+        for (; i0 + 8 <= N; i0 += 8) batch(i0, std::true_type{}, bits_tag);
+        if (i0 < N) batch(i0, std::false_type{}, bits_tag);
+    };
+    if constexpr (GEN) {
+        switch (a.bits) {
+        case 2: run(std::integral_constant<int, 2>{}); break;
+        case 3: run(std::integral_constant<int, 3>{}); break;
+        case 5: run(std::integral_constant<int, 5>{}); break;
+        case 6: run(std::integral_constant<int, 6>{}); break;
+        default: run(std::integral_constant<int, 8>{}); break;
+        }
+    } else {
+        run(std::integral_constant<int, 4>{});
+    }
+    if (bad) return;
+    __shared__ u32x4 stage[4 * 64];
+    store_pass<OUT>(stage + wave * 64u, acc, out_row, lane, entries, nb, nall, e0, e1);
 }
 
 // ---------------------------------------------------------------------------
@@ -635,8 +824,36 @@ static int rows_per_wave(bool is_static, int64_t T, int tasks)
     return (is_static && T * tasks >= 2 * 8192) ? TPQ_STATIC_RPW : 1;
 }
 
+// How the sums are taken (see the kernels for what each is good at).  Rows need workgroups that are all there at once, or an
+// odd number of them per row: consecutive workgroups of an XCD go to its shader engines in turn, so that with 2 or 4 a row the
+// last, partly idle one always falls to the same engines (N = 16, 2048 x 2048, k = 32, 2 a row: 16.7 us, as columns 12.2; 2048 x
+// 5120, 3 a row: k = 128 25.9 / 26.8; 4 a row: k = 182 33.8 / 28.3; 64 rows of either 4.1 / 4.8).
+enum class Decode { kStatic, kRows, kColumns, kColumnsLanes };
+static Decode decode_form(const DecodeArgs &a, int out_dtype)
+{
+    if (a.step_c) return Decode::kStatic;
+    const bool few = 32 * a.k <= a.E;  // (16 selected columns a pass)
+    if (a.n_ranks > 8 && out_dtype == TPQ_OUT_BF16 && !a.addend && !a.bias) {
+        const int groups = (a.chunks_padded / 64 + (a.k + 63) / 64 + 3) / 4;
+        if (a.T * groups <= 512 || (few && groups % 2 == 1)) return Decode::kRows;
+    }
+    return a.n_ranks > 8 || !few ? Decode::kColumnsLanes : Decode::kColumns;
+}
+
+template <int LPG, int ACC, int OUT, bool LANES>
+static void launch_columns(dim3 grid, hipStream_t s, const DecodeArgs &a, const RankPtrs &codes, const RankPtrs &scale,
+                           const RankPtrs &zero, const RankPtrs &outl)
+{
+    if (a.addend || a.bias)  // (4 bits only: the host refuses the epilogue at other widths)
+        launch_kernel(k_decode_pass<LPG, ACC, OUT, false, true, LANES>, grid, dim3(256), 0, s, a, codes, scale, zero, outl);
+    else if (a.bits != 4)
+        launch_kernel(k_decode_pass<LPG, ACC, OUT, true, false, LANES>, grid, dim3(256), 0, s, a, codes, scale, zero, outl);
+    else
+        launch_kernel(k_decode_pass<LPG, ACC, OUT, false, false, LANES>, grid, dim3(256), 0, s, a, codes, scale, zero, outl);
+}
+
 template <int LPG, int ACC, int OUT>
-static void launch_rows(int rpw, dim3 grid, hipStream_t s, const DecodeArgs &a, const RankPtrs &codes,
+static void launch_rows(Decode form, int rpw, dim3 grid, hipStream_t s, const DecodeArgs &a, const RankPtrs &codes,
                         const RankPtrs &scale, const RankPtrs &zero, const RankPtrs &outl)
 {
     if constexpr (LPG == 0) {
@@ -650,13 +867,15 @@ static void launch_rows(int rpw, dim3 grid, hipStream_t s, const DecodeArgs &a, 
         } else {
             launch_kernel(k_decode_static<ACC, OUT, 1, false>, grid, dim3(256), 0, s, a, codes, outl);
         }
-    } else {
-        if (a.addend || a.bias)  // (4 bits only: the host refuses the epilogue at other widths)
-            launch_kernel(k_decode_pass<LPG, ACC, OUT, false, true>, grid, dim3(256), 0, s, a, codes, scale, zero, outl);
-        else if (a.bits != 4)
-            launch_kernel(k_decode_pass<LPG, ACC, OUT, true, false>, grid, dim3(256), 0, s, a, codes, scale, zero, outl);
+    } else if (form == Decode::kColumns) {
+        launch_columns<LPG, ACC, OUT, false>(grid, s, a, codes, scale, zero, outl);
+    } else if (form == Decode::kColumnsLanes) {
+        launch_columns<LPG, ACC, OUT, true>(grid, s, a, codes, scale, zero, outl);
+    } else if constexpr (OUT == TPQ_OUT_BF16) {
+        if (a.bits != 4)
+            launch_kernel(k_decode_rows<LPG, ACC, true>, grid, dim3(256), 0, s, a, codes, scale, zero, outl);
         else
-            launch_kernel(k_decode_pass<LPG, ACC, OUT, false, false>, grid, dim3(256), 0, s, a, codes, scale, zero, outl);
+            launch_kernel(k_decode_rows<LPG, ACC, false>, grid, dim3(256), 0, s, a, codes, scale, zero, outl);
     }
 }
 
@@ -668,7 +887,9 @@ int launch_decode(const DecodeArgs &a_in, const RankPtrs &codes_in, const RankPt
     if (accum == TPQ_ACC_FAST) accum = TPQ_ACC_FP32;
     const int lpg = a_in.G / 8;
     // waves per row
-    const int tasks = a_in.step_c ? a_in.chunks_padded / 64 + (a_in.k + 63) / 64 : cpass_cap_of(a_in.E);
+    const Decode form = decode_form(a_in, out_dtype);
+    const bool columns = form == Decode::kColumns || form == Decode::kColumnsLanes;
+    const int tasks = !columns ? a_in.chunks_padded / 64 + (a_in.k + 63) / 64 : cpass_cap_of(a_in.E);
     if (tasks == 0) return TPQ_OK;
     // The kernel addresses a rank's sections with 32-bit byte offsets: rows are handed
     // over in blocks whose sections stay below 2 GiB (one block unless T is huge).
@@ -706,7 +927,7 @@ int launch_decode(const DecodeArgs &a_in, const RankPtrs &codes_in, const RankPt
             if (zero.p[i]) zero.p[i] = static_cast<const uint8_t *>(zero.p[i]) + row0 * a_in.pitch_meta;
             if (outl.p[i]) outl.p[i] = static_cast<const uint8_t *>(outl.p[i]) + row0 * a_in.pitch_outl;
         }
-        if (!a.step_c) {  // the kernel reads 8 ranks' pointers and a value of each, whether or not it looks at them
+        if (columns) {  // the kernel reads 8 ranks' pointers and a value of each, whether or not it looks at them
             if (a.k == 0) {  // no section to read from: the codes' first bytes, whatever pitch_outl the caller chose
                 outl = codes;
                 a.pitch_outl = 0;
@@ -714,11 +935,11 @@ int launch_decode(const DecodeArgs &a_in, const RankPtrs &codes_in, const RankPt
             for (int i = a.n_ranks; i & 7; ++i) outl.p[i] = outl.p[0];
         }
         const int rpw = rows_per_wave(a.step_c != nullptr, a.T, tasks);
-        // one dimension, dealt out over the XCDs by the kernel: (row block, wave group) pairs in the static mode, else
-        // 4 (row, pass) pairs a workgroup
-        const int64_t blocks = a.step_c ? (a.T + rpw - 1) / rpw * ny : (a.T * cpass_stride_of(a.E) + 3) / 4;
+        // one dimension, dealt out over the XCDs by the kernel: 4 (row, column pass) pairs a workgroup, else (row block,
+        // wave group) pairs
+        const int64_t blocks = !columns ? (a.T + rpw - 1) / rpw * ny : (a.T * cpass_stride_of(a.E) + 3) / 4;
         const dim3 grid(static_cast<unsigned>((blocks + 7) / 8 * 8));
-#define TPQ_LAUNCH3(LPG, ACC, OUT) launch_rows<LPG, ACC, OUT>(rpw, grid, s, a, codes, scale, zero, outl)
+#define TPQ_LAUNCH3(LPG, ACC, OUT) launch_rows<LPG, ACC, OUT>(form, rpw, grid, s, a, codes, scale, zero, outl)
 #define TPQ_LAUNCH2(LPG)                                                                     \
     do {                                                                                     \
         if (accum == TPQ_ACC_FP32 && out_dtype == TPQ_OUT_BF16)                              \

@@ -1,4 +1,4 @@
-// Prints what tpq_decode_reduce hands to its kernels, without a GPU: this program's own launch functions take the
+// Prints what tpq_decode_reduce (fp32 output: column passes at any size) hands to its kernels, without a GPU: this program's own launch functions take the
 // place of the runtime's for the library it loads; they read the argument block and launch nothing.
 //
 //   launch_args libtpq.so E k G bits N T pitch_outl
@@ -48,7 +48,7 @@ int main(int argc, char **argv)
         for (int s = 0; s < 3; ++s) rest[s][i] = reinterpret_cast<const uint16_t *>((2ull + 4 * i + s) << 40);
     }
     return decode(&L, reinterpret_cast<void *>(1ull << 39), N, atoll(argv[7]), codes, rest[0], rest[1], rest[2], TPQ_ACC_FP32,
-                  TPQ_OUT_BF16, reinterpret_cast<void *>(1ull << 38), L.E, nullptr) == TPQ_OK
+                  TPQ_OUT_FP32, reinterpret_cast<void *>(1ull << 38), L.E, nullptr) == TPQ_OK
                ? 0
                : 5;
 }

@@ -133,3 +133,12 @@ def test_llama_prefill_full_size(b):
     Ys = wl.partial_sums(w, device="cuda")
     L = _case(w.E, w.G, b, Ys, idx_for(w))
     assert tpq.payload_bits(L) == b + (16 - b) * w.k / w.E
+
+
+@pytest.mark.parametrize("b", [3, 8])
+@pytest.mark.parametrize("N,k", [(8, 33), (9, 32), (9, 33), (64, 16)])
+def test_either_side_of_the_decoders_forms(b, N, k):
+    """More than 8 ranks and more than one selected feature in 32 take the sums in other ways."""
+    E = 1032
+    idx = np.sort(np.random.default_rng(N + k).choice(E, k, replace=False)).astype(np.int32)
+    _case(E, 128, b, [torch.randn((5, E), device="cuda").mul(1 + i).to(torch.bfloat16) for i in range(N)], idx)

@@ -173,6 +173,18 @@ def test_column_passes(N, E, cols):
     _case(E, 64, Ys, idx, None, None, ld_out=E + 8)
 
 
+@pytest.mark.parametrize("N", [8, 9, 12, 64])
+@pytest.mark.parametrize("E,k", [(1032, 0), (1032, 32), (1032, 33), (1032, 70), (1032, 400)])
+def test_either_side_of_the_decoders_forms(N, E, k):
+    """How the sums are taken depends on the ranks (more than 8), on the selected features (more than one in 32) and on the
+    epilogue and output: both sides of each, selected features spread, and in one run longer than a wave's lanes."""
+    g = np.random.default_rng(N + k)
+    for idx in (np.sort(g.choice(E, k, replace=False)), np.arange(200, 200 + k)):
+        Ys, addend, bias = _inputs(E, 5, N, N + k)
+        _case(E, 64, Ys, idx.astype(np.int32), None, None)
+        _case(E, 64, Ys, idx.astype(np.int32), addend, bias)
+
+
 @pytest.mark.parametrize("bits", [4, 6])
 def test_no_selected_features_at_a_raised_pitch(bits):
     """k = 0: pitch_outl may be anything and no outl section is read (there is none here)."""
