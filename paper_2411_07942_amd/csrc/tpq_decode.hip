@@ -226,9 +226,9 @@ __global__ __launch_bounds__(256, (GEN ? 7 : 8) - LANES) void k_decode_pass(Deco
     // the other: the lines two neighbouring waves share (a row's scales and zeros, the ends of their code
     // ranges) then meet in one L2, close in time.
     const uint32_t E = static_cast<uint32_t>(a.E), k = static_cast<uint32_t>(a.k);
-    const uint32_t passes = static_cast<uint32_t>(cpass_cap_of(a.E));
+    const uint32_t passes = static_cast<uint32_t>(a.cpasses);
     const uint32_t pair = xcd_contiguous_index(blockIdx.x, gridDim.x) * 4u + wave;
-    const uint32_t stride = static_cast<uint32_t>(cpass_stride_of(a.E));
+    const uint32_t stride = static_cast<uint32_t>(a.cpass_stride);
     const uint32_t t = pair / stride, task = pair - t * stride;
     if (t >= static_cast<uint32_t>(a.T) || task >= passes) return;  // (the grid is rounded up to 8 blocks of 4)
 
@@ -354,9 +354,11 @@ __global__ __launch_bounds__(256, (GEN ? 7 : 8) - LANES) void k_decode_pass(Deco
             return;
         }
         batch(0, std::true_type{}, bits_tag, std::true_type{});
-        uint32_t i0 = 8;
-        for (; i0 + 8 <= N; i0 += 8) batch(i0, std::true_type{}, bits_tag, std::false_type{});
-        if (i0 < N) batch(i0, std::false_type{}, bits_tag, std::false_type{});
+        if constexpr (LANES) {
+            uint32_t i0 = 8;
+            for (; i0 + 8 <= N; i0 += 8) batch(i0, std::true_type{}, bits_tag, std::false_type{});
+            if (i0 < N) batch(i0, std::false_type{}, bits_tag, std::false_type{});
+        }
     };
     __shared__ u32x4 rows[4 * kRowQuads];
     float *const row = reinterpret_cast<float *>(rows + wave * kRowQuads);
@@ -467,7 +469,7 @@ __global__ __launch_bounds__(256, (GEN ? 7 : 8) - LANES) void k_decode_pass(Deco
 
 // ---------------------------------------------------------------------------
 // The same sums by passes of 512 compacted features, selected features in waves of their own: for more than 8 ranks, bf16
-// output and no epilogue (decode_form()).  With that many ranks the loads are what counts: a pass's codes are two whole lines
+// output and no epilogue, or 8 ranks' wide codes (decode_form()).  With that many ranks the loads are what counts: a pass's codes are two whole lines
 // per rank (a column pass's lie across three), and the selected features' lines are asked for once a row instead of in every
 // pass, so that the L2 gets 10.3 million requests where column passes make 12.4 (N = 16, 8192 x 8192, k = 128).  Kernel
 // times, rows / column passes (LANES): that 166 / 193 us; N = 12, 8192 x 5120, k = 80 85.7 / 91.7; N = 16, 8192 x 5120 100 / 116;
@@ -827,13 +829,14 @@ static int rows_per_wave(bool is_static, int64_t T, int tasks)
 // How the sums are taken (see the kernels for what each is good at).  Rows need workgroups that are all there at once, or an
 // odd number of them per row: consecutive workgroups of an XCD go to its shader engines in turn, so that with 2 or 4 a row the
 // last, partly idle one always falls to the same engines (N = 16, 2048 x 2048, k = 32, 2 a row: 16.7 us, as columns 12.2; 2048 x
-// 5120, 3 a row: k = 128 25.9 / 26.8; 4 a row: k = 182 33.8 / 28.3; 64 rows of either 4.1 / 4.8).
+// 5120, 3 a row: k = 128 25.9 / 26.8; 4 a row: k = 182 33.8 / 28.3; 64 rows of either 4.1 / 4.8).  Codes of 5 bits and more
+// bring 8 ranks to the same side (6 bits, 2048 x 5120 26.0 / 27.1, 512 rows 7.6 / 8.7; 5 ranks 24.8 / 23.7).
 enum class Decode { kStatic, kRows, kColumns, kColumnsLanes };
 static Decode decode_form(const DecodeArgs &a, int out_dtype)
 {
     if (a.step_c) return Decode::kStatic;
     const bool few = 32 * a.k <= a.E;  // (16 selected columns a pass)
-    if (a.n_ranks > 8 && out_dtype == TPQ_OUT_BF16 && !a.addend && !a.bias) {
+    if (a.n_ranks >= (a.bits > 4 ? 8 : 9) && out_dtype == TPQ_OUT_BF16 && !a.addend && !a.bias) {
         const int groups = (a.chunks_padded / 64 + (a.k + 63) / 64 + 3) / 4;
         if (a.T * groups <= 512 || (few && groups % 2 == 1)) return Decode::kRows;
     }
@@ -916,6 +919,8 @@ int launch_decode(const DecodeArgs &a_in, const RankPtrs &codes_in, const RankPt
             a.sblk_cap = sblk_cap_of(a.k, a.r);
             a.off_src = o.src;
             a.off_cpass = o.cpass;
+            a.cpasses = cpass_cap_of(a.E);
+            a.cpass_stride = cpass_stride_of(a.E);
         }
         RankPtrs codes = codes_in, scale = scale_in, zero = zero_in, outl = outl_in;
         a.T = a_in.T - row0 < rows_per_launch ? a_in.T - row0 : rows_per_launch;
@@ -937,7 +942,7 @@ int launch_decode(const DecodeArgs &a_in, const RankPtrs &codes_in, const RankPt
         const int rpw = rows_per_wave(a.step_c != nullptr, a.T, tasks);
         // one dimension, dealt out over the XCDs by the kernel: 4 (row, column pass) pairs a workgroup, else (row block,
         // wave group) pairs
-        const int64_t blocks = !columns ? (a.T + rpw - 1) / rpw * ny : (a.T * cpass_stride_of(a.E) + 3) / 4;
+        const int64_t blocks = !columns ? (a.T + rpw - 1) / rpw * ny : (a.T * a.cpass_stride + 3) / 4;
         const dim3 grid(static_cast<unsigned>((blocks + 7) / 8 * 8));
 #define TPQ_LAUNCH3(LPG, ACC, OUT) launch_rows<LPG, ACC, OUT>(form, rpw, grid, s, a, codes, scale, zero, outl)
 #define TPQ_LAUNCH2(LPG)                                                                     \

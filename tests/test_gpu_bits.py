@@ -136,9 +136,12 @@ def test_llama_prefill_full_size(b):
 
 
 @pytest.mark.parametrize("b", [3, 8])
-@pytest.mark.parametrize("N,k", [(8, 33), (9, 32), (9, 33), (64, 16)])
+@pytest.mark.parametrize("N,k", [(7, 32), (8, 32), (8, 33), (9, 32), (9, 33), (64, 16)])
 def test_either_side_of_the_decoders_forms(b, N, k):
-    """More than 8 ranks and more than one selected feature in 32 take the sums in other ways."""
-    E = 1032
-    idx = np.sort(np.random.default_rng(N + k).choice(E, k, replace=False)).astype(np.int32)
-    _case(E, 128, b, [torch.randn((5, E), device="cuda").mul(1 + i).to(torch.bfloat16) for i in range(N)], idx)
+    """More than 8 ranks (8 with wide codes) and more than one selected feature in 32 take the sums in other ways;
+    so do few rows (here: workgroups that are all there at once)."""
+    for E, T in ((1032, 5), (4616, 300)):
+        k_E = k * E // 1032
+        idx = np.sort(np.random.default_rng(N + k).choice(E, k_E, replace=False)).astype(np.int32)
+        _case(E, 128, b, [torch.randn((T, E), device="cuda").mul(1 + i).to(torch.bfloat16) for i in range(N)], idx,
+              rows=np.array([0, T - 1]))
