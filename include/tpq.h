@@ -53,7 +53,8 @@
  *   - The library never allocates, frees or retains device memory; all buffers
  *     belong to the caller.  There is no global state beyond two thread-local
  *     items (the last HIP error, a pending tpq_bench_time_next_launch request), the
- *     number of compute units of each device (looked up once), and the static device
+ *     number of compute units of each device (looked up once), which kernels a device has
+ *     been told to let use more than 64 KiB of LDS, and the static device
  *     array of tpq_calibrate_fixed, the one call that brings its own scratch; calls
  *     are re-entrant across streams (tpq_calibrate_fixed: see there).
  *   - Work is enqueued on the given HIP stream (a hipStream_t passed as void*,
@@ -170,7 +171,7 @@ int tpq_calibrate(const uint16_t *Y, int64_t S, int64_t ldY, int E, int rank,
 
 /* tpq_calibrate for callers that cannot provide scratch memory they have allocated (code
  * under HIP graph capture, serving loops or harnesses that forbid hipMalloc): the same
- * kernels, with the partial minima / maxima of the row slices in a buffer that is part
+ * kernels (short sequences need no scratch), with the partial minima / maxima of the row slices in a buffer that is part
  * of the library's device image (TPQ_CALIBRATE_FIXED_SCRATCH_BYTES per GPU, held until the
  * process ends) instead of a workspace argument.  Allocates nothing and calls no allocating
  * routine.  E <= TPQ_CALIBRATE_FIXED_MAX_E (TPQ_ERR_SHAPE beyond that); everything else as

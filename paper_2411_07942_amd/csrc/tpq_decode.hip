@@ -193,9 +193,10 @@ __device__ __forceinline__ void add_quad(float &acc, uint32_t v, uint32_t rq, ui
 // Why by columns: as passes of 512 compacted features the sums left in runs between selected columns -- 2-byte
 // aligned stores, a second, nearly empty round of them per pass, the epilogue's operands loaded the same way,
 // and waves of their own for the selected features.  Kernel times, before and now (T = 2048, E = 5120, k = 80, N = 8
-// unless said): with residual and bias 25.3 -> 20.9 us (fp32), 29.6 -> 25.4 (bf16 chain); without 17.5 -> 17.4; 16384 x
-// 8192, k = 341, N = 16, fp32 output 480 -> 431; 6 bits, 1777 x 5000, N = 5 22.8 -> 22.0.  Bound by instruction issue and
-// memory latency together.  Eight waves per SIMD; the other code widths need 72 registers: seven.
+// unless said): with residual and bias 25.3 -> 19.9 us (fp32), 29.6 -> 23.7 (bf16 chain); without 17.5 -> 17.2; 16384 x
+// 8192, k = 341, N = 16, fp32 output 480 -> 420; 6 bits, 1777 x 5000, N = 5 22.8 -> 21.3.  Bound by what a compute unit has
+// outstanding to memory, a wave's chain of loads at small sizes; with 1 to 7 ranks the loads of 8 are issued all the
+// same (a rank past the last is the last one again).  Eight waves per SIMD.
 // grid: (row, pass) pairs, 4 per workgroup, workgroups rounded up to a multiple of 8.
 // ---------------------------------------------------------------------------
 //

@@ -25,14 +25,14 @@
 // products, in that order (the scheduler is pinned), and a stage costs one barrier.  One
 // workgroup holds a compute unit, one wave a SIMD.
 //
-// What bounds it, at T = 2048, E = 5120, K = 1728 (one MI355X, launched back to back): 37.5 us =
-// 966 TFLOP/s where operands that went through registers, 64 x 64 per wave and two barriers a
-// stage took 61 us; the loop runs at 85 % of the matrix cores' rate in cycles, at a clock that
-// the full chip's power limit holds near 1.6 GHz; about 10 us are the ends (first loads, epilogue,
-// launch), which a single round of tiles cannot hide.  With few tokens it is bound by what one
+// What bounds it, at T = 2048, E = 5120, K = 1728 (one MI355X): 37.9 to 38.5 us a launch timed by itself, 39.4 to 40.6
+// behind other kernels (920 to 890 TFLOP/s), 43.8 in a loop of nothing else, which the chip's power limit slows down;
+// operands that went through registers, 64 x 64 per wave and two barriers a stage took 54 to 61.  The matrix cores are
+// busy for 62 % of a wave's 66 thousand cycles; the rest is mostly the ends (first loads, epilogue), which a single
+// round of tiles cannot hide.  With few tokens it is bound by what one
 // compute unit can have outstanding to memory beyond its L2, about 52 bytes/ns whatever the
-// access pattern, on E / 128 of them (a group's features stay on one): 18 -> 16 us against 30 us
-// before at T = 13, K = 1728, 9.4 against 14.1 at K = 640.
+// access pattern, on E / 128 of them (a group's features stay on one): 15.5 us against 29 us
+// before at T = 13, K = 1728, 8.9 (10.1 behind other kernels) against 13.6 at K = 640.
 #include <atomic>
 
 #include "tpq_device.h"
@@ -61,7 +61,7 @@ struct GemmArgs {
     const uint16_t *X;
     int64_t ldX, T;
     const uint16_t *Wp;
-    int32_t K, E, k, G, r, ng, chunks;
+    int32_t K, E, k, G, r, ng;
     uint8_t *codes, *scale, *zero, *outl;
     int64_t pitch_codes, pitch_meta, pitch_outl;
     uint16_t *Ymsg;  // optional: the rounded product itself, [T][ldYm] in message order
@@ -516,8 +516,9 @@ static int launch_tile(const GemmArgs &a, hipStream_t s)
 }
 
 // The tile: the one whose rounds over the chip cost least.  A compute unit holds one workgroup, so a launch
-// takes ceil(tiles / compute units) rounds; a round of a tile costs what the table says, measured at
-// K = 1728 (and in the same ratios at K = 640), E = 5120, in us of a launch of one round: 128 features x 64 tokens
+// takes ceil(tiles / compute units) rounds; a round of a tile costs what the table says, measured back to back at
+// K = 1728 (and in the same ratios at K = 640; at K = 128 the ends are most of it, and 4096 x 2048 would be 6 % faster in
+// smaller tiles), E = 5120, in us of a launch of one round: 128 features x 64 tokens
 // 16.3, 128 x 128 17.5, 256 x 64 17.7 (the loads' time: more tokens are free), 256 x 128 24, 256 x 192 31, 256 x 256
 // 39 (the products' time, and 8 to 10 us of ends whatever the tile).  Where a smaller tile needs no further round it
 // wins: 512 tokens 18.7 us at 128 x 128 against 23.7 at 256 x 128; 1024 tokens 25.6 at 256 x 128 against 33.9
@@ -574,7 +575,6 @@ int launch_gemm_encode(const tpq_layout *L, const uint16_t *X, int64_t T, int64_
     a.G = L->G;
     a.r = L->r;
     a.ng = L->ng;
-    a.chunks = chunks_of(L->r);
     a.codes = codes;
     a.scale = reinterpret_cast<uint8_t *>(scale);
     a.zero = reinterpret_cast<uint8_t *>(zero);
