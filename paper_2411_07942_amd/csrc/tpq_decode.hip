@@ -8,6 +8,22 @@
 
 namespace tpq {
 
+// A word's 8 codes -> code * scale + zero.  One code per byte; the bytes 0 .. 15 read as FP8 (E4M3) are the codes times
+// 2^-9 (subnormals and the first binade have the same spacing), so the scaled pair conversion turns two codes into floats
+// at once; the product is exact.
+__device__ __forceinline__ void dequantise8(float (&x)[8], uint32_t w, float sc, float ze)
+{
+    const uint32_t lo = w & 0x0F0F0F0Fu, hi = (w >> 4) & 0x0F0F0F0Fu;
+    const f32x2 c02 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(lo, 512.0f, false);
+    const f32x2 c46 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(lo, 512.0f, true);
+    const f32x2 c13 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(hi, 512.0f, false);
+    const f32x2 c57 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(hi, 512.0f, true);
+    x[0] = __builtin_fmaf(c02.x, sc, ze); x[1] = __builtin_fmaf(c13.x, sc, ze);
+    x[2] = __builtin_fmaf(c02.y, sc, ze); x[3] = __builtin_fmaf(c13.y, sc, ze);
+    x[4] = __builtin_fmaf(c46.x, sc, ze); x[5] = __builtin_fmaf(c57.x, sc, ze);
+    x[6] = __builtin_fmaf(c46.y, sc, ze); x[7] = __builtin_fmaf(c57.y, sc, ze);
+}
+
 // The 8 B-bit fields of a 64-bit word as floats: field e at bits B*e .. B*e + B - 1.
 template <int B>
 __device__ __forceinline__ void unpack_codes(uint64_t w, float (&c)[8])
@@ -17,24 +33,28 @@ __device__ __forceinline__ void unpack_codes(uint64_t w, float (&c)[8])
         c[e] = static_cast<float>(static_cast<uint32_t>(w >> (B * e)) & ((1u << B) - 1u));
 }
 
-// acc <- acc (+) x for 8 features at once, in the requested arithmetic
+// acc <- acc (+) x for 8 features at once, in the requested arithmetic.  In the bf16 chain acc is the last sum before its
+// rounding: term and sum are rounded by one pair conversion and added by one dot product with (1, 1).  Finished by round8().
 template <int ACC>
-__device__ __forceinline__ void accumulate8(float (&acc)[8], float (&x)[8], bool first)
+__device__ __forceinline__ void accumulate8(float (&acc)[8], const float (&x)[8], bool first)
 {
-    if (ACC == TPQ_ACC_BF16) {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) x[e] = round_via_bf16(x[e]);
-    }
     if (first) {
 #pragma unroll
         for (int e = 0; e < 8; ++e) acc[e] = x[e];
+    } else if (ACC == TPQ_ACC_BF16) {
+        bf16_chain8(acc, x);
     } else {
 #pragma unroll
         for (int e = 0; e < 8; ++e) acc[e] = acc[e] + x[e];
-        if (ACC == TPQ_ACC_BF16) {
+    }
+}
+
+template <int ACC>
+__device__ __forceinline__ void round8(float (&acc)[8])
+{
+    if (ACC == TPQ_ACC_BF16) {
 #pragma unroll
-            for (int e = 0; e < 8; ++e) acc[e] = round_via_bf16(acc[e]);
-        }
+        for (int e = 0; e < 8; ++e) acc[e] = round_via_bf16(acc[e]);
     }
 }
 
@@ -121,6 +141,10 @@ __device__ __forceinline__ void store_pass(u32x4 *st, const float (&acc)[8], uin
     __builtin_amdgcn_wave_barrier();
 }
 
+// Before a batch's loads and behind each rank's.  Else the compiler takes the first loads that two batch sizes have in common ahead
+// of the branch between them, leaves the others behind a wait for those, and moves the last rank's behind the others' arithmetic.
+#define TPQ_LOADS_STAY(NB) asm volatile("; %0 ranks" ::"n"(NB) : "memory")
+
 // one more term of the accumulation (fp32 add; rounded to bf16 in the literal bf16 chain)
 template <int ACC>
 __device__ __forceinline__ float add_term(float acc, float x)
@@ -195,8 +219,12 @@ __device__ __forceinline__ void add_quad(float &acc, uint32_t v, uint32_t rq, ui
 // and waves of their own for the selected features.  Kernel times, before and now (T = 2048, E = 5120, k = 80, N = 8
 // unless said): with residual and bias 25.3 -> 19.9 us (fp32), 29.6 -> 23.7 (bf16 chain); without 17.5 -> 17.2; 16384 x
 // 8192, k = 341, N = 16, fp32 output 480 -> 420; 6 bits, 1777 x 5000, N = 5 22.8 -> 21.3.  Bound by what a compute unit has
-// outstanding to memory, a wave's chain of loads at small sizes; with 1 to 7 ranks the loads of 8 are issued all the
-// same (a rank past the last is the last one again).  Eight waves per SIMD.
+// outstanding to memory, a wave's chain of loads at small sizes, and by instruction issue in the bf16 chain.  Eight waves per SIMD.
+// Ranks come in batches with code of their own for 1 to 8 (2, 4, 6 and 8 where that code is long: other code widths, LANES).
+// As batches of 8 whatever was left, the loads of ranks that are not there were issued too (the last rank's again), and the
+// compiler put a rank's loads behind the others' arithmetic, a second wait for memory.  Kernel times at T = 2048, E = 5120, k = 80, fp32 / bf16 chain,
+// before -> now: N = 2 13.4 -> 11.3 / 13.5 -> 11.7 us, N = 3 14.1 -> 12.1 / 14.4 -> 12.6, N = 5, 6 bits 19.6 -> 17.7 / 19.9 -> 17.9,
+// N = 8 16.4 -> 16.3 / 20.8 -> 19.1, with residual and bias 19.3 -> 19.3 / 23.1 -> 21.5; N = 12, k = 20, 5 bits (rows) 41.3 -> 34.4 / 41.9 -> 34.8.
 // grid: (row, pass) pairs, 4 per workgroup, workgroups rounded up to a multiple of 8.
 // ---------------------------------------------------------------------------
 //
@@ -274,56 +302,55 @@ __global__ __launch_bounds__(256, (GEN ? 7 : 8) - LANES) void k_decode_pass(Deco
     const u32x4 cols = reinterpret_cast<const u32x4 *>(a.plan + a.off_src)[chunk];  // (in the plan also where there is none)
     float acc[8];
 
-    // 8 ranks at a time: all 24 loads first, then the arithmetic.  FULL batches index
-    // the pointer tables with constants (one wide scalar load each); the last, partial
-    // batch guards every rank.
+    // NB ranks at a time: all loads first, then the arithmetic, a rank's as soon as its loads are there.  left: ranks from i0
+    // on, NB or one less (GEN, LANES; the host fills the pointer tables up to an even number).
     // (the code width is a compile-time constant inside: one copy of the loop per width)
-    auto batch = [&](uint32_t i0, auto full_tag, auto bits_tag, auto first_tag) __attribute__((always_inline)) {
-        constexpr bool FULL = decltype(full_tag)::value;
+    auto batch = [&](uint32_t i0, uint32_t left, auto size_tag, auto bits_tag, auto first_tag) __attribute__((always_inline)) {
+        constexpr int NB = decltype(size_tag)::value;
         constexpr int BITS = decltype(bits_tag)::value;
         constexpr bool FIRST = decltype(first_tag)::value;
-        uint32_t w[8], sb[8], zb[8];
-        uint64_t wq[8];  // GEN
+        uint32_t w[NB], sb[NB], zb[NB];
+        uint64_t wq[NB];  // GEN
         const void *const *pc = codesp.p + i0;
         const void *const *ps = scalep.p + i0;
         const void *const *pz = zerop.p + i0;
-        uint32_t vb[8];  // LANES
+        uint32_t oc = off_codes, om = off_meta;
+        TPQ_LOADS_STAY(NB);
+        asm volatile("" : "+v"(oc), "+v"(om));  // (offsets of this branch's own: a base per rank beside them in one load instruction, no 64-bit sums)
+        uint32_t vb[NB];  // LANES
         if constexpr (LANES) {
 #pragma unroll
-            for (int j = 0; j < 8; ++j)
-                vb[j] = load_sel((outlp.p + i0)[FULL ? static_cast<uint32_t>(j) : min(static_cast<uint32_t>(j), N - 1u - i0)]);
+            for (int j = 0; j < NB; ++j) vb[j] = load_sel((outlp.p + i0)[j]);
         }
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const uint32_t i = FULL ? static_cast<uint32_t>(j) : min(static_cast<uint32_t>(j), N - 1u - i0);
+        for (int j = 0; j < NB; ++j) {
             if constexpr (GEN)
                 wq[j] = __builtin_nontemporal_load(reinterpret_cast<const u64_a1 *>(
-                    static_cast<const uint8_t *>(pc[i]) + off_codes));
+                    static_cast<const uint8_t *>(pc[j]) + oc));
             else
                 w[j] = __builtin_nontemporal_load(reinterpret_cast<const uint32_t *>(
-                    static_cast<const uint8_t *>(pc[i]) + off_codes));
-            sb[j] = *reinterpret_cast<const uint16_t *>(static_cast<const uint8_t *>(ps[i]) + off_meta);
-            zb[j] = *reinterpret_cast<const uint16_t *>(static_cast<const uint8_t *>(pz[i]) + off_meta);
+                    static_cast<const uint8_t *>(pc[j]) + oc));
+            sb[j] = *reinterpret_cast<const uint16_t *>(static_cast<const uint8_t *>(ps[j]) + om);
+            zb[j] = *reinterpret_cast<const uint16_t *>(static_cast<const uint8_t *>(pz[j]) + om);
+            TPQ_LOADS_STAY(NB);
         }
         if constexpr (FIRST && !LANES) {
+            __builtin_amdgcn_sched_barrier(0);  // (else the wait for their pointers comes before the messages' loads)
             sel_v0 = load_sel(sel_p0);
             sel_v1 = load_sel(sel_p1);
             sel_col = static_cast<uint32_t>(idx[sel_at]);
         }
         if constexpr (LANES) {
 #pragma unroll
-            for (int j = 0; j < 8; ++j) {
+            for (int j = 0; j < NB; ++j) {
                 const float v = bf16_bits_to_f32(vb[j]);
-                if (FULL || i0 + j < N) sel = FIRST && j == 0 ? v : add_term<ACC>(sel, v);  // uniform
+                if (j < NB - 1 || left == NB) sel = FIRST && j == 0 ? v : add_term<ACC>(sel, v);  // uniform
             }
         }
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            if (FULL || i0 + j < N) {  // uniform
+        for (int j = 0; j < NB; ++j) {
+            if ((!GEN && !LANES) || j < NB - 1 || left == NB) {  // uniform
                 const float sc = bf16_bits_to_f32(sb[j]), ze = bf16_bits_to_f32(zb[j]);
-                // one code per byte, so that each converts with a single byte-to-float
-                // instruction (the masks are hidden from the optimiser, which would
-                // otherwise fold them into separate bit-field extracts)
                 float x[8];
                 if constexpr (GEN) {
                     float c[8];
@@ -331,35 +358,46 @@ __global__ __launch_bounds__(256, (GEN ? 7 : 8) - LANES) void k_decode_pass(Deco
 #pragma unroll
                     for (int e = 0; e < 8; ++e) x[e] = __builtin_fmaf(c[e], sc, ze);  // product exact
                 } else {
-                    // one code per byte; the bytes 0 .. 15 read as FP8 (E4M3) are the codes
-                    // times 2^-9 (subnormals and the first binade have the same spacing), so
-                    // the scaled pair conversion turns two codes into floats at once
-                    const uint32_t lo = w[j] & 0x0F0F0F0Fu, hi = (w[j] >> 4) & 0x0F0F0F0Fu;
-                    const f32x2 c02 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(lo, 512.0f, false);
-                    const f32x2 c46 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(lo, 512.0f, true);
-                    const f32x2 c13 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(hi, 512.0f, false);
-                    const f32x2 c57 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(hi, 512.0f, true);
-                    x[0] = __builtin_fmaf(c02.x, sc, ze); x[1] = __builtin_fmaf(c13.x, sc, ze);
-                    x[2] = __builtin_fmaf(c02.y, sc, ze); x[3] = __builtin_fmaf(c13.y, sc, ze);
-                    x[4] = __builtin_fmaf(c46.x, sc, ze); x[5] = __builtin_fmaf(c57.x, sc, ze);
-                    x[6] = __builtin_fmaf(c46.y, sc, ze); x[7] = __builtin_fmaf(c57.y, sc, ze);
+                    dequantise8(x, w[j], sc, ze);
                 }
-                accumulate8<ACC>(acc, x, i0 + j == 0);
+                accumulate8<ACC>(acc, x, FIRST && j == 0);
             }
         }
     };
+    auto size = [&](uint32_t i0, uint32_t left, auto size_tag, auto bits_tag, auto first_tag) __attribute__((always_inline)) {
+        constexpr int NB = decltype(size_tag)::value;
+        if constexpr (!GEN && !LANES) {
+            if (left < NB) {
+                batch(i0, left, std::integral_constant<int, NB - 1>{}, bits_tag, first_tag);
+                return;
+            }
+        }
+        batch(i0, left, size_tag, bits_tag, first_tag);
+    };
+    // ranks i0 .. N - 1, at most 8
+    auto some = [&](uint32_t i0, auto bits_tag, auto first_tag) __attribute__((always_inline)) {
+        const uint32_t left = N - i0;
+        if (left > 6u) size(i0, left, std::integral_constant<int, 8>{}, bits_tag, first_tag);
+        else if (left > 4u) size(i0, left, std::integral_constant<int, 6>{}, bits_tag, first_tag);
+        else if (left > 2u) size(i0, left, std::integral_constant<int, 4>{}, bits_tag, first_tag);
+        else size(i0, left, std::integral_constant<int, 2>{}, bits_tag, first_tag);
+    };
     auto run = [&](auto bits_tag) __attribute__((always_inline)) {
-        // (the first batch is code of its own: it has constant pointers and fetches the selected features)
-        if (N < 8) {
-            batch(0, std::false_type{}, bits_tag, std::true_type{});
-            return;
+        // (the first batch is code of its own: it starts the sums and fetches the selected features)
+        if constexpr (!LANES) {
+            some(0, bits_tag, std::true_type{});  // 8 ranks at most
+        } else {
+            if (N <= 8u) {
+                some(0, bits_tag, std::true_type{});
+            } else {
+                const std::integral_constant<int, 8> eight;
+                batch(0, 8u, eight, bits_tag, std::true_type{});
+                uint32_t i0 = 8;
+                for (; i0 + 8 < N; i0 += 8) batch(i0, 8u, eight, bits_tag, std::false_type{});
+                some(i0, bits_tag, std::false_type{});
+            }
         }
-        batch(0, std::true_type{}, bits_tag, std::true_type{});
-        if constexpr (LANES) {
-            uint32_t i0 = 8;
-            for (; i0 + 8 <= N; i0 += 8) batch(i0, std::true_type{}, bits_tag, std::false_type{});
-            if (i0 < N) batch(i0, std::false_type{}, bits_tag, std::false_type{});
-        }
+        round8<ACC>(acc);
     };
     __shared__ u32x4 rows[4 * kRowQuads];
     float *const row = reinterpret_cast<float *>(rows + wave * kRowQuads);
@@ -554,37 +592,38 @@ __global__ __launch_bounds__(256) void k_decode_rows(DecodeArgs a, RankPtrs code
     const uint32_t off_meta = t * static_cast<uint32_t>(a.pitch_meta) + 2u * g;
     float acc[8];
 
-    // 8 ranks at a time: all 24 loads first, then the arithmetic.  FULL batches index
-    // the pointer tables with constants (one wide scalar load each); the last, partial
-    // batch guards every rank.
-    // (the code width is a compile-time constant inside: one copy of the loop per width)
-    auto batch = [&](uint32_t i0, auto full_tag, auto bits_tag) {
-        constexpr bool FULL = decltype(full_tag)::value;
+    // NB ranks at a time, as in k_decode_pass; FULL: 8, and the compiler may load the next ones ahead of a batch's arithmetic
+    // (held back, N = 64, 64 rows takes 12.0 us instead of 10.2)
+    auto batch = [&](uint32_t i0, uint32_t left, auto size_tag, auto bits_tag, auto full_tag) __attribute__((always_inline)) {
+        constexpr int NB = decltype(size_tag)::value;
         constexpr int BITS = decltype(bits_tag)::value;
-        uint32_t w[8], sb[8], zb[8];
-        uint64_t wq[8];  // GEN
+        constexpr bool FULL = decltype(full_tag)::value;
+        uint32_t w[NB], sb[NB], zb[NB];
+        uint64_t wq[NB];  // GEN
         const void *const *pc = codesp.p + i0;
         const void *const *ps = scalep.p + i0;
         const void *const *pz = zerop.p + i0;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const uint32_t i = FULL ? static_cast<uint32_t>(j) : min(static_cast<uint32_t>(j), N - 1u - i0);
-            if constexpr (GEN)
-                wq[j] = __builtin_nontemporal_load(reinterpret_cast<const u64_a1 *>(
-                    static_cast<const uint8_t *>(pc[i]) + off_codes));
-            else
-                w[j] = __builtin_nontemporal_load(reinterpret_cast<const uint32_t *>(
-                    static_cast<const uint8_t *>(pc[i]) + off_codes));
-            sb[j] = *reinterpret_cast<const uint16_t *>(static_cast<const uint8_t *>(ps[i]) + off_meta);
-            zb[j] = *reinterpret_cast<const uint16_t *>(static_cast<const uint8_t *>(pz[i]) + off_meta);
+        uint32_t oc = off_codes, om = off_meta;
+        if constexpr (!FULL) {
+            TPQ_LOADS_STAY(NB);
+            asm volatile("" : "+v"(oc), "+v"(om));
         }
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            if (FULL || i0 + j < N) {  // uniform
+        for (int j = 0; j < NB; ++j) {
+            if constexpr (GEN)
+                wq[j] = __builtin_nontemporal_load(reinterpret_cast<const u64_a1 *>(
+                    static_cast<const uint8_t *>(pc[j]) + oc));
+            else
+                w[j] = __builtin_nontemporal_load(reinterpret_cast<const uint32_t *>(
+                    static_cast<const uint8_t *>(pc[j]) + oc));
+            sb[j] = *reinterpret_cast<const uint16_t *>(static_cast<const uint8_t *>(ps[j]) + om);
+            zb[j] = *reinterpret_cast<const uint16_t *>(static_cast<const uint8_t *>(pz[j]) + om);
+        }
+        if constexpr (!FULL) TPQ_LOADS_STAY(NB);
+#pragma unroll
+        for (int j = 0; j < NB; ++j) {
+            if (FULL || j < NB - 1 || left == NB) {  // uniform
                 const float sc = bf16_bits_to_f32(sb[j]), ze = bf16_bits_to_f32(zb[j]);
-                // one code per byte, so that each converts with a single byte-to-float
-                // instruction (the masks are hidden from the optimiser, which would
-                // otherwise fold them into separate bit-field extracts)
                 float x[8];
                 if constexpr (GEN) {
                     float c[8];
@@ -592,27 +631,22 @@ __global__ __launch_bounds__(256) void k_decode_rows(DecodeArgs a, RankPtrs code
 #pragma unroll
                     for (int e = 0; e < 8; ++e) x[e] = __builtin_fmaf(c[e], sc, ze);  // product exact
                 } else {
-                    // one code per byte; the bytes 0 .. 15 read as FP8 (E4M3) are the codes
-                    // times 2^-9 (subnormals and the first binade have the same spacing), so
-                    // the scaled pair conversion turns two codes into floats at once
-                    const uint32_t lo = w[j] & 0x0F0F0F0Fu, hi = (w[j] >> 4) & 0x0F0F0F0Fu;
-                    const f32x2 c02 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(lo, 512.0f, false);
-                    const f32x2 c46 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(lo, 512.0f, true);
-                    const f32x2 c13 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(hi, 512.0f, false);
-                    const f32x2 c57 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(hi, 512.0f, true);
-                    x[0] = __builtin_fmaf(c02.x, sc, ze); x[1] = __builtin_fmaf(c13.x, sc, ze);
-                    x[2] = __builtin_fmaf(c02.y, sc, ze); x[3] = __builtin_fmaf(c13.y, sc, ze);
-                    x[4] = __builtin_fmaf(c46.x, sc, ze); x[5] = __builtin_fmaf(c57.x, sc, ze);
-                    x[6] = __builtin_fmaf(c46.y, sc, ze); x[7] = __builtin_fmaf(c57.y, sc, ze);
+                    dequantise8(x, w[j], sc, ze);
                 }
-                accumulate8<ACC>(acc, x, i0 + j == 0);
+                accumulate8<ACC>(acc, x, FULL && i0 + j == 0);
             }
         }
     };
-    auto run = [&](auto bits_tag) {
+    auto run = [&](auto bits_tag) __attribute__((always_inline)) {  // (8 ranks or more)
+        const std::integral_constant<int, 8> eight;
         uint32_t i0 = 0;
-        for (; i0 + 8 <= N; i0 += 8) batch(i0, std::true_type{}, bits_tag);
-        if (i0 < N) batch(i0, std::false_type{}, bits_tag);
+        for (; i0 + 8 <= N; i0 += 8) batch(i0, 8u, eight, bits_tag, std::true_type{});
+        const uint32_t left = N - i0;
+        if (left > 6u) batch(i0, left, eight, bits_tag, std::false_type{});
+        else if (left > 4u) batch(i0, left, std::integral_constant<int, 6>{}, bits_tag, std::false_type{});
+        else if (left > 2u) batch(i0, left, std::integral_constant<int, 4>{}, bits_tag, std::false_type{});
+        else if (left > 0u) batch(i0, left, std::integral_constant<int, 2>{}, bits_tag, std::false_type{});
+        round8<ACC>(acc);
     };
     if constexpr (GEN) {
         switch (a.bits) {
@@ -812,6 +846,7 @@ __global__ __launch_bounds__(256) void k_decode_static(DecodeArgs a, RankPtrs co
 #pragma unroll
     for (int rr = 0; rr < R; ++rr) {
         if (static_cast<uint32_t>(rr) >= n_rows) break;  // uniform
+        round8<ACC>(acc[rr]);
         store_pass<OUT>(stage + wave * (64u * (OUT == TPQ_OUT_FP32 ? 2u : 1u)), acc[rr], out_row[rr], lane,
                         entries, nb, nall, e0, e1);
     }
@@ -933,13 +968,19 @@ int launch_decode(const DecodeArgs &a_in, const RankPtrs &codes_in, const RankPt
             if (zero.p[i]) zero.p[i] = static_cast<const uint8_t *>(zero.p[i]) + row0 * a_in.pitch_meta;
             if (outl.p[i]) outl.p[i] = static_cast<const uint8_t *>(outl.p[i]) + row0 * a_in.pitch_outl;
         }
-        if (columns) {  // the kernel reads 8 ranks' pointers and a value of each, whether or not it looks at them
-            if (a.k == 0) {  // no section to read from: the codes' first bytes, whatever pitch_outl the caller chose
-                outl = codes;
-                a.pitch_outl = 0;
-            }
-            for (int i = a.n_ranks; i & 7; ++i) outl.p[i] = outl.p[0];
+        if (columns && a.k == 0) {  // no section to read from: the codes' first bytes, whatever pitch_outl the caller chose
+            outl = codes;
+            a.pitch_outl = 0;
         }
+        // The kernels read two ranks' pointers at a time, and the selected features' of 8, whether or not they look at what is
+        // there: the last rank again, and the first.
+        if (a.n_ranks & 1) {
+            codes.p[a.n_ranks] = codes.p[a.n_ranks - 1];
+            scale.p[a.n_ranks] = scale.p[a.n_ranks - 1];
+            zero.p[a.n_ranks] = zero.p[a.n_ranks - 1];
+        }
+        if (columns)
+            for (int i = a.n_ranks; i & 7; ++i) outl.p[i] = outl.p[0];
         const int rpw = rows_per_wave(a.step_c != nullptr, a.T, tasks);
         // one dimension, dealt out over the XCDs by the kernel: 4 (row, column pass) pairs a workgroup, else (row block,
         // wave group) pairs
