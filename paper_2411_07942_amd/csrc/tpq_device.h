@@ -113,6 +113,50 @@ __device__ __forceinline__ float dpp_f32(float v)
     return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, true));
 }
 
+// Sum over the lanes up to and with the caller's.  All in the vector unit: shifts by 1, 2, 4, 8 within rows of 16 lanes
+// (row_shr), then a row's last lane to the next row (row_bcast:15) and lane 31 to the upper half (row_bcast:31).
+__device__ __forceinline__ int wave_inclusive_sum(int v)
+{
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);
+    return v;
+}
+
+// Largest of the wave's values, in every lane (the same steps; lane 63 has it first).
+__device__ __forceinline__ uint32_t wave_max(uint32_t v)
+{
+    v = max(v, static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), 0x111, 0xF, 0xF, false)));
+    v = max(v, static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), 0x112, 0xF, 0xF, false)));
+    v = max(v, static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), 0x114, 0xF, 0xF, false)));
+    v = max(v, static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), 0x118, 0xF, 0xF, false)));
+    v = max(v, static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), 0x142, 0xA, 0xF, false)));
+    v = max(v, static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), 0x143, 0xC, 0xF, false)));
+    return static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(v), 63));
+}
+
+// Largest value and sum of the caller's row of 16 lanes, in every lane of it.
+__device__ __forceinline__ uint32_t row16_max(uint32_t v)
+{
+    v = max(v, static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), 0x128, 0xF, 0xF, true)));
+    v = max(v, static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), 0x124, 0xF, 0xF, true)));
+    v = max(v, static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), 0x122, 0xF, 0xF, true)));
+    v = max(v, static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), 0x121, 0xF, 0xF, true)));
+    return v;
+}
+
+__device__ __forceinline__ int row16_sum(int v)
+{
+    v += __builtin_amdgcn_update_dpp(0, v, 0x128, 0xF, 0xF, true);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x124, 0xF, 0xF, true);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x122, 0xF, 0xF, true);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x121, 0xF, 0xF, true);
+    return v;
+}
+
 // min and max over aligned groups of LPG lanes (LPG in {2, 4, 8, 16, 32}); every lane
 // of the group ends up with the group's result.
 template <int LPG>
