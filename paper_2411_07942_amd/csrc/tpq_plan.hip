@@ -29,81 +29,36 @@ __device__ inline int dir_slot_offset(int col, int wa, int E)
     return -1;
 }
 
-// does chunk c need a slot?
-__device__ inline bool dir_needs_slot(const uint16_t *src, int c, int E, int r)
+// does chunk c need a slot?  f: its features (16 bits each), last: the last real one, next0: the next chunk's first, or -1
+__device__ inline bool dir_needs_slot(const u32x4 &f, int last, int next0, int c, int E, int r)
 {
-    const int nv = r - 8 * c < 8 ? r - 8 * c : 8;
-    const int c0 = src[8 * c], clast = src[8 * c + nv - 1];
-    const int next0 = 8 * c + 8 < r ? src[8 * c + 8] : -1;
-    const bool contiguous = nv == 8 && clast == c0 + 7;
+    const int nv = r - 8 * c < 8 ? r - 8 * c : 8, c0 = f.x & 0xFFFFu;
+    const bool contiguous = nv == 8 && last == c0 + 7;
     // selected features inside the chunk, between it and the next one (or the row's
     // end), or before the first chunk: this chunk's slot holds them
-    const bool hosts = clast - c0 != nv - 1 || (next0 >= 0 ? next0 : E) - clast - 1 > 0 ||
-                       (c == 0 && c0 > 0);
-    bool slot = !contiguous || hosts;
-    if (!slot && (c0 & 1)) {
-        // the 8th feature is the first half-word of the next lane's window
-        const bool next_ok = (c & 63) != 63 && next0 == c0 + 8 &&
-                             dir_window_a(src, c + 1, E, r) == (c0 & ~1) + 8;
-        slot = !next_ok;
-    }
-    return slot;
+    const bool hosts = last - c0 != nv - 1 || (next0 >= 0 ? next0 : E) - last - 1 > 0 || (c == 0 && c0 > 0);
+    // where the first feature is odd the 8th is the first half-word of the next lane's window
+    const bool next_ok = (c & 63) != 63 && next0 == c0 + 8 && min(next0 & ~1, E - 8) == (c0 & ~1) + 8;
+    return !contiguous || hosts || ((c0 & 1) && !next_ok);
 }
 
-// One wave: exclusive prefix sum over the lanes.
-__device__ inline int wave_exclusive_sum(int v, int lane)
+// The store entries of 64 positions, word w of a pass of n (tables of the decoder's stores), by one wave: `starts` = the
+// pass's 512-bit mask of positions that start a run.  lead: a block of 8 starts at the lane's position; single: it is a
+// feature of a run shorter than 8; re: where its run ends.
+__device__ inline void word_entries(const uint64_t *starts, int w, int n, int lane, bool &lead, bool &single, int &re)
 {
-    int s = v;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const int o = __shfl_up(s, d, 64);
-        if (lane >= d) s += o;
-    }
-    return s - v;
-}
-
-// The store entries of one pass, by one wave (tables of the decoder's stores): `starts` = the pass's
-// 512-bit mask of features that start a run, n = features of the pass.  Counts the blocks and the
-// narrow entries; FILL writes them (blocks from `out` on, narrow entries from out + n_blocks on).
-template <bool FILL>
-__device__ inline void pass_entries(const uint64_t *starts, int n, int lane, const uint16_t *src, uint32_t *out,
-                                    int n_blocks, int &blocks, int &narrow)
-{
-    int b = 0, w2 = 0, last = 0;
-    for (int w = 0; 64 * w < n; ++w) {
-        const uint64_t m = starts[w];
-        const int a0 = 64 * w + lane;
-        const uint64_t upto = m & (lane == 63 ? ~0ull : (2ull << lane) - 1ull), after = m & ~(lane == 63 ? ~0ull : (2ull << lane) - 1ull);
-        const int rs = upto ? 64 * w + 63 - __builtin_clzll(upto) : last;  // the run [rs, re) that holds a0
-        int re = n;
-        if (after) {
-            re = 64 * w + __builtin_ctzll(after);
-        } else {
-            for (int w1 = w + 1; 64 * w1 < n; ++w1)
-                if (starts[w1]) {
-                    re = 64 * w1 + __builtin_ctzll(starts[w1]);
-                    break;
-                }
-        }
-        const bool real = a0 < n;
-        const bool lead = real && re - rs >= 8 && ((a0 - rs) & 7) == 0;
-        const bool single = real && re - rs < 8;
-        const uint64_t bl = __builtin_amdgcn_ballot_w64(lead), bn = __builtin_amdgcn_ballot_w64(single);
-        if (FILL) {
-            const uint64_t below = (1ull << lane) - 1ull;
-            if (lead) {
-                const int a = a0 + 8 <= re ? a0 : re - 8;
-                out[b + __builtin_popcountll(bl & below)] = src[a] | (static_cast<uint32_t>(a) << 16);
-            } else if (single) {
-                out[n_blocks + w2 + __builtin_popcountll(bn & below)] = src[a0] | (static_cast<uint32_t>(a0) << 16);
-            }
-        }
-        b += __builtin_popcountll(bl);
-        w2 += __builtin_popcountll(bn);
-        if (m) last = 64 * w + 63 - __builtin_clzll(m);
-    }
-    blocks = b;
-    narrow = w2;
+    // the last start before the word and the first one behind it: a lane per word of the pass (the second half of each row of 16
+    // lanes repeats the first), met by row
+    const int i = lane & 7;
+    const uint64_t m = starts[i], own = starts[w];
+    const int last = static_cast<int>(row16_max(i < w && m ? 64u * i + 63u - __builtin_clzll(m) : 0u));
+    const int next = n - static_cast<int>(row16_max(i > w && m ? static_cast<uint32_t>(n - 64 * i - __builtin_ctzll(m)) : 0u));
+    const uint64_t upto = lane == 63 ? ~0ull : (2ull << lane) - 1ull;
+    const int a0 = 64 * w + lane;
+    const int rs = own & upto ? 64 * w + 63 - __builtin_clzll(own & upto) : last;
+    re = own & ~upto ? 64 * w + __builtin_ctzll(own & ~upto) : next;
+    lead = a0 < n && re - rs >= 8 && ((a0 - rs) & 7) == 0;
+    single = a0 < n && re - rs < 8;
 }
 
 // The decoder's column passes, by one thread: as many blocks as fit.  (Serial over at most 66 passes, in a
@@ -132,18 +87,19 @@ __device__ inline void column_passes(const uint32_t *sel, const uint16_t *sel_be
     }
 }
 
-// All tables in one launch.  A workgroup builds the tables of one of the encoder's segments (up to
-// 5 passes), the last one the decoder's column passes; what it needs of the rest of the row -- which feature sits where, how many slots and
-// store entries come before its own -- it works out itself in LDS (a few thousand integers), so
-// that no workgroup waits for another and no table makes a round trip through memory.  The work is
-// latency, not bytes: as twelve dependent launches, three of them serial walks over the row, it took
-// 165 us at E = 5120, k = 80; this takes 13.
+// All tables in one launch.  A workgroup builds the encoder's tables of one segment (up to 5 passes), another one its store
+// entries, the last one the decoder's column passes; what they need of the rest of the row -- which feature sits where, how
+// many slots and store entries come before their own -- they work out themselves in LDS (a few thousand integers; the runs of consecutive
+// columns straight from the index list), so that no workgroup waits for another and no table makes a round trip through memory.
+// Bound by instruction issue and LDS latency on the compute unit that holds the workgroup, not by bytes.  E = 5120, k = 80: as twelve dependent
+// launches, three of them serial walks over the row, it took 165 us; in one launch with the store entries in the same
+// workgroups, counted word by word for the whole row, 13.6; now 6.0.
 constexpr int kPlanThreads = 1024;
-constexpr int kPlanMaxPasses = TPQ_MAX_E / 512;
+constexpr int kPlanMaxPasses = TPQ_MAX_E / 512, kPlanWords = 8 * 5;  // (a segment has 5 passes at most)
 static size_t plan_lds_bytes(int chunks_padded)
 {
-    // features of the compacted positions, the bit per position that starts a run
-    return static_cast<size_t>(chunks_padded) * 16 + static_cast<size_t>(chunks_padded) + 16;
+    // features of the compacted positions
+    return static_cast<size_t>(chunks_padded) * 16;
 }
 
 __global__ __launch_bounds__(kPlanThreads) void k_plan(uint8_t *plan, const int32_t *__restrict__ idx, int E, int k,
@@ -152,89 +108,133 @@ __global__ __launch_bounds__(kPlanThreads) void k_plan(uint8_t *plan, const int3
 {
     extern __shared__ u32x4 smem_plan[];
     uint16_t *src = reinterpret_cast<uint16_t *>(smem_plan);                       // [8 * chunks_padded]
-    uint64_t *starts = reinterpret_cast<uint64_t *>(src + 8 * chunks_padded);      // [chunks_padded / 8]
+    __shared__ uint64_t starts[kPlanWords];             // bit of position in the segment: starts a run
     __shared__ uint32_t sel[TPQ_MAX_E / 32];            // bit j: feature j is selected
     __shared__ uint16_t sel_before[TPQ_MAX_E / 32];     // selected features below 32 w
     __shared__ int wave_part[kPlanThreads / 64];
     __shared__ uint64_t flags[kPlanMaxPasses];          // bit of chunk: has a slot
     __shared__ int slots_before[kPlanMaxPasses + 1];
     __shared__ int n_blocks[kPlanMaxPasses], n_narrow[kPlanMaxPasses], entry0[kPlanMaxPasses + 1];
+    __shared__ uint32_t word_count[kPlanWords];         // store entries of the segment's words: blocks | narrow ones << 16
+    __shared__ int invalid;                             // the index set is not ascending
     __shared__ uint16_t pos16[64][8];                   // the segment's window entries
     __shared__ uint32_t seg_slot[128][2], seg_sel[128]; // its first 128 slots and selected features
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int passes = chunks_padded / 64, P = dir_passes_of(passes);
-    const int sg = blockIdx.x, p0 = sg * P, p1 = min(p0 + P, passes);  // this workgroup's segment
+    // this workgroup's segment, and whether it builds the decoder's store entries or the encoder's tables
+    const int segs = static_cast<int>(gridDim.x) / 2;
+    const bool stores = static_cast<int>(blockIdx.x) >= segs;
+    const int sg = stores ? blockIdx.x - segs : blockIdx.x, p0 = sg * P, p1 = min(p0 + P, passes);
+    const int n_words = 8 * max(p1 - p0, 0);
 
     // ---- the index set: valid? as a bit mask -------------------------------------------
+    // (a thread's first entry and its neighbours are fetched before anything else)
+    int v0 = 0, prev0 = -1, next0 = E;
+    if (tid < k) {
+        v0 = idx[tid];
+        if (tid > 0) prev0 = idx[tid - 1];
+        if (tid + 1 < k) next0 = idx[tid + 1];
+    }
     const int words = (E + 31) / 32;
     for (int w = tid; w < words; w += kPlanThreads) sel[w] = 0u;
     if (tid < 512) pos16[tid >> 3][tid & 7] = 0;
+    if (tid < kPlanMaxPasses) n_blocks[tid] = n_narrow[tid] = 0;
+    if (tid < n_words) starts[tid] = (tid & 7) == 0 ? 1u : 0u;  // (every pass starts one)
+    if (tid == 0) invalid = 0;
     __syncthreads();
-    bool bad = false;
+    // a run of consecutive columns in the compacted row, [start, end) within one pass, in blocks of 8 or one by one
+    auto count_run = [&](int start, int end) {
+        const int q = start >> 9, n = min(min(end, r), 512 * (q + 1)) - start;
+        if (n >= 8)
+            atomicAdd(&n_blocks[q], (n + 7) / 8);
+        else
+            atomicAdd(&n_narrow[q], n);
+    };
     int32_t *pidx = reinterpret_cast<int32_t *>(plan + o.idx);
-    for (int p = tid; p < (k + 3) / 4 * 4; p += kPlanThreads) {
-        int v = 0;
+    auto take = [&](int p, int v, int prev, int next) {
         if (p < k) {
-            v = idx[p];
-            const bool ok = v >= 0 && v < E && (p == 0 || v > idx[p - 1]);
-            if (ok)
+            if (v >= 0 && v < E && v > prev) {
                 atomicOr(&sel[v >> 5], 1u << (v & 31));
-            else
+                // the run behind it, if there is one and it does not start with its pass (those are counted below).
+                // (Of an invalid set the counts are not used, but they have to stay in their arrays: 0 < start < r.)
+                const int start = v - p, w = (start >> 6) - 8 * p0;
+                if (next > v + 1 && start > 0 && start < r && (start & 511)) {
+                    count_run(start, max(next - p - 1, start + 1));
+                    if (w >= 0 && w < n_words) atomicOr(reinterpret_cast<uint32_t *>(starts + w) + ((start >> 5) & 1), 1u << (start & 31));
+                }
+            } else {
                 v = 0;
-            bad |= !ok;
+                invalid = 1;
+            }
         }
-        if (sg == 0) pidx[p] = v;
-    }
-    bad = __syncthreads_or(bad);
+        if (blockIdx.x == 0) pidx[p] = p < k ? v : 0;
+    };
+    const int k4 = (k + 3) / 4 * 4;
+    if (tid < k4) take(tid, v0, prev0, next0);
+    for (int p = tid + kPlanThreads; p < k4; p += kPlanThreads)
+        take(p, idx[min(p, k - 1)], idx[min(p, k) - 1], p + 1 < k ? idx[p + 1] : E);
+    __syncthreads();
+    const bool bad = invalid != 0;
 
+    // the words of the segment's store entries that this wave takes
+    constexpr int kPlanShare = (kPlanWords + kPlanThreads / 64 - 1) / (kPlanThreads / 64);
+    bool lead[kPlanShare] = {}, single[kPlanShare] = {};
+    int re[kPlanShare] = {};
     if (!bad) {
         // ---- compacted positions -> features -----------------------------------------------
         const int mine = tid < words ? __builtin_popcount(sel[tid]) : 0;  // (TPQ_MAX_E / 32 = one word a thread)
-        int before = wave_exclusive_sum(mine, lane);
+        int before = wave_inclusive_sum(mine) - mine;
         if (lane == 63) wave_part[wave] = before + mine;
         __syncthreads();
-        for (int w = 0; w < wave; ++w) before += wave_part[w];
+        before += row16_sum((lane & 15) < wave ? wave_part[lane & 15] : 0);
         if (tid < words) sel_before[tid] = static_cast<uint16_t>(before);
         __syncthreads();
         if (blockIdx.x == gridDim.x - 1) {
             if (tid == 0) column_passes(sel, sel_before, E, k, cpass_cap_of(E), reinterpret_cast<uint4 *>(plan + o.cpass));
             return;
         }
-        for (int j = tid; j < E; j += kPlanThreads) {
-            const uint32_t m = sel[j >> 5], bit = 1u << (j & 31);
-            if (!(m & bit)) src[j - sel_before[j >> 5] - __builtin_popcount(m & (bit - 1u))] = static_cast<uint16_t>(j);
+        for (int j = 8 * tid; j < E; j += 8 * kPlanThreads) {  // 8 features a thread (E is a multiple of 8)
+            const uint32_t word = sel[j >> 5], m = word >> (j & 24);
+            int c = j - sel_before[j >> 5] - __builtin_popcount(word & ((1u << (j & 24)) - 1u));
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                if (!((m >> e) & 1u)) src[c++] = static_cast<uint16_t>(j + e);
         }
         __syncthreads();
         // positions past r repeat the last real one
         for (int c = r + tid; c < 8 * chunks_padded; c += kPlanThreads) src[c] = src[r - 1];
-        // runs of consecutive columns (cut at every pass), and the chunks that need a slot
-        for (int c = tid; c < 8 * chunks_padded; c += kPlanThreads) {
-            const bool s = c < r && ((c & 511) == 0 || src[c] != src[c - 1] + 1);
-            const uint64_t m = __builtin_amdgcn_ballot_w64(s);
-            if (lane == 0) starts[c >> 6] = m;
-        }
-        for (int c = tid; c < chunks_padded; c += kPlanThreads) {
-            const uint64_t m = __builtin_amdgcn_ballot_w64(c < chunks && dir_needs_slot(src, c, E, r));
+        // the chunks that need a slot
+        for (int c = tid; c < chunks_padded && !stores; c += kPlanThreads) {
+            const u32x4 f = reinterpret_cast<const u32x4 *>(src)[c];
+            const int last = 8 * c + 8 < r ? static_cast<int>(f.w >> 16) : src[r - 1];
+            const uint64_t m = __builtin_amdgcn_ballot_w64(
+                c < chunks && dir_needs_slot(f, last, 8 * c + 8 < r ? src[8 * c + 8] : -1, c, E, r));
             if (lane == 0) flags[c >> 6] = m;
+        }
+        // the runs that start with their pass
+        if (tid < passes) {
+            const int start = 512 * tid, p = src[start] - start;  // (selected columns before it)
+            count_run(start, p < k ? idx[p] - p : r);
         }
         __syncthreads();
 
         // ---- slots and store entries of every pass, and how many come before ---------------
-        for (int p = wave; p < passes; p += kPlanThreads / 64) {
-            int nb, nn;
-            pass_entries<false>(starts + 8 * p, min(512, r - 512 * p), lane, nullptr, nullptr, 0, nb, nn);
-            if (lane == 0) {
-                n_blocks[p] = nb;
-                n_narrow[p] = nn;
+        if (stores) {
+#pragma unroll
+            for (int u = 0; u < kPlanShare; ++u) {
+                const int w = wave + u * (kPlanThreads / 64);
+                if (w >= n_words) break;
+                word_entries(starts + (w & ~7), w & 7, min(512, r - 512 * (p0 + w / 8)), lane, lead[u], single[u], re[u]);
+                const uint64_t bl = __builtin_amdgcn_ballot_w64(lead[u]), bn = __builtin_amdgcn_ballot_w64(single[u]);
+                if (lane == 0) word_count[w] = __builtin_popcountll(bl) | (static_cast<uint32_t>(__builtin_popcountll(bn)) << 16);
             }
         }
-        __syncthreads();
-        if (wave == 0) {
-            const int nq = lane < passes ? __builtin_popcountll(flags[lane]) : 0;
+        if (wave == kPlanThreads / 64 - 1) {
+            const int nq = lane < passes && !stores ? __builtin_popcountll(flags[lane]) : 0;
             const int ne = lane < passes ? n_blocks[lane] + n_narrow[lane] : 0;
-            const int q = wave_exclusive_sum(nq, lane), e = wave_exclusive_sum(ne, lane);
+            const int q = wave_inclusive_sum(nq) - nq, e = wave_inclusive_sum(ne) - ne;
             slots_before[lane] = q;
             entry0[lane] = e;
             if (lane == 63) {
@@ -246,7 +246,7 @@ __global__ __launch_bounds__(kPlanThreads) void k_plan(uint8_t *plan, const int3
     }
 
     // ---- header ------------------------------------------------------------------------
-    if (sg == 0 && tid == 0) {
+    if (blockIdx.x == 0 && tid == 0) {
         PlanHeader h = {};
         h.magic = kPlanMagic;
         h.status = bad ? kPlanBadIndex : kPlanOk;
@@ -281,10 +281,34 @@ __global__ __launch_bounds__(kPlanThreads) void k_plan(uint8_t *plan, const int3
     if (bad || p0 >= passes || slots_before[64] > dslots || entry0[64] > sblk_cap) return;
 
     // ---- this segment's tables -----------------------------------------------------------
-    {
-        uint32_t *dst = reinterpret_cast<uint32_t *>(plan + o.src);
-        const uint32_t *s32 = reinterpret_cast<const uint32_t *>(src);
-        for (int i = 256 * p0 + tid; i < 256 * p1; i += kPlanThreads) dst[i] = s32[i];
+    if (stores) {
+        {
+            uint32_t *dst = reinterpret_cast<uint32_t *>(plan + o.src);
+            const uint32_t *s32 = reinterpret_cast<const uint32_t *>(src);
+            for (int i = 256 * p0 + tid; i < 256 * p1; i += kPlanThreads) dst[i] = s32[i];
+        }
+        // store entries
+        if (tid < p1 - p0) {
+            const int p = p0 + tid;
+            reinterpret_cast<uint4 *>(plan + o.spass)[p] = make_uint4(
+                static_cast<uint32_t>(entry0[p]), static_cast<uint32_t>(n_blocks[p]), static_cast<uint32_t>(n_narrow[p]), 0u);
+        }
+#pragma unroll
+        for (int u = 0; u < kPlanShare; ++u) {
+            const int w = wave + u * (kPlanThreads / 64), p = p0 + w / 8, c0 = 512 * p;
+            if (w >= n_words) break;
+            const int earlier = row16_sum((lane & 15) < (w & 7) ? static_cast<int>(word_count[(w & ~7) + (lane & 7)]) : 0);
+            const uint64_t bl = __builtin_amdgcn_ballot_w64(lead[u]), bn = __builtin_amdgcn_ballot_w64(single[u]), below = (1ull << lane) - 1ull;
+            uint32_t *out = reinterpret_cast<uint32_t *>(plan + o.sblk) + entry0[p];
+            const int a0 = 64 * (w & 7) + lane;
+            if (lead[u]) {
+                const int a = a0 + 8 <= re[u] ? a0 : re[u] - 8;
+                out[(earlier & 0xFFFF) + __builtin_popcountll(bl & below)] = src[c0 + a] | (static_cast<uint32_t>(a) << 16);
+            } else if (single[u]) {
+                out[n_blocks[p] + (earlier >> 16) + __builtin_popcountll(bn & below)] = src[c0 + a0] | (static_cast<uint32_t>(a0) << 16);
+            }
+        }
+        return;
     }
     const int q_lo = slots_before[p0], n_q = slots_before[p1] - q_lo;
     const int s_lo = sg == 0 ? 0 : src[512 * p0] - 512 * p0;                      // selected columns below the
@@ -294,26 +318,31 @@ __global__ __launch_bounds__(kPlanThreads) void k_plan(uint8_t *plan, const int3
         return slots_before[c >> 6] + __builtin_popcountll(flags[c >> 6] & ((1ull << (c & 63)) - 1ull));
     };
     for (int c = 64 * p0 + tid; c < min(64 * p1, chunks); c += kPlanThreads) {
-        const int p = (c >> 6) - p0, c0 = src[8 * c];
+        const u32x4 f4 = reinterpret_cast<const u32x4 *>(src)[c];
+        const uint32_t fw[4] = {f4.x, f4.y, f4.z, f4.w};
+        const int p = (c >> 6) - p0, c0 = fw[0] & 0xFFFFu;
         if (!((flags[c >> 6] >> (c & 63)) & 1u)) {
             pos16[c & 63][p] = static_cast<uint16_t>((c0 >> 1) | ((c0 & 1) ? kDir16Odd : 0u));
             continue;
         }
         const int q = slot_of(c);
-        const int nv = min(r - 8 * c, 8), wa = dir_window_a(src, c, E, r), wb = min(wa + 8, E - 8);
+        const int wa = dir_window_a(src, c, E, r), wb = min(wa + 8, E - 8);
         pos16[c & 63][p] = static_cast<uint16_t>((wa >> 1) | kDir16Slot);
         int at[8];
         bool wide = false;
+#pragma unroll
         for (int e = 0; e < 8; ++e) {  // (absent features repeat the last one)
-            at[e] = dir_slot_offset(src[8 * c + min(e, nv - 1)], wa, E);
+            at[e] = dir_slot_offset((fw[e >> 1] >> (16 * (e & 1))) & 0xFFFFu, wa, E);
             wide |= at[e] < 0;
         }
-        uint16_t *dirr = reinterpret_cast<uint16_t *>(plan + o.dirr) + 8 * q;
-        uint32_t nib = 0;
-        for (int e = 0; e < 8; ++e) {
-            dirr[e] = static_cast<uint16_t>(wide ? kDirWide | src[8 * c + min(e, nv - 1)] : static_cast<uint32_t>(at[e]));
+        uint32_t nib = 0, dw[4];
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
             if (!wide) nib |= static_cast<uint32_t>(at[e] >> 1) << (4 * e);
-        }
+#pragma unroll
+        for (int w = 0; w < 4; ++w)
+            dw[w] = wide ? fw[w] | (kDirWide | (kDirWide << 16)) : static_cast<uint32_t>(at[2 * w]) | (static_cast<uint32_t>(at[2 * w + 1]) << 16);
+        reinterpret_cast<u32x4 *>(plan + o.dirr)[q] = u32x4{dw[0], dw[1], dw[2], dw[3]};
         // does the next lane of the pass load exactly the second window?
         bool next_has_b = false;
         if ((c & 63) != 63 && c + 1 < chunks) {
@@ -329,7 +358,7 @@ __global__ __launch_bounds__(kPlanThreads) void k_plan(uint8_t *plan, const int3
     }
     // the slot that holds each selected column of the segment: that of the chunk with the feature
     // before it
-    for (int p = s_lo + tid; p < s_hi; p += kPlanThreads) {
+    for (int p = s_lo + (kPlanThreads - 1 - tid); p < s_hi; p += kPlanThreads) {  // (from the last waves down: the first ones have the chunks)
         const int j = idx[p], f = j - p;  // compacted features before column j
         const int c = f >= 1 ? (f - 1) / 8 : 0;
         uint32_t v = kDirFar;
@@ -339,16 +368,6 @@ __global__ __launch_bounds__(kPlanThreads) void k_plan(uint8_t *plan, const int3
         }
         reinterpret_cast<uint32_t *>(plan + o.dsel)[p] = v;
         if (p - s_lo < 128) seg_sel[p - s_lo] = v;
-    }
-    // store entries, from the last waves down (the first ones have the chunks)
-    for (int p = p0 + kPlanThreads / 64 - 1 - wave; p < p1; p += kPlanThreads / 64) {
-        if (lane == 0)
-            reinterpret_cast<uint4 *>(plan + o.spass)[p] =
-                make_uint4(static_cast<uint32_t>(entry0[p]), static_cast<uint32_t>(n_blocks[p]),
-                           static_cast<uint32_t>(n_narrow[p]), 0u);
-        int nb, nn;
-        pass_entries<true>(starts + 8 * p, min(512, r - 512 * p), lane, src + 512 * p,
-                           reinterpret_cast<uint32_t *>(plan + o.sblk) + entry0[p], n_blocks[p], nb, nn);
     }
     __syncthreads();
     // the records the encoder's lanes start from
@@ -419,7 +438,7 @@ int launch_plan_build(const tpq_layout *L, const int32_t *idx, void *plan, hipSt
         if (e != hipSuccess) return hip_result(e);
     }
     const int segs = dir_segs_of(cp / 64);
-    k_plan<<<(segs > 0 ? segs : 1) + 1, kPlanThreads, lds, s>>>(
+    k_plan<<<2 * (segs > 0 ? segs : 1) + 1, kPlanThreads, lds, s>>>(
         static_cast<uint8_t *>(plan), idx, L->E, L->k, L->G, L->r, chunks_of(L->r), cp, dir_slots_of(L->k, L->r),
         sblk_cap_of(L->k, L->r), plan_offsets(L->k, L->r, L->G));
     return hip_result(hipGetLastError());
