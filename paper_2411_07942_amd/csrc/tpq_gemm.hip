@@ -29,10 +29,9 @@
 // behind other kernels (920 to 890 TFLOP/s), 43.8 in a loop of nothing else, which the chip's power limit slows down;
 // operands that went through registers, 64 x 64 per wave and two barriers a stage took 54 to 61.  The matrix cores are
 // busy for 62 % of a wave's 66 thousand cycles; the rest is mostly the ends (first loads, epilogue), which a single
-// round of tiles cannot hide.  With few tokens it is bound by what one
-// compute unit can have outstanding to memory beyond its L2, about 52 bytes/ns whatever the
-// access pattern, on E / 128 of them (a group's features stay on one): 15.5 us against 29 us
-// before at T = 13, K = 1728, 8.9 (10.1 behind other kernels) against 13.6 at K = 640.
+// round of tiles cannot hide.  With few tokens a tile is bound by its stages, 0.19 us each from barrier to barrier: k_gemm_few
+// instead.
+#include <algorithm>
 #include <atomic>
 
 #include "tpq_device.h"
@@ -477,6 +476,237 @@ __global__ __launch_bounds__(64 * FW * TW, 1) void k_gemm_tile(GemmArgs a, uint3
     }
 }
 
+// Few tokens: a workgroup has the G features of one group and all the tokens (at most 16 NTB), and its 8 waves share K: wave w takes
+// the stages of 32 k that are w modulo their number, through a ring in LDS of its own, so that nothing waits for a barrier and
+// all of a short K is on its way at once.  The partial sums meet in LDS, where all threads share the epilogue.  Bound by what a
+// compute unit can have outstanding to memory; E / G of them hold a group each.  In the tiles below one wave does the
+// products and the epilogue of 16 tokens by itself, at E / 128 units whatever G, and a stage costs it 0.19 us from barrier to barrier.
+// (Fragments loaded straight into registers, 16 rows by 64 bytes an instruction with neighbouring lanes in different rows:
+// 41 bytes/ns a compute unit, where four lanes to a row, as here, reach twice that.)
+// T = 13, E = 5120: K = 640 9.0 -> 4.1 us, K = 1728 15.3 -> 6.1 (tiles -> this).  T = 64, K = 1728 15.8 -> 6.9: more tokens are more
+// workgroups, until the chip is full (launch_tiles()).
+template <int G, int NTB>
+struct FewShape {
+    static constexpr int waves = 8, threads = 64 * waves;
+    static constexpr int FW = G == 256 ? 2 : 1, KW = waves / FW; // waves across features and k
+    static constexpr int FB = G / (16 * FW);                     // blocks of 16 features of a wave
+    static constexpr int nl = FB + NTB, stage = nl * 1024;       // loads and LDS bytes of a stage: 16 rows of 64 bytes each
+    static constexpr int fit = 163840 / waves / stage, ring = fit < 4 ? fit : 4;
+    static constexpr int pitch = G + 4;                          // floats of a token's row of partial sums
+    static constexpr int sums = KW * 16 * pitch * 4, lds = sums > waves * ring * stage ? sums : waves * ring * stage;
+    static_assert(ring >= 2 && lds <= 163840 && (ring - 1) * nl <= 63, "the ring fits, its waits can be counted");
+};
+
+template <int G, int NTB>
+__global__ __launch_bounds__((FewShape<G, NTB>::threads)) void k_gemm_few(GemmArgs a, uint32_t tiles_t)
+{
+    typedef FewShape<G, NTB> S;
+    constexpr int FB = S::FB, NL = S::nl;
+    extern __shared__ u32x4 smem_gemm[];
+    float *const part = reinterpret_cast<float *>(smem_gemm);  // [k share][token of 16][pitch], once the ring is done with
+    const uint32_t tid = threadIdx.x, ln = tid & 63u;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const uint32_t wf = wave % S::FW, wk = wave / S::FW;
+    // (a group's workgroups one after the other on one XCD: its weights come from memory once)
+    const uint32_t id = xcd_contiguous_index(blockIdx.x, gridDim.x);
+    const uint32_t gi = id / tiles_t, F0 = gi * static_cast<uint32_t>(G);
+    if (F0 >= static_cast<uint32_t>(a.E)) return;  // (the grid is rounded up to a multiple of 8)
+    const int T0 = 16 * NTB * static_cast<int>(id - gi * tiles_t);
+    const int K = a.K, T = static_cast<int>(a.T);
+
+    // a load instruction fills 16 rows of 64 bytes, four lanes a row; rows past the last are the last again, and a stage that
+    // would leave the row starts earlier (what it has twice is multiplied by zero): every load is in bounds and unconditional
+    const uint32_t prow = ln / 4u;
+    const int pk = static_cast<int>((ln % 4u) ^ ((prow >> 1) & 3u)) * 8, pkc = min(pk, K - 8);
+    uint32_t voff[NL];
+#pragma unroll
+    for (int f = 0; f < FB; ++f)
+        voff[f] = 2u * (min(F0 + (wf * FB + f) * 16u + prow, static_cast<uint32_t>(a.E) - 1u) * static_cast<uint32_t>(K) + pkc);
+#pragma unroll
+    for (int t = 0; t < NTB; ++t)
+        voff[FB + t] = 2u * (static_cast<uint32_t>(min(T0 + 16 * t + static_cast<int>(prow), T - 1)) * static_cast<uint32_t>(a.ldX) + pkc);
+    const uint64_t pa = reinterpret_cast<uint64_t>(a.Wp), pb = reinterpret_cast<uint64_t>(a.X);
+    const u32x4 ra = {static_cast<uint32_t>(pa), static_cast<uint32_t>(pa >> 32),
+                      static_cast<uint32_t>(static_cast<int64_t>(a.E) * K * 2), 0x00020000u};
+    const u32x4 rb = {static_cast<uint32_t>(pb), static_cast<uint32_t>(pb >> 32),
+                      static_cast<uint32_t>(((a.T - 1) * a.ldX + K) * 2), 0x00020000u};
+    uint8_t *const ring = reinterpret_cast<uint8_t *>(smem_gemm) + wave * (S::ring * S::stage);
+    const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) uint8_t *)ring));
+    const int k_last = max(K - kTileBK, 0), all = (K + kTileBK - 1) / kTileBK;
+    const int mine = (all - static_cast<int>(wk) + S::KW - 1) / S::KW;  // this wave's stages (at most 0 where K is short)
+    auto stage_k = [&](int i) { return kTileBK * (static_cast<int>(wk) + i * S::KW); };
+    auto dma = [&](int i, uint32_t buf) __attribute__((always_inline)) {
+        const uint32_t kb2 = static_cast<uint32_t>(2 * min(stage_k(i), k_last));
+#pragma unroll
+        for (int l = 0; l < NL; ++l) {
+            const uint32_t m = lds0 + buf * S::stage + 1024u * l;
+            if (l < FB)
+                asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(m), "v"(voff[l]), "s"(ra), "s"(kb2) : "memory");
+            else
+                asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(m), "v"(voff[l]), "s"(rb), "s"(kb2) : "memory");
+        }
+    };
+
+    typedef float f32x4_t __attribute__((ext_vector_type(4)));
+    f32x4_t acc[FB][NTB];
+#pragma unroll
+    for (int f = 0; f < FB; ++f)
+#pragma unroll
+        for (int t = 0; t < NTB; ++t) acc[f][t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    const uint32_t row = ln & 15u, kq = ln >> 4;
+    const uint32_t at = row * 64u + ((kq ^ ((row >> 1) & 3u)) * 16u);
+#pragma unroll
+    for (int i = 0; i < S::ring; ++i)
+        if (i < mine) dma(i, i);
+    uint32_t buf = 0;
+    for (int i = 0; i < mine; ++i) {
+        // the stages behind this one are on their way: as many as the ring holds, fewer at the end
+        const int behind = mine - 1 - i;
+        if (behind >= S::ring - 1)
+            asm volatile("s_waitcnt vmcnt(%0)" ::"n"((S::ring - 1) * NL) : "memory");
+        else if (S::ring > 3 && behind == 2)
+            asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * NL) : "memory");
+        else if (S::ring > 2 && behind == 1)
+            asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NL) : "memory");
+        else
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        const uint8_t *st = ring + buf * S::stage + at;
+        u32x4 w[FB], x[NTB];
+#pragma unroll
+        for (int t = 0; t < NTB; ++t) x[t] = *reinterpret_cast<const u32x4 *>(st + 1024 * (FB + t));
+#pragma unroll
+        for (int f = 0; f < FB; ++f) w[f] = *reinterpret_cast<const u32x4 *>(st + 1024 * f);
+        if (i + S::ring < mine) {  // the buffer is free once its fragments are in registers
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            dma(i + S::ring, buf);
+        }
+        const int k = min(stage_k(i), k_last) + 8 * static_cast<int>(kq);
+        const bool in = k >= stage_k(i) && k < K;
+#pragma unroll
+        for (int t = 0; t < NTB; ++t) x[t] = in ? x[t] : u32x4{0u, 0u, 0u, 0u};
+#pragma unroll
+        for (int f = 0; f < FB; ++f)
+#pragma unroll
+            for (int t = 0; t < NTB; ++t)
+                acc[f][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, w[f]),
+                                                                    __builtin_bit_cast(bf16x8_t, x[t]), acc[f][t], 0, 0, 0);
+        buf = buf + 1u == S::ring ? 0u : buf + 1u;
+    }
+    __syncthreads();  // (every wave has taken its last fragments)
+
+    // ---- 16 tokens at a time: the shares meet, then G / 4 lanes have a token's group, 4 features each
+    constexpr uint32_t LPT = G / 4;  // lanes of a token
+    const int n_tb = (T - T0 + 15) / 16;
+    const bool whole = F0 + G <= static_cast<uint32_t>(a.r);
+#pragma unroll
+    for (int t0 = 0; t0 < NTB; ++t0) {
+        if (t0 >= n_tb) break;
+        if (t0) __syncthreads();
+#pragma unroll
+        for (int f = 0; f < FB; ++f)
+            *reinterpret_cast<f32x4_t *>(part + (wk * 16u + row) * S::pitch + (wf * FB + f) * 16u + 4u * kq) = acc[f][t0];
+        __syncthreads();
+#pragma unroll
+        for (uint32_t i0 = 0; i0 < 16u * LPT; i0 += S::threads) {
+            const uint32_t i = i0 + tid;
+            if (16u * LPT < S::threads && i >= 16u * LPT) break;  // (whole waves)
+            const uint32_t tok = i / LPT, q = i % LPT, n0 = F0 + 4u * q;
+            f32x4_t p[S::KW];
+#pragma unroll
+            for (int w = 0; w < S::KW; ++w) p[w] = *reinterpret_cast<const f32x4_t *>(part + (w * 16u + tok) * S::pitch + 4u * q);
+            float y[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                float v = p[0][e];
+#pragma unroll
+                for (int w = 1; w < S::KW; ++w) v += p[w][e];
+                y[e] = round_via_bf16(v);
+            }
+            const int64_t t = T0 + 16 * t0 + static_cast<int>(tok);
+            const bool t_ok = t < a.T;
+            if (a.Ymsg && t_ok && n0 < static_cast<uint32_t>(a.E))
+                *reinterpret_cast<uint2 *>(a.Ymsg + t * a.ldYm + n0) = make_uint2(
+                    (__float_as_uint(y[0]) >> 16) | __float_as_uint(y[1]), (__float_as_uint(y[2]) >> 16) | __float_as_uint(y[3]));
+            const int live = whole ? 4 : a.r - static_cast<int>(n0);  // quantised features from n0 on
+            if (!whole && t_ok) {
+                uint16_t *out = reinterpret_cast<uint16_t *>(a.outl + t * a.pitch_outl);
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (e >= live && n0 + e < static_cast<uint32_t>(a.E)) out[n0 + e - a.r] = static_cast<uint16_t>(__float_as_uint(y[e]) >> 16);
+            }
+            if (F0 >= static_cast<uint32_t>(a.r)) continue;  // (no quantised feature in the workgroup)
+            constexpr float kBig = 3.3895314e38f;
+            float mn = kBig, mx = -kBig;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                mn = fminf(mn, e < live ? y[e] : kBig);
+                mx = fmaxf(mx, e < live ? y[e] : -kBig);
+            }
+            group_minmax<LPT == 64 ? 32 : static_cast<int>(LPT)>(mn, mx);
+            if (LPT == 64) {
+                mn = fminf(mn, __shfl_xor(mn, 32, 64));
+                mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+            }
+            mn = mn + 0.0f;
+            const float s32 = div_by_15(mx - mn);
+            const uint32_t sb = pack_bf16x2(s32, s32) & 0xFFFFu;
+            const float sc = bf16_bits_to_f32(sb);
+            const bool constant = sc < 1e-30f;
+            const float inv = constant ? 0.0f : reciprocal_of_scale(sc);
+            if (q == 0 && t_ok) {
+                reinterpret_cast<uint16_t *>(a.scale + t * a.pitch_meta)[gi] = static_cast<uint16_t>(constant ? 0u : sb);
+                reinterpret_cast<uint16_t *>(a.zero + t * a.pitch_meta)[gi] = static_cast<uint16_t>(__float_as_uint(mn) >> 16);
+            }
+            float pr[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float df = (e < live ? y[e] : mn) - mn;
+                pr[e] = df * inv;
+            }
+            uint32_t w = __builtin_amdgcn_cvt_pk_u8_f32(pr[1], 0u, 0u);
+            w = __builtin_amdgcn_cvt_pk_u8_f32(pr[0], 1u, w);
+            w = __builtin_amdgcn_cvt_pk_u8_f32(pr[3], 2u, w);
+            w = __builtin_amdgcn_cvt_pk_u8_f32(pr[2], 3u, w);
+            w = (w << 12) | w;
+            w = __builtin_amdgcn_perm(w, w, 0x0C0C0301u);  // the four codes in the low half
+            const uint32_t other = __builtin_amdgcn_update_dpp(0u, w, 0xB1, 0xF, 0xF, true);
+            if (!(q & 1u) && live > 0 && t_ok)
+                *reinterpret_cast<uint32_t *>(a.codes + t * a.pitch_codes + n0 / 2u) = w | (other << 16);
+        }
+    }
+}
+
+// the kernel may use more LDS than the default limit: allowed once per device
+template <typename Kernel>
+static hipError_t allow_lds(Kernel kernel, int bytes, std::atomic<uint64_t> &allowed)
+{
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    const uint64_t bit = dev < 64 ? 1ull << dev : 0ull;
+    if (!(allowed.load(std::memory_order_relaxed) & bit)) {
+        e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+        if (e != hipSuccess) return e;
+        allowed.fetch_or(bit, std::memory_order_relaxed);
+    }
+    return hipSuccess;
+}
+
+template <int G, int NTB>
+static int launch_few_g(const GemmArgs &a, hipStream_t s)
+{
+    typedef FewShape<G, NTB> S;
+    const auto kernel = &k_gemm_few<G, NTB>;
+    static std::atomic<uint64_t> allowed;
+    const hipError_t e = S::lds > 65536 ? allow_lds(kernel, S::lds, allowed) : hipSuccess;
+    if (e != hipSuccess) return hip_result(e);
+    const int64_t tiles_t = (a.T + 16 * NTB - 1) / (16 * NTB), blocks = ((a.E + G - 1) / G * tiles_t + 7) / 8 * 8;
+    if (blocks * S::threads >= (1ll << 32)) return TPQ_ERR_SHAPE;
+    launch_kernel(kernel, dim3(static_cast<unsigned>(blocks)), dim3(S::threads), static_cast<size_t>(S::lds), s, a,
+                  static_cast<uint32_t>(tiles_t));
+    return hip_result(hipGetLastError());
+}
+
 template <int G, int FW, int TW, int NTB>
 static int launch_tile_g(const GemmArgs &a, hipStream_t s)
 {
@@ -485,17 +715,9 @@ static int launch_tile_g(const GemmArgs &a, hipStream_t s)
     const int64_t tiles_f = (a.E + S::ft - 1) / S::ft, tiles_t = (a.T + S::tt - 1) / S::tt;
     const int64_t blocks = (tiles_f * tiles_t + 7) / 8 * 8;  // (a multiple of 8 for the XCD order)
     if (blocks * S::threads >= (1ll << 32)) return TPQ_ERR_SHAPE;
-    // more than 64 KiB of LDS: allowed once per device
     static std::atomic<uint64_t> allowed;
-    int dev = 0;
-    hipError_t e = hipGetDevice(&dev);
+    const hipError_t e = allow_lds(kernel, S::lds, allowed);
     if (e != hipSuccess) return hip_result(e);
-    const uint64_t bit = dev < 64 ? 1ull << dev : 0ull;
-    if (!(allowed.load(std::memory_order_relaxed) & bit)) {
-        e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, S::lds);
-        if (e != hipSuccess) return hip_result(e);
-        allowed.fetch_or(bit, std::memory_order_relaxed);
-    }
     launch_kernel(kernel, dim3(static_cast<unsigned>(blocks)), dim3(S::threads), static_cast<size_t>(S::lds), s, a,
                   static_cast<uint32_t>(tiles_t));
     return hip_result(hipGetLastError());
@@ -538,16 +760,50 @@ static int launch_tiles(const GemmArgs &a, hipStream_t s)
     const hipError_t e = compute_units_of_current_device(&cus);
     if (e != hipSuccess) return hip_result(e);
     const Tile *best = nullptr;
-    int64_t least = 0;
+    int64_t least = 0, rounds = 0;
     for (const Tile &t : tiles) {
         if (a.G > t.ft) continue;  // a group lies inside a tile
-        const int64_t n = ((a.E + t.ft - 1) / t.ft) * ((a.T + t.tt - 1) / t.tt);
+        const int64_t n = static_cast<int64_t>((a.E + t.ft - 1) / t.ft) * ((a.T + t.tt - 1) / t.tt);
         const int64_t cost = (n + cus - 1) / cus * t.cost;
         if (!best || cost < least) {
             best = &t;
             least = cost;
+            rounds = (n + cus - 1) / cus;
         }
     }
+    // The same launch in ns, or with few tokens a workgroup (k_gemm_few): what a round takes with weights from L2 is ns + slope K / 1000, 52 bytes/ns
+    // a compute unit where the weights are larger than the L2s; then there are what all units together get from their L2s
+    // (13 bytes/ps, 10 with groups of 256), and 2.5 us of launch and ends.  Measured (tiles' best / few, us): T = 16, K = 640, E = 5120 9.0 / 4.1 (G = 128), 9.4 / 5.7 (256),
+    // 9.2 / 4.0 (32); K = 1728 15.3 / 6.1, 16.5 / 10.0, 15.6 / 4.2; T = 64 15.8 / 6.9, 16.8 / 10.6, 16.1 / 7.5; T = 100, K = 3584, E = 8192,
+    // G = 128 27.1 / 20.3; T = 400, K = 1000, E = 2248 11.6 / 8.3.  The tiles win with many tokens (T = 400, K = 640, E = 5120 11.0 / 13.9)
+    // and where a unit has groups of 256 to fetch from beyond its L2 (T = 16, K = 3584, E = 8192 30.4 / 37.1).  The estimates are within 30 %;
+    // the few have to be 10 % ahead.
+    struct Few {
+        int G, tt, ns, slope;
+        int (*launch)(const GemmArgs &, hipStream_t);
+    };
+    static const Few fews[] = {
+        {32, 16, 2100, 1200, launch_few_g<32, 1>},    {32, 32, 2500, 1500, launch_few_g<32, 2>},
+        {32, 64, 4200, 1800, launch_few_g<32, 4>},    {64, 16, 2200, 1800, launch_few_g<64, 1>},
+        {64, 32, 2800, 2000, launch_few_g<64, 2>},    {64, 64, 4800, 2400, launch_few_g<64, 4>},
+        {128, 16, 2000, 2700, launch_few_g<128, 1>},  {128, 32, 3900, 2500, launch_few_g<128, 2>},
+        {256, 16, 3000, 4600, launch_few_g<256, 1>},  {256, 32, 4800, 5000, launch_few_g<256, 2>},
+    };
+    const int64_t K = a.K, tile_ns = rounds * (5300 + (best->cost * 1000 - 5300) * K / 1728);
+    const int64_t beyond_l2 = static_cast<int64_t>(a.E) * K * 2 > (32 << 20) ? 2000 * a.G / 52 : 0;
+    const Few *few = nullptr;
+    int64_t few_ns = 0;
+    for (const Few &f : fews) {
+        if (f.G != a.G) continue;
+        const int64_t n = static_cast<int64_t>((a.E + f.G - 1) / f.G) * ((a.T + f.tt - 1) / f.tt), r = (n + cus - 1) / cus;
+        int64_t ns = 1500 + r * (f.ns - 1500 + (f.slope > beyond_l2 ? f.slope : beyond_l2) * K / 1000);
+        ns = std::max(ns, std::max(2950 + 1000 * r, 2500 + n * (f.G + f.tt) * K * 2 / (f.G == 256 ? 10000 : 13000)));
+        if (!few || ns < few_ns) {
+            few = &f;
+            few_ns = ns;
+        }
+    }
+    if (few && 10 * few_ns <= 9 * tile_ns) return few->launch(a, s);
     return best->launch(a, s);
 }
 
