@@ -8,20 +8,26 @@
 
 namespace tpq {
 
-// A word's 8 codes -> code * scale + zero.  One code per byte; the bytes 0 .. 15 read as FP8 (E4M3) are the codes times
-// 2^-9 (subnormals and the first binade have the same spacing), so the scaled pair conversion turns two codes into floats
-// at once; the product is exact.
-__device__ __forceinline__ void dequantise8(float (&x)[8], uint32_t w, float sc, float ze)
+// A word's 8 codes as floats.  One code per byte; the bytes 0 .. 15 read as FP8 (E4M3) are the codes times 2^-9 (subnormals
+// and the first binade have the same spacing), so the scaled pair conversion turns two codes into floats at once.
+__device__ __forceinline__ void codes8(float (&c)[8], uint32_t w)
 {
     const uint32_t lo = w & 0x0F0F0F0Fu, hi = (w >> 4) & 0x0F0F0F0Fu;
     const f32x2 c02 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(lo, 512.0f, false);
     const f32x2 c46 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(lo, 512.0f, true);
     const f32x2 c13 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(hi, 512.0f, false);
     const f32x2 c57 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(hi, 512.0f, true);
-    x[0] = __builtin_fmaf(c02.x, sc, ze); x[1] = __builtin_fmaf(c13.x, sc, ze);
-    x[2] = __builtin_fmaf(c02.y, sc, ze); x[3] = __builtin_fmaf(c13.y, sc, ze);
-    x[4] = __builtin_fmaf(c46.x, sc, ze); x[5] = __builtin_fmaf(c57.x, sc, ze);
-    x[6] = __builtin_fmaf(c46.y, sc, ze); x[7] = __builtin_fmaf(c57.y, sc, ze);
+    c[0] = c02.x; c[1] = c13.x; c[2] = c02.y; c[3] = c13.y;
+    c[4] = c46.x; c[5] = c57.x; c[6] = c46.y; c[7] = c57.y;
+}
+
+// ... -> code * scale + zero (the product is exact)
+__device__ __forceinline__ void dequantise8(float (&x)[8], uint32_t w, float sc, float ze)
+{
+    float c[8];
+    codes8(c, w);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) x[e] = __builtin_fmaf(c[e], sc, ze);
 }
 
 // The 8 B-bit fields of a 64-bit word as floats: field e at bits B*e .. B*e + B - 1.
@@ -852,6 +858,181 @@ __global__ __launch_bounds__(256) void k_decode_static(DecodeArgs a, RankPtrs co
     }
 }
 
+// ---------------------------------------------------------------------------
+// The static mode with many rows and up to kStaticLdsRanks ranks: a workgroup takes one pass of 512 compacted features of 16 rows
+// (8 PAIRS), 2 rows of a wave at a time, and holds the pass's steps of all ranks in LDS, so that the table is read from L2 once for 16 rows
+// instead of once for 4 and a wave's registers hold codes and sums only (6 waves per SIMD; k_decode_static with 4
+// rows has 4, and twice as many waves as fit at once at the size below).  Kernel times, k_decode_static / this, fp32 and bf16 chain: 2048 x 5120, N = 8
+// 20.2 / 17.8 us and 21.4 / 21.4; N = 3 13.6 / 12.3; N = 5 18.2 / 14.3 and 18.2 / 16.8; 1300 x 5120, N = 8 21.5 / 13.2 and 21.0 / 16.1;
+// 5332 x 4216, N = 2 27.2 / 23.3; 8192 x 8192, N = 8 107 / 95 and 110 / 98.  Where the line lies: 700 x 5120, N = 8 10.5 / 10.0 and 11.1 / 13.0, 600 x 8192 14.6 / 11.0 and
+// 15.0 / 13.6, 512 x 5120 8.2 / 8.5; N = 16, bf16 chain 34.5 / 36.5.
+// grid: (block of rows, pass or 64 selected features) pairs, rounded up to a multiple of 8.
+// ---------------------------------------------------------------------------
+constexpr int kStaticLdsRanks = 16;
+template <int ACC, int OUT, int PAIRS, bool GEN>
+__global__ __launch_bounds__(256, GEN ? 5 : 6) void k_decode_static_lds(DecodeArgs a, RankPtrs codesp, RankPtrs outlp)
+{
+    const bool bad = plan_header_bad(a.plan, a.E, a.k, a.G);  // checked before any store
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t passes = static_cast<uint32_t>(a.chunks_padded) >> 6;
+    const uint32_t tasks = passes + ((static_cast<uint32_t>(a.k) + 63u) >> 6);
+    const uint32_t logical = xcd_contiguous_index(blockIdx.x, gridDim.x);
+    const uint32_t rb = logical / tasks, task = logical - rb * tasks;
+    const uint32_t T = static_cast<uint32_t>(a.T), t0 = rb * (8u * PAIRS);
+    if (t0 >= T) return;  // (grid rounded up to 8)
+
+    constexpr uint32_t OB = OUT == TPQ_OUT_FP32 ? 4u : 2u;  // bytes per output value
+    const uint32_t N = static_cast<uint32_t>(a.n_ranks);
+    const uint32_t row0 = t0 + wave * (2u * PAIRS);  // the wave's first row; rows past the end are read as the last and not stored
+    auto out_of = [&](uint32_t t) { return static_cast<uint8_t *>(a.out) + static_cast<int64_t>(t) * a.ldOut * OB; };
+
+    if (task >= passes) {
+        // ---- selected features ------------------------------------------------------
+        const uint32_t p = (task - passes) * 64u + lane;
+        if (bad || p >= static_cast<uint32_t>(a.k)) return;
+        const uint32_t j = static_cast<uint32_t>(reinterpret_cast<const int32_t *>(a.plan + a.off_idx)[p]);
+#pragma unroll
+        for (uint32_t rr = 0; rr < 2u * PAIRS; ++rr) {
+            const uint32_t t = row0 + rr;
+            if (t >= T) break;  // uniform
+            float acc = 0.f;
+            for (uint32_t i0 = 0; i0 < N; i0 += 8) {
+                uint32_t v[8];
+#pragma unroll
+                for (int jj = 0; jj < 8; ++jj)
+                    v[jj] = reinterpret_cast<const uint16_t *>(static_cast<const uint8_t *>(outlp.p[min(i0 + jj, N - 1u)]) +
+                                                               t * static_cast<uint32_t>(a.pitch_outl))[p];
+#pragma unroll
+                for (int jj = 0; jj < 8; ++jj)
+                    if (i0 + jj < N) acc = i0 + jj == 0 ? bf16_bits_to_f32(v[jj]) : add_term<ACC>(acc, bf16_bits_to_f32(v[jj]));
+            }
+            if (OUT == TPQ_OUT_FP32)
+                *reinterpret_cast<float *>(out_of(t) + 4u * j) = acc;
+            else
+                *reinterpret_cast<uint16_t *>(out_of(t) + 2u * j) = static_cast<uint16_t>(pack_bf16x2(acc, acc));
+        }
+        return;
+    }
+
+    // ---- one pass of quantised features ---------------------------------------------
+    const uint32_t chunk = task * 64u + lane;
+    extern __shared__ u32x4 smem_static[];
+    u32x4 *const table = smem_static;                                                // [rank][first / second four of a chunk][64]
+    u32x4 *const stage = smem_static + N * 128u + wave * (64u * (OUT == TPQ_OUT_FP32 ? 2u : 1u));
+    for (uint32_t u = threadIdx.x; u < N * 128u; u += 256u) {
+        const uint32_t i = u >> 7, q = u & 127u;  // (q < 128: inside the pass, and the table's row has whole passes)
+        table[i * 128u + (q & 1u) * 64u + (q >> 1)] =
+            *reinterpret_cast<const u32x4 *>(a.step_c + static_cast<int64_t>(i) * a.static_stride + 512u * task + 4u * q);
+    }
+    // the pass's store entries: where they start, blocks, blocks + narrow entries
+    const uint4 sp = reinterpret_cast<const uint4 *>(a.plan + a.off_spass)[task];
+    const uint32_t first = min(sp.x, static_cast<uint32_t>(a.sblk_cap));
+    const uint32_t *entries = reinterpret_cast<const uint32_t *>(a.plan + a.off_sblk) + first;
+    const uint32_t nall = min(sp.y + sp.z, static_cast<uint32_t>(a.sblk_cap) - first), nb = min(sp.y, nall);
+    const uint32_t e0 = lane < nall ? entries[lane] : 0u;
+    const uint32_t e1 = 64u + lane < nall ? entries[64u + lane] : 0u;
+    __syncthreads();
+
+    const uint32_t at = (GEN ? static_cast<uint32_t>(a.bits) : 4u) * min(chunk, static_cast<uint32_t>(a.chunks) - 1u);
+#pragma nounroll
+    for (uint32_t pr = 0; pr < static_cast<uint32_t>(PAIRS); ++pr) {
+        const uint32_t ta = row0 + 2u * pr;
+        if (ta >= T) break;  // uniform
+        const uint32_t off_a = ta * static_cast<uint32_t>(a.pitch_codes) + at;
+        const uint32_t off_b = min(ta + 1u, T - 1u) * static_cast<uint32_t>(a.pitch_codes) + at;
+        float acc[2][8];
+        // NB ranks at a time, as in k_decode_pass
+        auto batch = [&](uint32_t i0, uint32_t left, auto size_tag, auto bits_tag, auto first_tag) __attribute__((always_inline)) {
+            constexpr int NB = decltype(size_tag)::value;
+            constexpr int BITS = decltype(bits_tag)::value;
+            constexpr bool FIRST = decltype(first_tag)::value;
+            uint32_t w[2][NB];
+            uint64_t wq[2][NB];  // GEN
+            const void *const *pc = codesp.p + i0;
+            uint32_t oa = off_a, ob = off_b;
+            TPQ_LOADS_STAY(NB);
+            asm volatile("" : "+v"(oa), "+v"(ob));
+#pragma unroll
+            for (int j = 0; j < NB; ++j) {
+#pragma unroll
+                for (int rr = 0; rr < 2; ++rr) {
+                    const uint8_t *src = static_cast<const uint8_t *>(pc[j]) + (rr ? ob : oa);
+                    if constexpr (GEN)
+                        wq[rr][j] = __builtin_nontemporal_load(reinterpret_cast<const u64_a1 *>(src));
+                    else
+                        w[rr][j] = __builtin_nontemporal_load(reinterpret_cast<const uint32_t *>(src));
+                }
+                TPQ_LOADS_STAY(NB);
+            }
+#pragma unroll
+            for (int j = 0; j < NB; ++j) {
+                if (j < NB - 1 || left == NB) {  // uniform
+
+                    const u32x4 sa = table[(i0 + j) * 128u + lane], sb = table[(i0 + j) * 128u + 64u + lane];
+                    const float st[8] = {__uint_as_float(sa.x), __uint_as_float(sa.y), __uint_as_float(sa.z), __uint_as_float(sa.w),
+                                         __uint_as_float(sb.x), __uint_as_float(sb.y), __uint_as_float(sb.z), __uint_as_float(sb.w)};
+                    // (field - half) * step as one fused multiply-add per value: half * step is exact, so the sum is rounded
+                    // once, from the same exact product; shared by the rows
+                    constexpr float half = static_cast<float>(1u << (BITS - 1));
+                    float m[8];
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) m[e] = -half * st[e];
+#pragma unroll
+                    for (int rr = 0; rr < 2; ++rr) {
+                        float c[8], x[8];
+                        if constexpr (GEN)
+                            unpack_codes<BITS>(wq[rr][j], c);
+                        else
+                            codes8(c, w[rr][j]);
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) x[e] = __builtin_fmaf(c[e], st[e], m[e]);
+                        accumulate8<ACC>(acc[rr], x, FIRST && j == 0);
+                        // (rank by rank: all ranks' steps and terms at once do not fit the registers)
+                        asm volatile("" : "+v"(acc[rr][0]), "+v"(acc[rr][1]), "+v"(acc[rr][2]), "+v"(acc[rr][3]), "+v"(acc[rr][4]),
+                                     "+v"(acc[rr][5]), "+v"(acc[rr][6]), "+v"(acc[rr][7]) :: "memory");
+                    }
+                }
+            }
+        };
+        auto some = [&](uint32_t i0, auto bits_tag, auto first_tag) __attribute__((always_inline)) {
+            const uint32_t left = N - i0;
+            if (left > 6u) batch(i0, left, std::integral_constant<int, 8>{}, bits_tag, first_tag);
+            else if (left > 4u) batch(i0, left, std::integral_constant<int, 6>{}, bits_tag, first_tag);
+            else if (left > 2u) batch(i0, left, std::integral_constant<int, 4>{}, bits_tag, first_tag);
+            else batch(i0, left, std::integral_constant<int, 2>{}, bits_tag, first_tag);
+        };
+        auto run = [&](auto bits_tag) __attribute__((always_inline)) {
+            if (N <= 8u) {
+                some(0, bits_tag, std::true_type{});
+            } else {
+                batch(0, 8u, std::integral_constant<int, 8>{}, bits_tag, std::true_type{});
+                some(8, bits_tag, std::false_type{});
+            }
+        };
+        if constexpr (GEN) {
+            switch (a.bits) {
+            case 2: run(std::integral_constant<int, 2>{}); break;
+            case 3: run(std::integral_constant<int, 3>{}); break;
+            case 5: run(std::integral_constant<int, 5>{}); break;
+            case 6: run(std::integral_constant<int, 6>{}); break;
+            default: run(std::integral_constant<int, 8>{}); break;
+            }
+        } else {
+            run(std::integral_constant<int, 4>{});
+        }
+        if (bad) return;
+#pragma unroll
+        for (uint32_t rr = 0; rr < 2; ++rr) {
+            if (ta + rr >= T) break;  // uniform
+            round8<ACC>(acc[rr]);
+            uint32_t f0 = e0, f1 = e1;
+            asm volatile("" : "+v"(f0), "+v"(f1));  // (what follows from the entries is worked out anew, not kept across the rows)
+            store_pass<OUT>(stage, acc[rr], out_of(ta + rr), lane, entries, nb, nall, f0, f1);
+        }
+    }
+}
+
 #ifndef TPQ_STATIC_RPW
 #define TPQ_STATIC_RPW 4
 #endif
@@ -867,10 +1048,15 @@ static int rows_per_wave(bool is_static, int64_t T, int tasks)
 // last, partly idle one always falls to the same engines (N = 16, 2048 x 2048, k = 32, 2 a row: 16.7 us, as columns 12.2; 2048 x
 // 5120, 3 a row: k = 128 25.9 / 26.8; 4 a row: k = 182 33.8 / 28.3; 64 rows of either 4.1 / 4.8).  Codes of 5 bits and more
 // bring 8 ranks to the same side (6 bits, 2048 x 5120 26.0 / 27.1, 512 rows 7.6 / 8.7; 5 ranks 24.8 / 23.7).
-enum class Decode { kStatic, kRows, kColumns, kColumnsLanes };
-static Decode decode_form(const DecodeArgs &a, int out_dtype)
+enum class Decode { kStatic, kStaticLds, kRows, kColumns, kColumnsLanes };
+static Decode decode_form(const DecodeArgs &a, int accum, int out_dtype)
 {
-    if (a.step_c) return Decode::kStatic;
+    if (a.step_c) {
+        // (k_decode_static_lds, which says what was measured on either side)
+        const int64_t waves = a.T * (a.chunks_padded / 64 + (a.k + 63) / 64);
+        const bool bf16 = accum == TPQ_ACC_BF16;
+        return a.n_ranks <= (bf16 ? 12 : kStaticLdsRanks) && waves >= (bf16 ? 10000 : 8000) ? Decode::kStaticLds : Decode::kStatic;
+    }
     const bool few = 32 * a.k <= a.E;  // (16 selected columns a pass)
     if (a.n_ranks >= (a.bits > 4 ? 8 : 9) && out_dtype == TPQ_OUT_BF16 && !a.addend && !a.bias) {
         const int groups = (a.chunks_padded / 64 + (a.k + 63) / 64 + 3) / 4;
@@ -896,7 +1082,13 @@ static void launch_rows(Decode form, int rpw, dim3 grid, hipStream_t s, const De
                         const RankPtrs &scale, const RankPtrs &zero, const RankPtrs &outl)
 {
     if constexpr (LPG == 0) {
-        if (a.bits != 4) {
+        const size_t lds = a.n_ranks * 2048 + 4 * 64 * 16 * (OUT == TPQ_OUT_FP32 ? 2 : 1);
+        if (form == Decode::kStaticLds) {
+            if (a.bits != 4)
+                launch_kernel(k_decode_static_lds<ACC, OUT, 2, true>, grid, dim3(256), lds, s, a, codes, outl);
+            else
+                launch_kernel(k_decode_static_lds<ACC, OUT, 2, false>, grid, dim3(256), lds, s, a, codes, outl);
+        } else if (a.bits != 4) {
             if (rpw == 4)
                 launch_kernel(k_decode_static<ACC, OUT, 4, true>, grid, dim3(256), 0, s, a, codes, outl);
             else
@@ -926,7 +1118,7 @@ int launch_decode(const DecodeArgs &a_in, const RankPtrs &codes_in, const RankPt
     if (accum == TPQ_ACC_FAST) accum = TPQ_ACC_FP32;
     const int lpg = a_in.G / 8;
     // waves per row
-    const Decode form = decode_form(a_in, out_dtype);
+    const Decode form = decode_form(a_in, accum, out_dtype);
     const bool columns = form == Decode::kColumns || form == Decode::kColumnsLanes;
     const int tasks = !columns ? a_in.chunks_padded / 64 + (a_in.k + 63) / 64 : cpass_cap_of(a_in.E);
     if (tasks == 0) return TPQ_OK;
@@ -974,7 +1166,7 @@ int launch_decode(const DecodeArgs &a_in, const RankPtrs &codes_in, const RankPt
         }
         // The kernels read two ranks' pointers at a time, and the selected features' of 8, whether or not they look at what is
         // there: the last rank again, and the first.
-        if (a.n_ranks & 1) {
+        if (a.n_ranks & 1) {  // (the static mode has no scale and zero: null pointers)
             codes.p[a.n_ranks] = codes.p[a.n_ranks - 1];
             scale.p[a.n_ranks] = scale.p[a.n_ranks - 1];
             zero.p[a.n_ranks] = zero.p[a.n_ranks - 1];
@@ -984,7 +1176,7 @@ int launch_decode(const DecodeArgs &a_in, const RankPtrs &codes_in, const RankPt
         const int rpw = rows_per_wave(a.step_c != nullptr, a.T, tasks);
         // one dimension, dealt out over the XCDs by the kernel: 4 (row, column pass) pairs a workgroup, else (row block,
         // wave group) pairs
-        const int64_t blocks = !columns ? (a.T + rpw - 1) / rpw * ny : (a.T * a.cpass_stride + 3) / 4;
+        const int64_t blocks = columns ? (a.T * a.cpass_stride + 3) / 4 : form == Decode::kStaticLds ? (a.T + 15) / 16 * tasks : (a.T + rpw - 1) / rpw * ny;
         const dim3 grid(static_cast<unsigned>((blocks + 7) / 8 * 8));
 #define TPQ_LAUNCH3(LPG, ACC, OUT) launch_rows<LPG, ACC, OUT>(form, rpw, grid, s, a, codes, scale, zero, outl)
 #define TPQ_LAUNCH2(LPG)                                                                     \
