@@ -229,8 +229,9 @@ __device__ __forceinline__ void add_quad(float &acc, uint32_t v, uint32_t rq, ui
 // Ranks come in batches with code of their own for 1 to 8 (2, 4, 6 and 8 where that code is long: other code widths, LANES).
 // As batches of 8 whatever was left, the loads of ranks that are not there were issued too (the last rank's again), and the
 // compiler put a rank's loads behind the others' arithmetic, a second wait for memory.  Kernel times at T = 2048, E = 5120, k = 80, fp32 / bf16 chain,
-// before -> now: N = 2 13.4 -> 11.3 / 13.5 -> 11.7 us, N = 3 14.1 -> 12.1 / 14.4 -> 12.6, N = 5, 6 bits 19.6 -> 17.7 / 19.9 -> 17.9,
-// N = 8 16.4 -> 16.3 / 20.8 -> 19.1, with residual and bias 19.3 -> 19.3 / 23.1 -> 21.5; N = 12, k = 20, 5 bits (rows) 41.3 -> 34.4 / 41.9 -> 34.8.
+// before -> now: N = 2 13.4 -> 11.2 / 13.5 -> 11.6 us, N = 3 13.8 -> 11.8 / 14.4 -> 12.4, N = 5, 6 bits 19.7 -> 17.8 / 19.9 -> 17.9,
+// N = 8 16.7 -> 16.2 / 20.7 -> 18.4, with residual and bias 19.3 -> 19.4 / 23.1 -> 21.8; N = 12, k = 20, 5 bits (rows) 41.3 -> 34.4 / 41.9 -> 34.8; N = 12, 4096 rows, k = 200
+// 45.3 -> 39.8 / 52.7 -> 45.8.
 // grid: (row, pass) pairs, 4 per workgroup, workgroups rounded up to a multiple of 8.
 // ---------------------------------------------------------------------------
 //
@@ -264,7 +265,8 @@ __global__ __launch_bounds__(256, (GEN ? 7 : 8) - LANES) void k_decode_pass(Deco
     const uint32_t passes = static_cast<uint32_t>(a.cpasses);
     const uint32_t pair = xcd_contiguous_index(blockIdx.x, gridDim.x) * 4u + wave;
     const uint32_t stride = static_cast<uint32_t>(a.cpass_stride);
-    const uint32_t t = pair / stride, task = pair - t * stride;
+    // (by multiplication: exact below 2^32 / stride, which the host keeps)
+    const uint32_t t = stride == 1u ? pair : __umulhi(pair, a.cpass_magic), task = pair - t * stride;
     if (t >= static_cast<uint32_t>(a.T) || task >= passes) return;  // (the grid is rounded up to 8 blocks of 4)
 
     constexpr uint32_t OB = OUT == TPQ_OUT_FP32 ? 4u : 2u;  // bytes per output value
@@ -311,22 +313,27 @@ __global__ __launch_bounds__(256, (GEN ? 7 : 8) - LANES) void k_decode_pass(Deco
     // NB ranks at a time: all loads first, then the arithmetic, a rank's as soon as its loads are there.  left: ranks from i0
     // on, NB or one less (GEN, LANES; the host fills the pointer tables up to an even number).
     // (the code width is a compile-time constant inside: one copy of the loop per width)
-    auto batch = [&](uint32_t i0, uint32_t left, auto size_tag, auto bits_tag, auto first_tag) __attribute__((always_inline)) {
+    auto batch = [&](uint32_t i0, uint32_t left, auto size_tag, auto bits_tag, auto first_tag, auto order_tag) __attribute__((always_inline)) {
         constexpr int NB = decltype(size_tag)::value;
         constexpr int BITS = decltype(bits_tag)::value;
         constexpr bool FIRST = decltype(first_tag)::value;
+        constexpr bool ORDER = decltype(order_tag)::value;
         uint32_t w[NB], sb[NB], zb[NB];
         uint64_t wq[NB];  // GEN
-        const void *const *pc = codesp.p + i0;
-        const void *const *ps = scalep.p + i0;
-        const void *const *pz = zerop.p + i0;
+        // (a base of this branch's own: else all sizes' pointers are loaded ahead of the branch, and spill where registers are
+        // short: bf16 chain, N = 8 18.3 -> 24.5 us.  With residual and bias in fp32 they fit, and that is faster: 19.4 against 19.8)
+        uint32_t base = i0;
+        if constexpr (ACC == TPQ_ACC_BF16 || GEN || LANES) asm volatile("" : "+s"(base));
+        const void *const *pc = codesp.p + base;
+        const void *const *ps = scalep.p + base;
+        const void *const *pz = zerop.p + base;
         uint32_t oc = off_codes, om = off_meta;
-        TPQ_LOADS_STAY(NB);
+        if constexpr (ORDER) TPQ_LOADS_STAY(NB);
         asm volatile("" : "+v"(oc), "+v"(om));  // (offsets of this branch's own: a base per rank beside them in one load instruction, no 64-bit sums)
         uint32_t vb[NB];  // LANES
         if constexpr (LANES) {
 #pragma unroll
-            for (int j = 0; j < NB; ++j) vb[j] = load_sel((outlp.p + i0)[j]);
+            for (int j = 0; j < NB; ++j) vb[j] = load_sel((outlp.p + base)[j]);
         }
 #pragma unroll
         for (int j = 0; j < NB; ++j) {
@@ -338,7 +345,7 @@ __global__ __launch_bounds__(256, (GEN ? 7 : 8) - LANES) void k_decode_pass(Deco
                     static_cast<const uint8_t *>(pc[j]) + oc));
             sb[j] = *reinterpret_cast<const uint16_t *>(static_cast<const uint8_t *>(ps[j]) + om);
             zb[j] = *reinterpret_cast<const uint16_t *>(static_cast<const uint8_t *>(pz[j]) + om);
-            TPQ_LOADS_STAY(NB);
+            if constexpr (ORDER) TPQ_LOADS_STAY(NB);
         }
         if constexpr (FIRST && !LANES) {
             __builtin_amdgcn_sched_barrier(0);  // (else the wait for their pointers comes before the messages' loads)
@@ -374,11 +381,11 @@ __global__ __launch_bounds__(256, (GEN ? 7 : 8) - LANES) void k_decode_pass(Deco
         constexpr int NB = decltype(size_tag)::value;
         if constexpr (!GEN && !LANES) {
             if (left < NB) {
-                batch(i0, left, std::integral_constant<int, NB - 1>{}, bits_tag, first_tag);
+                batch(i0, left, std::integral_constant<int, NB - 1>{}, bits_tag, first_tag, std::true_type{});
                 return;
             }
         }
-        batch(i0, left, size_tag, bits_tag, first_tag);
+        batch(i0, left, size_tag, bits_tag, first_tag, std::true_type{});
     };
     // ranks i0 .. N - 1, at most 8
     auto some = [&](uint32_t i0, auto bits_tag, auto first_tag) __attribute__((always_inline)) {
@@ -396,11 +403,23 @@ __global__ __launch_bounds__(256, (GEN ? 7 : 8) - LANES) void k_decode_pass(Deco
             if (N <= 8u) {
                 some(0, bits_tag, std::true_type{});
             } else {
+                // in fp32 the compiler may load the next ranks ahead of a batch's arithmetic (held back, N = 16, 8192 x 8192, fp32
+                // output takes 241 us instead of 218); in the bf16 chain that costs more than it gives (N = 12, 4096 x 5120
+                // 46.1 against 43.8)
                 const std::integral_constant<int, 8> eight;
-                batch(0, 8u, eight, bits_tag, std::true_type{});
+                const std::integral_constant<bool, ACC == TPQ_ACC_BF16> order;
+                batch(0, 8u, eight, bits_tag, std::true_type{}, order);
                 uint32_t i0 = 8;
-                for (; i0 + 8 < N; i0 += 8) batch(i0, 8u, eight, bits_tag, std::false_type{});
-                some(i0, bits_tag, std::false_type{});
+                if constexpr (GEN) {
+                    for (; i0 + 8 <= N; i0 += 8) batch(i0, 8u, eight, bits_tag, std::false_type{}, order);
+                    if (i0 < N) some(i0, bits_tag, std::false_type{});
+                } else {  // (the last 8 outside of the loop: N = 16 220 us instead of 230; at other code widths that would spill)
+                    for (; i0 + 8 < N; i0 += 8) batch(i0, 8u, eight, bits_tag, std::false_type{}, order);
+                    if (i0 + 8 == N)
+                        batch(i0, 8u, eight, bits_tag, std::false_type{}, order);
+                    else
+                        some(i0, bits_tag, std::false_type{});
+                }
             }
         }
         round8<ACC>(acc);
@@ -1134,6 +1153,10 @@ int launch_decode(const DecodeArgs &a_in, const RankPtrs &codes_in, const RankPt
     // one-dimensional grid of 256-thread workgroups: grid * block stays below 2^32
     const int64_t max_blocks = (1LL << 24) - 8;
     if (rows_per_launch > max_blocks / ny) rows_per_launch = max_blocks / ny;
+    if (columns) {  // the numbers of a launch's waves, those that fill up its grid with them, stay below 2^32 / stride
+        const int64_t stride = cpass_stride_of(a_in.E), most = ((1LL << 32) / stride - 64) / stride;
+        if (rows_per_launch > most) rows_per_launch = most;
+    }
     if (rows_per_launch < 1) return TPQ_ERR_SHAPE;
     const size_t ob = out_dtype == TPQ_OUT_FP32 ? 4 : 2;
     hipError_t e = hipSuccess;
@@ -1149,6 +1172,7 @@ int launch_decode(const DecodeArgs &a_in, const RankPtrs &codes_in, const RankPt
             a.off_cpass = o.cpass;
             a.cpasses = cpass_cap_of(a.E);
             a.cpass_stride = cpass_stride_of(a.E);
+            a.cpass_magic = a.cpass_stride > 1 ? static_cast<uint32_t>((1ull << 32) / a.cpass_stride + 1) : 0u;  // unused for 1
         }
         RankPtrs codes = codes_in, scale = scale_in, zero = zero_in, outl = outl_in;
         a.T = a_in.T - row0 < rows_per_launch ? a_in.T - row0 : rows_per_launch;

@@ -71,7 +71,7 @@ __device__ __forceinline__ float round_via_bf16(float x)
 // One step of the literal bf16 chain for 8 values: acc <- bf16(acc) + bf16(x), not yet rounded itself.  A pair conversion
 // rounds term and sum together, a dot product of the pair with (1, 1) adds them: two instructions a value where rounding
 // the term, adding and rounding the sum are three, and the conversions take twice an addition's time (decoder, T = 2048, E = 5120, N = 8
-// 20.8 -> 19.1 us; the same addition as a 4 x 4 x 4 matrix product with ones on the diagonal 21.3).
+// 20.7 -> 18.4 us; the same addition as a 4 x 4 x 4 matrix product with ones on the diagonal 21.3).
 // After the rounding that follows, the dot product is the fp32 addition: a sum of two bf16 values that has more
 // than 24 bits lies so close to the larger one that both round to it (no difference on the GPU for all significands and signs of
 // both, 91 exponent gaps at 17 exponents).  But -0 + -0 is +0 here; no message of the encoder's holds a -0.

@@ -248,6 +248,7 @@ struct DecodeArgs {
     // byte offsets of the plan's tables (what the header holds, known to the host too)
     int32_t off_idx, off_spass, off_sblk, sblk_cap, off_src, off_cpass;
     int32_t cpasses, cpass_stride;  // cpass_cap_of(E), cpass_stride_of(E): a wave would spend 20 instructions on them
+    uint32_t cpass_magic;           // 2^32 / cpass_stride + 1: pair / cpass_stride = mulhi(pair, cpass_magic)
 };
 
 // What a kernel checks before it trusts a plan: one wide scalar load, no branches between
