@@ -40,18 +40,20 @@ __device__ __forceinline__ void unpack_codes(uint64_t w, float (&c)[8])
 }
 
 // acc <- acc (+) x for 8 features at once, in the requested arithmetic.  In the bf16 chain acc is the last sum before its
-// rounding: term and sum are rounded by one pair conversion and added by one dot product with (1, 1).  Finished by round8().
-template <int ACC>
+// rounding: term and sum are rounded by one pair conversion and added by one dot product with (1, 1), which takes -0 + -0 for +0;
+// without DOT by an addition.  Finished by round8().
+template <int ACC, bool DOT = true>
 __device__ __forceinline__ void accumulate8(float (&acc)[8], const float (&x)[8], bool first)
 {
     if (first) {
 #pragma unroll
         for (int e = 0; e < 8; ++e) acc[e] = x[e];
-    } else if (ACC == TPQ_ACC_BF16) {
+    } else if (ACC == TPQ_ACC_BF16 && DOT) {
         bf16_chain8(acc, x);
     } else {
 #pragma unroll
-        for (int e = 0; e < 8; ++e) acc[e] = acc[e] + x[e];
+        for (int e = 0; e < 8; ++e)
+            acc[e] = ACC == TPQ_ACC_BF16 ? round_via_bf16(acc[e]) + round_via_bf16(x[e]) : acc[e] + x[e];
     }
 }
 
@@ -61,6 +63,27 @@ __device__ __forceinline__ void round8(float (&acc)[8])
     if (ACC == TPQ_ACC_BF16) {
 #pragma unroll
         for (int e = 0; e < 8; ++e) acc[e] = round_via_bf16(acc[e]);
+    }
+}
+
+// The literal bf16 chain by additions, a rank at a time, for the sums that bf16_chain8() gets wrong: those that are -0.  They are only where every
+// term is: a zero point of -0 and a scale with its sign set (less than 0, or -0) in every message.  The encoder sends neither, so
+// callers come here only where a lane sees that sign in the first rank's message.
+template <bool GEN>
+__device__ __forceinline__ void exact_chain(float (&acc)[8], uint32_t N, uint32_t bits, const RankPtrs &codesp, const RankPtrs &scalep,
+                                            const RankPtrs &zerop, uint32_t off_codes, uint32_t off_meta)
+{
+#pragma nounroll
+    for (uint32_t i = 0; i < N; ++i) {
+        const uint8_t *pc = static_cast<const uint8_t *>(codesp.p[i]) + off_codes;
+        const uint64_t w = GEN ? *reinterpret_cast<const u64_a1 *>(pc) : *reinterpret_cast<const uint32_t *>(pc);
+        const float sc = bf16_bits_to_f32(*reinterpret_cast<const uint16_t *>(static_cast<const uint8_t *>(scalep.p[i]) + off_meta));
+        const float ze = bf16_bits_to_f32(*reinterpret_cast<const uint16_t *>(static_cast<const uint8_t *>(zerop.p[i]) + off_meta));
+        float x[8];
+#pragma unroll
+        for (uint32_t e = 0; e < 8; ++e)
+            x[e] = __builtin_fmaf(static_cast<float>(static_cast<uint32_t>(w >> (bits * e)) & ((1u << bits) - 1u)), sc, ze);
+        accumulate8<TPQ_ACC_BF16, false>(acc, x, i == 0u);
     }
 }
 
@@ -309,6 +332,7 @@ __global__ __launch_bounds__(256, (GEN ? 7 : 8) - LANES) void k_decode_pass(Deco
     const bool quant = n_chunk > 0 && chunks > 0;
     const u32x4 cols = reinterpret_cast<const u32x4 *>(a.plan + a.off_src)[chunk];  // (in the plan also where there is none)
     float acc[8];
+    uint64_t signs = 0u;  // bf16 chain: the lanes that see a sign in the first rank's scale (exact_chain())
 
     // NB ranks at a time: all loads first, then the arithmetic, a rank's as soon as its loads are there.  left: ranks from i0
     // on, NB or one less (GEN, LANES; the host fills the pointer tables up to an even number).
@@ -373,6 +397,7 @@ __global__ __launch_bounds__(256, (GEN ? 7 : 8) - LANES) void k_decode_pass(Deco
                 } else {
                     dequantise8(x, w[j], sc, ze);
                 }
+                if (ACC == TPQ_ACC_BF16 && FIRST && j == 0) signs = __builtin_amdgcn_ballot_w64(sb[j] >= 0x8000u);
                 accumulate8<ACC>(acc, x, FIRST && j == 0);
             }
         }
@@ -409,6 +434,7 @@ __global__ __launch_bounds__(256, (GEN ? 7 : 8) - LANES) void k_decode_pass(Deco
                 const std::integral_constant<int, 8> eight;
                 const std::integral_constant<bool, ACC == TPQ_ACC_BF16> order;
                 batch(0, 8u, eight, bits_tag, std::true_type{}, order);
+                if (ACC == TPQ_ACC_BF16 && signs) return;  // (begun again below)
                 uint32_t i0 = 8;
                 if constexpr (GEN) {
                     for (; i0 + 8 <= N; i0 += 8) batch(i0, 8u, eight, bits_tag, std::false_type{}, order);
@@ -422,7 +448,6 @@ __global__ __launch_bounds__(256, (GEN ? 7 : 8) - LANES) void k_decode_pass(Deco
                 }
             }
         }
-        round8<ACC>(acc);
     };
     __shared__ u32x4 rows[4 * kRowQuads];
     float *const row = reinterpret_cast<float *>(rows + wave * kRowQuads);
@@ -438,6 +463,17 @@ __global__ __launch_bounds__(256, (GEN ? 7 : 8) - LANES) void k_decode_pass(Deco
         } else {
             run(std::integral_constant<int, 4>{});
         }
+        if (ACC == TPQ_ACC_BF16 && signs) {
+            exact_chain<GEN>(acc, N, GEN ? static_cast<uint32_t>(a.bits) : 4u, codesp, scalep, zerop, off_codes, off_meta);
+            if constexpr (LANES) {
+#pragma nounroll
+                for (uint32_t i = 0; i < N; ++i) {
+                    const float v = bf16_bits_to_f32(load_sel(outlp.p[i]));
+                    sel = i == 0u ? v : add_term<ACC>(sel, v);
+                }
+            }
+        }
+        round8<ACC>(acc);
         scatter_chunk(row, acc, cols, col0, chunk < static_cast<uint32_t>(a.r) >> 3);
     }
     if (refuse) return;
@@ -616,6 +652,7 @@ __global__ __launch_bounds__(256) void k_decode_rows(DecodeArgs a, RankPtrs code
                                (GEN ? static_cast<uint32_t>(a.bits) : 4u) * min(chunk, chunks - 1u);
     const uint32_t off_meta = t * static_cast<uint32_t>(a.pitch_meta) + 2u * g;
     float acc[8];
+    uint32_t sign = 0u;  // bf16 chain: of the first rank's scale (exact_chain())
 
     // NB ranks at a time, as in k_decode_pass; FULL: 8, and the compiler may load the next ones ahead of a batch's arithmetic
     // (held back, N = 64, 64 rows takes 12.0 us instead of 10.2)
@@ -658,6 +695,7 @@ __global__ __launch_bounds__(256) void k_decode_rows(DecodeArgs a, RankPtrs code
                 } else {
                     dequantise8(x, w[j], sc, ze);
                 }
+                if (ACC == TPQ_ACC_BF16 && FULL && i0 + j == 0) sign = sb[j];
                 accumulate8<ACC>(acc, x, FULL && i0 + j == 0);
             }
         }
@@ -671,7 +709,6 @@ __global__ __launch_bounds__(256) void k_decode_rows(DecodeArgs a, RankPtrs code
         else if (left > 4u) batch(i0, left, std::integral_constant<int, 6>{}, bits_tag, std::false_type{});
         else if (left > 2u) batch(i0, left, std::integral_constant<int, 4>{}, bits_tag, std::false_type{});
         else if (left > 0u) batch(i0, left, std::integral_constant<int, 2>{}, bits_tag, std::false_type{});
-        round8<ACC>(acc);
     };
     if constexpr (GEN) {
         switch (a.bits) {
@@ -684,6 +721,9 @@ __global__ __launch_bounds__(256) void k_decode_rows(DecodeArgs a, RankPtrs code
     } else {
         run(std::integral_constant<int, 4>{});
     }
+    if (ACC == TPQ_ACC_BF16 && __builtin_amdgcn_ballot_w64(sign >= 0x8000u))
+        exact_chain<GEN>(acc, N, GEN ? static_cast<uint32_t>(a.bits) : 4u, codesp, scalep, zerop, off_codes, off_meta);
+    round8<ACC>(acc);
     if (bad) return;
     __shared__ u32x4 stage[4 * 64];
     store_pass<OUT>(stage + wave * 64u, acc, out_row, lane, entries, nb, nall, e0, e1);
@@ -845,7 +885,7 @@ __global__ __launch_bounds__(256) void k_decode_static(DecodeArgs a, RankPtrs co
                         x[4] = __builtin_fmaf(c46.x, st[4], m8[4]); x[5] = __builtin_fmaf(c57.x, st[5], m8[5]);
                         x[6] = __builtin_fmaf(c46.y, st[6], m8[6]); x[7] = __builtin_fmaf(c57.y, st[7], m8[7]);
                     }
-                    accumulate8<ACC>(acc[rr], x, i0 + j == 0);
+                    accumulate8<ACC, !GEN>(acc[rr], x, i0 + j == 0);  // (GEN: a step of 0 makes -0 of a negative code)
                 }
             }
         }

@@ -74,7 +74,8 @@ __device__ __forceinline__ float round_via_bf16(float x)
 // 20.7 -> 18.4 us; the same addition as a 4 x 4 x 4 matrix product with ones on the diagonal 21.3).
 // After the rounding that follows, the dot product is the fp32 addition: a sum of two bf16 values that has more
 // than 24 bits lies so close to the larger one that both round to it (no difference on the GPU for all significands and signs of
-// both, 91 exponent gaps at 17 exponents).  But -0 + -0 is +0 here; no message of the encoder's holds a -0.
+// both, 91 exponent gaps at 17 exponents, subnormals among them).  Except that -0 + -0 is +0, whatever zero is added to it: callers see to sums of
+// nothing but -0.
 // One asm block: a dot product's result may be read by another kind of instruction only three instructions later, and the
 // builtin becomes the accumulating form, with a zero moved into its accumulator first.
 __device__ __forceinline__ void bf16_chain8(float (&acc)[8], const float (&x)[8])
