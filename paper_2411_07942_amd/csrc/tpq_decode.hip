@@ -39,6 +39,19 @@ __device__ __forceinline__ void unpack_codes(uint64_t w, float (&c)[8])
         c[e] = static_cast<float>(static_cast<uint32_t>(w >> (B * e)) & ((1u << B) - 1u));
 }
 
+// ... less half their range: field - 2^(B - 1) as a float.
+template <int B>
+__device__ __forceinline__ void unpack_signed(uint64_t w, float (&c)[8])
+{
+    uint64_t half = 0;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) half |= 1ull << (B * e + B - 1);
+    w ^= half;
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+        c[e] = static_cast<float>(static_cast<int32_t>(static_cast<uint32_t>(w >> (B * e)) << (32 - B)) >> (32 - B));
+}
+
 // acc <- acc (+) x for 8 features at once, in the requested arithmetic.  In the bf16 chain acc is the last sum before its
 // rounding: term and sum are rounded by one pair conversion and added by one dot product with (1, 1), which takes -0 + -0 for +0;
 // without DOT by an addition.  Finished by round8().
@@ -1031,22 +1044,25 @@ __global__ __launch_bounds__(256, GEN ? 5 : 6) void k_decode_static_lds(DecodeAr
                     const u32x4 sa = table[(i0 + j) * 128u + lane], sb = table[(i0 + j) * 128u + 64u + lane];
                     const float st[8] = {__uint_as_float(sa.x), __uint_as_float(sa.y), __uint_as_float(sa.z), __uint_as_float(sa.w),
                                          __uint_as_float(sb.x), __uint_as_float(sb.y), __uint_as_float(sb.z), __uint_as_float(sb.w)};
-                    // (field - half) * step as one fused multiply-add per value: half * step is exact, so the sum is rounded
-                    // once, from the same exact product; shared by the rows
-                    constexpr float half = static_cast<float>(1u << (BITS - 1));
-                    float m[8];
+                    // 4 bits: (field - 8) * step as one fused multiply-add per value: 8 * step is exact, so the sum is rounded
+                    // once, from the same exact product; shared by the rows.  Other widths: the product itself (a step of
+                    // 0 makes -0 of a negative code)
+                    float m8[8];
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) m[e] = -half * st[e];
+                    for (int e = 0; e < 8; ++e) m8[e] = -8.0f * st[e];
 #pragma unroll
                     for (int rr = 0; rr < 2; ++rr) {
                         float c[8], x[8];
-                        if constexpr (GEN)
-                            unpack_codes<BITS>(wq[rr][j], c);
-                        else
+                        if constexpr (GEN) {
+                            unpack_signed<BITS>(wq[rr][j], c);
+#pragma unroll
+                            for (int e = 0; e < 8; ++e) x[e] = c[e] * st[e];
+                        } else {
                             codes8(c, w[rr][j]);
 #pragma unroll
-                        for (int e = 0; e < 8; ++e) x[e] = __builtin_fmaf(c[e], st[e], m[e]);
-                        accumulate8<ACC>(acc[rr], x, FIRST && j == 0);
+                            for (int e = 0; e < 8; ++e) x[e] = __builtin_fmaf(c[e], st[e], m8[e]);
+                        }
+                        accumulate8<ACC, !GEN>(acc[rr], x, FIRST && j == 0);
                         // (rank by rank: all ranks' steps and terms at once do not fit the registers)
                         asm volatile("" : "+v"(acc[rr][0]), "+v"(acc[rr][1]), "+v"(acc[rr][2]), "+v"(acc[rr][3]), "+v"(acc[rr][4]),
                                      "+v"(acc[rr][5]), "+v"(acc[rr][6]), "+v"(acc[rr][7]) :: "memory");

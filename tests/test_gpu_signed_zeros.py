@@ -85,7 +85,7 @@ def test_chain_over_the_range_of_bf16(N, scale):
 
 
 @pytest.mark.parametrize("bits", [3, 8])
-@pytest.mark.parametrize("T", [7])
+@pytest.mark.parametrize("T", [7, 5003])           # a wave per row; where 5003, a workgroup per 16 rows
 def test_static_steps_of_zero(T, bits):
     """A code below 0 times a step of 0 is -0."""
     E, k, G, N = 520, 9, 32, 3
