@@ -266,7 +266,7 @@ __device__ __forceinline__ void add_quad(float &acc, uint32_t v, uint32_t rq, ui
 // As batches of 8 whatever was left, the loads of ranks that are not there were issued too (the last rank's again), and the
 // compiler put a rank's loads behind the others' arithmetic, a second wait for memory.  Kernel times at T = 2048, E = 5120, k = 80, fp32 / bf16 chain,
 // before -> now: N = 2 13.4 -> 11.2 / 13.5 -> 11.6 us, N = 3 13.8 -> 11.8 / 14.4 -> 12.4, N = 5, 6 bits 19.7 -> 17.8 / 19.9 -> 17.9,
-// N = 8 16.7 -> 16.2 / 20.7 -> 18.4, with residual and bias 19.3 -> 19.4 / 23.1 -> 21.8; N = 12, k = 20, 5 bits (rows) 41.3 -> 34.4 / 41.9 -> 34.8; N = 12, 4096 rows, k = 200
+// N = 8 16.7 -> 16.2 / 20.7 -> 18.4, with fp32 output 20.2 -> 20.0 / 22.6 -> 21.1, with residual and bias 19.3 -> 19.4 / 23.1 -> 21.6; N = 12, k = 20, 5 bits (rows) 41.3 -> 34.4 / 41.9 -> 34.8; N = 12, 4096 rows, k = 200
 // 45.3 -> 39.8 / 52.7 -> 45.8.
 // grid: (row, pass) pairs, 4 per workgroup, workgroups rounded up to a multiple of 8.
 // ---------------------------------------------------------------------------
@@ -358,15 +358,18 @@ __global__ __launch_bounds__(256, (GEN ? 7 : 8) - LANES) void k_decode_pass(Deco
         uint32_t w[NB], sb[NB], zb[NB];
         uint64_t wq[NB];  // GEN
         // (a base of this branch's own: else all sizes' pointers are loaded ahead of the branch, and spill where registers are
-        // short: bf16 chain, N = 8 18.3 -> 24.5 us.  With residual and bias in fp32 they fit, and that is faster: 19.4 against 19.8)
+        // short: N = 8, bf16 chain 18.3 -> 24.5 us, fp32 with fp32 output 20.0 -> 25.2.  In fp32 with bf16 output they nearly fit, and
+        // that is faster: with residual and bias 19.4 against 19.8)
         uint32_t base = i0;
-        if constexpr (ACC == TPQ_ACC_BF16 || GEN || LANES) asm volatile("" : "+s"(base));
+        if constexpr (ACC == TPQ_ACC_BF16 || OUT == TPQ_OUT_FP32 || GEN || LANES) asm volatile("" : "+s"(base));
         const void *const *pc = codesp.p + base;
         const void *const *ps = scalep.p + base;
         const void *const *pz = zerop.p + base;
         uint32_t oc = off_codes, om = off_meta;
         if constexpr (ORDER) TPQ_LOADS_STAY(NB);
-        asm volatile("" : "+v"(oc), "+v"(om));  // (offsets of this branch's own: a base per rank beside them in one load instruction, no 64-bit sums)
+        // (offsets of this branch's own: a base per rank beside them in one load instruction, no 64-bit sums.  Batches without an
+        // order share theirs: N = 64, 64 rows, fp32 output 12.5 -> 11.1 us)
+        if constexpr (ORDER) asm volatile("" : "+v"(oc), "+v"(om));
         uint32_t vb[NB];  // LANES
         if constexpr (LANES) {
 #pragma unroll
