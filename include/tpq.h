@@ -190,7 +190,8 @@ int tpq_calibrate_fixed(const uint16_t *Y, int64_t S, int64_t ldY, int E, int ra
  *   Rbar       [device] fp32 [E]
  *   idx_sorted [device] int32[k], ascending feature order (what tpq_plan_build takes)
  *   idx_ranked [device] int32[k], by descending Rbar; may be NULL
- *   workspace  [device] >= tpq_calibrate_finalize_workspace_bytes(E) bytes */
+ *   workspace  [device] >= tpq_calibrate_finalize_workspace_bytes(E) bytes; written only where idx_ranked
+ *              is asked for, required always */
 size_t tpq_calibrate_finalize_workspace_bytes(int E);
 int tpq_calibrate_finalize(const float *m, const float *M, int n_ranks, int E, int k,
                            float *R, float *Rbar, int32_t *idx_sorted,

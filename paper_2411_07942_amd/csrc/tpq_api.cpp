@@ -252,7 +252,8 @@ int tpq_calibrate_finalize(const float *m, const float *M, int n_ranks, int E, i
         (reinterpret_cast<uintptr_t>(workspace) & 3u))
         return TPQ_ERR_ALIGN;
     if (ws_bytes < tpq_calibrate_finalize_workspace_bytes(E)) return TPQ_ERR_WORKSPACE;
-    return launch_finalize(m, M, n_ranks, E, k, R, Rbar, idx_sorted, idx_ranked, static_cast<hipStream_t>(stream));
+    return launch_finalize(m, M, n_ranks, E, k, R, Rbar, idx_sorted, idx_ranked,
+                           static_cast<int32_t *>(workspace), static_cast<hipStream_t>(stream));
 }
 
 // ---- encode / decode_reduce ---------------------------------------------------

@@ -390,7 +390,7 @@ __global__ __launch_bounds__(256) void k_ranges(const float *__restrict__ m, con
 // 7 us this way.
 constexpr int kRankOwn = 16, kRankTile = 8192;
 __global__ __launch_bounds__(1024) void k_rank(const float *__restrict__ Rbar, int E, int k,
-                                               int32_t *__restrict__ idx_ranked)
+                                               int32_t *__restrict__ rank_of, int32_t *__restrict__ idx_ranked)
 {
     __shared__ float4 tile[kRankTile / 4];
     __shared__ int32_t part[16][kRankOwn];
@@ -432,8 +432,38 @@ __global__ __launch_bounds__(1024) void k_rank(const float *__restrict__ Rbar, i
         int rank = 0;
 #pragma unroll
         for (int w = 0; w < 16; ++w) rank += part[w][lane];
+        rank_of[j] = rank;
         if (rank < k) idx_ranked[rank] = j;
     }
+}
+
+// Ascending list of the selected features, from their ranks: position = selected features below j.  A workgroup of 1024 features counts
+// the selected ones before its own in one sweep over their ranks, all loads in flight at once (it was a serial walk, 256 at a time through
+// LDS: 130 us at E = 5120, now 4).
+constexpr int kSelectTile = 1024;
+__global__ __launch_bounds__(kSelectTile) void k_select(const int32_t *__restrict__ rank_of, int E, int k,
+                                                        int32_t *__restrict__ idx_sorted)
+{
+    __shared__ int32_t wave_sum[2][kSelectTile / 64];  // selected before the tile / in the tile, per wave
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int base = blockIdx.x * kSelectTile;
+    const int j = base + threadIdx.x;
+    const int rank = j < E ? rank_of[j] : k;
+    int earlier = 0;
+#pragma unroll 8
+    for (int o = threadIdx.x; o < base; o += kSelectTile) earlier += rank_of[o] < k;
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) earlier += __shfl_xor(earlier, d, 64);
+    const uint64_t sel = __builtin_amdgcn_ballot_w64(rank < k);
+    if (lane == 0) {
+        wave_sum[0][wave] = earlier;
+        wave_sum[1][wave] = __builtin_popcountll(sel);
+    }
+    __syncthreads();
+    int pos = __builtin_popcountll(sel & ((1ull << lane) - 1ull));
+#pragma unroll
+    for (int w = 0; w < kSelectTile / 64; ++w) pos += wave_sum[0][w] + (w < wave ? wave_sum[1][w] : 0);
+    if (rank < k && pos < k) idx_sorted[pos] = j;  // (ranges that are NaN share ranks: more than k features may have one below k)
 }
 
 // Ascending list of the k features with the largest ranges, the lower index first where ranges are equal: the k-th largest
@@ -442,7 +472,8 @@ __global__ __launch_bounds__(1024) void k_rank(const float *__restrict__ Rbar, i
 // would cost a second launch wherever they meet, and counting every feature's rank over the chip takes E / 64 steps for what is
 // three rounds of digits here.  Digits are 11 bits, from the first bit in which the ranges differ; a round counts
 // them in LDS, and is the last if all of a digit's features are wanted.  Bound by latency: launch, one load, some ten barriers.
-// E = 5120: 6.4 us, against 7.6 for all ranks and 3.9 for the list that followed.
+// E = 5120: 6.4 us, against 7.6 for all ranks and 3.9 for the list that follows from them.  R is the smallest of 4, 8, 16 and 32 that holds the row: every round of
+// it is paid for (E = 8200 with 32 of them 23 us a call, the ranks' list 18.7).
 // Ranges that are NaN come before all others and do not count towards the k; the list ends at k all the same.
 constexpr int kTopWaves = 16, kTopDigit = 11, kTopBins = 1 << kTopDigit;
 constexpr uint32_t kTopLow = 0x007FFFFFu, kTopHigh = 0xFF800000u;  // keys of -inf and +inf
@@ -545,12 +576,17 @@ __global__ __launch_bounds__(64 * kTopWaves) void k_top(const float *__restrict_
 static_assert(kTopBins == 2 * 64 * kTopWaves, "two digits a thread");
 
 int launch_finalize(const float *m, const float *M, int N, int E, int k, float *R, float *Rbar,
-                    int32_t *idx_sorted, int32_t *idx_ranked, hipStream_t s)
+                    int32_t *idx_sorted, int32_t *idx_ranked, int32_t *ws, hipStream_t s)
 {
     k_ranges<<<(E + 255) / 256, 256, 0, s>>>(m, M, N, E, R, Rbar);
-    if (k > 0) {
-        if (idx_ranked) k_rank<<<(E + kRankOwn - 1) / kRankOwn, 1024, 0, s>>>(Rbar, E, k, idx_ranked);
-        const auto top = E <= 4096 ? k_top<4> : E <= 8192 ? k_top<8> : k_top<32>;  // (1024 features a round)
+    // Where the ranked list is asked for, every rank is there and the ascending list follows from them in 3.9 us (k_top 6.4): the whole call,
+    // E = 5120, 12.1 us against 15.2 with k_top behind the ranks, E = 8200 18.7 against 35.  Without it k_top alone: E = 5120 8.4 us
+    // against 12.3, E = 32768 23 against 99.
+    if (k > 0 && idx_ranked) {
+        k_rank<<<(E + kRankOwn - 1) / kRankOwn, 1024, 0, s>>>(Rbar, E, k, ws, idx_ranked);
+        k_select<<<(E + kSelectTile - 1) / kSelectTile, kSelectTile, 0, s>>>(ws, E, k, idx_sorted);
+    } else if (k > 0) {
+        const auto top = E <= 4096 ? k_top<4> : E <= 8192 ? k_top<8> : E <= 16384 ? k_top<16> : k_top<32>;  // (1024 features a round)
         top<<<1, 64 * kTopWaves, 0, s>>>(Rbar, E, k, idx_sorted);
     }
     return hip_result(hipGetLastError());

@@ -315,6 +315,7 @@ int calibrate_fixed_scratch(void **ptr);
 int launch_static_params(const tpq_layout *L, const void *plan, const float *m, const float *M,
                          int n_ranks, float *step, float *inv, hipStream_t s);
 int launch_finalize(const float *m, const float *M, int N, int E, int k, float *R,
-                    float *Rbar, int32_t *idx_sorted, int32_t *idx_ranked, hipStream_t s);
+                    float *Rbar, int32_t *idx_sorted, int32_t *idx_ranked, int32_t *ws,
+                    hipStream_t s);
 
 }  // namespace tpq
