@@ -476,15 +476,16 @@ __global__ __launch_bounds__(64 * FW * TW, 1) void k_gemm_tile(GemmArgs a, uint3
     }
 }
 
-// Few tokens: a workgroup has the G features of one group and all the tokens (at most 16 NTB), and its 8 waves share K: wave w takes
+// Few tokens: a workgroup has the G features of one group and 16 NTB tokens, and its 8 waves share K: wave w takes
 // the stages of 32 k that are w modulo their number, through a ring in LDS of its own, so that nothing waits for a barrier and
 // all of a short K is on its way at once.  The partial sums meet in LDS, where all threads share the epilogue.  Bound by what a
 // compute unit can have outstanding to memory; E / G of them hold a group each.  In the tiles below one wave does the
 // products and the epilogue of 16 tokens by itself, at E / 128 units whatever G, and a stage costs it 0.19 us from barrier to barrier.
 // (Fragments loaded straight into registers, 16 rows by 64 bytes an instruction with neighbouring lanes in different rows:
 // 41 bytes/ns a compute unit, where four lanes to a row, as here, reach twice that.)
-// T = 13, E = 5120: K = 640 9.0 -> 4.1 us, K = 1728 15.3 -> 6.1 (tiles -> this).  T = 64, K = 1728 15.8 -> 6.9: more tokens are more
-// workgroups, until the chip is full (launch_tiles()).
+// Stages taken in pairs by a wave, so that it has both halves of a line, are 6 to 14 % slower.
+// E = 5120, G = 128, T = 16, weights in the L2s (in the memory-side cache): K = 640 8.8 -> 4.2 us (9.0 -> 6.0), K = 1728 15.3 -> 6.5 (15.1 -> 10.8); T = 64,
+// K = 1728 15.6 -> 7.2 (16.0 -> 9.3): more tokens are more workgroups, until the chip is full (launch_tiles()).
 template <int G, int NTB>
 struct FewShape {
     static constexpr int waves = 8, threads = 64 * waves;
@@ -746,19 +747,45 @@ static int launch_tile(const GemmArgs &a, hipStream_t s)
 // wins: 512 tokens 18.7 us at 128 x 128 against 23.7 at 256 x 128; 1024 tokens 25.6 at 256 x 128 against 33.9
 // (two rounds) and 31.7 (256 x 192); 2048 tokens 37.5 at 256 x 192 against 49 and 54 (two and three rounds)
 // and 44 (256 x 256).
+//
+// Few tokens: k_gemm_few where its estimate is 5 % below the tile's.  Both estimates are fits to 3400 launches (E 128 .. 16384, K 16 .. 14400, 1 to 1500
+// tokens) whose weights came from the memory-side cache, as a layer's do that ran a few layers ago: ns of a launch = ends + rounds * (round + slope * K
+// / 1000), the slope larger where an XCD's workgroups read more than its L2 holds (far) and smaller where several have the same weights
+// (shared); k_gemm_few besides not under 3.95 us, nor under what all units get from their L2s together.  Half of the launches are within 2 to 14 % of
+// their fit, nine of ten within 30 %.  Of 1000 launches that the fits have not seen, the form taken is more than 5 % slower than the tile for 5 to 8 (32 before,
+// by estimates from weights in L2), and 0.6 % off the fastest form in the mean (1.2 % before); for 24 (42) with weights from memory, where a unit's
+// one group is bound by the lines it can have outstanding in either form and the tile has a line's halves together.
+// Tile / 16 / 32 tokens a workgroup, us, weights in the memory-side cache (and in the L2s): E = 5120, T = 16, K = 640 9.0 / 6.0 / 6.1 (8.8 / 4.2 / 4.7) with G = 128,
+// 10.0 / 9.5 / 9.5 (9.4 / 6.1 / 6.5) with 256; K = 1728 15.1 / 10.8 / 10.8 (15.3 / 6.5 / 7.1), and 16.8 / 18.8 / 19.2 (16.6 / 10.1 / 11.4) with 256; T = 64, K = 1728 16.0 / 9.3 / 11.8
+// (15.6 / 7.2 / 8.3); E = 8192, K = 3584, T = 16 25.8 / 20.0 / 20.4, and 30.2 / 37.6 / 38.2 with 256.
 static int launch_tiles(const GemmArgs &a, hipStream_t s)
 {
     struct Tile {
         int ft, tt, cost;
+        int ends, round, slope, far;  // the estimate; slope 0: none, k_gemm_few is never faster
         int (*launch)(const GemmArgs &, hipStream_t);
     };
     static const Tile tiles[] = {
-        {128, 64, 16, launch_tile<1, 2, 1>},  {128, 128, 17, launch_tile<1, 4, 1>}, {256, 64, 18, launch_tile<2, 2, 1>},
-        {256, 128, 24, launch_tile<2, 2, 2>}, {256, 192, 31, launch_tile<2, 2, 3>}, {256, 256, 39, launch_tile<2, 2, 4>},
+        {128, 64, 16, 2960, 2420, 6030, 150, launch_tile<1, 2, 1>},    {128, 128, 17, 5000, 1470, 8140, 0, launch_tile<1, 4, 1>},
+        {256, 64, 18, 1370, 4240, 8410, 2050, launch_tile<2, 2, 1>},   {256, 128, 24, 1990, 7440, 11280, 1770, launch_tile<2, 2, 2>},
+        {256, 192, 31, 6500, 9580, 11990, 5380, launch_tile<2, 2, 3>}, {256, 256, 39, 0, 0, 0, 0, launch_tile<2, 2, 4>},
+    };
+    struct Few {
+        int G, tt;
+        int ends, round, slope, far, shared, chip, mb;  // shared: per mille of the slope saved where a group's workgroups are many; all units together: chip ns, and mb ns a MB
+        int (*launch)(const GemmArgs &, hipStream_t);
+    };
+    static const Few fews[] = {
+        {32, 16, 1240, 1220, 1220, 470, 41, 3040, 72, launch_few_g<32, 1>},     {32, 32, 800, 1930, 1470, 640, 0, 2880, 70, launch_few_g<32, 2>},
+        {32, 64, 0, 3180, 2000, 940, 0, 4030, 50, launch_few_g<32, 4>},         {64, 16, 1030, 1360, 2370, 660, 101, 3450, 44, launch_few_g<64, 1>},
+        {64, 32, 170, 2470, 2610, 640, 0, 3690, 57, launch_few_g<64, 2>},       {64, 64, 0, 3630, 2850, 1260, 0, 4150, 73, launch_few_g<64, 4>},
+        {128, 16, 700, 1820, 4550, 1220, 137, 2900, 79, launch_few_g<128, 1>},  {128, 32, 0, 3040, 4800, 1180, 0, 4070, 80, launch_few_g<128, 2>},
+        {256, 16, 440, 2510, 8820, 3470, 123, 3740, 65, launch_few_g<256, 1>},  {256, 32, 0, 3930, 9320, 3120, 0, 5130, 82, launch_few_g<256, 2>},
     };
     int cus = 0;
     const hipError_t e = compute_units_of_current_device(&cus);
     if (e != hipSuccess) return hip_result(e);
+    const int64_t K = a.K;
     const Tile *best = nullptr;
     int64_t least = 0, rounds = 0;
     for (const Tile &t : tiles) {
@@ -771,40 +798,27 @@ static int launch_tiles(const GemmArgs &a, hipStream_t s)
             rounds = (n + cus - 1) / cus;
         }
     }
-    // The same launch in ns, or with few tokens a workgroup (k_gemm_few): what a round takes with weights from L2 is ns + slope K / 1000, 52 bytes/ns
-    // a compute unit where the weights are larger than the L2s; then there are what all units together get from their L2s
-    // (13 bytes/ps, 10 with groups of 256), and 2.5 us of launch and ends.  Measured (tiles' best / few, us): T = 16, K = 640, E = 5120 9.0 / 4.1 (G = 128), 9.4 / 5.7 (256),
-    // 9.2 / 4.0 (32); K = 1728 15.3 / 6.1, 16.5 / 10.0, 15.6 / 4.2; T = 64 15.8 / 6.9, 16.8 / 10.6, 16.1 / 7.5; T = 100, K = 3584, E = 8192,
-    // G = 128 27.1 / 20.3; T = 400, K = 1000, E = 2248 11.6 / 8.3.  The tiles win with many tokens (T = 400, K = 640, E = 5120 11.0 / 13.9)
-    // and where a unit has groups of 256 to fetch from beyond its L2 (T = 16, K = 3584, E = 8192 30.4 / 37.1).  The estimates are within 30 %;
-    // the few have to be 10 % ahead.
-    struct Few {
-        int G, tt, ns, slope;
-        int (*launch)(const GemmArgs &, hipStream_t);
+    if (!best->slope) return best->launch(a, s);
+    // ns per 1000 k: of the XCD's contiguous share of the workgroups, tokens fastest, how many features' weights; from 3 MB on beyond its L2
+    const auto slope = [&](int64_t features, int64_t tokens, int near, int far, int shared) {
+        const int64_t nf = (a.E + features - 1) / features, nt = (a.T + tokens - 1) / tokens, share = (nf * nt + 7) / 8;
+        const int64_t bytes = 2 * K * (std::min(nf, (share + nt - 2) / nt + 1) * features + a.T);
+        const int64_t s0 = near + far * std::min<int64_t>(std::max<int64_t>((bytes - 3000000) / 2000, 0), 1000) / 1000;
+        return s0 - s0 * shared / 1000 * (nt - 1) / nt;
     };
-    static const Few fews[] = {
-        {32, 16, 2100, 1200, launch_few_g<32, 1>},    {32, 32, 2500, 1500, launch_few_g<32, 2>},
-        {32, 64, 4200, 1800, launch_few_g<32, 4>},    {64, 16, 2200, 1800, launch_few_g<64, 1>},
-        {64, 32, 2800, 2000, launch_few_g<64, 2>},    {64, 64, 4800, 2400, launch_few_g<64, 4>},
-        {128, 16, 2000, 2700, launch_few_g<128, 1>},  {128, 32, 3900, 2500, launch_few_g<128, 2>},
-        {256, 16, 3000, 4600, launch_few_g<256, 1>},  {256, 32, 4800, 5000, launch_few_g<256, 2>},
-    };
-    const int64_t K = a.K, tile_ns = rounds * (5300 + (best->cost * 1000 - 5300) * K / 1728);
-    const int64_t beyond_l2 = static_cast<int64_t>(a.E) * K * 2 > (32 << 20) ? 2000 * a.G / 52 : 0;
+    int64_t ns = 95 * (best->ends + rounds * (best->round + slope(best->ft, best->tt, best->slope, best->far, 0) * K / 1000)) / 100;
     const Few *few = nullptr;
-    int64_t few_ns = 0;
     for (const Few &f : fews) {
         if (f.G != a.G) continue;
-        const int64_t n = static_cast<int64_t>((a.E + f.G - 1) / f.G) * ((a.T + f.tt - 1) / f.tt), r = (n + cus - 1) / cus;
-        int64_t ns = 1500 + r * (f.ns - 1500 + (f.slope > beyond_l2 ? f.slope : beyond_l2) * K / 1000);
-        ns = std::max(ns, std::max(2950 + 1000 * r, 2500 + n * (f.G + f.tt) * K * 2 / (f.G == 256 ? 10000 : 13000)));
-        if (!few || ns < few_ns) {
+        const int64_t n = static_cast<int64_t>((a.E + f.G - 1) / f.G) * ((a.T + f.tt - 1) / f.tt);
+        const int64_t unit = f.ends + (n + cus - 1) / cus * (f.round + slope(f.G, f.tt, f.slope, f.far, f.shared) * K / 1000);
+        const int64_t all = std::max<int64_t>(3950, f.chip + n * (f.G + f.tt) * K * 2 / 1000 * f.mb / 1000);
+        if (std::max(unit, all) < ns) {
             few = &f;
-            few_ns = ns;
+            ns = std::max(unit, all);
         }
     }
-    if (few && 10 * few_ns <= 9 * tile_ns) return few->launch(a, s);
-    return best->launch(a, s);
+    return few ? few->launch(a, s) : best->launch(a, s);
 }
 
 int launch_gemm_weights(const tpq_layout *L, const void *plan, const uint16_t *Wt, int64_t ldW, int K,

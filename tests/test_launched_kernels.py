@@ -37,3 +37,37 @@ def test_finalize(launched, E):
     assert alone == ["k_ranges", "k_top<%d>" % rounds]
     assert both == ["k_ranges", "k_rank", "k_select"]
     assert none == ["k_ranges"]
+
+
+# Kernel times in us, weights in the memory-side cache: the tile that the rounds choose, then 16, 32 and 64 tokens a workgroup of
+# k_gemm_few.
+GEMM_TIMES = [
+    # T, K, E, G
+    ((13, 640, 5120, 128), (9.0, 6.0, 6.1)),
+    ((16, 640, 5120, 256), (10.0, 9.5, 9.5)),
+    ((16, 1728, 5120, 128), (15.1, 10.8, 10.8)),
+    ((64, 1728, 5120, 128), (16.0, 9.3, 11.8)),
+    ((400, 1728, 5120, 128), (17.8, 29.0, 22.8)),
+    ((700, 640, 5120, 128), (11.2, 26.8, 21.5)),
+    ((1, 640, 5120, 64), (9.0, 4.0, 4.2, 4.8)),
+    ((160, 1728, 5120, 64), (16.4, 17.4, 13.6, 10.6)),
+    ((64, 640, 5120, 32), (10.0, 7.5, 7.0, 6.3)),
+    ((33, 3584, 8192, 64), (26.0, 18.2, 12.7, 16.2)),
+    ((64, 3584, 8192, 64), (26.7, 19.9, 14.0, 19.4)),
+    ((16, 3584, 8192, 256), (30.2, 37.6, 38.2)),
+    ((256, 256, 8192, 32), (7.9, 25.9, 19.0, 15.3)),
+    ((429, 11824, 2416, 64), (78.8, 183.8, 130.7, 121.4)),
+    ((14, 2880, 4144, 256), (23.9, 29.8, 30.6)),
+    ((3, 13312, 296, 256), (96.5, 121.3, 121.9)),
+    ((756, 7536, 1168, 256), (85.2, 88.0, 101.7)),
+    ((23, 6712, 2264, 256), (78.1, 93.7, 100.4)),
+]
+
+
+def test_gemm_takes_a_fast_form(launched):
+    """Never a form slower than the tile, nor more than 10 % off the fastest."""
+    kernels = launched([("gemm", E, E // 64, G, T, K) for (T, K, E, G), _ in GEMM_TIMES])
+    for (size, times), (kernel,) in zip(GEMM_TIMES, kernels):
+        m = re.match(r"k_gemm_few<%d, (\d)>" % size[3], kernel)
+        taken = times[{1: 1, 2: 2, 4: 3}[int(m.group(1))]] if m else times[0]
+        assert taken <= times[0] and taken <= 1.1 * min(times), (size, kernel, times)
