@@ -102,11 +102,11 @@ def _run(T, K, E, k, G, seed, integer=False, ld_pad=0, rows=None, want_y=True, i
 
 
 @pytest.mark.parametrize("T,K,E,k,G", [
-    (200, 96, 512, 8, 128),       # two feature tiles, two token tiles, ragged T
+    (200, 96, 512, 8, 128),       # four groups of features, ragged T (but for Gemma's width all of these have few tokens a workgroup)
     (70, 1728, 5120, 80, 128),    # Llama width and depth of one device's slice
     (130, 40, 264, 5, 32),        # K and E off the tile sizes, groups of 32
     (64, 64, 1024, 16, 64),       # groups of 64
-    (129, 128, 1024, 16, 256),    # groups of 256: two waves share a group
+    (129, 128, 1024, 16, 256),    # groups of 256: the features of one belong to two sets of waves
     (5, 32, 1032, 1, 128),        # odd r: a pad nibble
     (33, 64, 768, 0, 128),        # k = 0
     (17, 64, 256, 256, 32),       # k = E: everything stays bf16
@@ -141,7 +141,7 @@ def test_random_shapes(seed):
 
 
 @pytest.mark.parametrize("T,K,E,k,G", [
-    (65, 72, 5120, 80, 128),      # tiles of 128 features x 64 tokens, one token in the second
+    (65, 72, 5120, 80, 128),      # no tile: 16 tokens a workgroup, one in the last (k_gemm_few; tiles of 128 x 64: test_gpu_gemm_few)
     (500, 104, 5128, 77, 64),     # 128 x 128, three stages of k and a quarter
     (900, 40, 5128, 77, 32),      # 256 x 128, an odd selection that starts inside a chunk
     (300, 328, 5120, 80, 256),    # 256 x 64 (a group of 256 in two waves)
@@ -150,7 +150,7 @@ def test_random_shapes(seed):
     (4090, 136, 8192, 341, 64),   # 256 x 256
 ])
 def test_every_tile_at_its_edges(T, K, E, k, G):
-    """The product's tile follows from the sizes: one case per tile, first and last rows of every
+    """The product's tile follows from the sizes: one case per tile but the first, first and last rows of every
     tile of tokens, k not a multiple of the stages (in pairs of 32)."""
     edges = np.concatenate([np.arange(0, T, 64), np.arange(0, T, 64) - 1, [T - 1]])
     _run(T, K, E, k, G, seed=T + G, rows=np.unique(edges[(edges >= 0) & (edges < T)]))

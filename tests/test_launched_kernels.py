@@ -71,3 +71,37 @@ def test_gemm_takes_a_fast_form(launched):
         m = re.match(r"k_gemm_few<%d, (\d)>" % size[3], kernel)
         taken = times[{1: 1, 2: 2, 4: 3}[int(m.group(1))]] if m else times[0]
         assert taken <= times[0] and taken <= 1.1 * min(times), (size, kernel, times)
+
+
+def test_gemm_forms_of_the_tests(launched):
+    """The cases of test_gpu_gemm_few's FORMS, and the tiles that test_gpu_gemm names, run the kernels they say."""
+    from test_gpu_gemm_few import FORMS
+    cases = [(name, case) for name, of in FORMS for case in of] + [
+        ("k_gemm_few<128, 1>", (65, 72, 5120, 80, 128)), ("k_gemm_tile<64, 1, 4, 1>", (500, 104, 5128, 77, 64)),
+        ("k_gemm_tile<32, 2, 2, 2>", (900, 40, 5128, 77, 32)), ("k_gemm_tile<256, 2, 2, 1>", (300, 328, 5120, 80, 256)),
+        ("k_gemm_tile<128, 2, 2, 3>", (2040, 200, 5120, 80, 128)), ("k_gemm_tile<256, 2, 2, 3>", (2040, 200, 5120, 300, 256)),
+        ("k_gemm_tile<64, 2, 2, 4>", (4090, 136, 8192, 341, 64)), ("k_gemm_tile<128, 1, 2, 1>", (300, 1728, 5120, 80, 128)),
+        ("k_gemm_tile<256, 2, 2, 1>", (200, 1728, 5120, 80, 256)), ("k_gemm_tile<64, 1, 2, 1>", (200, 2400, 8192, 80, 64)),
+        ("k_gemm_few<64, 4>", (100, 640, 5120, 80, 64)), ("k_gemm_few<64, 4>", (230, 752, 2248, 35, 64)),
+        ("k_gemm_few<32, 4>", (100, 1728, 5120, 80, 32)), ("k_gemm_few<128, 1>", (16, 3584, 8192, 128, 128))]
+    ran = launched([("gemm", E, k, G, T, K) for _, (T, K, E, k, G) in cases])
+    assert [(n, c) for (n, c), r in zip(cases, ran) if r != [n]] == []
+
+
+def test_static_forms_of_the_tests(launched):
+    """The cases of test_gpu_static_rows: the bf16 chain of every one of FOUR_ROWS has 4 rows a wave, and so have fp32 sums of more than
+    16 ranks; full sizes of up to 12 ranks have the steps in LDS."""
+    from test_gpu_static_rows import FOUR_ROWS
+    for T, E, N, k, bits in FOUR_ROWS:
+        gen = "true" if bits != 4 else "false"
+        fp32, fp32_out, bf16 = launched([("static", E, k, 128, bits, N, T, acc, out) for acc, out in ((0, 0), (0, 1), (1, 0))])
+        assert bf16 == ["k_decode_static<1, 0, 4, %s>" % gen]
+        if N > 16:
+            assert fp32 == ["k_decode_static<0, 0, 4, %s>" % gen] and fp32_out == ["k_decode_static<0, 1, 4, %s>" % gen]
+        else:
+            assert fp32 == ["k_decode_static_lds<0, 0, 2, %s>" % gen]
+    for acc in (0, 1):
+        assert launched([("static", 5120, 80, 128, 4, 8, 2048, acc, 0), ("static", 520, 9, 128, 4, 12, 5003, acc, 0)]) == [
+            ["k_decode_static_lds<%d, 0, 2, false>" % acc]] * 2
+        assert launched([("static", 520, 9, 128, 4, 17, 5003, acc, 0), ("static", 5120, 80, 128, 4, 8, 64, acc, 0)]) == [
+            ["k_decode_static<%d, 0, 1, false>" % acc]] * 2
