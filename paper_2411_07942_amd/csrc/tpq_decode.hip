@@ -446,14 +446,16 @@ __global__ __launch_bounds__(256, (GEN ? 7 : 8) - LANES) void k_decode_pass(Deco
             } else {
                 // in fp32 the compiler may load the next ranks ahead of a batch's arithmetic (held back, N = 16, 8192 x 8192, fp32
                 // output takes 241 us instead of 218); in the bf16 chain that costs more than it gives (N = 12, 4096 x 5120
-                // 46.1 against 43.8)
+                // 46.1 against 43.8).  Except from the second batch on at other code widths, where few rows of many ranks wait for the chain
+                // of batches (N = 32, 81 rows of 4608, 5 bits, fp32 output 10.9 -> 9.4 us; many rows, N = 64, 245 x 5120, 6 bits 32.8 -> 33.8)
                 const std::integral_constant<int, 8> eight;
                 const std::integral_constant<bool, ACC == TPQ_ACC_BF16> order;
+                const std::integral_constant<bool, ACC == TPQ_ACC_BF16 && !GEN> later;
                 batch(0, 8u, eight, bits_tag, std::true_type{}, order);
                 if (ACC == TPQ_ACC_BF16 && signs) return;  // (begun again below)
                 uint32_t i0 = 8;
                 if constexpr (GEN) {
-                    for (; i0 + 8 <= N; i0 += 8) batch(i0, 8u, eight, bits_tag, std::false_type{}, order);
+                    for (; i0 + 8 <= N; i0 += 8) batch(i0, 8u, eight, bits_tag, std::false_type{}, later);
                     if (i0 < N) some(i0, bits_tag, std::false_type{});
                 } else {  // (the last 8 outside of the loop: N = 16 220 us instead of 230; at other code widths that would spill)
                     for (; i0 + 8 < N; i0 += 8) batch(i0, 8u, eight, bits_tag, std::false_type{}, order);
